@@ -123,10 +123,10 @@ moe_status moe_pack_weights(const moe_shape *s, const void *W1, const void *W2,
 size_t moe_packed_gate_bytes(const moe_shape *s);
 
 /* One-time re-layout of the gating network's matrix (Sec. 2.1: "its trainable
- * matrix"): Wg [d_model, E] in `dtype` -> Wgp fp32 [EP][dP], expert-major:
- * Wgp[e*dP + i] = Wg[i, e], EP = E rounded up to a power of two, dP = d_model
- * rounded up to a multiple of 128, zeros elsewhere (moe_packed_gate_bytes =
- * EP*dP*4).  Every bf16 value converts exactly.  Treat the buffer as opaque:
+ * matrix"): Wg [d_model, E] in `dtype` -> Wgp fp32 [EP][dP], expert-major, EP = E
+ * rounded up to a power of two, dP = d_model rounded up to a multiple of 128, zeros
+ * elsewhere (moe_packed_gate_bytes = EP*dP*4); inside a run of 16 columns the order is
+ * the gate kernel's.  Every bf16 value converts exactly.  Treat the buffer as opaque:
  * build it with this call, not by hand. */
 moe_status moe_pack_gate(const moe_shape *s, const void *Wg, float *Wgp, void *stream);
 
@@ -161,7 +161,7 @@ moe_status moe_dispatch(const moe_shape *s, const void *x, const int32_t *expert
  * workspace to hand over: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments and results as moe_dispatch
  * minus `workspace`; the plan's scratch (256 bytes per plan segment; a segment
- * is 4 to 64 tokens by shape) lives in an array of
+ * is 16 to 64 tokens by shape) lives in an array of
  * moe_dispatch_static_limit() = 4 MiB inside the library's device image, which
  * every GPU the library runs on holds until the process ends.  The call
  * allocates and frees nothing (its first call on a device looks the array's

@@ -916,9 +916,16 @@ __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
 }
 
 // ---------------------------------------------------------------- gate backward
+// columns i .. i + 3 (i a multiple of 4) of a row of the packed gate matrix
+__device__ __forceinline__ float4 packed_columns(const float *row, int i)
+{
+    const float *p = row + packed_gate_column(i);
+    return make_float4(p[0], p[4], p[8], p[12]);
+}
+
 // One wavefront per token.  Logits: lane = four consecutive columns of the model dimension,
 // EP partial sums per lane (Wgp is the forward's packed gate matrix, fp32 [EP][dP],
-// expert-major, zero padded), then a butterfly sum per expert; the order of the additions
+// expert-major, zero padded, columns ordered by packed_gate_column), then a butterfly sum per expert; the order of the additions
 // differs from the forward's chain, which only the top-k decision needed.  Softmax, dz with
 // lane = expert, and finally, lane = column again,
 // dx[t, i] = sum of the token's kept dxe rows + sum_e dz[e] Wg[i, e].
@@ -950,8 +957,7 @@ __global__ __launch_bounds__(MODE != 0 ? 1024 : 256) void gate_bwd_kernel(
         const int rv = d / 4;                                        // 16-byte vectors per row
         for (int v = threadIdx.x; v < EP * rv; v += NW * kWave) {
             const int e = v / rv, i = (v % rv) * 4;
-            *reinterpret_cast<float4 *>(wlds + e * d + i) =
-                *reinterpret_cast<const float4 *>(Wgp + static_cast<size_t>(e) * dP + i);
+            *reinterpret_cast<float4 *>(wlds + e * d + i) = packed_columns(Wgp + static_cast<size_t>(e) * dP, i);
         }
         __syncthreads();
         Wsrc = wlds;
@@ -967,7 +973,7 @@ __global__ __launch_bounds__(MODE != 0 ? 1024 : 256) void gate_bwd_kernel(
         for (int v = threadIdx.x; v < EP * rv; v += NW * kWave) {
             const int e = v / rv, i = (v % rv) * 4;
             float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (c0 + i < dP) q = *reinterpret_cast<const float4 *>(Wgp + static_cast<size_t>(e) * dP + c0 + i);
+            if (c0 + i < dP) q = packed_columns(Wgp + static_cast<size_t>(e) * dP, c0 + i);
             *reinterpret_cast<float4 *>(wlds + e * DC + i) = q;
         }
         __syncthreads();
@@ -982,7 +988,8 @@ __global__ __launch_bounds__(MODE != 0 ? 1024 : 256) void gate_bwd_kernel(
         const float x2 = __uint_as_float(xq[1] << 16), x3 = __uint_as_float(xq[1] & 0xFFFF0000u);
 #pragma unroll
         for (int e = 0; e < EP; ++e) {
-            const float4 wv = *reinterpret_cast<const float4 *>(wbase + static_cast<size_t>(e) * pitch + iw);
+            const float *wrow = wbase + static_cast<size_t>(e) * pitch;
+            const float4 wv = MODE == 0 ? packed_columns(wrow, iw) : *reinterpret_cast<const float4 *>(wrow + iw);
             acc[e] = __builtin_fmaf(x0, wv.x, acc[e]);
             acc[e] = __builtin_fmaf(x1, wv.y, acc[e]);
             acc[e] = __builtin_fmaf(x2, wv.z, acc[e]);
@@ -1044,7 +1051,8 @@ __global__ __launch_bounds__(MODE != 0 ? 1024 : 256) void gate_bwd_kernel(
         }
 #pragma unroll
         for (int ee = 0; ee < EP; ++ee) {
-            const float4 wv = *reinterpret_cast<const float4 *>(wbase + static_cast<size_t>(ee) * pitch + iw);
+            const float *wrow = wbase + static_cast<size_t>(ee) * pitch;
+            const float4 wv = MODE == 0 ? packed_columns(wrow, iw) : *reinterpret_cast<const float4 *>(wrow + iw);
             o.x = __builtin_fmaf(dzr[ee], wv.x, o.x);
             o.y = __builtin_fmaf(dzr[ee], wv.y, o.y);
             o.z = __builtin_fmaf(dzr[ee], wv.z, o.z);

@@ -161,6 +161,13 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f)
     u += 0x7FFFu + ((u >> 16) & 1u);
     return static_cast<uint16_t>(u >> 16);
 }
+// Order of the packed gate matrix inside a run of 16 columns: position 4 g + i holds column
+// 4 i + g (its own inverse), so that 16 bytes are what a 16-lane group g of the gate kernel's
+// matrix instruction needs for four steps.
+__host__ __device__ __forceinline__ int packed_gate_column(int i)
+{
+    return (i & ~15) | ((i & 3) << 2) | ((i >> 2) & 3);
+}
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 #endif
 

@@ -28,6 +28,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 
@@ -49,13 +50,19 @@ __device__ __forceinline__ float normal_cdf_fast(float v)
     return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * q));
 }
 
+// 0.5 (1 + tanh u) with u = sqrt(2 / pi) (v + 0.044715 v^3), as 1 / (1 + e^-2u)
+__device__ __forceinline__ float half_one_plus_tanh(float v)
+{
+    return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * (-2.3022082f - 0.10294324f * v * v)));
+}
+
 template <int ACT>
 __device__ __forceinline__ float act_value(float v)
 {
     if constexpr (ACT == MOE_ACT_GELU_ERF)
         return v * normal_cdf_fast(v);
     else if constexpr (ACT == MOE_ACT_GELU_TANH)
-        return 0.5f * v * (1.0f + tanhf(0.7978845608028654f * (v + 0.044715f * v * v * v)));
+        return v * half_one_plus_tanh(v);
     else if constexpr (ACT == MOE_ACT_RELU)
         return fmaxf(v, 0.0f);
     else
@@ -70,9 +77,9 @@ __device__ __forceinline__ float act_derivative(float v)
         const float pdf = 0.3989422804014327f * __builtin_amdgcn_exp2f(-0.72134752044448171f * v * v);
         return normal_cdf_fast(v) + v * pdf;
     } else if constexpr (ACT == MOE_ACT_GELU_TANH) {
-        const float c = 0.7978845608028654f, a = 0.044715f;
-        const float th = tanhf(c * (v + a * v * v * v));
-        return 0.5f * (1.0f + th) + 0.5f * v * (1.0f - th * th) * c * (1.0f + 3.0f * a * v * v);
+        // s = (1 + tanh u) / 2:  s + v s' with s' = 2 s (1 - s) u'
+        const float c = 0.7978845608028654f, a = 0.044715f, s = half_one_plus_tanh(v);
+        return s + 2.0f * v * s * (1.0f - s) * c * (1.0f + 3.0f * a * v * v);
     } else if constexpr (ACT == MOE_ACT_RELU) {
         return v > 0.0f ? 1.0f : 0.0f;
     } else {
@@ -312,7 +319,7 @@ __global__ __launch_bounds__(128 * WN, 2) void bwd_gemm_kernel(
 // row GEMMs have enough 256 x 256 tiles to fill the chip.  The tile leaves through LDS as
 // whole lines (16-bit outputs) or straight from the registers (fp32); for EPI 2 the tile of
 // pre-activations comes in through the same LDS patch, as whole lines.
-template <int EPI, int ACT>
+template <int EPI, int ACT, bool KTAIL>
 __global__ __launch_bounds__(256, 1) void bwd_gemm_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, void *__restrict__ Cout,
     _Float16 *__restrict__ Pbuf, const WorkItem *__restrict__ items,
@@ -324,38 +331,35 @@ __global__ __launch_bounds__(256, 1) void bwd_gemm_w4_kernel(
     constexpr int row_div = 1, a_rows = 0;
 #include "gemm_w4_body.inc"
 
-    // acc[i][j][4*g + c]: column (wn*TN + i)*32 + 8*g + 4*(lane/32) + c, row (wm*TM + j)*32 +
-    // lane%32 of the tile.  Every wavefront is past its last LDS read after the barrier, the
-    // MFMA results have left the pipeline after the no-ops.
+    // Every wavefront is past its last LDS read after the barrier, the matrix results have left
+    // the pipeline after the no-ops.
     MOE_LGKM0();
     MOE_BAR();
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    const int rbase = item.row0 + wm * TM * 32;
+    const int rbase = item.row0 + wm * 128;
     if constexpr (EPI == 0) {
         float *out = static_cast<float *>(Cout);
 #pragma unroll
-        for (int i = 0; i < TN; ++i)
+        for (int i = 0; i < TN; ++i) {
+            const int n = n0 + wn * 128 + i * 16 + 4 * oct;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int n = n0 + (wn * TN + i) * 32 + 8 * g + 4 * (lane >> 5);
-#pragma unroll
-                for (int j = 0; j < TM; ++j) {
-                    const int r = rbase + j * 32 + fr;
-                    if (r < item.row1 && n < N)
-                        *reinterpret_cast<float4 *>(out + static_cast<size_t>(r) * N + n) =
-                            make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
-                                        acc[i][j][4 * g + 3]);
-                }
-                MOE_SB();      // a few accumulator registers at a time leave the AGPRs
+            for (int j = 0; j < TM; ++j) {
+                const int r = rbase + j * 16 + fr;
+                if (r < item.row1 && n < N)
+                    *reinterpret_cast<float4 *>(out + static_cast<size_t>(r) * N + n) =
+                        make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+                if (j == TM / 2 - 1) MOE_SB();
             }
+            MOE_SB();          // a few accumulator registers at a time leave the AGPRs
+        }
     } else {
         constexpr int PITCH = 272;                   // the wavefront's 128 x 128 patch of 16-bit values
-        char *patch = reinterpret_cast<char *>(smem) + wave * (TM * 32) * PITCH;
-        const int ncol = n0 + wn * TN * 32 + (lane & 15) * 8;
+        char *patch = lds + wave * 128 * PITCH;
+        const int ncol = n0 + wn * 128 + (lane & 15) * 8;
         // whole 256-byte row pieces between the patch and a [rows, N] matrix of 16-bit values
         auto lines_out = [&](uint16_t *dst) {
 #pragma unroll 8
-            for (int it = 0; it < TM * 8; ++it) {
+            for (int it = 0; it < 32; ++it) {
                 const int rr = it * 4 + (lane >> 4);
                 const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * PITCH + (lane & 15) * 16);
                 const int r = rbase + rr;
@@ -366,7 +370,7 @@ __global__ __launch_bounds__(256, 1) void bwd_gemm_w4_kernel(
         if constexpr (EPI == 2) {
             const uint16_t *src = reinterpret_cast<const uint16_t *>(Pbuf);
 #pragma unroll 8
-            for (int it = 0; it < TM * 8; ++it) {
+            for (int it = 0; it < 32; ++it) {
                 const int rr = it * 4 + (lane >> 4);
                 const int r = rbase + rr;
                 u32x4 q = {0u, 0u, 0u, 0u};
@@ -380,37 +384,35 @@ __global__ __launch_bounds__(256, 1) void bwd_gemm_w4_kernel(
 #pragma unroll
         for (int pass = EPI == 1 ? 0 : 1; pass < 2; ++pass) {     // EPI 1, pass 0: the pre-activations
 #pragma unroll
-            for (int i = 0; i < TN; ++i)
+            for (int i = 0; i < TN; ++i) {
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int col = i * 32 + 8 * g + 4 * (lane >> 5);
+                for (int j = 0; j < TM; ++j) {
+                    char *at = patch + (j * 16 + fr) * PITCH + (i * 16 + 4 * oct) * 2;
+                    float v[4];
 #pragma unroll
-                    for (int j = 0; j < TM; ++j) {
-                        char *at = patch + (j * 32 + fr) * PITCH + col * 2;
-                        float v[4];
+                    for (int c = 0; c < 4; ++c) v[c] = acc[i][j][c];
+                    if (EPI == 1 && pass == 0) {
+                        f16x4 p;
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) v[c] = acc[i][j][4 * g + c];
-                        if (EPI == 1 && pass == 0) {
-                            f16x4 p;
+                        for (int c = 0; c < 4; ++c) p[c] = static_cast<_Float16>(v[c]);
+                        *reinterpret_cast<f16x4 *>(at) = p;
+                    } else {
+                        float a[4];
+                        if constexpr (EPI == 1) {
 #pragma unroll
-                            for (int c = 0; c < 4; ++c) p[c] = static_cast<_Float16>(v[c]);
-                            *reinterpret_cast<f16x4 *>(at) = p;
+                            for (int c = 0; c < 4; ++c) a[c] = act_value<ACT>(v[c]);
                         } else {
-                            float a[4];
-                            if constexpr (EPI == 1) {
+                            const f16x4 p = *reinterpret_cast<const f16x4 *>(at);
 #pragma unroll
-                                for (int c = 0; c < 4; ++c) a[c] = act_value<ACT>(v[c]);
-                            } else {
-                                const f16x4 p = *reinterpret_cast<const f16x4 *>(at);
-#pragma unroll
-                                for (int c = 0; c < 4; ++c)
-                                    a[c] = v[c] * act_derivative<ACT>(static_cast<float>(p[c]));
-                            }
-                            store_bf16x4(reinterpret_cast<uint16_t *>(at), a);
+                            for (int c = 0; c < 4; ++c)
+                                a[c] = v[c] * act_derivative<ACT>(static_cast<float>(p[c]));
                         }
+                        store_bf16x4(reinterpret_cast<uint16_t *>(at), a);
                     }
-                    MOE_SB();
+                    if (j == TM / 2 - 1) MOE_SB();
                 }
+                MOE_SB();
+            }
             MOE_LGKM0();
             __builtin_amdgcn_wave_barrier();
             lines_out(EPI == 1 && pass == 0 ? reinterpret_cast<uint16_t *>(Pbuf)
@@ -650,6 +652,11 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(
 // MFMAs in a fixed order.  The operands' buffer resources end with the expert's last row, so
 // rows past it -- and whole stages past the last one -- read as zeros: no clamping, no tail
 // code.  M and N are multiples of 256 (the host checks).
+__device__ __forceinline__ void mfma_32x32x16_agpr(f32x16 &acc, const u32x4 &a, const u32x4 &b)
+{
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+
 template <bool AF16>
 __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, float *__restrict__ C,
@@ -765,7 +772,7 @@ __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
 #define WG4_MM(slot_, m)                                                                          \
     do {                                                                                         \
         constexpr int i_ = (m) & 3, j_ = (m) >> 2;                                               \
-        mfma_32x32x16_agpr<false>(acc[i_][j_], bf[slot_][i_], af[slot_][j_]);                    \
+        mfma_32x32x16_agpr(acc[i_][j_], bf[slot_][i_], af[slot_][j_]);                    \
     } while (0)
 // MFMA m, the fragment read m of the next step, and after every second MFMA one of the eight
 // write / load instructions of the step
@@ -1154,8 +1161,8 @@ GemmPlan plan_rows(int N, int K, int64_t max_rows, int E)
 {
     GemmPlan gp;
     const int64_t big_tiles = (max_rows / 256 + E / 2) * ((N + 255) / 256);
-    const bool fits = K % 64 == 0 && static_cast<uint64_t>(N) * K * 2 < (1ull << 31) &&
-                      256ull * K * 2 < (1ull << 31);
+    constexpr uint64_t most = (1ull << 31) - 64;       // byte offsets into the operands
+    const bool fits = static_cast<uint64_t>(N) * K * 2 < most && 256ull * K * 2 < most;
     if (big_tiles >= 768 && fits) {
         gp.bm = 256;
         gp.bn = 256;
@@ -1232,14 +1239,13 @@ void launch_gemm(const uint16_t *A, const uint16_t *W, void *C, _Float16 *P, con
 {
     const int grid_items = gp.max_items;
     if (gp.bm == 256) {
-        constexpr size_t lds = 2 * (256 + 256) * (64 + 8) * sizeof(uint16_t);
-        auto kern = bwd_gemm_w4_kernel<EPI, ACT>;
-        static PerDeviceOnce once;
-        once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
+        auto kern = K % 64 == 0 ? bwd_gemm_w4_kernel<EPI, ACT, false> : bwd_gemm_w4_kernel<EPI, ACT, true>;
+        static PerDeviceOnce once[2];
+        once[K % 64 == 0].raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kW4Lds));
         const int grid = static_cast<int>(align_up(static_cast<size_t>(grid_items), 8));
         hipEvent_t t0, t1;
         prof_kernel_events(stage, &t0, &t1);
-        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, t0, t1, 0, A, W, C, P, items, nitems,
+        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), kW4Lds, st, t0, t1, 0, A, W, C, P, items, nitems,
                               N, K);
         return;
     }

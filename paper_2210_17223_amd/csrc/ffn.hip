@@ -27,6 +27,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // ---------------------------------------------------------------- activations
 // GeLU(v) = v Phi(v) with Phi(v) ~ 1 / (1 + 2^(v Q(min(v^2, 49)))), Q a cubic fitted (minimax
@@ -52,6 +53,9 @@ __device__ __forceinline__ float activate(float v)
         if constexpr (FAST) return gelu_erf_fast(v);
         return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
     } else if constexpr (ACT == MOE_ACT_GELU_TANH) {
+        // 0.5 (1 + tanh u) = 1 / (1 + e^-2u): two transcendental instructions instead of tanhf
+        if constexpr (FAST)
+            return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * (-2.3022082f - 0.10294324f * v * v)));
         return 0.5f * v * (1.0f + tanhf(0.7978845608028654f * (v + 0.044715f * v * v * v)));
     } else if constexpr (ACT == MOE_ACT_RELU) {
         return fmaxf(v, 0.0f);
@@ -244,12 +248,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_mfma_kernel(
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-    // Register stages between the global loads and the LDS tile: two where the registers
-    // allow it (the loads then have two stages of multiplies to arrive), one for the
-    // 256 x 256 tile.
-    constexpr int DEPTH = BM * BN < 256 * 256 ? 2 : 1;
+    // register stages between the global loads and the LDS tile: the loads have two stages of
+    // multiplies to arrive
+    constexpr int DEPTH = 2;
     u32x4 a_reg[AV], w_reg[WV];
-    u32x4 a_reg2[DEPTH == 2 ? AV : 1], w_reg2[DEPTH == 2 ? WV : 1];
+    u32x4 a_reg2[AV], w_reg2[WV];
     u32x4 wf[2][TN], af[2][TM];
     const int KT = (K + BK - 1) / BK;
     const int fr = lane & 31, fk = (lane >> 5) * 8;
@@ -314,7 +317,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_mfma_kernel(
         MOE_MMA(1)                                                                              \
     }
 #define MOE_MAIN_LOOP                                                                           \
-    if constexpr (DEPTH == 2) {                                                                 \
+    {                                                                                           \
         int kt = 0;                                                                             \
         for (; kt + 1 < KT; kt += 2) {                                                          \
             MOE_STAGE(0, a_reg, w_reg)                                                          \
@@ -323,19 +326,13 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_mfma_kernel(
             --kt;                                                                               \
         }                                                                                       \
         if (kt < KT) MOE_STAGE(0, a_reg, w_reg)                                                 \
-    } else {                                                                                    \
-        for (int kt = 0; kt < KT; ++kt) {                                                       \
-            const int buf = kt & 1;                                                             \
-            MOE_STAGE(buf, a_reg, w_reg)                                                        \
-        }                                                                                       \
     }
 
-    // Prologue: stage 0 into LDS, stage 1 (and with two register stages also stage 2) in
-    // flight.
+    // prologue: stage 0 into LDS, stages 1 and 2 in flight
     MOE_LOADG(0, a_reg, w_reg)
     MOE_STOREL(0, a_reg, w_reg)
     if (KT > 1) MOE_LOADG(1, a_reg, w_reg)
-    if (DEPTH == 2 && KT > 2) MOE_LOADG(2, a_reg2, w_reg2)
+    if (KT > 2) MOE_LOADG(2, a_reg2, w_reg2)
     __syncthreads();
     MOE_READF(0, 0, 0)
     if (jact == TM) {          // every sub-tile of this wavefront holds rows: branch-free loop
@@ -385,7 +382,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_mfma_kernel(
 // ABL (measurement only, 0 in the layer): bit 0 leaves out the MFMAs, bit 1 the LDS fragment
 // reads after the first step, bit 2 the global loads and LDS writes inside the loop, bit 3 the
 // output stores.  Results are then wrong by construction; every access stays inside the buffers.
-template <bool F16, int ACT, bool KEEP, int ABL = 0>
+template <bool F16, int ACT, bool KEEP, bool KTAIL, int ABL = 0>
 __global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
@@ -394,48 +391,46 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
 {
 #include "gemm_w4_body.inc"
 
-    // Epilogue.  acc[i][j][4*g + c]: column (wn*TN + i)*32 + 8*g + 4*(lane/32) + c, row
-    // (wm*TM + j)*32 + lane%32 of the tile.  Every wavefront is past its last LDS read after
-    // the barrier; the MFMA results have left the pipeline after the no-ops (the compiler does
-    // not see through the inline assembly).  The wavefront's 128 x 128 sub-tile goes to its
-    // own patch, row pitch 272 bytes.
+    // Epilogue.  Every wavefront is past its last LDS read after the barrier; the matrix
+    // results have left the pipeline after the no-ops (the compiler does not see through the
+    // inline assembly).  The wavefront's 128 x 128 sub-tile goes to its own patch, row pitch 272
+    // bytes, and leaves as whole lines, 16 bytes per lane.
     MOE_LGKM0();
     MOE_BAR();
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     constexpr int PITCH = 272;
-    char *patch = reinterpret_cast<char *>(smem) + wave * (TM * 32) * PITCH;
+    char *patch = lds + wave * 128 * PITCH;
     const float *bexp = bias != nullptr ? bias + static_cast<size_t>(item.expert) * N : nullptr;
-    const int rbase = item.row0 + wm * TM * 32;
-    const int ncol = n0 + wn * TN * 32 + (lane & 15) * 8;
+    const int rbase = item.row0 + wm * 128;
+    const int ncol = n0 + wn * 128 + (lane & 15) * 8;
 #pragma unroll
     for (int pass = KEEP ? 0 : 1; pass < 2; ++pass) {      // pass 0: pre-activations, 1: outputs
         _Float16 *out = pass == 0 ? Pre : C;
 #pragma unroll
-        for (int i = 0; i < TN; ++i)
+        for (int i = 0; i < TN; ++i) {
+            const int col = i * 16 + 4 * oct;
+            float b4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (bexp != nullptr) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int col = i * 32 + 8 * g + 4 * (lane >> 5);
-                float b4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (bexp != nullptr) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) b4[c] = bexp[min(n0 + wn * TN * 32 + col + c, N - 1)];
-                }
-#pragma unroll
-                for (int j = 0; j < TM; ++j) {
-                    float v[4];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const float s = acc[i][j][4 * g + c] + b4[c];
-                        v[c] = pass == 0 ? s : activate<ACT, true>(s);
-                    }
-                    store4(reinterpret_cast<_Float16 *>(patch + (j * 32 + fr) * PITCH) + col, v);
-                }
-                MOE_SB();      // a few accumulator registers at a time leave the AGPRs
+                for (int c = 0; c < 4; ++c) b4[c] = bexp[min(n0 + wn * 128 + col + c, N - 1)];
             }
+#pragma unroll
+            for (int j = 0; j < TM; ++j) {
+                float v[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float s = acc[i][j][c] + b4[c];
+                    v[c] = pass == 0 ? s : activate<ACT, true>(s);
+                }
+                store4(reinterpret_cast<_Float16 *>(patch + (j * 16 + fr) * PITCH) + col, v);
+                if (j == TM / 2 - 1) MOE_SB();
+            }
+            MOE_SB();          // a few accumulator registers at a time leave the AGPRs
+        }
         MOE_LGKM0();
         __builtin_amdgcn_wave_barrier();
 #pragma unroll 8
-        for (int it = 0; it < TM * 8; ++it) {
+        for (int it = 0; it < 32; ++it) {
             const int rr = it * 4 + (lane >> 4);
             const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * PITCH + (lane & 15) * 16);
             const int r = rbase + rr;
@@ -449,6 +444,7 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
     }
 }
 #undef MOE_LGKM0
+#undef MOE_VMCNT
 #undef MOE_SB
 #undef MOE_BAR
 
@@ -535,11 +531,12 @@ void launch_mfma_cfg(const uint16_t *A, const uint16_t *W, const float *bias, TO
 
 // The four-wavefront kernel addresses its operands with 32-bit byte offsets into buffer
 // resources (the expert's weight matrix; the tile's rows, or the whole token matrix when the
-// rows are gathered) and walks whole 64-deep stages.
+// rows are gathered).
 inline bool w4_kernel_fits(int N, int K, bool gathered, uint64_t row_limit)
 {
-    return K % 64 == 0 && static_cast<uint64_t>(N) * K * 2 < (1ull << 31) &&
-           (gathered ? row_limit * static_cast<uint64_t>(K) : 256ull * K) * 2 < (1ull << 31);
+    constexpr uint64_t most = (1ull << 31) - 64;
+    return static_cast<uint64_t>(N) * K * 2 < most &&
+           (gathered ? row_limit * static_cast<uint64_t>(K) : 256ull * K) * 2 < most;
 }
 
 template <bool F16, typename TOut, int ACT, bool KEEP>
@@ -553,22 +550,16 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
                                                               gp.max_items, N, K, stage, st,       \
                                                               row_src, row_div)
     if (gp.bm == 256) {
-        if constexpr (std::is_same<TOut, _Float16>::value) {
-            if (w4_kernel_fits(N, K, row_src != nullptr, row_limit)) {
-                constexpr size_t lds = 2 * (256 + 256) * (64 + 8) * sizeof(uint16_t);
-                auto kern = grouped_gemm_w4_kernel<F16, ACT, KEEP>;
-                static PerDeviceOnce once;
-                once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
-                const int grid = static_cast<int>(align_up(static_cast<size_t>(gp.max_items), 8));
-                hipEvent_t t0, t1;
-                prof_kernel_events(stage, &t0, &t1);
-                hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, t0, t1, 0, A, W, bias, C,
-                                      pre, items, nitems, N, K, row_src, row_div,
-                                      static_cast<int>(row_limit));
-                return;
-            }
-        }
-        MOE_MFMA_SHAPE(2, 4, 4, 2);
+        auto kern = K % 64 == 0 ? grouped_gemm_w4_kernel<F16, ACT, KEEP, false>
+                                : grouped_gemm_w4_kernel<F16, ACT, KEEP, true>;
+        static PerDeviceOnce once[2];
+        once[K % 64 == 0].raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kW4Lds));
+        const int grid = static_cast<int>(align_up(static_cast<size_t>(gp.max_items), 8));
+        hipEvent_t t0, t1;
+        prof_kernel_events(stage, &t0, &t1);
+        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), kW4Lds, st, t0, t1, 0, A, W, bias, C,
+                              pre, items, nitems, N, K, row_src, row_div,
+                              static_cast<int>(row_limit));
     }
     else if (gp.bm == 64)
         MOE_MFMA_SHAPE(1, 8, 2, 1);
@@ -608,9 +599,7 @@ void launch_mfma_pair(const moe_shape &s, const uint16_t *xe, const uint16_t *W1
 void expert_gemm_kernel_name(const moe_shape &s, int which, int n_chunks, char *name, size_t len)
 {
     const GemmPlan gp = choose_gemm_plan(s, which, n_chunks);
-    const int N = which == 0 ? s.d_ff : s.d_model, K = which == 0 ? s.d_model : s.d_ff;
-    const bool w4 = gp.bm == 256 && w4_kernel_fits(N, K, which == 0, static_cast<uint64_t>(s.T));
-    std::snprintf(name, len, "%s %dx%d", w4 ? "grouped_gemm_w4_kernel" : "grouped_gemm_mfma_kernel",
+    std::snprintf(name, len, "%s %dx%d", gp.bm == 256 ? "grouped_gemm_w4_kernel" : "grouped_gemm_mfma_kernel",
                   gp.bm, gp.bn);
 }
 
@@ -620,12 +609,12 @@ moe_status launch_calib_gemm(const uint16_t *A, const uint16_t *W, _Float16 *C, 
                              const int32_t *nitems, int max_items, int N, int K, int abl, int gelu,
                              hipStream_t st)
 {
-    constexpr size_t lds = 2 * (256 + 256) * (64 + 8) * sizeof(uint16_t);
+    constexpr size_t lds = kW4Lds;
     const int grid = static_cast<int>(align_up(static_cast<size_t>(max_items), 8));
 #define MOE_CALIB_CASE(ABL_)                                                                      \
     case ABL_: {                                                                                  \
-        auto k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, ABL_>;                   \
-        auto k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, ABL_>;                   \
+        auto k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, false, ABL_>;                   \
+        auto k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, false, ABL_>;                   \
         static PerDeviceOnce once1, once0;                                                        \
         once1.raise_lds(reinterpret_cast<const void *>(k1), static_cast<int>(lds));               \
         once0.raise_lds(reinterpret_cast<const void *>(k0), static_cast<int>(lds));               \
@@ -666,7 +655,7 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_chunks)
         gp.concurrent = 256;
     } else {
         const int64_t big_tiles = (chunk_rows / 256 + s.E / 2) * ((N + 255) / 256);
-        if (big_tiles >= 768) {
+        if (big_tiles >= 768 && w4_kernel_fits(N, K, which == 0, static_cast<uint64_t>(s.T))) {
             gp.bm = 256; gp.bn = 256; gp.concurrent = 32;
         } else if (K >= 2048 && N >= 256 && chunk_rows / s.E < 96 &&
                    (chunk_rows / 128 + s.E / 2) * ((N + 255) / 256) < 256) {

@@ -4,29 +4,38 @@
 // with an epilogue of its own.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 // ---------------------------------------------------------------- 256 x 256 GEMM, four wavefronts
-// The same product as grouped_gemm_mfma_kernel for 256 x 256 output tiles, fp16 output and a
-// contraction depth that is a multiple of 64, laid out for one wavefront per SIMD:
-//  * four wavefronts of 128 x 128 (2 x 2): every operand fragment read from LDS feeds four
-//    MFMAs (128 KB of LDS reads per 64-deep stage against 196 KB for eight wavefronts of
-//    128 x 64); the 16 accumulators of a wavefront (256 registers) are pinned to AGPRs, which
-//    leaves the 256 VGPRs to fragments and staging;
-//  * TWO stages of global loads in flight in registers (2 x 64 VGPRs) beside the double-buffered
-//    LDS tiles, through buffer loads whose per-lane byte offsets never change (the stage goes
-//    into the scalar offset): no address arithmetic in the loop;
-//  * one barrier per stage, and every memory instruction of a stage (32 LDS fragment reads,
-//    16 LDS writes, 16 global loads per wavefront) issued singly between two MFMAs in a fixed
-//    order: fragment reads one 16-deep step ahead, the LDS writes of the next stage spread
-//    over the first three steps (all before the barrier), a register reloaded after it was
-//    written.  The MFMAs are inline assembly so that the accumulators stay in AGPRs and the
-//    order holds; nothing depends on an MFMA result before the loop ends.
-//  * The tile leaves through LDS: every wavefront writes its 128 x 128 sub-tile to a patch of
-//    its own and stores it as whole lines, 16 bytes per lane.
-// Loads past the last stage fetch the last stage again (never used) instead of branching.
+// 256 x 256 output tiles, 64-deep stages, one wavefront per SIMD:
+//  * four wavefronts of 128 x 128 (2 x 2) of 16 x 16 x 32 matrix instructions, the 64
+//    accumulators of a wavefront (256 registers) pinned to AGPRs; an operand fragment read from
+//    LDS feeds eight of them.
+//  * Operands go from global memory straight into LDS (16-byte buffer loads to LDS: no staging
+//    registers, no LDS write instructions) through a ring of five 32 KiB units (256 rows x 64 deep
+//    of one operand), all 160 KiB of it: while stage k is multiplied, the token rows of stage
+//    k + 2 and the weights of stage k + 1 .. k + 2 are on their way.  A unit is written linearly,
+//    1 KiB per instruction, so the 16-byte pieces of a row are XOR-swizzled with the row on the
+//    global side: fragment reads are free of bank conflicts.
+//  * One barrier per stage, in its middle: behind it the next stage's fragments are read while
+//    the second half is multiplied, and the finished stage's units are refilled.
+//  * Every memory instruction is issued singly between two matrix instructions in a fixed order;
+//    those are inline assembly so that the accumulators stay in AGPRs and the order holds.
+//    Neighbouring ones share an operand (serpentine order).
+// What bounds it is power: the chip lowers its clock with the energy per operation (the 32 x 32 x
+// 16 form of this kernel kept the matrix cores busy for 81 % of the cycles at 1.33 GHz).  At
+// 65536 rows: N = 2048, K = 8192 1527-1611 us (1780-1835 with 32 x 32 x 16 instructions and
+// operands staged through registers; a vendor library's dense product 1506), N = 8192, K = 2048
+// 1674-1750 (1942-1985).  With the same tile for every block it takes 1290: the rest is the way
+// from HBM.
 // Operand addresses are 32-bit byte offsets into two buffer resources (the tile's rows, or
 // the whole token matrix when the rows are gathered through row_src; the expert's weight
 // matrix), which the host checks fit.
+constexpr size_t kW4Lds = 5 * 32768;
+
 #define MOE_LGKM0() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
+#define MOE_VMCNT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n) : "memory")
 #define MOE_SB() __builtin_amdgcn_sched_barrier(0)
 #define MOE_BAR()                                                                                 \
     do {                                                                                         \
@@ -36,11 +45,36 @@
     } while (0)
 
 template <bool F16>
-__device__ __forceinline__ void mfma_32x32x16_agpr(f32x16 &acc, const u32x4 &a, const u32x4 &b)
+__device__ __forceinline__ void mfma_16x16x32_agpr(f32x4 &acc, const u32x4 &a, const u32x4 &b)
 {
     if constexpr (F16)
-        asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
     else
-        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 
+// 16 bytes per lane from base + voff + soff to LDS at `at` + 16 * lane.  Written out because
+// behind the compiler's builtin every later LDS read waits for all loads; completion is counted
+// by hand (MOE_VMCNT).  The range check that turns a load into zeros sees voff only.
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rs, int voff, uint32_t at, int soff)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %3 offen lds"
+                 ::"v"(voff), "s"(rs), "s"(at), "s"(soff) : "memory");
+#endif
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void *)p));
+}
+
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_each(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F f)
+{
+    static_for_each(std::make_integer_sequence<int, N>{}, f);
+}

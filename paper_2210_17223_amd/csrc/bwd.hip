@@ -644,27 +644,23 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(
 }
 
 // ---------------------------------------------------------------- weight gradient, 256 x 256 tiles
-// The same product on the four-wavefront layout of gemm_w4.h, for layers whose weight
-// gradients have enough 256 x 256 tiles: four wavefronts of 128 x 128 with their accumulators in
-// AGPRs, two 64-row stages of buffer loads in flight in registers, double-buffered LDS stages
-// [64 rows][256 columns] per operand (64-byte pieces XOR-swizzled with the row, as above), the
-// MFMA fragments through the transposing LDS read, every memory instruction issued between
-// MFMAs in a fixed order.  The operands' buffer resources end with the expert's last row, so
-// rows past it -- and whole stages past the last one -- read as zeros: no clamping, no tail
-// code.  M and N are multiples of 256 (the host checks).
-__device__ __forceinline__ void mfma_32x32x16_agpr(f32x16 &acc, const u32x4 &a, const u32x4 &b)
-{
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-
+// The same product on the four-wavefront layout of gemm_w4.h (operands straight into an LDS ring
+// of five 32 KiB units, accumulators in AGPRs, every memory instruction between two matrix
+// instructions), for layers whose weight gradients have enough 256 x 256 tiles.  A unit is 64
+// rows x 256 columns of one operand; the fragments of the 16 x 16 x 32 instruction (eight rows
+// of one column per lane) are two transposing LDS reads each.  The 64-byte pieces of a row are
+// XOR-swizzled with the row's low two bits and its 32-byte halves with bit 3, so that the four
+// rows of a 16-lane group, and two groups eight rows apart, fall into different banks.  The
+// operands' buffer resources end with the expert's last row: rows past it -- and whole stages
+// past the last one -- read as zeros, without clamping or tail code.
+// AF16: A holds fp16 values, rounded to bf16 between the LDS read and the multiply.
 template <bool AF16>
 __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, float *__restrict__ C,
     const int32_t *__restrict__ offsets, int E, int M, int N, int tiles_m, int tiles_n)
 {
-    constexpr int TM = 4, TN = 4, NV = 8;
+    constexpr int TM = 8, TN = 8, UNIT = 32768;
     constexpr int kRow = 512;                     // bytes of a 256-column LDS row
-    constexpr int kOp = 64 * kRow;                // bytes of one operand's stage
     int expert, m0, n0;
     {
         const int total = E * tiles_m * tiles_n;
@@ -680,18 +676,19 @@ __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
     const int r0 = offsets[expert], r1 = offsets[expert + 1];
     const int KT = (r1 - r0 + 63) / 64;
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    char *lds = reinterpret_cast<char *>(smem);   // A stages at 0 and kOp, B stages at 2 kOp and 3 kOp
+    char *const lds = reinterpret_cast<char *>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave & 1, wn = wave >> 1;
+    const int fr = lane & 15, oct = lane >> 4;
 
-    f32x16 acc[TN][TM];
+    f32x4 acc[TN][TM];
 #pragma unroll
     for (int i = 0; i < TN; ++i)
 #pragma unroll
         for (int j = 0; j < TM; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+            for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f;
 
     if (KT > 0) {
         // an operand's resource: from the tile's first column of the expert's first row to the end
@@ -703,219 +700,128 @@ __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
         const __amdgpu_buffer_rsrc_t rsb = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint16_t *>(B + static_cast<size_t>(r0) * N + n0), 0,
             (rows * static_cast<unsigned>(N) - static_cast<unsigned>(n0)) * 2u, 0x00020000);
-        // staging: vector q of a stage is row tid / 32 + 8 q, 16-byte piece tid % 32 of the row
-        const int srow = tid >> 5, piece = tid & 31;
-        const int a_voff = (srow * M + piece * 8) * 2, b_voff = (srow * N + piece * 8) * 2;
-        const int a_rowstep = 8 * M * 2, b_rowstep = 8 * N * 2;       // vector q -> q + 1
-        const int a_stage = 64 * M * 2, b_stage = 64 * N * 2;         // stage kt -> kt + 1
-        const int st_off = srow * kRow + (((piece >> 2) ^ (srow & 3)) << 6) + ((piece & 3) << 4);
-        // fragments: lane = 16 g + i reads row 8 (g / 2) + i / 4 (+ 4 for the upper half) of the
-        // 16-row step, columns 16 (g % 2) + 4 (i % 4) .. + 3 of the 32-column sub-tile t, whose
-        // 64-byte piece sits at (t ^ swizzle) inside the wavefront's 256-byte half of the row
-        const int fi = lane & 15, fg = lane >> 4;
-        const int frow = 8 * (fg >> 1) + (fi >> 2), fcol = 16 * (fg & 1) + 4 * (fi & 3), fswz = fi >> 2;
-        int a_fr[TM], b_fr[TN];
+        // load q of this wavefront's eight of a unit: rows wave * 16 + 2 q and + 1, 32 pieces of 16
+        // bytes each; lane l lands at row l / 32, place l % 32
+        int a_src[8], b_src[8];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            a_fr[t] = frow * kRow + wm * 256 + ((t ^ fswz) << 6) + fcol * 2;
-            b_fr[t] = 2 * kOp + frow * kRow + wn * 256 + ((t ^ fswz) << 6) + fcol * 2;
+        for (int q = 0; q < 8; ++q) {
+            const int row = wave * 16 + q * 2 + (lane >> 5), place = lane & 31;
+            const int piece = (place ^ ((row & 3) << 2)) ^ (((row >> 3) & 1) << 1);
+            a_src[q] = (row * M + piece * 8) * 2;
+            b_src[q] = (row * N + piece * 8) * 2;
         }
-        u32x4 ra[2][NV], rb[2][NV];
+        const int a_stage = 64 * M * 2, b_stage = 64 * N * 2;         // stage kt -> kt + 1
+        // fragment of the 16-column sub-tile t, half h, of a 32-row step: lane = 16 oct + i reads
+        // row 8 oct + i / 4 (+ 4 h), columns 4 (i % 4) .. + 3
+        const int frow = 8 * oct + (fr >> 2);
+        const int fbase = frow * kRow + (fr & 3) * 8;
+        int fcol[4];                                                  // sub-tiles 2 u and 2 u + 1
+#pragma unroll
+        for (int u = 0; u < 4; ++u) fcol[u] = (u ^ (fr >> 2)) * 64 + (oct & 1) * 32;
         u32x4 bf[2][TN], af[2][TM];
+        const uint32_t dest = lds_address(lds) + wave * 8192;
 // (the whole offset goes into the per-lane operand: the range check that turns rows past the
 // expert's end into zeros does not see the scalar offset)
-#define WG4_LDA(set, q, kt_)                                                                      \
-    ra[set][q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(                \
-                                               rsa, a_voff + ((kt_) * a_stage + (q) * a_rowstep), 0, 0))
-#define WG4_LDB(set, q, kt_)                                                                      \
-    rb[set][q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(                \
-                                               rsb, b_voff + ((kt_) * b_stage + (q) * b_rowstep), 0, 0))
-#define WG4_STA(set, q, buf)                                                                      \
-    {                                                                                            \
-        u32x4 av_ = ra[set][q];                                                                  \
-        if constexpr (AF16)                                                                      \
-            av_ = (u32x4){f16x2_to_bf16x2(av_[0]), f16x2_to_bf16x2(av_[1]),                      \
-                          f16x2_to_bf16x2(av_[2]), f16x2_to_bf16x2(av_[3])};                     \
-        *reinterpret_cast<u32x4 *>(lds + (buf) * kOp + st_off + (q) * 8 * kRow) = av_;           \
-    }
-#define WG4_STB(set, q, buf)                                                                      \
-    *reinterpret_cast<u32x4 *>(lds + (2 + (buf)) * kOp + st_off + (q) * 8 * kRow) = rb[set][q]
-// half h (0: rows k .. k + 3, 1: rows k + 4 .. k + 7 of the lane's eight) of fragment t, step ks
-#define WG4_RDA(slot_, t, h, buf, ks)                                                             \
-    {                                                                                            \
-        const u32x2 v_ = lds_read_tr16(reinterpret_cast<const uint16_t *>(                      \
-            lds + a_fr[t] + (buf) * kOp + (ks) * 16 * kRow + (h) * 4 * kRow));                   \
-        af[slot_][t][2 * (h)] = v_[0];                                                           \
-        af[slot_][t][2 * (h) + 1] = v_[1];                                                       \
-    }
-#define WG4_RDB(slot_, t, h, buf, ks)                                                             \
-    {                                                                                            \
-        const u32x2 v_ = lds_read_tr16(reinterpret_cast<const uint16_t *>(                      \
-            lds + b_fr[t] + (buf) * kOp + (ks) * 16 * kRow + (h) * 4 * kRow));                   \
-        bf[slot_][t][2 * (h)] = v_[0];                                                           \
-        bf[slot_][t][2 * (h) + 1] = v_[1];                                                       \
-    }
-// read v (0 .. 15) of a step: B fragments first (v < 8), halves interleaved
-#define WG4_RD(slot_, v, buf, ks)                                                                 \
-    do {                                                                                         \
-        if constexpr ((v) < 8) WG4_RDB(slot_, (v) >> 1, (v) & 1, buf, ks)                        \
-        else WG4_RDA(slot_, ((v) - 8) >> 1, (v) & 1, buf, ks)                                    \
-    } while (0)
-#define WG4_WR(set, v, buf)                                                                       \
-    do {                                                                                         \
-        if constexpr ((v) < 8) WG4_STA(set, (v), buf) else WG4_STB(set, (v) - 8, buf);           \
-    } while (0)
-#define WG4_LD(set, v, kt_)                                                                       \
-    do {                                                                                         \
-        if constexpr ((v) < 8) WG4_LDA(set, (v), kt_); else WG4_LDB(set, (v) - 8, kt_);          \
-    } while (0)
-#define WG4_MM(slot_, m)                                                                          \
-    do {                                                                                         \
-        constexpr int i_ = (m) & 3, j_ = (m) >> 2;                                               \
-        mfma_32x32x16_agpr(acc[i_][j_], bf[slot_][i_], af[slot_][j_]);                    \
-    } while (0)
-// MFMA m, the fragment read m of the next step, and after every second MFMA one of the eight
-// write / load instructions of the step
-#define WG4_PAIR(slot_, m, F)                                                                     \
-    WG4_MM(slot_, m);                                                                            \
-    F(std::integral_constant<int, (m)>{});                                                       \
-    if constexpr (((m) & 1) != 0) F(std::integral_constant<int, 16 + ((m) >> 1)>{});             \
-    MOE_SB();
-#define WG4_KSTEP(slot_, F)                                                                       \
-    {                                                                                            \
-        WG4_PAIR(slot_, 0, F) WG4_PAIR(slot_, 1, F) WG4_PAIR(slot_, 2, F) WG4_PAIR(slot_, 3, F)   \
-        WG4_PAIR(slot_, 4, F) WG4_PAIR(slot_, 5, F) WG4_PAIR(slot_, 6, F) WG4_PAIR(slot_, 7, F)   \
-        WG4_PAIR(slot_, 8, F) WG4_PAIR(slot_, 9, F) WG4_PAIR(slot_, 10, F) WG4_PAIR(slot_, 11, F) \
-        WG4_PAIR(slot_, 12, F) WG4_PAIR(slot_, 13, F) WG4_PAIR(slot_, 14, F) WG4_PAIR(slot_, 15, F) \
-    }
-// Stage kt from LDS buffer kt & 1; register set SET (stage kt + 1) goes to the other buffer
-// (writes 6 / 5 / 5 over steps 0 .. 2) and is refilled with stage kt + 3 (loads 2 / 3 / 3 / 8).
-#define WG4_STAGE(kt_, SET)                                                                       \
-    {                                                                                            \
-        const int kt = (kt_);                                                                    \
-        const int buf = kt & 1;                                                                  \
-        {                                                                                        \
-            auto mem0 = [&](auto mc) {                                                           \
-                constexpr int m = decltype(mc)::value;                                           \
-                if constexpr (m < 16) WG4_RD(1, m, buf, 1);                                      \
-                else if constexpr (m < 22) WG4_WR(SET, m - 16, buf ^ 1);                         \
-                else WG4_LD(SET, m - 22, kt + 3);                                                \
-            };                                                                                   \
-            WG4_KSTEP(0, mem0)                                                                   \
-        }                                                                                        \
-        {                                                                                        \
-            auto mem1 = [&](auto mc) {                                                           \
-                constexpr int m = decltype(mc)::value;                                           \
-                if constexpr (m < 16) WG4_RD(0, m, buf, 2);                                      \
-                else if constexpr (m < 21) WG4_WR(SET, m - 16 + 6, buf ^ 1);                     \
-                else WG4_LD(SET, m - 21 + 2, kt + 3);                                            \
-            };                                                                                   \
-            WG4_KSTEP(1, mem1)                                                                   \
-        }                                                                                        \
-        {                                                                                        \
-            auto mem2 = [&](auto mc) {                                                           \
-                constexpr int m = decltype(mc)::value;                                           \
-                if constexpr (m < 16) WG4_RD(1, m, buf, 3);                                      \
-                else if constexpr (m < 21) WG4_WR(SET, m - 16 + 11, buf ^ 1);                    \
-                else WG4_LD(SET, m - 21 + 5, kt + 3);                                            \
-            };                                                                                   \
-            WG4_KSTEP(0, mem2)                                                                   \
-        }                                                                                        \
-        MOE_LGKM0();                                                                             \
-        MOE_BAR();                                                                               \
-        {                                                                                        \
-            auto mem3 = [&](auto mc) {                                                           \
-                constexpr int m = decltype(mc)::value;                                           \
-                if constexpr (m < 16) WG4_RD(0, m, buf ^ 1, 0);                                  \
-                else WG4_LD(SET, m - 16 + 8, kt + 3);                                            \
-            };                                                                                   \
-            WG4_KSTEP(1, mem3)                                                                   \
-        }                                                                                        \
-    }
-        // prologue: stage 0 through set 0 into LDS buffer 0, stage 1 in set 1, stage 2 in set 0
-#pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            WG4_LDA(0, q, 0);
-            WG4_LDB(0, q, 0);
-        }
-#pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            WG4_LDA(1, q, 1);
-            WG4_LDB(1, q, 1);
-        }
-#pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            WG4_STA(0, q, 0)
-            WG4_STB(0, q, 0);
-        }
-#pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            WG4_LDA(0, q, 2);
-            WG4_LDB(0, q, 2);
-        }
-        MOE_LGKM0();
-        MOE_BAR();
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            WG4_RDB(0, t, 0, 0, 0)
-            WG4_RDB(0, t, 1, 0, 0)
-            WG4_RDA(0, t, 0, 0, 0)
-            WG4_RDA(0, t, 1, 0, 0)
-        }
-        {
-            int k2 = 0;
-            for (; k2 + 1 < KT; k2 += 2) {
-                WG4_STAGE(k2, 1)
-                WG4_STAGE(k2 + 1, 0)
+#define WG4_LDA(q, unit, kt_) load_to_lds(rsa, a_src[q] + (kt_) * a_stage, dest + (unit) + (q) * 1024, 0)
+#define WG4_LDB(q, unit, kt_) load_to_lds(rsb, b_src[q] + (kt_) * b_stage, dest + (unit) + (q) * 1024, 0)
+        // read v (0 .. 31) of a step's fragments: B first, halves interleaved
+        auto read = [&](auto slotc, auto vc, int bat, int aat, int ks) {
+            constexpr int s = decltype(slotc)::value, v = decltype(vc)::value;
+            constexpr int t = (v & 15) >> 1, h = v & 1;
+            const int at = (v < 16 ? bat + wn * 256 : aat + wm * 256) + ks * 32 * kRow + h * 4 * kRow + fbase +
+                           (fcol[t >> 1] ^ ((t & 1) * 32));
+            const u32x2 q = lds_read_tr16(reinterpret_cast<const uint16_t *>(lds + at));
+            if constexpr (v < 16) {
+                bf[s][t][2 * h] = q[0];
+                bf[s][t][2 * h + 1] = q[1];
+            } else {
+                af[s][t][2 * h] = q[0];
+                af[s][t][2 * h + 1] = q[1];
             }
-            if (k2 < KT) WG4_STAGE(k2, 1)
+        };
+        // 64 matrix instructions of a 32-row step; AF16: column j's fragment is converted before its
+        // first use
+        auto step = [&](auto slotc, auto mem) {
+            constexpr int s = decltype(slotc)::value;
+            static_for<64>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                constexpr int j = m >> 3, i = (j & 1) != 0 ? 7 - (m & 7) : (m & 7);
+                if constexpr (AF16 && (m & 7) == 0) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) af[s][j][c] = f16x2_to_bf16x2(af[s][j][c]);
+                }
+                mfma_16x16x32_agpr<false>(acc[i][j], bf[s][i], af[s][j]);
+                mem(mc);
+                MOE_SB();
+            });
+        };
+        using std::integral_constant;
+        int ua = 0, ub = UNIT, ua1 = 2 * UNIT, ub1 = 3 * UNIT, uf = 4 * UNIT;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) WG4_LDA(q, ua, 0);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) WG4_LDB(q, ub, 0);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) WG4_LDA(q, ua1, 1);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) WG4_LDB(q, ub1, 1);
+        MOE_VMCNT(16);
+        MOE_BAR();
+        static_for<32>([&](auto v) { read(integral_constant<int, 0>{}, v, ub, ua, 0); });
+        for (int kt = 0; kt < KT; ++kt) {
+            step(integral_constant<int, 0>{}, [&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                if constexpr (m < 32) read(integral_constant<int, 1>{}, mc, ub, ua, 1);
+                else if constexpr (m % 4 == 0) WG4_LDA((m - 32) / 4, uf, kt + 2);
+            });
+            MOE_LGKM0();
+            MOE_VMCNT(8);                        // stage kt + 1 has landed; A of kt + 2 may be on its way
+            MOE_BAR();
+            step(integral_constant<int, 1>{}, [&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                if constexpr (m < 32) read(integral_constant<int, 0>{}, mc, ub1, ua1, 0);
+                if constexpr (m < 32 && m % 4 == 1) WG4_LDB(m / 4, ua, kt + 2);
+            });
+            const int na1 = uf, nb1 = ua, nf = ub;
+            ua = ua1;
+            ub = ub1;
+            ua1 = na1;
+            ub1 = nb1;
+            uf = nf;
         }
-#undef WG4_STAGE
-#undef WG4_KSTEP
-#undef WG4_PAIR
-#undef WG4_MM
-#undef WG4_LD
-#undef WG4_WR
-#undef WG4_RD
-#undef WG4_RDB
-#undef WG4_RDA
-#undef WG4_STB
-#undef WG4_STA
 #undef WG4_LDB
 #undef WG4_LDA
+        MOE_VMCNT(0);
         MOE_LGKM0();
         MOE_BAR();
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     }
 
-    // acc[i][j][4*g + c]: column n0 + (wn*TN + i)*32 + 8*g + 4*(lane/32) + c,
-    //                     row m0 + (wm*TM + j)*32 + lane%32.
-    // The tile leaves through LDS, 32 columns of the wavefront's 128 x 128 at a time (a patch of
-    // 128 rows, pitch 144 bytes, per wavefront), as whole 128-byte lines, 16 bytes per lane:
-    // stores straight from the registers would put 32 bytes into each of 32 lines per instruction.
+    // acc[i][j][c]: column n0 + wn * 128 + i * 16 + oct * 4 + c, row m0 + wm * 128 + j * 16 + fr.
+    // The tile leaves through LDS, 64 columns of the wavefront's 128 x 128 at a time (a patch of
+    // 128 rows, pitch 272 bytes, per wavefront), as whole lines, 16 bytes per lane.
     float *Ce = C + static_cast<size_t>(expert) * M * N;
-    const int fr = lane & 31;
-    constexpr int PITCH = 144;
-    char *patch = reinterpret_cast<char *>(smem) + wave * (TM * 32) * PITCH;
+    constexpr int PITCH = 272;
+    char *patch = lds + wave * 128 * PITCH;
 #pragma unroll
-    for (int i = 0; i < TN; ++i) {
+    for (int half = 0; half < 2; ++half) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int i = 0; i < TN / 2; ++i) {
 #pragma unroll
             for (int j = 0; j < TM; ++j)
-                *reinterpret_cast<float4 *>(patch + (j * 32 + fr) * PITCH + (8 * g + 4 * (lane >> 5)) * 4) =
-                    make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
-                                acc[i][j][4 * g + 3]);
+                *reinterpret_cast<f32x4 *>(patch + (j * 16 + fr) * PITCH + (i * 16 + 4 * oct) * 4) =
+                    acc[half * 4 + i][j];
             MOE_SB();      // a few accumulator registers at a time leave the AGPRs
         }
         MOE_LGKM0();
         __builtin_amdgcn_wave_barrier();
-        const int n = n0 + (wn * TN + i) * 32 + (lane & 7) * 4;
+        const int n = n0 + wn * 128 + half * 64 + (lane & 15) * 4;
 #pragma unroll 8
-        for (int it = 0; it < TM * 4; ++it) {
-            const int rr = it * 8 + (lane >> 3);
-            const float4 q = *reinterpret_cast<const float4 *>(patch + rr * PITCH + (lane & 7) * 16);
-            *reinterpret_cast<float4 *>(Ce + static_cast<size_t>(m0 + wm * TM * 32 + rr) * N + n) = q;
+        for (int it = 0; it < 32; ++it) {
+            const int rr = it * 4 + (lane >> 4);
+            const float4 q = *reinterpret_cast<const float4 *>(patch + rr * PITCH + (lane & 15) * 16);
+            const int m = m0 + wm * 128 + rr;
+            if (m < M && n < N) *reinterpret_cast<float4 *>(Ce + static_cast<size_t>(m) * N + n) = q;
         }
         MOE_LGKM0();
         __builtin_amdgcn_wave_barrier();
@@ -1266,12 +1172,12 @@ void launch_wgrad(const uint16_t *A, const uint16_t *B, float *C, const int32_t 
                   int N, int64_t max_rows, int stage, hipStream_t st)
 {
     hipEvent_t t0, t1;
-    // 256 x 256 tiles on four wavefronts when they divide the matrix, fill the chip, and the
+    // 256 x 256 tiles on four wavefronts when they fit the matrix, fill the chip, and the
     // buffer offsets (an expert's rows times the row length, in bytes) stay below 2^31
     const uint64_t span = static_cast<uint64_t>(max_rows + 192) * static_cast<uint64_t>(std::max(M, N)) * 2;
     if (M % 256 == 0 && N % 256 == 0 && static_cast<int64_t>(E) * (M / 256) * (N / 256) >= 768 &&
         span < (1ull << 31)) {
-        constexpr size_t kLds4 = 4 * 64 * 512;
+        constexpr size_t kLds4 = kW4Lds;
         auto kern = wgrad_w4_kernel<AF16>;
         static PerDeviceOnce once;
         once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kLds4));

@@ -749,6 +749,9 @@ __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
                 if constexpr (AF16 && (m & 7) == 0) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) af[s][j][c] = f16x2_to_bf16x2(af[s][j][c]);
+                    // two wait states between a vector instruction's result and the matrix
+                    // instruction that reads it (the compiler does not see that one)
+                    asm volatile("s_nop 1" : "+v"(af[s][j]));
                 }
                 mfma_16x16x32_agpr<false>(acc[i][j], bf[s][i], af[s][j]);
                 mem(mc);

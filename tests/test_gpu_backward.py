@@ -181,6 +181,21 @@ def test_backward_with_empty_experts_and_gate_bias(d, h, E, T, C):
             assert not got["dW1"].reshape(li.W1.shape)[e].any() and not got["dW2"].reshape(li.W2.shape)[e].any()
 
 
+def test_kept_activations_through_the_large_weight_gradient_tiles():
+    """dW2 from the kept fp16 activations, rounded to bf16 between the LDS read and the multiply, on
+    256 x 256 tiles (64 experts x 3 x 4 tiles): against the oracle, expert by expert.  An element sums
+    at most 66 products of two factors rounded to bf16 (relative error up to 2 x 2^-9 each): few enough
+    that the largest elements carry an error of their own size, so the bound has a part relative to
+    the element (2^-7, twice one product's) beside TOL of the expert's RMS, as for the small experts
+    above."""
+    li = wl.make_layer(wl.scaled("gpt2s_moe", T=2100, d=768, h=1024, E=64, k=2, cf=1.0), seed=9)
+    got, o = run_backward(li, keep=True)
+    for n, shape in (("dW1", li.W1.shape), ("dW2", li.W2.shape)):
+        for e in range(li.E):
+            ref, err = getattr(o, n)[e], np.abs(got[n].reshape(shape)[e] - getattr(o, n)[e])
+            assert (err <= 2.0 ** -7 * np.abs(ref) + TOL * np.sqrt(np.mean(ref ** 2))).all(), (n, e)
+
+
 def test_kept_buffers_come_together():
     li = wl.make_layer(wl.scaled("gpt2s_moe", T=64, d=64, h=64, E=4), seed=0)
     s = shape_of(li)

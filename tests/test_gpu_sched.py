@@ -106,3 +106,23 @@ def test_estimate_of_an_empty_batch_and_unprofiled_paths():
     moe.moe_popularity_estimate(s, hist, 10, top_e, top_q, S)         # nothing profiled: all zero
     torch.cuda.synchronize()
     assert not S.cpu().numpy().any()
+
+
+@pytest.mark.parametrize("L,T0,reps,E,k,l", [
+    (5, 1501, 3, 16, 2, 3),          # a table of 65536 counters: 16-bit counters in LDS
+    (4, 2501, 2, 32, 3, 3),          # 2^20 counters, more of them in use than the LDS hash has places
+    (300, 1, 70001, 3, 1, 1),        # one counter takes every token: shares end before 16 bits do
+], ids=["counters_in_lds", "hashed", "sixteen_bit_limit"])
+def test_tables_of_many_tokens(L, T0, reps, E, k, l):
+    """Every token repeated `reps` times: the oracle's counts of the distinct ones, times reps."""
+    rng = np.random.default_rng(11)
+    sel = np.argsort(rng.random((L, T0, E)), axis=2)[:, :, :k].astype(np.int32)
+    if T0 > 100:
+        sel[1, 5, 0], sel[L - 1, 17, k - 1] = -1, E
+    s = moe.PathShape(L, E, k, l)
+    P, tables = moe.moe_path_count(s), L - l
+    counts = torch.zeros(tables * P * E, dtype=torch.int32, device=DEV)
+    moe.moe_path_profile(s, torch.from_numpy(np.tile(sel, (1, reps, 1))).to(DEV), T0 * reps, counts)
+    got = counts.cpu().numpy().view(np.uint32).reshape(tables, P, E).astype(np.int64)
+    for a, want in enumerate(so.profile_counts(sel, l, E)):
+        assert np.array_equal(got[a], want * reps), a

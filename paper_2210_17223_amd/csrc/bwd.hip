@@ -12,9 +12,8 @@
 //                    dx = sum of the token's dxe rows + dz Wg^T
 //   dwg              dWg = x^T dz (partial sums over token ranges, then a fixed-order sum)
 //
-// The contractions use 128 x 128 (or 128 x 256) output tiles of 32x32x16 bf16 MFMAs fed
-// through a double-buffered LDS tile, like the forward's expert GEMM; a row-grouped GEMM walks
-// the forward's kind of work list, a weight-gradient GEMM contracts over one expert's rows.
+// The row-grouped GEMMs run on the forward's four-wavefront kernels (gemm_w4.h) and its kind of
+// work list; a weight-gradient GEMM contracts over one expert's rows.
 #include "common.h"
 #include "moe_train.h"
 
@@ -34,9 +33,8 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 
 #include "gemm_w4.h"
 
-constexpr int kBM = 128, kBK = 64, kLD = kBK + 8;
-// output tile 128 x (64 WN): WN = 2 (four wavefronts) or 4 (eight)
-constexpr size_t gemm_lds(int wn) { return 2 * (kBM + 64 * wn) * kLD * sizeof(uint16_t); }
+constexpr int kBM = 128, kBN = 256, kBK = 64, kLD = kBK + 8;
+constexpr size_t kGemmLds = 2 * (kBM + kBN) * kLD * sizeof(uint16_t);
 
 // Phi(v), the normal CDF, as 1 / (1 + 2^(v Q(min(v^2, 49)))) with the cubic Q of the forward's
 // GeLU (absolute error of v Phi(v) below 1.5e-5).
@@ -135,17 +133,17 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
 }
 
 // ---------------------------------------------------------------- GEMM
+// (For operands that the four-wavefront kernels' 32-bit offsets do not reach.)
 // C[r, n] = sum_k A[r, k] W[e][n, k] for the rows of one work item.
 // EPI 0: fp32 store.  EPI 1: P = acc as fp16 into Pbuf and act(acc) as bf16 into C.
 // EPI 2: acc * act'(Pbuf) as bf16 into C.
-template <int EPI, int ACT, bool KTAIL, int WN>
-__global__ __launch_bounds__(128 * WN, 2) void bwd_gemm_kernel(
+template <int EPI, int ACT, bool KTAIL>
+__global__ __launch_bounds__(512, 2) void bwd_gemm_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, void *__restrict__ Cout,
     _Float16 *__restrict__ Pbuf, const WorkItem *__restrict__ items,
     const int32_t *__restrict__ nitems, int N, int K)
 {
-    constexpr int WM = 2, TM = 2, TN = 2, NT = 128 * WN;   // 2 x WN wavefronts of 64 x 64
-    constexpr int kBN = 64 * WN;
+    constexpr int WM = 2, TM = 2, TN = 2, NT = 512;        // 2 x 4 wavefronts of 64 x 64
     constexpr int AV = kBM * 8 / NT, WV = kBN * 8 / NT;
     int expert, row0, row1, n0;
     {
@@ -314,13 +312,12 @@ __global__ __launch_bounds__(128 * WN, 2) void bwd_gemm_kernel(
     }
 }
 
-// ---------------------------------------------------------------- GEMM, 256 x 256 tiles
-// The same three products on the forward's four-wavefront layout (gemm_w4.h), for layers whose
-// row GEMMs have enough 256 x 256 tiles to fill the chip.  The tile leaves through LDS as
+// ---------------------------------------------------------------- GEMM, four wavefronts
+// The same three products on the forward's four-wavefront layout (gemm_w4.h).  The tile leaves through LDS as
 // whole lines (16-bit outputs) or straight from the registers (fp32); for EPI 2 the tile of
 // pre-activations comes in through the same LDS patch, as whole lines.
-template <int EPI, int ACT, bool KTAIL>
-__global__ __launch_bounds__(256, 1) void bwd_gemm_w4_kernel(
+template <int EPI, int ACT, bool KTAIL, int BM, int BN>
+__global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void bwd_gemm_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, void *__restrict__ Cout,
     _Float16 *__restrict__ Pbuf, const WorkItem *__restrict__ items,
     const int32_t *__restrict__ nitems, int N, int K)
@@ -336,12 +333,12 @@ __global__ __launch_bounds__(256, 1) void bwd_gemm_w4_kernel(
     MOE_LGKM0();
     MOE_BAR();
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    const int rbase = item.row0 + wm * 128;
+    const int rbase = item.row0 + wm * (BM / 2);
     if constexpr (EPI == 0) {
         float *out = static_cast<float *>(Cout);
 #pragma unroll
         for (int i = 0; i < TN; ++i) {
-            const int n = n0 + wn * 128 + i * 16 + 4 * oct;
+            const int n = n0 + wn * (BN / 2) + i * 16 + 4 * oct;
 #pragma unroll
             for (int j = 0; j < TM; ++j) {
                 const int r = rbase + j * 16 + fr;
@@ -353,15 +350,16 @@ __global__ __launch_bounds__(256, 1) void bwd_gemm_w4_kernel(
             MOE_SB();          // a few accumulator registers at a time leave the AGPRs
         }
     } else {
-        constexpr int PITCH = 272;                   // the wavefront's 128 x 128 patch of 16-bit values
-        char *patch = lds + wave * 128 * PITCH;
-        const int ncol = n0 + wn * 128 + (lane & 15) * 8;
-        // whole 256-byte row pieces between the patch and a [rows, N] matrix of 16-bit values
+        // the wavefront's BM / 2 x BN / 2 patch of 16-bit values; lanes per row, rows per instruction
+        constexpr int PITCH = BN + 16, LPR = BN / 16, RPI = 64 / LPR;
+        char *patch = lds + wave * (BM / 2) * PITCH;
+        const int ncol = n0 + wn * (BN / 2) + lane % LPR * 8;
+        // whole row pieces between the patch and a [rows, N] matrix of 16-bit values
         auto lines_out = [&](uint16_t *dst) {
 #pragma unroll 8
-            for (int it = 0; it < 32; ++it) {
-                const int rr = it * 4 + (lane >> 4);
-                const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * PITCH + (lane & 15) * 16);
+            for (int it = 0; it < BM / 2 / RPI; ++it) {
+                const int rr = it * RPI + lane / LPR;
+                const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * PITCH + lane % LPR * 16);
                 const int r = rbase + rr;
                 if (r < item.row1 && ncol < N)
                     *reinterpret_cast<u32x4 *>(dst + static_cast<size_t>(r) * N + ncol) = q;
@@ -370,13 +368,13 @@ __global__ __launch_bounds__(256, 1) void bwd_gemm_w4_kernel(
         if constexpr (EPI == 2) {
             const uint16_t *src = reinterpret_cast<const uint16_t *>(Pbuf);
 #pragma unroll 8
-            for (int it = 0; it < 32; ++it) {
-                const int rr = it * 4 + (lane >> 4);
+            for (int it = 0; it < BM / 2 / RPI; ++it) {
+                const int rr = it * RPI + lane / LPR;
                 const int r = rbase + rr;
                 u32x4 q = {0u, 0u, 0u, 0u};
                 if (r < item.row1 && ncol < N)
                     q = *reinterpret_cast<const u32x4 *>(src + static_cast<size_t>(r) * N + ncol);
-                *reinterpret_cast<u32x4 *>(patch + rr * PITCH + (lane & 15) * 16) = q;
+                *reinterpret_cast<u32x4 *>(patch + rr * PITCH + lane % LPR * 16) = q;
             }
             MOE_LGKM0();
             __builtin_amdgcn_wave_barrier();
@@ -1063,23 +1061,17 @@ struct BwdWorkspace {
     size_t bytes;
 };
 
-// 256 x 256 tiles (the four-wavefront kernel) when there are enough of them to fill the chip,
-// as in the forward; else 128-row tiles, 256 columns wide when the contraction is long enough
-// to pay for the larger tile's prologue, else 128
+// the forward's choice of tile; where the operands are past 32-bit offsets, the general kernel
 GemmPlan plan_rows(int N, int K, int64_t max_rows, int E)
 {
     GemmPlan gp;
-    const int64_t big_tiles = (max_rows / 256 + E / 2) * ((N + 255) / 256);
     constexpr uint64_t most = (1ull << 31) - 64;       // byte offsets into the operands
-    const bool fits = static_cast<uint64_t>(N) * K * 2 < most && 256ull * K * 2 < most;
-    if (big_tiles >= 768 && fits) {
-        gp.bm = 256;
-        gp.bn = 256;
-        gp.concurrent = 32;
+    if (static_cast<uint64_t>(N) * K * 2 < most && 256ull * K * 2 < most) {
+        choose_w4_tile(max_rows, E, N, K, &gp);
     } else {
         gp.bm = kBM;
-        gp.bn = (K >= 2048 && N >= 256) ? 256 : 128;
-        gp.concurrent = gp.bn == 256 ? 32 : 64;
+        gp.bn = kBN;
+        gp.concurrent = 32;
     }
     gp.tiles_n = (N + gp.bn - 1) / gp.bn;
     gp.max_row_tiles = static_cast<int32_t>((max_rows + gp.bm - 1) / gp.bm + E);
@@ -1127,18 +1119,17 @@ bool supported(const moe_shape *s)
     return s->d_model % 8 == 0 && s->d_ff % 8 == 0;
 }
 
-template <int EPI, int ACT, bool KTAIL, int WN>
+template <int EPI, int ACT, bool KTAIL>
 void launch_gemm_k(const uint16_t *A, const uint16_t *W, void *C, _Float16 *P, const WorkItem *items,
                    const int32_t *nitems, int N, int K, int grid_items, int stage, hipStream_t st)
 {
-    auto kern = bwd_gemm_kernel<EPI, ACT, KTAIL, WN>;
-    constexpr size_t kGemmLds = gemm_lds(WN);
+    auto kern = bwd_gemm_kernel<EPI, ACT, KTAIL>;
     static PerDeviceOnce once;   // raising the dynamic LDS limit: once per kernel and device
     once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kGemmLds));
     const int grid = static_cast<int>(align_up(static_cast<size_t>(grid_items), 8));
     hipEvent_t t0, t1;
     prof_kernel_events(stage, &t0, &t1);
-    hipExtLaunchKernelGGL(kern, dim3(grid), dim3(128 * WN), kGemmLds, st, t0, t1, 0, A, W, C, P, items,
+    hipExtLaunchKernelGGL(kern, dim3(grid), dim3(512), kGemmLds, st, t0, t1, 0, A, W, C, P, items,
                           nitems, N, K);
 }
 
@@ -1147,26 +1138,37 @@ void launch_gemm(const uint16_t *A, const uint16_t *W, void *C, _Float16 *P, con
                  const int32_t *nitems, int N, int K, const GemmPlan &gp, int stage, hipStream_t st)
 {
     const int grid_items = gp.max_items;
-    if (gp.bm == 256) {
-        auto kern = K % 64 == 0 ? bwd_gemm_w4_kernel<EPI, ACT, false> : bwd_gemm_w4_kernel<EPI, ACT, true>;
-        static PerDeviceOnce once[2];
-        once[K % 64 == 0].raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kW4Lds));
-        const int grid = static_cast<int>(align_up(static_cast<size_t>(grid_items), 8));
-        hipEvent_t t0, t1;
-        prof_kernel_events(stage, &t0, &t1);
-        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), kW4Lds, st, t0, t1, 0, A, W, C, P, items, nitems,
-                              N, K);
+    if (gp.w4) {
+        auto launch = [&](auto bm, auto bn, auto tail) {
+            constexpr int BM = decltype(bm)::value, BN = decltype(bn)::value;
+            auto kern = bwd_gemm_w4_kernel<EPI, ACT, decltype(tail)::value, BM, BN>;
+            constexpr size_t lds = w4_lds(BM, BN);
+            static PerDeviceOnce once;
+            once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
+            const int grid = static_cast<int>(align_up(static_cast<size_t>(grid_items), 8));
+            hipEvent_t t0, t1;
+            prof_kernel_events(stage, &t0, &t1);
+            hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, t0, t1, 0, A, W, C, P, items, nitems,
+                                  N, K);
+        };
+        auto shape = [&](auto tail) {
+            if (gp.bm == 256)
+                launch(std::integral_constant<int, 256>{}, std::integral_constant<int, 256>{}, tail);
+            else if (gp.bn == 256)
+                launch(std::integral_constant<int, 128>{}, std::integral_constant<int, 256>{}, tail);
+            else
+                launch(std::integral_constant<int, 128>{}, std::integral_constant<int, 128>{}, tail);
+        };
+        if (K % 64 == 0)
+            shape(std::false_type{});
+        else
+            shape(std::true_type{});
         return;
     }
-#define MOE_BWD_GEMM(KTAIL_, WN_)                                                                 \
-    launch_gemm_k<EPI, ACT, KTAIL_, WN_>(A, W, C, P, items, nitems, N, K, grid_items, stage, st)
-    const bool tail = K % kBK != 0;
-    if (gp.bn == 256) {
-        if (tail) MOE_BWD_GEMM(true, 4); else MOE_BWD_GEMM(false, 4);
-    } else {
-        if (tail) MOE_BWD_GEMM(true, 2); else MOE_BWD_GEMM(false, 2);
-    }
-#undef MOE_BWD_GEMM
+    if (K % kBK != 0)
+        launch_gemm_k<EPI, ACT, true>(A, W, C, P, items, nitems, N, K, grid_items, stage, st);
+    else
+        launch_gemm_k<EPI, ACT, false>(A, W, C, P, items, nitems, N, K, grid_items, stage, st);
 }
 
 // dW[e] [M][N] = A[rows of e]^T B[rows of e] from row-major operands

@@ -62,11 +62,47 @@ struct WorkItem {
 // Tile shape and work-list bounds of one of the two expert GEMMs.
 struct GemmPlan {
     int32_t bm, bn;          // rows / columns per output tile
+    bool w4 = false;         // the four-wavefront kernels (gemm_w4.h)
     int32_t tiles_n;         // column tiles
     int32_t max_row_tiles;   // upper bound of row tiles per chunk
     int32_t max_items;       // upper bound of work items per chunk
     int32_t concurrent;      // work items in flight per XCD (sets the panel width)
 };
+// Tile of a row-grouped GEMM on the four-wavefront kernels (gemm_w4.h): `rows` rows in all over E
+// experts.  256 x 256 where there are many such tiles and a contraction that pays for their prologue
+// and epilogue; else by the number of rounds the tiles take on the chip -- 256 of 256 x 256 at a
+// time, 512 of 128 x 128 (two per compute unit), and a tile's time in 64-deep stages -- with the
+// times measured over layers of 256 .. 20000 tokens (us: a 256 x 256 stage 1.25, or 1.5 once the
+// chip is full and lowers its clock, prologue and epilogue 10; a round of 128 x 128 0.85, or 0.55
+// where compute units hold one, and 3; rows that do not start on 128-byte lines cost the smaller
+// tile 1.7 times as much).  E.g. rows, E, N, K -> us of the layer with 256 x 256 / 128 x 128:
+// 24249, 8, 1152, 2560 344 / 384; 12092, 8, 1024, 2624 182 / 189; 6002, 13, 1000, 2600 176 / 195;
+// 23127, 64, 1600, 512 202 / 173; 8192, 16, 768, 3072 150 / 130; 39780, 16, 7048, 2032 2674 / 3003.
+// 128 x 256 instead of 128 x 128 for long contractions with more tiles than the chip takes one per
+// unit of (8192, 16, 768, 3072: 128 / 130; a skewed layer of K = 4096: 390 / 403; with few tiles it
+// loses: 839 tokens, K = 6920: 190 / 166).
+inline void choose_w4_tile(int64_t rows, int E, int N, int K, GemmPlan *gp)
+{
+    const int64_t tiles256 = (rows / 256 + E / 2) * ((N + 255) / 256);
+    const int64_t tiles128 = (rows / 128 + E / 2) * ((N + 127) / 128);
+    const double stages = (K + 63) / 64;
+    const double t256 = static_cast<double>((tiles256 + 255) / 256) * (stages * (tiles256 > 256 ? 1.5 : 1.25) + 10.0);
+    const double t128 = static_cast<double>((tiles128 + 511) / 512) *
+                        (stages * (tiles128 > 256 ? 0.85 : 0.55) * (K % 64 != 0 ? 1.7 : 1.0) + 3.0);
+    const bool many = tiles256 >= 768;
+    if (many ? K >= 1024 : t256 < t128) {
+        gp->bm = gp->bn = 256;
+        gp->concurrent = 32;
+    } else if (K >= 3072 && tiles128 > 400) {
+        gp->bm = 128;
+        gp->bn = 256;
+        gp->concurrent = 32;
+    } else {
+        gp->bm = gp->bn = 128;
+        gp->concurrent = 64;
+    }
+    gp->w4 = true;
+}
 GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_chunks);
 void expert_gemm_kernel_name(const moe_shape &s, int which, int n_chunks, char *name, size_t len);
 

@@ -6,13 +6,12 @@
 // table of row tiles (plan_tiles) and the grid is sized for the worst case, surplus
 // blocks exit at once.
 //
-// bf16 layers: MFMA 32x32x16 tiles.  Both operands are stored with the contraction
-// index contiguous (activations by nature, weights after moe_pack_weights), staged
-// through LDS in 64-deep stages, and the weight tile is fed as the MFMA "A" operand
+// bf16 layers: both operands are stored with the contraction index contiguous (activations by
+// nature, weights after moe_pack_weights), and the weights are fed as the MFMA "A" operand
 // so that each lane ends up with four consecutive output columns of one row.
-// grouped_gemm_w4_kernel runs the 256 x 256 output tiles of the large layers,
-// grouped_gemm_mfma_kernel the smaller tile shapes.  H and ye are kept in fp16.
-// fp32 layers: a plain LDS-tiled vector-ALU GEMM (correctness configuration).
+// grouped_gemm_w4_kernel runs tiles of 128 x 128 up to 256 x 256, grouped_gemm_stream_kernel
+// decode steps, grouped_gemm_mfma_kernel what lies between (64 x 256).  H and ye are kept in fp16.
+// fp32 layers: grouped_gemm_f32_kernel, on the fp32 matrix instruction.
 #include "common.h"
 #include <cstdio>
 
@@ -156,10 +155,6 @@ __device__ __forceinline__ f32x16 mfma_32x32x16(const u32x4 &a, const u32x4 &b, 
                                                        __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-__device__ __forceinline__ void store4(float *p, const float (&v)[4])
-{
-    *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
-}
 __device__ __forceinline__ void store4(_Float16 *p, const float (&v)[4])
 {
     f16x4 h;
@@ -382,8 +377,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_mfma_kernel(
 // ABL (measurement only, 0 in the layer): bit 0 leaves out the MFMAs, bit 1 the LDS fragment
 // reads after the first step, bit 2 the global loads and LDS writes inside the loop, bit 3 the
 // output stores.  Results are then wrong by construction; every access stays inside the buffers.
-template <bool F16, int ACT, bool KEEP, bool KTAIL, int ABL = 0>
-__global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
+template <bool F16, int ACT, bool KEEP, bool KTAIL, int BM, int BN, int ABL = 0>
+__global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void grouped_gemm_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
     const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int N, int K,
@@ -393,16 +388,16 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
 
     // Epilogue.  Every wavefront is past its last LDS read after the barrier; the matrix
     // results have left the pipeline after the no-ops (the compiler does not see through the
-    // inline assembly).  The wavefront's 128 x 128 sub-tile goes to its own patch, row pitch 272
-    // bytes, and leaves as whole lines, 16 bytes per lane.
+    // inline assembly).  The wavefront's BM / 2 x BN / 2 sub-tile goes to its own patch (16
+    // bytes of row padding) and leaves as whole lines, 16 bytes per lane.
     MOE_LGKM0();
     MOE_BAR();
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    constexpr int PITCH = 272;
-    char *patch = lds + wave * 128 * PITCH;
+    constexpr int PITCH = BN + 16, LPR = BN / 16, RPI = 64 / LPR;   // lanes per row, rows per instruction
+    char *patch = lds + wave * (BM / 2) * PITCH;
     const float *bexp = bias != nullptr ? bias + static_cast<size_t>(item.expert) * N : nullptr;
-    const int rbase = item.row0 + wm * 128;
-    const int ncol = n0 + wn * 128 + (lane & 15) * 8;
+    const int rbase = item.row0 + wm * (BM / 2);
+    const int ncol = n0 + wn * (BN / 2) + lane % LPR * 8;
 #pragma unroll
     for (int pass = KEEP ? 0 : 1; pass < 2; ++pass) {      // pass 0: pre-activations, 1: outputs
         _Float16 *out = pass == 0 ? Pre : C;
@@ -412,7 +407,7 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
             float b4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
             if (bexp != nullptr) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) b4[c] = bexp[min(n0 + wn * 128 + col + c, N - 1)];
+                for (int c = 0; c < 4; ++c) b4[c] = bexp[min(n0 + wn * (BN / 2) + col + c, N - 1)];
             }
 #pragma unroll
             for (int j = 0; j < TM; ++j) {
@@ -430,9 +425,9 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
         MOE_LGKM0();
         __builtin_amdgcn_wave_barrier();
 #pragma unroll 8
-        for (int it = 0; it < 32; ++it) {
-            const int rr = it * 4 + (lane >> 4);
-            const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * PITCH + (lane & 15) * 16);
+        for (int it = 0; it < BM / 2 / RPI; ++it) {
+            const int rr = it * RPI + lane / LPR;
+            const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * PITCH + lane % LPR * 16);
             const int r = rbase + rr;
             if (r < item.row1 && ncol < N && (!(ABL & 8) || q[0] == 0x7fc07fc1u))
                 *reinterpret_cast<u32x4 *>(out + static_cast<size_t>(r) * N + ncol) = q;
@@ -549,24 +544,36 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
     launch_mfma_cfg<F16, TOut, ACT, KEEP, WM_, WN_, TM_, TN_>(A, W, bias, C, pre, items, nitems,    \
                                                               gp.max_items, N, K, stage, st,       \
                                                               row_src, row_div)
-    if (gp.bm == 256) {
-        auto kern = K % 64 == 0 ? grouped_gemm_w4_kernel<F16, ACT, KEEP, false>
-                                : grouped_gemm_w4_kernel<F16, ACT, KEEP, true>;
-        static PerDeviceOnce once[2];
-        once[K % 64 == 0].raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kW4Lds));
-        const int grid = static_cast<int>(align_up(static_cast<size_t>(gp.max_items), 8));
-        hipEvent_t t0, t1;
-        prof_kernel_events(stage, &t0, &t1);
-        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), kW4Lds, st, t0, t1, 0, A, W, bias, C,
-                              pre, items, nitems, N, K, row_src, row_div,
-                              static_cast<int>(row_limit));
+    if (gp.w4) {
+        auto launch = [&](auto bm, auto bn, auto tail) {
+            constexpr int BM = decltype(bm)::value, BN = decltype(bn)::value;
+            auto kern = grouped_gemm_w4_kernel<F16, ACT, KEEP, decltype(tail)::value, BM, BN>;
+            constexpr size_t lds = w4_lds(BM, BN);
+            static PerDeviceOnce once;
+            once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
+            const int grid = static_cast<int>(align_up(static_cast<size_t>(gp.max_items), 8));
+            hipEvent_t t0, t1;
+            prof_kernel_events(stage, &t0, &t1);
+            hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, t0, t1, 0, A, W, bias, C, pre,
+                                  items, nitems, N, K, row_src, row_div, static_cast<int>(row_limit));
+        };
+        auto shape = [&](auto tail) {
+            if (gp.bm == 256)
+                launch(std::integral_constant<int, 256>{}, std::integral_constant<int, 256>{}, tail);
+            else if (gp.bn == 256)
+                launch(std::integral_constant<int, 128>{}, std::integral_constant<int, 256>{}, tail);
+            else
+                launch(std::integral_constant<int, 128>{}, std::integral_constant<int, 128>{}, tail);
+        };
+        if (K % 64 == 0)
+            shape(std::false_type{});
+        else
+            shape(std::true_type{});
     }
     else if (gp.bm == 64)
         MOE_MFMA_SHAPE(1, 8, 2, 1);
-    else if (gp.bn == 256)
-        MOE_MFMA_SHAPE(2, 4, 2, 2);
     else
-        MOE_MFMA_SHAPE(2, 2, 2, 2);
+        MOE_MFMA_SHAPE(2, 4, 2, 2);
 #undef MOE_MFMA_SHAPE
 }
 
@@ -599,7 +606,7 @@ void launch_mfma_pair(const moe_shape &s, const uint16_t *xe, const uint16_t *W1
 void expert_gemm_kernel_name(const moe_shape &s, int which, int n_chunks, char *name, size_t len)
 {
     const GemmPlan gp = choose_gemm_plan(s, which, n_chunks);
-    std::snprintf(name, len, "%s %dx%d", gp.bm == 256 ? "grouped_gemm_w4_kernel" : "grouped_gemm_mfma_kernel",
+    std::snprintf(name, len, "%s %dx%d", gp.w4 ? "grouped_gemm_w4_kernel" : "grouped_gemm_mfma_kernel",
                   gp.bm, gp.bn);
 }
 
@@ -613,8 +620,8 @@ moe_status launch_calib_gemm(const uint16_t *A, const uint16_t *W, _Float16 *C, 
     const int grid = static_cast<int>(align_up(static_cast<size_t>(max_items), 8));
 #define MOE_CALIB_CASE(ABL_)                                                                      \
     case ABL_: {                                                                                  \
-        auto k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, false, ABL_>;                   \
-        auto k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, false, ABL_>;                   \
+        auto k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, false, 256, 256, ABL_>;                   \
+        auto k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, false, 256, 256, ABL_>;                   \
         static PerDeviceOnce once1, once0;                                                        \
         once1.raise_lds(reinterpret_cast<const void *>(k1), static_cast<int>(lds));               \
         once0.raise_lds(reinterpret_cast<const void *>(k0), static_cast<int>(lds));               \
@@ -654,19 +661,19 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_chunks)
         gp.bm = gp.bn = kF32Tile;
         gp.concurrent = 256;
     } else {
-        const int64_t big_tiles = (chunk_rows / 256 + s.E / 2) * ((N + 255) / 256);
-        if (big_tiles >= 768 && w4_kernel_fits(N, K, which == 0, static_cast<uint64_t>(s.T))) {
-            gp.bm = 256; gp.bn = 256; gp.concurrent = 32;
-        } else if (K >= 2048 && N >= 256 && chunk_rows / s.E < 96 &&
-                   (chunk_rows / 128 + s.E / 2) * ((N + 255) / 256) < 256) {
-            // few rows per expert and fewer 128-row tiles than compute units: the GEMM
-            // streams the weights once; shorter tiles put more units on the stream and
-            // spend less of their loads on (mostly padded) rows
+        const int64_t per_expert = chunk_rows / s.E;
+        const int64_t tiles_n = (N + 255) / 256;
+        if ((chunk_rows / 64 + s.E / 2) * tiles_n >= 128 &&
+                   (per_expert < 48 || (per_expert <= 64 && (chunk_rows / 128 + s.E / 2) * tiles_n < 256))) {
+            // few rows per expert and enough 64-row tiles to keep the weight stream going: shorter
+            // tiles spend less of their loads on (mostly padded) rows (137 tokens, 16 experts, k = 3,
+            // first GEMM 1256 x 3096: 87 us of the layer, 92 with 128 x 128; 256 tokens, 8 experts,
+            // second GEMM 14336 x 4096: 1831 us of four layers, 1952)
             gp.bm = 64; gp.bn = 256; gp.concurrent = 32;
-        } else if (K >= 2048 && N >= 256) {
+        } else if (w4_kernel_fits(N, K, which == 0, static_cast<uint64_t>(s.T))) {
+            choose_w4_tile(chunk_rows, s.E, N, K, &gp);
+        } else {                       // operands past 32-bit offsets
             gp.bm = 128; gp.bn = 256; gp.concurrent = 32;
-        } else {
-            gp.bm = 128; gp.bn = 128; gp.concurrent = 64;
         }
     }
     gp.tiles_n = (N + gp.bn - 1) / gp.bn;

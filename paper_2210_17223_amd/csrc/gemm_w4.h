@@ -7,7 +7,7 @@
 #include <type_traits>
 #include <utility>
 
-// ---------------------------------------------------------------- 256 x 256 GEMM, four wavefronts
+// ---------------------------------------------------------------- GEMM tiles, four wavefronts
 // 256 x 256 output tiles, 64-deep stages, one wavefront per SIMD:
 //  * four wavefronts of 128 x 128 (2 x 2) of 16 x 16 x 32 matrix instructions, the 64
 //    accumulators of a wavefront (256 registers) pinned to AGPRs; an operand fragment read from
@@ -29,10 +29,16 @@
 // operands staged through registers; a vendor library's dense product 1506), N = 8192, K = 2048
 // 1674-1750 (1942-1985).  With the same tile for every block it takes 1290: the rest is the way
 // from HBM.
+// 128 x 256 (64 x 128 per wavefront) and 128 x 128 tiles (64 x 64) run the same loop.  128 x 256 has
+// LDS for three whole stages instead of the ring; of 128 x 128 a compute unit holds two blocks, one
+// of which multiplies through the other's prologue and epilogue.  Against 32 x 32 x 16 tiles staged
+// through registers, 8192 rows, 16 experts, us: N = 3072, K = 768 72.6 -> 57.7 (128 x 128); N = 768,
+// K = 3072 55.8 -> 40.8 (128 x 256).
 // Operand addresses are 32-bit byte offsets into two buffer resources (the tile's rows, or
 // the whole token matrix when the rows are gathered through row_src; the expert's weight
 // matrix), which the host checks fit.
-constexpr size_t kW4Lds = 5 * 32768;
+constexpr size_t w4_lds(int bm, int bn) { return (bm == bn ? 5 * bm : 3 * (bm + bn)) * 128; }
+constexpr size_t kW4Lds = w4_lds(256, 256);
 
 #define MOE_LGKM0() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
 #define MOE_VMCNT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n) : "memory")

@@ -65,10 +65,15 @@ __device__ __forceinline__ float activate(float v)
 
 // ---------------------------------------------------------------- fp32 GEMM
 // C[r, n] = act(sum_k A[r,k] B[e][k,n] + bias[e][n]); B canonical [E, K, N].
-constexpr int kF32Tile = 64;
-constexpr int kF32BK = 16;
-
-template <int ACT>
+// 2 x 2 wavefronts of TM x TN v_mfma_f32_16x16x4_f32 (fp32 products and sums, twice the rate of
+// v_fmac), 32-deep stages through a double-buffered LDS tile, PD stages of global loads in flight
+// in registers.  A lane reads four consecutive k of a token row at once and feeds them to four
+// instructions, the weights one by one at the same four k (no bank conflicts either way).
+// Small layers are bound by the latency of a few stages on a few tiles, hence the deep prefetch and
+// the 32 x 32 tile (TM = TN = 1) where 64 x 64 leaves compute units without one.
+// Layer of 512 tokens, 128 x 256, 4 experts: the two GEMMs 4.5 and 4.8 us (10.2 and 15.5 with a 4 x 4
+// register block of v_fmac per thread).
+template <int ACT, int TM, int TN>
 __global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(
     const float *__restrict__ A, const float *__restrict__ B, const float *__restrict__ bias,
     float *__restrict__ C, const WorkItem *__restrict__ items,
@@ -78,66 +83,113 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(
     const WorkItem tile = items[blockIdx.x];
     const int n0 = tile.n0;
 
-    __shared__ float As[kF32BK][kF32Tile + 4];
-    __shared__ float Bs[kF32BK][kF32Tile + 4];
-    const int tid = threadIdx.x;
-    const int tx = tid % 16, ty = tid / 16;
-    float acc[4][4] = {};
+    constexpr int BM = 32 * TM, BN = 32 * TN, BK = 32, PD = 4;
+    constexpr int LDA = BK + 4, LDB = BN + 4;
+    __shared__ __attribute__((aligned(16))) float As[2][BM * LDA];
+    __shared__ __attribute__((aligned(16))) float Bs[2][BK * LDB];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave & 1, wn = wave >> 1, r16 = lane & 15, kq = lane >> 4;
+    const int KT = (K + BK - 1) / BK;
 
-    const int a_row = tid / 4, a_k = (tid % 4) * 4;
-    const int a_row_g = min(tile.row0 + a_row, tile.row1 - 1);
-    const int b_k = tid / 16, b_n = (tid % 16) * 4;
-    const float *Bexp = B + static_cast<size_t>(tile.expert) * K * N;
-
-    // the loads of stage k0 + 16 are in flight while stage k0 is multiplied
-    float4 av, bv;
-#define MOE_F32_LOAD(k0_)                                                                        \
-    {                                                                                            \
-        av = make_float4(0.f, 0.f, 0.f, 0.f);                                                    \
-        bv = av;                                                                                 \
-        if ((k0_) + a_k < K)                                                                     \
-            av = *reinterpret_cast<const float4 *>(A + static_cast<size_t>(a_row_g) * K + (k0_) + a_k); \
-        if ((k0_) + b_k < K && n0 + b_n < N)                                                     \
-            bv = *reinterpret_cast<const float4 *>(Bexp + static_cast<size_t>((k0_) + b_k) * N + n0 + b_n); \
+    const float *a_src[TM], *b_src[TN];
+    int a_off[TM], b_off[TN], a_k[TM], b_k[TN];
+#pragma unroll
+    for (int q = 0; q < TM; ++q) {
+        const int v = tid + 256 * q, row = v / 8;
+        a_k[q] = v % 8 * 4;
+        a_src[q] = A + static_cast<size_t>(min(tile.row0 + row, tile.row1 - 1)) * K;
+        a_off[q] = row * LDA + a_k[q];
     }
-    MOE_F32_LOAD(0)
-    for (int k0 = 0; k0 < K; k0 += kF32BK) {
-        __syncthreads();
-        As[a_k + 0][a_row] = av.x;
-        As[a_k + 1][a_row] = av.y;
-        As[a_k + 2][a_row] = av.z;
-        As[a_k + 3][a_row] = av.w;
-        *reinterpret_cast<float4 *>(&Bs[b_k][b_n]) = bv;
-        __syncthreads();
-        if (k0 + kF32BK < K) MOE_F32_LOAD(k0 + kF32BK)
 #pragma unroll
-        for (int kk = 0; kk < kF32BK; ++kk) {
-            const float4 a4 = *reinterpret_cast<const float4 *>(&As[kk][ty * 4]);
-            const float4 b4 = *reinterpret_cast<const float4 *>(&Bs[kk][tx * 4]);
-            const float a[4] = {a4.x, a4.y, a4.z, a4.w};
-            const float b[4] = {b4.x, b4.y, b4.z, b4.w};
+    for (int q = 0; q < TN; ++q) {
+        const int v = tid + 256 * q, n = v % (BN / 4) * 4;
+        b_k[q] = v / (BN / 4);
+        b_src[q] = B + static_cast<size_t>(tile.expert) * K * N + min(n0 + n, N - 4);   // (columns past N are not stored)
+        b_off[q] = b_k[q] * LDB + n;
+    }
+    f32x4 ar[PD][TM], br[PD][TN];
+    // (no branches around the loads, or the compiler waits for all of them: what lies past K is read
+    // from inside the row or column and zeroed on its way into LDS)
+    auto load = [&](auto slot, int s) {
+        constexpr int u = decltype(slot)::value;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+        for (int q = 0; q < TM; ++q)
+            ar[u][q] = *reinterpret_cast<const f32x4 *>(a_src[q] + min(s * BK + a_k[q], K - 4));
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fmaf(a[i], b[j], acc[i][j]);
+        for (int q = 0; q < TN; ++q)
+            br[u][q] = *reinterpret_cast<const f32x4 *>(b_src[q] + static_cast<size_t>(min(s * BK + b_k[q], K - 1)) * N);
+    };
+    f32x4 acc[TN][TM];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) acc[i][j] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+
+    auto stage = [&](auto slot, int s) {
+        constexpr int u = decltype(slot)::value, buf = u & 1;
+#pragma unroll
+        for (int q = 0; q < TM; ++q)
+            *reinterpret_cast<f32x4 *>(&As[buf][a_off[q]]) =
+                s * BK + a_k[q] < K ? ar[u][q] : (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int q = 0; q < TN; ++q)
+            *reinterpret_cast<f32x4 *>(&Bs[buf][b_off[q]]) =
+                s * BK + b_k[q] < K ? br[u][q] : (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+        load(slot, min(s + PD, KT - 1));         // (past the last stage: loaded again, never used)
+        // LDS writes only are waited for: the loads stay in flight across the barrier
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int c = 0; c < BK; c += 16) {
+            f32x4 af[TM], wf[TN];
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+                af[j] = *reinterpret_cast<const f32x4 *>(&As[buf][((wm * TM + j) * 16 + r16) * LDA + c + 4 * kq]);
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    wf[i][q] = Bs[buf][(c + 4 * kq + q) * LDB + (wn * TN + i) * 16 + r16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < TN; ++i)
+#pragma unroll
+                    for (int j = 0; j < TM; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[i][q], af[j][q], acc[i][j], 0, 0, 0);
         }
-    }
-#undef MOE_F32_LOAD
-    const int n = n0 + tx * 4;
-    if (n >= N) return;
-    float4 bs = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (bias != nullptr)
-        bs = *reinterpret_cast<const float4 *>(bias + static_cast<size_t>(tile.expert) * N + n);
+    };
+    auto each = [&](auto body) {
+        body(std::integral_constant<int, 0>{});
+        body(std::integral_constant<int, 1>{});
+        body(std::integral_constant<int, 2>{});
+        body(std::integral_constant<int, 3>{});
+    };
+    each([&](auto u) { load(u, min(decltype(u)::value, KT - 1)); });
+    int s0 = 0;
+    for (; s0 + PD <= KT; s0 += PD) each([&](auto u) { stage(u, s0 + decltype(u)::value); });
+    each([&](auto u) {
+        if (s0 + decltype(u)::value < KT) stage(u, s0 + decltype(u)::value);
+    });
+
+    // acc[i][j][c]: column n0 + (wn * TN + i) * 16 + 4 * kq + c, row row0 + (wm * TM + j) * 16 + r16
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = tile.row0 + ty * 4 + i;
-        if (r >= tile.row1) continue;
-        float4 o;
-        o.x = activate<ACT, false>(acc[i][0] + bs.x);
-        o.y = activate<ACT, false>(acc[i][1] + bs.y);
-        o.z = activate<ACT, false>(acc[i][2] + bs.z);
-        o.w = activate<ACT, false>(acc[i][3] + bs.w);
-        *reinterpret_cast<float4 *>(C + static_cast<size_t>(r) * N + n) = o;
+    for (int i = 0; i < TN; ++i) {
+        const int n = n0 + (wn * TN + i) * 16 + 4 * kq;
+        if (n >= N) continue;
+        f32x4 bs = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+        if (bias != nullptr) bs = *reinterpret_cast<const f32x4 *>(bias + static_cast<size_t>(tile.expert) * N + n);
+#pragma unroll
+        for (int j = 0; j < TM; ++j) {
+            const int r = tile.row0 + (wm * TM + j) * 16 + r16;
+            if (r >= tile.row1) continue;
+            f32x4 o;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[c] = activate<ACT, false>(acc[i][j][c] + bs[c]);
+            *reinterpret_cast<f32x4 *>(C + static_cast<size_t>(r) * N + n) = o;
+        }
     }
 }
 
@@ -481,14 +533,19 @@ void launch_f32_pair(const moe_shape &s, const float *xe, const float *W1, const
     float *H = static_cast<float *>(w.hidden);
     const WorkItem *it1 = w.items[0] + static_cast<size_t>(chunk) * w.gp[0].max_items;
     const WorkItem *it2 = w.items[1] + static_cast<size_t>(chunk) * w.gp[1].max_items;
+    auto launch = [&](auto act, int g, const float *A, const float *B, const float *bias, float *C,
+                      const WorkItem *items, int N, int K) {
+        constexpr int A_ = decltype(act)::value;
+        const GemmPlan &gp = w.gp[g];
+        auto kern = gp.bm == 64 ? grouped_gemm_f32_kernel<A_, 2, 2> : grouped_gemm_f32_kernel<A_, 1, 1>;
+        hipLaunchKernelGGL(kern, dim3(gp.max_items), dim3(256), 0, st, A, B, bias, C, items,
+                           w.nitems[g] + chunk, N, K);
+    };
     prof_begin(kStageGemm1, st);
-    hipLaunchKernelGGL(grouped_gemm_f32_kernel<ACT>, dim3(w.gp[0].max_items), dim3(256), 0, st,
-                       xe, W1, b1, H, it1, w.nitems[0] + chunk, s.d_ff, s.d_model);
+    launch(std::integral_constant<int, ACT>{}, 0, xe, W1, b1, H, it1, s.d_ff, s.d_model);
     prof_end(kStageGemm1, st);
     prof_begin(kStageGemm2, st);
-    hipLaunchKernelGGL(grouped_gemm_f32_kernel<MOE_ACT_IDENTITY>, dim3(w.gp[1].max_items),
-                       dim3(256), 0, st, H, W2, b2, ye, it2, w.nitems[1] + chunk, s.d_model,
-                       s.d_ff);
+    launch(std::integral_constant<int, MOE_ACT_IDENTITY>{}, 1, H, W2, b2, ye, it2, s.d_model, s.d_ff);
     prof_end(kStageGemm2, st);
 }
 
@@ -658,7 +715,9 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_chunks)
     const int64_t chunk_tokens = (s.T + n_chunks - 1) / n_chunks;
     const int64_t chunk_rows = chunk_tokens * s.k < max_rows ? chunk_tokens * s.k : max_rows;
     if (s.dtype != MOE_BF16) {
-        gp.bm = gp.bn = kF32Tile;
+        // 64 x 64 tiles where they are a few per compute unit, else 32 x 32 (us of the layer, 32 / 64:
+        // 603 tokens, 420 x 1620 71 / 88; 951, k = 2, 780 x 2084 183 / 189; 3564, 764 x 1836 308 / 250)
+        gp.bm = gp.bn = (chunk_rows / 64 + s.E / 2) * ((N + 63) / 64) >= 1200 ? 64 : 32;
         gp.concurrent = 256;
     } else {
         const int64_t per_expert = chunk_rows / s.E;

@@ -426,6 +426,122 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_mfma_kernel(
 
 #include "gemm_w4.h"
 
+// ---------------------------------------------------------------- few rows per expert
+// The same product for decode steps: a few rows per expert, so the time is that of streaming the
+// weights once.  A wavefront owns 16 columns and the item's rows (up to 64, RT groups of 16) and takes
+// its fragments straight from global memory -- no LDS, no barriers -- with PD 64-deep stages of
+// loads in flight; a block is four of them.  64 columns per block instead of 256: at 768 columns
+// and 16 experts the second GEMM of a layer is 192 blocks, not 48.
+// The contraction order is that of the other 16-bit kernels (same bits).
+// 16 tokens, 16 experts, k = 2, 768 x 3072, the two GEMMs: 14.9 and 17.6 us (17.2 and 25.7 with 128 x 128
+// and 64 x 256 tiles).
+template <bool F16, int ACT, bool KEEP, bool KTAIL>
+__global__ __launch_bounds__(256, 2) void grouped_gemm_stream_kernel(
+    const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, const float *__restrict__ bias,
+    _Float16 *__restrict__ C, _Float16 *__restrict__ Pre, const WorkItem *__restrict__ items,
+    const int32_t *__restrict__ nitems, int N, int K, const int32_t *__restrict__ row_src, int row_div)
+{
+    const int total = *nitems;
+    const int per_xcd = (total + 7) / 8;
+    const int slot = blockIdx.x / 8;
+    const int item_idx = (blockIdx.x % 8) * per_xcd + slot;
+    if (slot >= per_xcd || item_idx >= total) return;
+    const WorkItem item = items[item_idx];
+    const int rows = item.row1 - item.row0;
+    const int lane = threadIdx.x & 63, fr = lane & 15, oct = lane >> 4;
+    const int nw = item.n0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 16;
+    if (nw >= N) return;
+    const int KT = (K + 63) / 64;
+    const uint16_t *wp = W + (static_cast<size_t>(item.expert) * N + min(nw + fr, N - 1)) * K + oct * 8;
+
+    auto body = [&](auto rt, auto pd) {
+        constexpr int RT = decltype(rt)::value, PD = decltype(pd)::value;
+        const uint16_t *ap[RT];
+#pragma unroll
+        for (int j = 0; j < RT; ++j) {
+            int arow = item.row0 + min(j * 16 + fr, rows - 1);
+            if (row_src != nullptr) arow = row_src[arow] / row_div;
+            ap[j] = A + static_cast<size_t>(arow) * K + oct * 8;
+        }
+        u32x4 wr[PD][2], ar[PD][RT][2];
+        // (no branches around the loads, or the compiler waits for all of them: a piece past K is read
+        // from inside the row, and zeroed when the last stage is multiplied)
+        auto load = [&](auto u, int s) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                int k0 = s * 64 + p * 32;
+                if constexpr (KTAIL) k0 = min(k0, K - 8 - oct * 8);
+                wr[decltype(u)::value][p] = *reinterpret_cast<const u32x4 *>(wp + k0);
+#pragma unroll
+                for (int j = 0; j < RT; ++j)
+                    ar[decltype(u)::value][j][p] = *reinterpret_cast<const u32x4 *>(ap[j] + k0);
+            }
+        };
+        f32x4 acc[RT];
+#pragma unroll
+        for (int j = 0; j < RT; ++j) acc[j] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+        auto use = [&](auto u, auto tail, int s) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const bool past = KTAIL && decltype(tail)::value && s * 64 + p * 32 + oct * 8 >= K;
+                const u32x4 zero = {0u, 0u, 0u, 0u}, w = past ? zero : wr[decltype(u)::value][p];
+#pragma unroll
+                for (int j = 0; j < RT; ++j) {
+                    const u32x4 a = past ? zero : ar[decltype(u)::value][j][p];
+                    if constexpr (F16)
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                            __builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, a), acc[j], 0, 0, 0);
+                    else
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, a), acc[j], 0, 0, 0);
+                }
+            }
+        };
+        static_for<PD>([&](auto u) { load(u, min(decltype(u)::value, KT - 1)); });
+        int s = 0;
+        for (; s + 2 * PD <= KT; s += PD)
+            static_for<PD>([&](auto u) {
+                use(u, std::false_type{}, 0);
+                load(u, s + decltype(u)::value + PD);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        for (; s < KT; s += PD)                      // the last stages: fewer than two rounds
+            static_for<PD>([&](auto u) {
+                if (s + decltype(u)::value < KT) use(u, std::true_type{}, s + decltype(u)::value);
+                if (s + decltype(u)::value + PD < KT) load(u, s + decltype(u)::value + PD);
+            });
+
+        // acc[j][c]: column nw + 4 * oct + c, row row0 + 16 * j + fr
+        const int n = nw + 4 * oct;
+        if (n >= N) return;
+        float b4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (bias != nullptr) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) b4[c] = bias[static_cast<size_t>(item.expert) * N + n + c];
+        }
+#pragma unroll
+        for (int j = 0; j < RT; ++j) {
+            if (j * 16 + fr >= rows) continue;
+            const size_t at = static_cast<size_t>(item.row0 + j * 16 + fr) * N + n;
+            float v[4], pre[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                pre[c] = acc[j][c] + b4[c];
+                v[c] = activate<ACT, true>(pre[c]);
+            }
+            if constexpr (KEEP) store4(Pre + at, pre);
+            store4(C + at, v);
+        }
+    };
+    using std::integral_constant;
+    if (rows <= 16)
+        body(integral_constant<int, 1>{}, integral_constant<int, 8>{});
+    else if (rows <= 32)
+        body(integral_constant<int, 2>{}, integral_constant<int, 5>{});
+    else
+        body(integral_constant<int, 4>{}, integral_constant<int, 3>{});
+}
+
 // ABL (measurement only, 0 in the layer): bit 0 leaves out the MFMAs, bit 1 the LDS fragment
 // reads after the first step, bit 2 the global loads and LDS writes inside the loop, bit 3 the
 // output stores.  Results are then wrong by construction; every access stays inside the buffers.
@@ -627,6 +743,15 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
         else
             shape(std::true_type{});
     }
+    else if (gp.bm == 64 && gp.bn == 64) {
+        auto kern = K % 64 == 0 ? grouped_gemm_stream_kernel<F16, ACT, KEEP, false>
+                                : grouped_gemm_stream_kernel<F16, ACT, KEEP, true>;
+        const int grid = static_cast<int>(align_up(static_cast<size_t>(gp.max_items), 8));
+        hipEvent_t t0, t1;
+        prof_kernel_events(stage, &t0, &t1);
+        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, t0, t1, 0, A, W, bias, C, pre, items,
+                              nitems, N, K, row_src, row_div);
+    }
     else if (gp.bm == 64)
         MOE_MFMA_SHAPE(1, 8, 2, 1);
     else
@@ -663,7 +788,7 @@ void launch_mfma_pair(const moe_shape &s, const uint16_t *xe, const uint16_t *W1
 void expert_gemm_kernel_name(const moe_shape &s, int which, int n_chunks, char *name, size_t len)
 {
     const GemmPlan gp = choose_gemm_plan(s, which, n_chunks);
-    std::snprintf(name, len, "%s %dx%d", gp.w4 ? "grouped_gemm_w4_kernel" : "grouped_gemm_mfma_kernel",
+    std::snprintf(name, len, "%s %dx%d", gp.w4 ? "grouped_gemm_w4_kernel" : gp.bn == 64 ? "grouped_gemm_stream_kernel" : "grouped_gemm_mfma_kernel",
                   gp.bm, gp.bn);
 }
 
@@ -722,7 +847,13 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_chunks)
     } else {
         const int64_t per_expert = chunk_rows / s.E;
         const int64_t tiles_n = (N + 255) / 256;
-        if ((chunk_rows / 64 + s.E / 2) * tiles_n >= 128 &&
+        if (chunk_rows <= 5 * static_cast<int64_t>(s.E)) {
+            // a decode step: the weights are streamed once, by as many blocks as there are (us of
+            // the layer, this / the best other tile: 16 tokens, 16 experts, k = 2, 768 x 3072 54 / 61;
+            // 9 tokens, 4 experts, 992 x 3344 50 / 64; 105, 64, 568 x 2056 100 / 106; at six rows
+            // per expert the 64-row tile is the better one)
+            gp.bm = 64; gp.bn = 64; gp.concurrent = 128;
+        } else if ((chunk_rows / 64 + s.E / 2) * tiles_n >= 128 &&
                    (per_expert < 48 || (per_expert <= 64 && (chunk_rows / 128 + s.E / 2) * tiles_n < 256))) {
             // few rows per expert and enough 64-row tiles to keep the weight stream going: shorter
             // tiles spend less of their loads on (mostly padded) rows (137 tokens, 16 experts, k = 3,

@@ -393,3 +393,29 @@ def test_gate_register_blocks_and_segments(name, base, T, d, E, k, cf):
         assert_ints_equal(L.ints(), o)
         y = b["y"].cpu().numpy().reshape(T, d)[sample]
         assert rel_rms_err(y, o.y) <= TOL[li.dtype if li.dtype == "bf16" else "f32"]
+
+
+@pytest.mark.parametrize("dtype,T,d,h,E,k,hot", [
+    ("bf16", 3, 72, 200, 16, 2, None),        # the 64 x 64 streaming tile: one group of rows, K tails
+    ("bf16", 17, 1096, 40, 16, 2, 5),         # ... 17 rows of one expert: two groups
+    ("bf16", 70, 136, 328, 32, 2, 5),         # ... 70 rows: a full item of four groups and a second one
+    ("bf16", 100, 2048, 264, 64, 3, None),    # ... a contraction of many rounds of loads
+    ("bf16", 1500, 1000, 2600, 4, 2, None),   # 256 x 256 with K tails by the count of rounds; 128 x 128
+    ("bf16", 700, 64, 4104, 13, 3, None),     # one stage; a ragged last column tile
+    ("bf16", 4100, 768, 3072, 16, 2, None),   # 128 x 256 for the second GEMM
+    ("f32", 70, 4, 20, 3, 1, None),           # 32 x 32: less than a stage, less than a tile
+    ("f32", 513, 100, 388, 5, 2, 1),          # ... stages that are no multiple of the prefetch depth
+    ("f32", 2100, 68, 3004, 4, 2, None),      # 64 x 64, K and N tails
+])
+def test_expert_gemm_tiles(dtype, T, d, h, E, k, hot):
+    """Every tile shape of the expert GEMMs at the edges of its tiles (bounds: TOL of the type)."""
+    base = "tiny_fp32" if dtype == "f32" else "gpt2s_moe"
+    li = wl.make_layer(wl.scaled(base, T=T, d=d, h=h, E=E, k=k, cf=None), seed=4)
+    if hot is not None:                       # every token also goes to this expert
+        li.gate_bias, li.bias_token_stride = np.zeros(E, np.float32), 0
+        li.gate_bias[hot % E] = 30.0
+    o = run_oracle(li)
+    L = DeviceLayer(li, shape_of(li))
+    L.layer(1)
+    assert_ints_equal(L.ints(), o)
+    assert rel_rms_err(L.b["y"].cpu().numpy().reshape(li.T, li.d), o.y) <= TOL[li.dtype]

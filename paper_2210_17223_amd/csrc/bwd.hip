@@ -830,213 +830,161 @@ __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
 }
 
 // ---------------------------------------------------------------- gate backward
-// columns i .. i + 3 (i a multiple of 4) of a row of the packed gate matrix
-__device__ __forceinline__ float4 packed_columns(const float *row, int i)
-{
-    const float *p = row + packed_gate_column(i);
-    return make_float4(p[0], p[4], p[8], p[12]);
-}
-
-// One wavefront per token.  Logits: lane = four consecutive columns of the model dimension,
-// EP partial sums per lane (Wgp is the forward's packed gate matrix, fp32 [EP][dP],
-// expert-major, zero padded, columns ordered by packed_gate_column), then a butterfly sum per expert; the order of the additions
-// differs from the forward's chain, which only the top-k decision needed.  Softmax, dz with
-// lane = expert, and finally, lane = column again,
-// dx[t, i] = sum of the token's kept dxe rows + sum_e dz[e] Wg[i, e].
-// MODE 1: the gate matrix (EP x d floats, at most 64 KiB) is copied to LDS once per block of
-// 16 wavefronts (16 tokens) and read from there -- a wavefront that reads the matrix twice
-// per token from the caches moves 8 EP d bytes per token through the L1, which is what
-// bounded the kernel.  (Still one token per wavefront and four wavefronts per SIMD: the
-// token's own chain of loads, butterflies and stores is covered by the other wavefronts.)
-// MODE 2: a larger matrix goes through LDS in chunks of 64 KiB of its columns, once for the
-// logits and once more for dx; every wavefront of the block walks all chunks (those without a
-// token only stage and wait).
-template <int EP, int MODE>
-__global__ __launch_bounds__(MODE != 0 ? 1024 : 256) void gate_bwd_kernel(
-    const uint16_t *__restrict__ x, const float *__restrict__ Wgp, const float *__restrict__ bias,
-    int bias_stride, const int32_t *__restrict__ expert_idx, const int32_t *__restrict__ slot_of,
-    const float *__restrict__ dgate, const float *__restrict__ dxe, float *__restrict__ dz,
-    float *__restrict__ dx, int t0, int T, int d, int dP, int E, int k, int max_rows)
-{   // tokens [t0, T).  MODE 0: the matrix from the caches; 1: staged whole in LDS; 2: staged in
-    // chunks of DC columns, once for the logits and once for dx
-    constexpr int NW = MODE != 0 ? 16 : 4;                           // wavefronts per block
-    constexpr int DC = 16384 / EP >= 256 ? 16384 / EP : 256;         // columns per 64 KiB chunk (MODE 2)
-    __shared__ float dzs[NW][kWave];
-    extern __shared__ __attribute__((aligned(16))) float wlds[];     // MODE 1: [EP][d]; 2: [EP][DC]
-    const int lane = lane_id();
-    const int w = threadIdx.x / kWave;
-    const float *Wsrc = Wgp;
-    int wpitch = dP;
-    if constexpr (MODE == 1) {
-        const int rv = d / 4;                                        // 16-byte vectors per row
-        for (int v = threadIdx.x; v < EP * rv; v += NW * kWave) {
-            const int e = v / rv, i = (v % rv) * 4;
-            *reinterpret_cast<float4 *>(wlds + e * d + i) = packed_columns(Wgp + static_cast<size_t>(e) * dP, i);
+// dx[t, i] = sum of the token's kept dxe rows + sum_e dz[e] Wg[i, e], on the fp32 matrix
+// instruction (products in ascending e, fused).  Block = 32 tokens x 256 columns, a wavefront 64
+// of them: the rows' sums are the accumulators' start, the tokens' dz stay in registers, and
+// the packed gate matrix (fp32 [EP][dP], expert-major, zero padded, columns ordered by
+// packed_gate_column) is read once per 32 tokens from L2.  Bound by HBM: k fp32 rows in, one out per
+// token.  T = 32768, d = 2048, E = 64, k = 2 (0.8 GB), us: 326, and 101 for the logit
+// gradients before it; the token-per-wavefront kernel they replace took 800 (LDS reads of the gate
+// matrix twice per token).  T = 4096, d = 768, E = 16: 14 + 9 (23).
+template <int NG>
+__global__ __launch_bounds__(256) void gate_dx_kernel(
+    const float *__restrict__ Wgp, const int32_t *__restrict__ slot_of, const float *__restrict__ dxe,
+    const float *__restrict__ dz, float *__restrict__ dx, int t0, int T, int d, int dP, int E, int EP,
+    int k, int max_rows)
+{   // tokens [t0, T); NG groups of 16 experts
+    constexpr int G = 2, CG = 4, NS = NG * 4;
+    const int lane = lane_id(), r16 = lane & 15, kq = lane >> 4;
+    const int tb = t0 + blockIdx.x * (16 * G);
+    const int c0 = blockIdx.y * 256 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64;
+    if (c0 >= d) return;
+    int tok[G];
+    float dzr[G][NS];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        tok[g] = min(tb + g * 16 + r16, T - 1);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const float v = dz[static_cast<size_t>(tok[g]) * E + min(4 * s + kq, E - 1)];
+            dzr[g][s] = 4 * s + kq < E ? v : 0.0f;
         }
-        __syncthreads();
-        Wsrc = wlds;
-        wpitch = d;
     }
-    const int t = t0 + blockIdx.x * NW + w;
-    const bool valid = t < T;
-    if (MODE != 2 && !valid) return;
-    // columns [c0, c0 + DC) of the packed matrix (zero padded up to dP) into LDS, all wavefronts
-    auto stage_chunk = [&](int c0) {
-        __syncthreads();
-        constexpr int rv = DC / 4;
-        for (int v = threadIdx.x; v < EP * rv; v += NW * kWave) {
-            const int e = v / rv, i = (v % rv) * 4;
-            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (c0 + i < dP) q = packed_columns(Wgp + static_cast<size_t>(e) * dP, c0 + i);
-            *reinterpret_cast<float4 *>(wlds + e * DC + i) = q;
+    // (the packed row is padded past d; experts past E: dz is zero)
+    const float *wcol = Wgp + c0 + packed_gate_column(r16);
+    float wr[CG][NS];
+#pragma unroll
+    for (int c = 0; c < CG; ++c)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) wr[c][s] = wcol[static_cast<size_t>(min(4 * s + kq, EP - 1)) * dP + c * 16];
+    f32x4 acc[G][CG];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int c = 0; c < CG; ++c) acc[g][c] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 2
+    for (int j = 0; j < k; ++j) {
+        int slot[G];
+        bool kept[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            slot[g] = slot_of[static_cast<size_t>(tok[g]) * k + j];
+            kept[g] = slot[g] >= 0 && slot[g] < max_rows;
         }
-        __syncthreads();
-    };
-    const uint16_t *xrow = x + static_cast<size_t>(valid ? t : 0) * d;
-    float acc[EP];
 #pragma unroll
-    for (int e = 0; e < EP; ++e) acc[e] = 0.0f;
-    auto logits_part = [&](const float *wbase, int pitch, int i, int iw) {    // columns i .. i + 3 (iw: in wbase)
-        const u32x2 xq = *reinterpret_cast<const u32x2 *>(xrow + i);
-        const float x0 = __uint_as_float(xq[0] << 16), x1 = __uint_as_float(xq[0] & 0xFFFF0000u);
-        const float x2 = __uint_as_float(xq[1] << 16), x3 = __uint_as_float(xq[1] & 0xFFFF0000u);
+        for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int e = 0; e < EP; ++e) {
-            const float *wrow = wbase + static_cast<size_t>(e) * pitch;
-            const float4 wv = MODE == 0 ? packed_columns(wrow, iw) : *reinterpret_cast<const float4 *>(wrow + iw);
-            acc[e] = __builtin_fmaf(x0, wv.x, acc[e]);
-            acc[e] = __builtin_fmaf(x1, wv.y, acc[e]);
-            acc[e] = __builtin_fmaf(x2, wv.z, acc[e]);
-            acc[e] = __builtin_fmaf(x3, wv.w, acc[e]);
-        }
-    };
-    if constexpr (MODE == 2) {
-        for (int c0 = 0; c0 < d; c0 += DC) {
-            stage_chunk(c0);
-            if (valid)
-                for (int il = lane * 4; il < DC && c0 + il < d; il += kWave * 4)
-                    logits_part(wlds, DC, c0 + il, il);
-        }
-    } else {
-        for (int i = lane * 4; i < d; i += kWave * 4) logits_part(Wsrc, wpitch, i, i);
-    }
-    float z = 0.0f;
-#pragma unroll
-    for (int e = 0; e < EP; ++e) {
-        float v = acc[e];
-#pragma unroll
-        for (int m = kWave / 2; m > 0; m >>= 1) v += __shfl_xor(v, m);
-        if (lane == e) z = v;
-    }
-    const int e = lane;
-    const bool live = e < E;
-    const int tt = valid ? t : 0;
-    if (bias != nullptr && live) z += bias[static_cast<size_t>(tt) * bias_stride + e];
-    float zmax = live ? z : -3.0e38f;
-#pragma unroll
-    for (int m = kWave / 2; m > 0; m >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, m));
-    float p = live ? expf(z - zmax) : 0.0f;
-    float denom = p;
-#pragma unroll
-    for (int m = kWave / 2; m > 0; m >>= 1) denom += __shfl_xor(denom, m);
-    p /= denom;
-    float dg = 0.0f;
-    if (live)
-        for (int j = 0; j < k; ++j)
-            if (expert_idx[static_cast<size_t>(tt) * k + j] == e) dg = dgate[static_cast<size_t>(tt) * k + j];
-    float s = p * dg;
-#pragma unroll
-    for (int m = kWave / 2; m > 0; m >>= 1) s += __shfl_xor(s, m);
-    const float dze = p * (dg - s);
-    if (live && valid) dz[static_cast<size_t>(t) * E + e] = dze;
-    dzs[w][lane] = live ? dze : 0.0f;
-    __builtin_amdgcn_wave_barrier();
-    float dzr[EP];
-#pragma unroll
-    for (int ee = 0; ee < EP; ++ee) dzr[ee] = dzs[w][ee];
-    auto dx_part = [&](const float *wbase, int pitch, int i, int iw) {
-        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int j = 0; j < k; ++j) {
-            const int slot = slot_of[static_cast<size_t>(t) * k + j];
-            if (slot >= 0 && slot < max_rows) {
-                const float4 r = *reinterpret_cast<const float4 *>(dxe + static_cast<size_t>(slot) * d + i);
-                o.x += r.x; o.y += r.y; o.z += r.z; o.w += r.w;
+            for (int c = 0; c < CG; ++c) {               // (a dropped assignment reads row 0, and drops it)
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(
+                    dxe + static_cast<size_t>(kept[g] ? slot[g] : 0) * d + min(c0 + c * 16 + 4 * kq, d - 4));
+                acc[g][c] += kept[g] ? v : (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
             }
-        }
+    }
 #pragma unroll
-        for (int ee = 0; ee < EP; ++ee) {
-            const float *wrow = wbase + static_cast<size_t>(ee) * pitch;
-            const float4 wv = MODE == 0 ? packed_columns(wrow, iw) : *reinterpret_cast<const float4 *>(wrow + iw);
-            o.x = __builtin_fmaf(dzr[ee], wv.x, o.x);
-            o.y = __builtin_fmaf(dzr[ee], wv.y, o.y);
-            o.z = __builtin_fmaf(dzr[ee], wv.z, o.z);
-            o.w = __builtin_fmaf(dzr[ee], wv.w, o.w);
-        }
-        *reinterpret_cast<float4 *>(dx + static_cast<size_t>(t) * d + i) = o;
-    };
-    if constexpr (MODE == 2) {
-        for (int c0 = 0; c0 < d; c0 += DC) {
-            stage_chunk(c0);
-            if (valid)
-                for (int il = lane * 4; il < DC && c0 + il < d; il += kWave * 4)
-                    dx_part(wlds, DC, c0 + il, il);
-        }
-    } else {
-        for (int i = lane * 4; i < d; i += kWave * 4) dx_part(Wsrc, wpitch, i, i);
+    for (int c = 0; c < CG; ++c) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+                acc[g][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[c][s], dzr[g][s], acc[g][c], 0, 0, 0);
+        // acc[g][c][v]: column c0 + 16 c + 4 kq + v, token tb + 16 g + r16
+        const int i = c0 + c * 16 + 4 * kq;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (i < d && tb + g * 16 + r16 < T)
+                *reinterpret_cast<f32x4 *>(dx + static_cast<size_t>(tok[g]) * d + i) = acc[g][c];
     }
 }
 
-// partial[s][i][e] = sum over the tokens of range s of x[t, i] dz[t, e].  Block = 64 columns
-// i x 4 expert groups of EQ = EP / 4 experts (EP < 4: one expert per group, surplus groups
-// idle); tokens go through LDS 64 at a time.
-template <int EP>
+// partial[s][i][e] = sum over the tokens of range s of x[t, i] dz[t, e], ascending t, on the fp32
+// matrix instruction.  Block = 64 columns i (16 per wavefront) x all experts (NG groups of 16);
+// tokens go through LDS 64 at a time, the next 64 on their way in registers.  The row pitches (16
+// mod 64 words) let the four tokens of an instruction fall into different banks.  T = 32768,
+// d = 2048, E = 64, us: 109 (381 with a v_fmac chain per column and a quarter of the experts).
+template <int NG>
 __global__ __launch_bounds__(256) void dwg_partial_kernel(
     const uint16_t *__restrict__ x, const float *__restrict__ dz, float *__restrict__ partial, int T,
     int d, int E, int per_split)
 {
-    constexpr int EQ = EP >= 4 ? EP / 4 : 1;
-    __shared__ float xs[64][65];
-    __shared__ float zs[64][EP + 1];
-    const int il = threadIdx.x % 64, eg = threadIdx.x / 64;
+    constexpr int XP = 80, ZP = NG == 1 ? 16 : NG == 2 ? 48 : 80, ZV = NG * 16 * 64 / 256;
+    __shared__ __attribute__((aligned(16))) float xs[64 * XP];
+    __shared__ float zs[64 * ZP];
+    const int tid = threadIdx.x, lane = lane_id(), r16 = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i0 = blockIdx.x * 64;
-    const int e0 = eg * EQ;
     const int t0 = blockIdx.y * per_split, t1 = min(T, t0 + per_split);
-    float acc[EQ];
+    f32x4 acc[NG];
 #pragma unroll
-    for (int q = 0; q < EQ; ++q) acc[q] = 0.0f;
+    for (int q = 0; q < NG; ++q) acc[q] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+    u32x4 xr[2];
+    float zr[ZV];
+    // eight columns per load; what lies past the range or the matrix is zeroed on its way into LDS
+    auto load = [&](int tb) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int v = tid + 256 * q;
+            xr[q] = *reinterpret_cast<const u32x4 *>(x + static_cast<size_t>(min(tb + v / 8, T - 1)) * d +
+                                                     min(i0 + v % 8 * 8, d - 8));
+        }
+#pragma unroll
+        for (int q = 0; q < ZV; ++q) {
+            const int v = tid + 256 * q;
+            zr[q] = dz[static_cast<size_t>(min(tb + v / (NG * 16), T - 1)) * E + min(v % (NG * 16), E - 1)];
+        }
+    };
+    load(t0);
     for (int tb = t0; tb < t1; tb += 64) {
         __syncthreads();
-        for (int v = threadIdx.x; v < 64 * 8; v += 256) {          // eight columns per load
-            const int tt = v / 8, c8 = (v % 8) * 8;
-            u32x4 q = {0u, 0u, 0u, 0u};
-            if (tb + tt < t1 && i0 + c8 < d)
-                q = *reinterpret_cast<const u32x4 *>(x + static_cast<size_t>(tb + tt) * d + i0 + c8);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                xs[tt][c8 + 2 * c] = __uint_as_float(q[c] << 16);
-                xs[tt][c8 + 2 * c + 1] = __uint_as_float(q[c] & 0xFFFF0000u);
+        for (int q = 0; q < 2; ++q) {
+            const int v = tid + 256 * q, tt = v / 8, c8 = v % 8 * 8;
+            const bool in = tb + tt < t1 && i0 + c8 < d;
+            f32x4 lo, hi;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                lo[2 * c] = in ? __uint_as_float(xr[q][c] << 16) : 0.0f;
+                lo[2 * c + 1] = in ? __uint_as_float(xr[q][c] & 0xFFFF0000u) : 0.0f;
+                hi[2 * c] = in ? __uint_as_float(xr[q][2 + c] << 16) : 0.0f;
+                hi[2 * c + 1] = in ? __uint_as_float(xr[q][2 + c] & 0xFFFF0000u) : 0.0f;
             }
+            *reinterpret_cast<f32x4 *>(xs + tt * XP + c8) = lo;
+            *reinterpret_cast<f32x4 *>(xs + tt * XP + c8 + 4) = hi;
         }
-        for (int v = threadIdx.x; v < 64 * EP; v += 256) {
-            const int tt = v / EP, ee = v % EP;
-            zs[tt][ee] = (tb + tt < t1 && ee < E) ? dz[static_cast<size_t>(tb + tt) * E + ee] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < ZV; ++q) {
+            const int v = tid + 256 * q, tt = v / (NG * 16), ee = v % (NG * 16);
+            zs[tt * ZP + ee] = (tb + tt < t1 && ee < E) ? zr[q] : 0.0f;
         }
         __syncthreads();
-        if (e0 < EP) {
-#pragma unroll 8
-            for (int tt = 0; tt < 64; ++tt) {
-                const float xv = xs[tt][il];
+        if (tb + 64 < t1) load(tb + 64);
 #pragma unroll
-                for (int q = 0; q < EQ; ++q) acc[q] = __builtin_fmaf(xv, zs[tt][e0 + q], acc[q]);
-            }
+        for (int s = 0; s < 16; ++s) {
+            const float xv = xs[(4 * s + kq) * XP + wave * 16 + r16];
+#pragma unroll
+            for (int q = 0; q < NG; ++q)
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(zs[(4 * s + kq) * ZP + q * 16 + r16], xv, acc[q], 0, 0, 0);
         }
     }
-    if (i0 + il < d && e0 < EP) {
+    // acc[q][c]: expert 16 q + 4 kq + c, column i0 + 16 wave + r16
+    const int i = i0 + wave * 16 + r16;
+    if (i >= d) return;
 #pragma unroll
-        for (int q = 0; q < EQ; ++q)
-            if (e0 + q < E)
-                partial[(static_cast<size_t>(blockIdx.y) * d + i0 + il) * E + e0 + q] = acc[q];
-    }
+    for (int q = 0; q < NG; ++q)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int e = q * 16 + 4 * kq + c;
+            if (e < E) partial[(static_cast<size_t>(blockIdx.y) * d + i) * E + e] = acc[q][c];
+        }
 }
 
 __global__ void dwg_reduce_kernel(const float *__restrict__ partial, float *__restrict__ dWg, int n,
@@ -1268,6 +1216,7 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
     _Float16 *P = pre != nullptr ? const_cast<_Float16 *>(pre) : w.P;
     int EP = 1;
     while (EP < E) EP <<= 1;
+    const int NG = EP <= 16 ? 1 : EP / 16;             // groups of 16 experts
     const int dPad = (d + 127) / 128 * 128;            // the packed gate matrix's row length
     auto bound = [&](int c) { return static_cast<int>(static_cast<int64_t>(c) * T / n_chunks); };
 
@@ -1302,45 +1251,26 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
         launch_wgrad<false>(xe, w.dP, dW1, offsets, E, d, h, R, kStageBwdWgrad1, st);
     };
     // gate: dz and dx for the tokens [t0, t1)
+    moe_status combine_rc = MOE_OK;
     auto grad_combine = [&](int t0, int t1, hipStream_t q) {
         if (t1 <= t0) return;
         const int n = t1 - t0;
-#define MOE_GATE_BWD_CASE(EP_)                                                                    \
-    if (EP == EP_) {                                                                              \
-        const size_t wbytes = static_cast<size_t>(EP_) * d * sizeof(float);                       \
-        if (wbytes <= 64 * 1024 && T >= 16 * 256) {                                               \
-            auto kern = gate_bwd_kernel<EP_, 1>;                                                  \
-            static PerDeviceOnce once;                                                            \
-            once.raise_lds(reinterpret_cast<const void *>(kern), 64 * 1024);                      \
-            hipLaunchKernelGGL(kern, dim3(ceil_div(n, 16)), dim3(1024), wbytes, q, x, Wgp, bias,  \
-                               bias_stride, expert_idx, slot_of, dgate, w.dxe, w.dz, dx, t0, t1,  \
-                               d, dPad, E, k, R);                                                 \
-        } else if (wbytes > 64 * 1024 && T >= 16 * 256) {                                         \
-            /* a matrix too large for LDS: 64 KiB chunks of its columns, staged per 16 tokens */  \
-            auto kern = gate_bwd_kernel<EP_, 2>;                                                  \
-            static PerDeviceOnce once;                                                            \
-            once.raise_lds(reinterpret_cast<const void *>(kern), 64 * 1024);                      \
-            hipLaunchKernelGGL(kern, dim3(ceil_div(n, 16)), dim3(1024), 64 * 1024, q, x, Wgp,     \
-                               bias, bias_stride, expert_idx, slot_of, dgate, w.dxe, w.dz, dx,    \
-                               t0, t1, d, dPad, E, k, R);                                         \
-        } else {                                                                                  \
-            hipLaunchKernelGGL((gate_bwd_kernel<EP_, 0>), dim3(ceil_div(n, 4)), dim3(256), 0,     \
-                               q, x, Wgp, bias, bias_stride, expert_idx, slot_of, dgate, w.dxe,   \
-                               w.dz, dx, t0, t1, d, dPad, E, k, R);                               \
-        }                                                                                         \
-    }
-        MOE_GATE_BWD_CASE(1) MOE_GATE_BWD_CASE(2) MOE_GATE_BWD_CASE(4) MOE_GATE_BWD_CASE(8)
-        MOE_GATE_BWD_CASE(16) MOE_GATE_BWD_CASE(32) MOE_GATE_BWD_CASE(64)
-#undef MOE_GATE_BWD_CASE
+        if (combine_rc == MOE_OK)
+            combine_rc = launch_gate_grad(s, t0, t1, x, Wgp, bias, bias_stride, expert_idx, dgate, w.dz, q);
+#define MOE_GATE_DX_CASE(NG_)                                                                     \
+    if (NG == NG_)                                                                                \
+        hipLaunchKernelGGL(gate_dx_kernel<NG_>, dim3(ceil_div(n, 32), ceil_div(d, 256)), dim3(256), 0, q, Wgp, \
+                           slot_of, w.dxe, w.dz, dx, t0, t1, d, dPad, E, EP, k, R);
+        MOE_GATE_DX_CASE(1) MOE_GATE_DX_CASE(2) MOE_GATE_DX_CASE(4)
+#undef MOE_GATE_DX_CASE
     };
     // dWg = x^T dz: partial sums over fixed token ranges, then a fixed-order sum
     auto gate_weight_grad = [&]() {
-#define MOE_DWG_CASE(EP_)                                                                         \
-    if (EP == EP_)                                                                                \
-        hipLaunchKernelGGL(dwg_partial_kernel<EP_>, dim3(ceil_div(d, 64), w.splits), dim3(256), 0, \
+#define MOE_DWG_CASE(NG_)                                                                         \
+    if (NG == NG_)                                                                                \
+        hipLaunchKernelGGL(dwg_partial_kernel<NG_>, dim3(ceil_div(d, 64), w.splits), dim3(256), 0, \
                            st, x, w.dz, w.partial, T, d, E, w.per_split);
-        MOE_DWG_CASE(1) MOE_DWG_CASE(2) MOE_DWG_CASE(4) MOE_DWG_CASE(8)
-        MOE_DWG_CASE(16) MOE_DWG_CASE(32) MOE_DWG_CASE(64)
+        MOE_DWG_CASE(1) MOE_DWG_CASE(2) MOE_DWG_CASE(4)
 #undef MOE_DWG_CASE
         hipLaunchKernelGGL(dwg_reduce_kernel, dim3(ceil_div(d * E, 256)), dim3(256), 0, st, w.partial,
                            dWg, d * E, w.splits);
@@ -1353,7 +1283,7 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
         grad_combine(0, T, st);
         gate_weight_grad();
         MOE_TRY_HIP(hipGetLastError());
-        return MOE_OK;
+        return combine_rc;
     }
 
     BwdResources *r = nullptr;
@@ -1391,7 +1321,7 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
     if (je != hipSuccess) return hip_fail(je, "joining the side streams");
     gate_weight_grad();
     MOE_TRY_HIP(hipGetLastError());
-    return MOE_OK;
+    return combine_rc;
 }
 
 }  // namespace

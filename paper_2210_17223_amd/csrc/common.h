@@ -138,6 +138,9 @@ void prof_kernel_events(int stage, hipEvent_t *start, hipEvent_t *stop);
 // ---- kernel launchers (each only enqueues on `st`) ---------------------------
 // when seg_cnt is not NULL the per-segment expert histogram of the dispatch plan is
 // produced in the same pass
+moe_status launch_gate_grad(const moe_shape &s, int t0, int t1, const uint16_t *x, const float *Wgp,
+                            const float *bias, int bias_stride, const int32_t *expert_idx,
+                            const float *dgate, float *dz, hipStream_t st);
 moe_status launch_route(const moe_shape &s, const void *x, const void *Wg,
                         const float *bias, int bias_stride, int32_t *expert_idx,
                         float *gate, int32_t *seg_cnt, hipStream_t st);

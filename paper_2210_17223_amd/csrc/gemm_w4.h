@@ -1,4 +1,4 @@
-// The 256 x 256 tile GEMM on four wavefronts: what its kernels share.  Included inside the
+// The tile GEMMs on four wavefronts: what its kernels share.  Included inside the
 // translation unit's own namespace; the loop itself is gemm_w4_body.inc, included in the body
 // of every kernel that runs it (the forward's expert GEMMs, the backward's row GEMMs), each
 // with an epilogue of its own.

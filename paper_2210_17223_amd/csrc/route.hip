@@ -105,6 +105,70 @@ __device__ __forceinline__ void route_tail(float (*zs)[kMaxExperts + 1], int32_t
     }
 }
 
+// What a block does with its tokens' logits: the gate's decision, or the gradient of the logits.
+struct RouteTail {
+    int32_t *expert_idx;
+    float *gate;
+    int32_t *seg_cnt;
+    int k, renorm;
+    template <int NQ, int LP, int TB>
+    __device__ __forceinline__ void run(float (*zs)[kMaxExperts + 1], int t0, int T, int E) const
+    {
+        route_tail<NQ, LP, TB>(zs, expert_idx, gate, seg_cnt, t0, T, E, k, renorm);
+    }
+};
+
+// dz = p (dg - <p, dg>) with p the softmax of the logits and dg the gradient of the selected gate
+// weights (zero elsewhere); lanes as in route_tail.
+struct GateGradTail {
+    const int32_t *expert_idx;
+    const float *dgate;
+    float *dz;
+    int k;
+    template <int NQ, int LP, int TB>
+    __device__ __forceinline__ void run(float (*zs)[kMaxExperts + 1], int t0, int T, int E) const
+    {
+        const int tl = threadIdx.x / LP, sub = threadIdx.x % LP;
+        const int t = t0 + tl;
+        const bool live = tl < TB && t < T;
+        float p[NQ], dg[NQ], zmax = -INFINITY;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            p[q] = (live && sub + LP * q < E) ? zs[tl][sub + LP * q] : -INFINITY;
+            dg[q] = 0.0f;
+            zmax = fmaxf(zmax, p[q]);
+        }
+#pragma unroll
+        for (int m = 1; m < LP; m <<= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, m));
+        if (live)
+            for (int j = 0; j < k; ++j) {
+                const int e = expert_idx[static_cast<size_t>(t) * k + j];
+                const float g = dgate[static_cast<size_t>(t) * k + j];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+                    if (e == sub + LP * q) dg[q] = g;
+            }
+        float denom = 0.0f, s = 0.0f;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            p[q] = sub + LP * q < E ? expf(p[q] - zmax) : 0.0f;
+            denom += p[q];
+        }
+#pragma unroll
+        for (int m = 1; m < LP; m <<= 1) denom += __shfl_xor(denom, m);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            p[q] /= denom;
+            s += p[q] * dg[q];
+        }
+#pragma unroll
+        for (int m = 1; m < LP; m <<= 1) s += __shfl_xor(s, m);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            if (live && sub + LP * q < E) dz[static_cast<size_t>(t) * E + sub + LP * q] = p[q] * (dg[q] - s);
+    }
+};
+
 // Logits on the fp32 matrix instruction.  v_mfma_f32_16x16x4_f32 adds its four products to the
 // accumulator one after the other in ascending k, each as a fused multiply-add: a chain of
 // these instructions over the model dimension is the chain of d fused multiply-adds the gate
@@ -149,11 +213,10 @@ struct RouteTile {
     static constexpr size_t LDS = 3 * static_cast<size_t>(STAGE) > LOGITS ? 3 * static_cast<size_t>(STAGE) : LOGITS;
 };
 
-template <typename XT, int TB, int EG>
+template <typename XT, int TB, int EG, typename Tail>
 __global__ __launch_bounds__((RouteTile<XT, TB, EG>::NT), 1) void route_mfma_kernel(
     const XT *__restrict__ x, const float *__restrict__ Wgp, const float *__restrict__ bias,
-    int bias_stride, int32_t *__restrict__ expert_idx, float *__restrict__ gate,
-    int32_t *__restrict__ seg_cnt, int T, int d, int dP, int E, int EP, int k, int renorm)
+    int bias_stride, Tail tail, int T, int d, int dP, int E, int EP)
 {
     using RT = RouteTile<XT, TB, EG>;
     constexpr int NACC = RT::NACC, TG = RT::TG, NC = RT::NC, STAGE = RT::STAGE, TILE = RT::TILE;
@@ -329,7 +392,7 @@ __global__ __launch_bounds__((RouteTile<XT, TB, EG>::NT), 1) void route_mfma_ker
     __syncthreads();
     // lanes per token in the tail, and logits per lane
     constexpr int LP = RT::NT / TB < EG * 16 ? RT::NT / TB : EG * 16, NQ = EG * 16 / LP;
-    route_tail<NQ, LP, TB>(zs, expert_idx, gate, seg_cnt, t0, T, E, k, renorm);
+    tail.template run<NQ, LP, TB>(zs, t0, T, E);
 }
 
 // Gate matrix [d][E] (fp32 or bf16) -> fp32 [EP][dP], expert-major, zero padded, each run of 16
@@ -365,10 +428,10 @@ int padded_dim(int d) { return (d + kGatePad - 1) / kGatePad * kGatePad; }
 // that many blocks would only read the gate matrix more often.
 int route_tokens(const moe_shape &s) { return s.T <= 16 * 512 ? 16 : s.T <= 32 * 512 ? 32 : 64; }
 
-template <typename XT>
-moe_status launch_route_t(const moe_shape &s, const XT *x, const float *Wgp,
-                          const float *bias, int bias_stride, int32_t *expert_idx,
-                          float *gate, int32_t *seg_cnt, hipStream_t st)
+// tokens: of the T of the shape (which choose the tile), those of this launch
+template <typename XT, typename Tail>
+moe_status launch_route_t(const moe_shape &s, int tokens, const XT *x, const float *Wgp,
+                          const float *bias, int bias_stride, const Tail &tail, hipStream_t st)
 {
     const int EP = pow2_ceil(s.E);
     const int dP = padded_dim(s.d_model);
@@ -376,13 +439,12 @@ moe_status launch_route_t(const moe_shape &s, const XT *x, const float *Wgp,
     bool launched = false;
 #define MOE_ROUTE_CASE(TB_, EG_)                                                              \
     if (tb == TB_ && eg == EG_) {                                                             \
-        auto kern = route_mfma_kernel<XT, TB_, EG_>;                                          \
+        auto kern = route_mfma_kernel<XT, TB_, EG_, Tail>;                                       \
         constexpr size_t lds = RouteTile<XT, TB_, EG_>::LDS;                                  \
         static PerDeviceOnce once;                                                            \
         once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));          \
-        hipLaunchKernelGGL(kern, dim3(ceil_div(s.T, TB_)), dim3(RouteTile<XT, TB_, EG_>::NT), lds, st, x, Wgp, bias,  \
-                           bias_stride, expert_idx, gate, seg_cnt, s.T, s.d_model, dP, s.E,   \
-                           EP, s.k, s.renorm_topk);                                           \
+        hipLaunchKernelGGL(kern, dim3(ceil_div(tokens, TB_)), dim3(RouteTile<XT, TB_, EG_>::NT), lds, st, x,  \
+                           Wgp, bias, bias_stride, tail, tokens, s.d_model, dP, s.E, EP);     \
         launched = true;                                                                      \
     }
     MOE_ROUTE_CASE(16, 1) MOE_ROUTE_CASE(16, 2) MOE_ROUTE_CASE(16, 4)
@@ -426,13 +488,24 @@ moe_status launch_route(const moe_shape &s, const void *x, const void *Wgp,
                         const float *bias, int bias_stride, int32_t *expert_idx,
                         float *gate, int32_t *seg_cnt, hipStream_t st)
 {
+    const RouteTail tail{expert_idx, gate, seg_cnt, s.k, s.renorm_topk};
     if (s.dtype == MOE_BF16)
-        return launch_route_t<uint16_t>(s, static_cast<const uint16_t *>(x),
-                                        static_cast<const float *>(Wgp), bias, bias_stride,
-                                        expert_idx, gate, seg_cnt, st);
-    return launch_route_t<float>(s, static_cast<const float *>(x),
-                                 static_cast<const float *>(Wgp), bias, bias_stride,
-                                 expert_idx, gate, seg_cnt, st);
+        return launch_route_t(s, s.T, static_cast<const uint16_t *>(x), static_cast<const float *>(Wgp),
+                              bias, bias_stride, tail, st);
+    return launch_route_t(s, s.T, static_cast<const float *>(x), static_cast<const float *>(Wgp), bias,
+                          bias_stride, tail, st);
+}
+
+// The logit gradients of tokens [t0, t1) of a bf16 layer: dz [T][E] from dgate [T][k].  The logits
+// are computed again, the same chain as in the forward pass.
+moe_status launch_gate_grad(const moe_shape &s, int t0, int t1, const uint16_t *x, const float *Wgp,
+                            const float *bias, int bias_stride, const int32_t *expert_idx,
+                            const float *dgate, float *dz, hipStream_t st)
+{
+    const size_t t = static_cast<size_t>(t0);
+    const GateGradTail tail{expert_idx + t * s.k, dgate + t * s.k, dz + t * s.E, s.k};
+    return launch_route_t(s, t1 - t0, x + t * s.d_model, Wgp, bias != nullptr ? bias + t * bias_stride : nullptr,
+                          bias_stride, tail, st);
 }
 
 }  // namespace moe

@@ -9,8 +9,8 @@
 // bf16 layers: both operands are stored with the contraction index contiguous (activations by
 // nature, weights after moe_pack_weights), and the weights are fed as the MFMA "A" operand
 // so that each lane ends up with four consecutive output columns of one row.
-// grouped_gemm_w4_kernel runs tiles of 128 x 128 up to 256 x 256, grouped_gemm_stream_kernel
-// decode steps, grouped_gemm_mfma_kernel what lies between (64 x 256).  H and ye are kept in fp16.
+// grouped_gemm_w4_kernel runs 256 x 256 tiles, grouped_gemm_mfma_kernel those of 128 and 64 rows,
+// grouped_gemm_stream_kernel decode steps.  H and ye are kept in fp16.
 // fp32 layers: grouped_gemm_f32_kernel, on the fp32 matrix instruction.
 #include "common.h"
 #include <cstdio>
@@ -545,8 +545,8 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_stream_kernel(
 // ABL (measurement only, 0 in the layer): bit 0 leaves out the MFMAs, bit 1 the LDS fragment
 // reads after the first step, bit 2 the global loads and LDS writes inside the loop, bit 3 the
 // output stores.  Results are then wrong by construction; every access stays inside the buffers.
-template <bool F16, int ACT, bool KEEP, bool KTAIL, int BM, int BN, int ABL = 0>
-__global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void grouped_gemm_w4_kernel(
+template <bool F16, int ACT, bool KEEP, bool KTAIL, int BM, int BN, int ABL>
+__device__ __forceinline__ void w4_gemm_tile(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
     const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int N, int K,
@@ -605,6 +605,30 @@ __global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void grouped_gemm_w4_k
             __builtin_amdgcn_wave_barrier();
         }
     }
+}
+
+// 256 x 256 tiles
+template <bool F16, int ACT, bool KEEP, bool KTAIL, int ABL = 0>
+__global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
+    const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
+    const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
+    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int N, int K,
+    const int32_t *__restrict__ row_src, int row_div, int a_rows)
+{
+    w4_gemm_tile<F16, ACT, KEEP, KTAIL, 256, 256, ABL>(A, W, bias, C, Pre, items, nitems, N, K, row_src,
+                                                       row_div, a_rows);
+}
+
+// 128 x BN tiles (beside the general form above, which takes a result type and a layout)
+template <bool F16, int ACT, bool KEEP, bool KTAIL, int BN>
+__global__ __launch_bounds__(256, BN == 128 ? 2 : 1) void grouped_gemm_mfma_kernel(
+    const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
+    const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
+    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int N, int K,
+    const int32_t *__restrict__ row_src, int row_div, int a_rows)
+{
+    w4_gemm_tile<F16, ACT, KEEP, KTAIL, 128, BN, 0>(A, W, bias, C, Pre, items, nitems, N, K, row_src,
+                                                    row_div, a_rows);
 }
 #undef MOE_LGKM0
 #undef MOE_VMCNT
@@ -718,11 +742,7 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
                                                               gp.max_items, N, K, stage, st,       \
                                                               row_src, row_div)
     if (gp.w4) {
-        auto launch = [&](auto bm, auto bn, auto tail) {
-            constexpr int BM = decltype(bm)::value, BN = decltype(bn)::value;
-            auto kern = grouped_gemm_w4_kernel<F16, ACT, KEEP, decltype(tail)::value, BM, BN>;
-            constexpr size_t lds = w4_lds(BM, BN);
-            static PerDeviceOnce once;
+        auto launch = [&](auto kern, PerDeviceOnce &once, size_t lds) {
             once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
             const int grid = static_cast<int>(align_up(static_cast<size_t>(gp.max_items), 8));
             hipEvent_t t0, t1;
@@ -731,12 +751,14 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
                                   items, nitems, N, K, row_src, row_div, static_cast<int>(row_limit));
         };
         auto shape = [&](auto tail) {
+            constexpr bool TAIL = decltype(tail)::value;
+            static PerDeviceOnce once[3];
             if (gp.bm == 256)
-                launch(std::integral_constant<int, 256>{}, std::integral_constant<int, 256>{}, tail);
+                launch(grouped_gemm_w4_kernel<F16, ACT, KEEP, TAIL>, once[0], w4_lds(256, 256));
             else if (gp.bn == 256)
-                launch(std::integral_constant<int, 128>{}, std::integral_constant<int, 256>{}, tail);
+                launch(grouped_gemm_mfma_kernel<F16, ACT, KEEP, TAIL, 256>, once[1], w4_lds(128, 256));
             else
-                launch(std::integral_constant<int, 128>{}, std::integral_constant<int, 128>{}, tail);
+                launch(grouped_gemm_mfma_kernel<F16, ACT, KEEP, TAIL, 128>, once[2], w4_lds(128, 128));
         };
         if (K % 64 == 0)
             shape(std::false_type{});
@@ -788,7 +810,7 @@ void launch_mfma_pair(const moe_shape &s, const uint16_t *xe, const uint16_t *W1
 void expert_gemm_kernel_name(const moe_shape &s, int which, int n_chunks, char *name, size_t len)
 {
     const GemmPlan gp = choose_gemm_plan(s, which, n_chunks);
-    std::snprintf(name, len, "%s %dx%d", gp.w4 ? "grouped_gemm_w4_kernel" : gp.bn == 64 ? "grouped_gemm_stream_kernel" : "grouped_gemm_mfma_kernel",
+    std::snprintf(name, len, "%s %dx%d", gp.bm == 256 ? "grouped_gemm_w4_kernel" : gp.bn == 64 ? "grouped_gemm_stream_kernel" : "grouped_gemm_mfma_kernel",
                   gp.bm, gp.bn);
 }
 
@@ -802,8 +824,8 @@ moe_status launch_calib_gemm(const uint16_t *A, const uint16_t *W, _Float16 *C, 
     const int grid = static_cast<int>(align_up(static_cast<size_t>(max_items), 8));
 #define MOE_CALIB_CASE(ABL_)                                                                      \
     case ABL_: {                                                                                  \
-        auto k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, false, 256, 256, ABL_>;                   \
-        auto k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, false, 256, 256, ABL_>;                   \
+        auto k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, false, ABL_>;                   \
+        auto k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, false, ABL_>;                   \
         static PerDeviceOnce once1, once0;                                                        \
         once1.raise_lds(reinterpret_cast<const void *>(k1), static_cast<int>(lds));               \
         once0.raise_lds(reinterpret_cast<const void *>(k0), static_cast<int>(lds));               \

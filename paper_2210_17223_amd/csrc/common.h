@@ -69,8 +69,9 @@ struct GemmPlan {
     int32_t concurrent;      // work items in flight per XCD (sets the panel width)
 };
 // Tile of a row-grouped GEMM on the four-wavefront kernels (gemm_w4.h): `rows` rows in all over E
-// experts.  256 x 256 where there are many such tiles and a contraction that pays for their prologue
-// and epilogue; else by the number of rounds the tiles take on the chip -- 256 of 256 x 256 at a
+// experts.  256 x 256 where there are many such tiles, unless the contraction is one of a few
+// stages that 128 x 128 tiles hide their prologue and epilogue behind better (K = 512 and 704 measured;
+// below four stages the larger tile stays, unmeasured against the smaller); where tiles are few, by the number of rounds the tiles take on the chip -- 256 of 256 x 256 at a
 // time, 512 of 128 x 128 (two per compute unit), and a tile's time in 64-deep stages -- with the
 // times measured over layers of 256 .. 20000 tokens (us: a 256 x 256 stage 1.25, or 1.5 once the
 // chip is full and lowers its clock, prologue and epilogue 10; a round of 128 x 128 0.85, or 0.55
@@ -90,7 +91,7 @@ inline void choose_w4_tile(int64_t rows, int E, int N, int K, GemmPlan *gp)
     const double t128 = static_cast<double>((tiles128 + 511) / 512) *
                         (stages * (tiles128 > 256 ? 0.85 : 0.55) * (K % 64 != 0 ? 1.7 : 1.0) + 3.0);
     const bool many = tiles256 >= 768;
-    if (many ? K >= 1024 : t256 < t128) {
+    if (many ? K >= 1024 || K < 256 : t256 < t128) {
         gp->bm = gp->bn = 256;
         gp->concurrent = 32;
     } else if (K >= 3072 && tiles128 > 400) {

@@ -155,42 +155,48 @@ __global__ __launch_bounds__(kProfThreads) void path_profile_lds_kernel(
 
 // Sixteen lanes per (table, path) row, up to four counters each: row total, then k rounds of
 // "largest remaining count, lowest index first" as a maximum over the lanes.  (36864
-// rows of 16: 5.2 us; 6.0 with one thread per row reading it k + 1 times.)
+// rows of 16: 5.2 us; 6.0 with one thread per row reading it k + 1 times.)  The blocks walk the
+// rows: sixteen lanes for each of 2^28 rows are more work-items than the 32 bits of a launch hold,
+// and the runtime drops what is above them without an error.
+constexpr int64_t kFinalizeBlocks = 1 << 20;
+
 __global__ __launch_bounds__(256) void path_finalize_kernel(
     const uint32_t *__restrict__ counts, int32_t *__restrict__ top_expert,
     unsigned long long *__restrict__ top_prob, long rows, int E, int k)
 {
     constexpr int LP = 16, NQ = kMaxExperts / LP;
-    const long r = (static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x) / LP;
+    const long step = static_cast<long>(gridDim.x) * (blockDim.x / LP);
     const int sub = threadIdx.x % LP;
-    if (r >= rows) return;                             // (whole groups of sixteen lanes)
-    const uint32_t *row = counts + r * E;
-    uint32_t v[NQ];
-    unsigned long long tot = 0;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const int e = sub + LP * q;
-        v[q] = e < E ? row[e] : 0u;
-        tot += v[q];
-    }
-#pragma unroll
-    for (int m = 1; m < LP; m <<= 1) tot += __shfl_xor(tot, m);
-    for (int c = 0; c < k; ++c) {
-        unsigned long long best = 0;                   // count, then 63 - index; count 0 never wins
+    // (whole groups of sixteen lanes leave the loop together)
+    for (long r = static_cast<long>(blockIdx.x) * (blockDim.x / LP) + threadIdx.x / LP; r < rows; r += step) {
+        const uint32_t *row = counts + r * E;
+        uint32_t v[NQ];
+        unsigned long long tot = 0;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const unsigned long long key = static_cast<unsigned long long>(v[q]) << 6 | (63 - sub - LP * q);
-            if (v[q] != 0u && key > best) best = key;
+            const int e = sub + LP * q;
+            v[q] = e < E ? row[e] : 0u;
+            tot += v[q];
         }
 #pragma unroll
-        for (int m = 1; m < LP; m <<= 1) best = max(best, __shfl_xor(best, m));
-        const int e = best != 0 ? 63 - static_cast<int>(best & 63u) : -1;
+        for (int m = 1; m < LP; m <<= 1) tot += __shfl_xor(tot, m);
+        for (int c = 0; c < k; ++c) {
+            unsigned long long best = 0;               // count, then 63 - index; count 0 never wins
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
-            if (e == sub + LP * q) v[q] = 0u;
-        if (sub == 0) {
-            top_expert[r * k + c] = e;
-            top_prob[r * k + c] = e >= 0 ? ((best >> 6) << kFix) / tot : 0ull;
+            for (int q = 0; q < NQ; ++q) {
+                const unsigned long long key = static_cast<unsigned long long>(v[q]) << 6 | (63 - sub - LP * q);
+                if (v[q] != 0u && key > best) best = key;
+            }
+#pragma unroll
+            for (int m = 1; m < LP; m <<= 1) best = max(best, __shfl_xor(best, m));
+            const int e = best != 0 ? 63 - static_cast<int>(best & 63u) : -1;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+                if (e == sub + LP * q) v[q] = 0u;
+            if (sub == 0) {
+                top_expert[r * k + c] = e;
+                top_prob[r * k + c] = e >= 0 ? ((best >> 6) << kFix) / tot : 0ull;
+            }
         }
     }
 }
@@ -405,8 +411,9 @@ moe_status moe_path_finalize(const moe_path_shape *s, const uint32_t *counts,
         return MOE_EINVAL;
     }
     const long rows = static_cast<long>(s->L - s->l) * paths;
-    hipLaunchKernelGGL(path_finalize_kernel, dim3(static_cast<unsigned>((rows + 15) / 16)),
-                       dim3(256), 0, static_cast<hipStream_t>(stream), counts, top_expert,
+    const int64_t blocks = std::min<int64_t>((rows + 15) / 16, kFinalizeBlocks);
+    hipLaunchKernelGGL(path_finalize_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
+                       static_cast<hipStream_t>(stream), counts, top_expert,
                        reinterpret_cast<unsigned long long *>(top_prob), rows, s->E, s->k);
     MOE_TRY_HIP(hipGetLastError());
     return MOE_OK;

@@ -126,3 +126,26 @@ def test_tables_of_many_tokens(L, T0, reps, E, k, l):
     got = counts.cpu().numpy().view(np.uint32).reshape(tables, P, E).astype(np.int64)
     for a, want in enumerate(so.profile_counts(sel, l, E)):
         assert np.array_equal(got[a], want * reps), a
+
+
+def test_finalize_of_more_rows_than_one_launch_has_lanes_for():
+    """19 tables of 3^15 paths: over 2^28 rows, sixteen lanes for each of which would be more
+    work-items than a launch can have; the rows are no multiple of what the grid walks at a time."""
+    s = moe.PathShape(34, 3, 2, 15)
+    P, tables, E, k = moe.moe_path_count(s), 19, 3, 2
+    assert P == 3 ** 15 and tables * P >= 1 << 28
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    counts = torch.randint(0, 4, (tables, P, E), dtype=torch.int32, device=DEV, generator=g)
+    counts[:, :, 1] *= 1000003
+    top_e = torch.full((tables, P, k), 77, dtype=torch.int32, device=DEV)
+    top_q = torch.full((tables, P, k), 77, dtype=torch.int64, device=DEV)
+    moe.moe_path_finalize(s, counts, top_e, top_q)
+    index = 63 - torch.arange(E, device=DEV)
+    for a in range(tables):
+        c = counts[a].long()
+        key = torch.where(c > 0, c * 64 + index, torch.zeros_like(c)).sort(dim=1, descending=True).values[:, :k]
+        listed = key > 0
+        assert torch.equal(top_e[a], torch.where(listed, 63 - key % 64, -1).int()), a
+        total = c.sum(dim=1, keepdim=True).clamp_min(1)
+        assert torch.equal(top_q[a], torch.where(listed, (key // 64 << 32) // total, 0)), a

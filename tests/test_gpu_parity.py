@@ -118,6 +118,33 @@ def test_dispatch_skips_indices_that_name_no_expert(name):
     assert not xe[A:].any()
 
 
+@pytest.mark.parametrize("T", [1, 17, 1023, 1024, 1025, 2048, 2049])
+def test_dispatch_where_blocks_share_a_segment(T):
+    """The plan's launch packs a segment of 16 tokens with four, two or one blocks (up to 64, up to
+    128 and more segments): token counts on either side of both changes, and segments cut short."""
+    E, k, d = 5, 3, 72
+    rng = np.random.default_rng(T)
+    idx = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    idx[T // 2, 1] = -1
+    C = max(1, T * k // E - T // 16)                      # some experts overflow
+    count, off, slot_of, src_of = oracle.plan(idx, E, C)
+    A = int(off[-1])
+    x = torch.randn((T, d), generator=torch.Generator().manual_seed(T)).to(DEV).bfloat16()
+    s = moe.Shape.make(T, d, E, 64, k, C, dtype="bf16")
+    b = moe.alloc_buffers(s, 1, DEV)
+    b["xe"].zero_()
+    moe.moe_dispatch(s, x, torch.from_numpy(idx.reshape(-1)).to(DEV), b["counts"], b["offsets"], b["slot_of"],
+                     b["src_of"], b["xe"], b["workspace"])
+    torch.cuda.synchronize()
+    assert np.array_equal(b["counts"].cpu().numpy(), count)
+    assert np.array_equal(b["offsets"].cpu().numpy(), off)
+    assert np.array_equal(b["slot_of"].cpu().numpy(), slot_of)
+    assert np.array_equal(b["src_of"].cpu().numpy()[:A], src_of)
+    xe = b["xe"].reshape(-1, d)
+    assert torch.equal(xe[:A], x[torch.from_numpy(np.ascontiguousarray(src_of)).to(DEV).long() // k])
+    assert not xe[A:].any()
+
+
 @pytest.mark.parametrize("group_rows", [1, 16, 512], ids=["ffn_per_chunk", "ffn_groups_of_16_rows", "default_groups"])
 @pytest.mark.parametrize("name", list(SMALL))
 def test_whole_layer_and_chunk_invariance(name, group_rows):

@@ -260,7 +260,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_prefix_kernel(
     int32_t *__restrict__ src_of, int n, int E, int capacity, int seg_len, int nseg, int padded,
     int with_items, WorkItem *__restrict__ items0, int32_t *__restrict__ nitems0, GemmPlan gp0,
     WorkItem *__restrict__ items1, int32_t *__restrict__ nitems1, GemmPlan gp1,
-    int spb, int parts, const uint4 *__restrict__ x, uint4 *__restrict__ xe, int vec, int k, int T)
+    int spb, int lg_parts, const uint4 *__restrict__ x, uint4 *__restrict__ xe, int vec, int k, int T)
 {
     constexpr int kParts = kPlanWaves * 4;          // partial sums: 16-byte loads, 4 segments per wavefront load
     __shared__ int32_t part_before[kParts][kMaxExperts], part_total[kParts][kMaxExperts];
@@ -271,8 +271,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_prefix_kernel(
     __shared__ int32_t cum_s[kMaxExperts + 1];
     const int lane = lane_id();
     const int wave = threadIdx.x / kWave;
-    const int first = min(static_cast<int>(blockIdx.x) / parts * spb, nseg);
-    const int part = static_cast<int>(blockIdx.x) % parts;      // of the blocks that share a segment
+    const int first = min(static_cast<int>(blockIdx.x >> lg_parts) * spb, nseg);
+    const int part = static_cast<int>(blockIdx.x) & ((1 << lg_parts) - 1);   // of the blocks that share a segment
     {
         // lane = (segment of the load, four experts): partial sum p = wave * 4 + lane / 16 walks the
         // segments p, p + 16, ...
@@ -363,14 +363,14 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_prefix_kernel(
         }
     }
     if (x == nullptr) return;
-    // Packing in the same launch (one segment per block, or per `parts` blocks: spb = 1): the
+    // Packing in the same launch (one segment per block, or per several: spb = 1): the
     // wavefronts copy the block's share of the segment's token rows to their kept slots, two tokens
     // per round.
     __syncthreads();
     const int seg_tok = seg_len / k;
     const int t_seg = first * seg_tok;
-    const int t_end = (part + 1) * seg_tok / parts;
-    for (int tt = part * seg_tok / parts + wave; tt < t_end; tt += 2 * kPlanWaves) {
+    const int t_end = (part + 1) * seg_tok >> lg_parts;
+    for (int tt = (part * seg_tok >> lg_parts) + wave; tt < t_end; tt += 2 * kPlanWaves) {
         const int ta = tt, tb = tt + kPlanWaves;
         const bool has_a = t_seg + ta < T, has_b = tb < t_end && t_seg + tb < T;
         int sa[kMaxTopK], sb[kMaxTopK];
@@ -551,13 +551,13 @@ moe_status launch_plan(const moe_shape &s, const int32_t *expert_idx, int32_t *c
         // alone would leave compute units without one, down to one token per wavefront.  us, one /
         // several blocks per segment: 16 tokens of d = 768 6.5 / 5.0; 256 of 4096 15.0 / 8.9; 1024
         // of 1024 8.0 / 7.4; 2048 of 2048 13.1 / 10.6.
-        const int parts = !pack || w.nseg > 128 ? 1 : w.nseg > 64 ? 2 : 4;
+        const int lg_parts = !pack || w.nseg > 128 ? 0 : w.nseg > 64 ? 1 : 2;
         hipLaunchKernelGGL(plan_rank_prefix_kernel,
-                           dim3(ceil_div(w.nseg, spb) * parts + (with_items ? kItemBlocks : 1)),
+                           dim3((ceil_div(w.nseg, spb) << lg_parts) + (with_items ? kItemBlocks : 1)),
                            dim3(kPlanThreads), 0, st,
                            expert_idx, w.seg_cnt, counts, offsets, slot_of, src_of, n, s.E,
                            s.capacity, seg_len, w.nseg, padded ? 1 : 0, with_items ? 1 : 0, w.items[0], w.nitems[0], w.gp[0],
-                           w.items[1], w.nitems[1], w.gp[1], spb, parts,
+                           w.items[1], w.nitems[1], w.gp[1], spb, lg_parts,
                            pack ? static_cast<const uint4 *>(x) : nullptr,
                            pack ? static_cast<uint4 *>(xe) : nullptr, s.d_model * elem / 16, s.k,
                            s.T);

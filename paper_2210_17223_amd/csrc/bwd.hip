@@ -328,11 +328,10 @@ __global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void bwd_gemm_w4_kerne
     constexpr int row_div = 1, a_rows = 0;
 #include "gemm_w4_body.inc"
 
-    // Every wavefront is past its last LDS read after the barrier, the matrix results have left
-    // the pipeline after the no-ops.
+    // Every wavefront is past its last LDS read after the barrier.
     MOE_LGKM0();
     MOE_BAR();
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    MOE_MATRIX_RESULTS();
     const int rbase = item.row0 + wm * (BM / 2);
     if constexpr (EPI == 0) {
         float *out = static_cast<float *>(Cout);
@@ -747,11 +746,8 @@ __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
                 if constexpr (AF16 && (m & 7) == 0) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) af[s][j][c] = f16x2_to_bf16x2(af[s][j][c]);
-                    // two wait states between a vector instruction's result and the matrix
-                    // instruction that reads it (the compiler does not see that one)
-                    asm volatile("s_nop 1" : "+v"(af[s][j]));
                 }
-                mfma_16x16x32_agpr<false>(acc[i][j], bf[s][i], af[s][j]);
+                mfma_16x16x32_agpr<false, AF16 ? (m & 7) == 0 : m == 0>(acc[i][j], bf[s][i], af[s][j]);
                 mem(mc);
                 MOE_SB();
             });
@@ -795,7 +791,7 @@ __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
         MOE_VMCNT(0);
         MOE_LGKM0();
         MOE_BAR();
-        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+        MOE_MATRIX_RESULTS();
     }
 
     // acc[i][j][c]: column n0 + wn * 128 + i * 16 + oct * 4 + c, row m0 + wm * 128 + j * 16 + fr.

@@ -554,13 +554,12 @@ __device__ __forceinline__ void w4_gemm_tile(
 {
 #include "gemm_w4_body.inc"
 
-    // Epilogue.  Every wavefront is past its last LDS read after the barrier; the matrix
-    // results have left the pipeline after the no-ops (the compiler does not see through the
-    // inline assembly).  The wavefront's BM / 2 x BN / 2 sub-tile goes to its own patch (16
-    // bytes of row padding) and leaves as whole lines, 16 bytes per lane.
+    // Epilogue.  Every wavefront is past its last LDS read after the barrier.  The wavefront's
+    // BM / 2 x BN / 2 sub-tile goes to its own patch (16 bytes of row padding) and leaves as whole
+    // lines, 16 bytes per lane.
     MOE_LGKM0();
     MOE_BAR();
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    MOE_MATRIX_RESULTS();
     constexpr int PITCH = BN + 16, LPR = BN / 16, RPI = 64 / LPR;   // lanes per row, rows per instruction
     char *patch = lds + wave * (BM / 2) * PITCH;
     const float *bexp = bias != nullptr ? bias + static_cast<size_t>(item.expert) * N : nullptr;
@@ -634,6 +633,7 @@ __global__ __launch_bounds__(256, BN == 128 ? 2 : 1) void grouped_gemm_mfma_kern
 #undef MOE_VMCNT
 #undef MOE_SB
 #undef MOE_BAR
+#undef MOE_MATRIX_RESULTS
 
 // ---------------------------------------------------------------- weight packing
 // Out[e][n][k] = convert(In[e][k][n]); 64 x 64 tiles through LDS.

@@ -50,14 +50,32 @@ constexpr size_t kW4Lds = w4_lds(256, 256);
         MOE_SB();                                                                                \
     } while (0)
 
-template <bool F16>
+// The compiler puts no wait states around inline assembly.  WAIT: two of them, what a vector
+// instruction's result needs before a matrix instruction reads it, in the same statement, so that
+// nothing gets in between (for the first one behind a conversion).  That nothing else comes too
+// close, registers moved on the way round a loop among it, tests/test_matrix_hazards.py reads
+// back from the built library.  (Two wait states at the top of every stage: gpt2s-sized layers, 8192
+// rows of 768 x 3072, 61.5 -> 61.9 us in the first GEMM.)
+template <bool F16, bool WAIT>
 __device__ __forceinline__ void mfma_16x16x32_agpr(f32x4 &acc, const u32x4 &a, const u32x4 &b)
 {
-    if constexpr (F16)
+    if constexpr (F16 && WAIT)
+        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    else if constexpr (F16)
         asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    else if constexpr (WAIT)
+        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
     else
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
+
+// Behind the last matrix instruction: the results have left the pipeline after the no-ops, and the
+// fence keeps reads of the accumulators behind them.
+#define MOE_MATRIX_RESULTS()                                                                     \
+    do {                                                                                         \
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");                                       \
+        MOE_SB();                                                                                \
+    } while (0)
 
 // 16 bytes per lane from base + voff + soff to LDS at `at` + 16 * lane.  Written out because
 // behind the compiler's builtin every later LDS read waits for all loads; completion is counted

@@ -84,7 +84,7 @@ __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rs, int voff,
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %3 offen lds"
-                 ::"v"(voff), "s"(rs), "s"(at), "s"(soff) : "memory");
+                 ::"v"(voff), "s"(rs), "s"(at), "s"(soff) : "memory", "m0");
 #endif
 }
 __device__ __forceinline__ uint32_t lds_address(const void *p)

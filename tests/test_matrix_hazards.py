@@ -15,6 +15,7 @@ import subprocess
 import pytest
 
 import paper_2210_17223_amd as moe
+from paper_2210_17223_amd import build
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 
@@ -185,3 +186,36 @@ def test_no_matrix_instruction_of_the_library_is_too_close(library):
     assert sum("w4_kernel" in n for n in library) >= 20 and len(library) >= 100
     bad = {n: h for n, f in library.items() if (h := hazards(f))}
     assert not bad, "\n".join(f"{n}: {len(h)}, e.g. {h[0][0]} -> {h[0][1]}" for n, h in bad.items())
+
+
+LOADS = """
+#include <hip/hip_runtime.h>
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+namespace {
+#include "gemm_w4.h"
+}
+__global__ void loads(const char *p, int n, uint32_t at)
+{
+    __shared__ char lds[4096];
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p), 0, n, 0x00020000);
+    auto *dst = (__attribute__((address_space(3))) void *)lds;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 4, threadIdx.x * 4, 0, 0, 0);
+    load_to_lds(rs, threadIdx.x * 16, at, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 4, threadIdx.x * 4, 0, 256, 0);
+}
+"""
+
+
+def test_a_load_to_lds_tells_the_compiler_that_m0_changes(tmp_path):
+    """The compiler's own loads to LDS keep their destination in M0 from one to the next: between
+    them `load_to_lds` takes M0 for its own, so the second has to set it again."""
+    (tmp_path / "loads.hip").write_text(LOADS)
+    flags = [f for f in build.FLAGS if f not in ("-fPIC", "-Wall")]
+    subprocess.run([build.HIPCC, *flags, "-w", "--cuda-device-only", "-S", "loads.hip", "-o", "loads.asm"],
+                   cwd=tmp_path, check=True, capture_output=True)
+    code = [l.split(";")[0].strip() for l in (tmp_path / "loads.asm").read_text().splitlines()]
+    loads = [i for i, l in enumerate(code) if l.startswith("buffer_load") and l.endswith(" lds")]
+    assert len(loads) == 3
+    for before, load in zip([0] + loads, loads):
+        assert any(re.match(r"s_\w+ m0,", l) for l in code[before:load]), code[before:load + 1]

@@ -9,8 +9,10 @@
 // bf16 layers: both operands are stored with the contraction index contiguous (activations by
 // nature, weights after moe_pack_weights), and the weights are fed as the MFMA "A" operand
 // so that each lane ends up with four consecutive output columns of one row.
-// grouped_gemm_w4_kernel runs 256 x 256 tiles, grouped_gemm_mfma_kernel those of 128 and 64 rows,
-// grouped_gemm_stream_kernel decode steps.  H and ye are kept in fp16.
+// grouped_gemm_w4_kernel runs 256 x 256 tiles and grouped_gemm_mfma_kernel those of 128 rows, both on the
+// loop of gemm_w4_body.inc; grouped_gemm_stream_kernel runs decode steps; grouped_gemm_staged_kernel, whose
+// operands go through registers, 64 x 256 tiles and operands past 32-bit offsets.  H and ye are
+// kept in fp16.
 // fp32 layers: grouped_gemm_f32_kernel, on the fp32 matrix instruction.
 #include "common.h"
 #include <cstdio>
@@ -234,7 +236,7 @@ __device__ __forceinline__ void store4(_Float16 *p, const float (&v)[4])
 // loader gathers the tokens where they lie, so the multiply does not wait for the pack.
 template <bool F16, typename TOut, int ACT, int WM, int WN, int TM, int TN, bool KTAIL, bool KEEP>
 // (two wavefronts per SIMD in every shape: two 4-wavefront blocks or one 8-wavefront block)
-__global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_mfma_kernel(
+__global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_staged_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, TOut *__restrict__ C, _Float16 *__restrict__ Pre,
     const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int N, int K,
@@ -618,7 +620,7 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
                                                        row_div, a_rows);
 }
 
-// 128 x BN tiles (beside the general form above, which takes a result type and a layout)
+// 128 x BN tiles
 template <bool F16, int ACT, bool KEEP, bool KTAIL, int BN>
 __global__ __launch_bounds__(256, BN == 128 ? 2 : 1) void grouped_gemm_mfma_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
@@ -696,7 +698,7 @@ void launch_mfma_cfg_k(const uint16_t *A, const uint16_t *W, const float *bias, 
 {
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
     constexpr size_t lds = 2 * (BM + BN) * (64 + 8) * sizeof(uint16_t);
-    auto kern = grouped_gemm_mfma_kernel<F16, TOut, ACT, WM, WN, TM, TN, KTAIL, KEEP>;
+    auto kern = grouped_gemm_staged_kernel<F16, TOut, ACT, WM, WN, TM, TN, KTAIL, KEEP>;
     static PerDeviceOnce once;   // raising the dynamic LDS limit: once per kernel and device
     once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
     const int grid = static_cast<int>(align_up(static_cast<size_t>(max_items), 8));
@@ -810,7 +812,9 @@ void launch_mfma_pair(const moe_shape &s, const uint16_t *xe, const uint16_t *W1
 void expert_gemm_kernel_name(const moe_shape &s, int which, int n_chunks, char *name, size_t len)
 {
     const GemmPlan gp = choose_gemm_plan(s, which, n_chunks);
-    std::snprintf(name, len, "%s %dx%d", gp.bm == 256 ? "grouped_gemm_w4_kernel" : gp.bn == 64 ? "grouped_gemm_stream_kernel" : "grouped_gemm_mfma_kernel",
+    std::snprintf(name, len, "%s %dx%d",
+                  gp.w4 ? gp.bm == 256 ? "grouped_gemm_w4_kernel" : "grouped_gemm_mfma_kernel"
+                        : gp.bn == 64 ? "grouped_gemm_stream_kernel" : "grouped_gemm_staged_kernel",
                   gp.bm, gp.bn);
 }
 

@@ -120,7 +120,7 @@ def test_static_dispatch_refuses_what_does_not_fit_its_array():
 
 def test_expert_gemm_kernel_names_the_kernel_and_its_tile():
     """moe_expert_gemm_kernel is host logic only: the large layer takes the 256 x 256 four-wavefront
-    kernel for both GEMMs, the GPT-2-small layer the 128-row tiles of the general kernel."""
+    kernel for both GEMMs, the GPT-2-small layer 128-row tiles."""
     big = wl.CONFIGS["large_chunked"]
     s = moe.Shape.make(big["T"], big["d"], big["E"], big["h"], big["k"], big["C"], dtype="bf16", act="gelu")
     assert moe.moe_expert_gemm_kernel(s, 0) == "grouped_gemm_w4_kernel 256x256"
@@ -134,3 +134,16 @@ def test_expert_gemm_kernel_names_the_kernel_and_its_tile():
         moe.moe_expert_gemm_kernel(s3, 0)
     with pytest.raises(moe.MoeError):
         moe.moe_expert_gemm_kernel(s, 2)
+
+
+def test_expert_gemm_kernel_tells_every_kernel_apart():
+    """Each name is one kernel: tiles of 128 rows on the four-wavefront loop are not called what the
+    register-staged kernel's are."""
+    def names(T, d, E, h, k, C):
+        s = moe.Shape.make(T, d, E, h, k, C, dtype="bf16", act="gelu")
+        return [moe.moe_expert_gemm_kernel(s, which) for which in (0, 1)]
+
+    assert names(16, 768, 16, 3072, 2, 16) == ["grouped_gemm_stream_kernel 64x64"] * 2       # a decode step
+    assert names(256, 4096, 8, 14336, 2, 256)[1] == "grouped_gemm_staged_kernel 64x256"      # few rows, long weights
+    assert names(300, 32776, 2, 32840, 1, 300) == ["grouped_gemm_staged_kernel 128x256"] * 2  # past 32-bit offsets
+    assert all(n.startswith("grouped_gemm_mfma_kernel 128x") for n in names(4096, 768, 16, 3072, 2, 640))

@@ -207,6 +207,40 @@ def test_gate_ties_go_to_the_lowest_index(T, d, E, k):
     np.testing.assert_allclose(b["gate"].cpu().numpy().reshape(T, k)[:T // 3], 1.0 / E, rtol=1e-6)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,d,scale", [(100, 776, "ordinary"), (9000, 72, "wide"), (17000, 40, "wide"),
+                                       (300, 1000, "denormal")])
+def test_gate_logits_are_the_fma_chain_bit_for_bit(T, d, scale, dtype):
+    """The bias takes the oracle's logit off again: the sum is zero exactly where the logit has the
+    oracle's bits, and then every token lists its experts in index order.  A logit that is off,
+    by one unit in the last place or by a denormal, moves its expert ahead or back; with the experts
+    reversed the other way round."""
+    E = k = 8
+    rng = np.random.default_rng(d)
+    x, Wg = rng.standard_normal((T, d)), rng.standard_normal((d, E))
+    if scale == "wide":                               # sums that cancel, of terms 2^24 apart
+        x *= 2.0 ** rng.integers(-12, 13, size=(T, d))
+        x[:, 1::2] = -x[:, ::2]
+    if scale == "denormal":
+        x, Wg = x * 2.0 ** -66, Wg * 2.0 ** -66
+    x, Wg = (wl.bf16_round(a.astype(np.float32)) for a in (x, Wg))
+    if dtype == "f32":
+        x, Wg = x * np.float32(1.0 + 2.0 ** -9), Wg * np.float32(1.0 - 2.0 ** -10)
+    s = moe.Shape.make(T, d, E, 64, k, T, dtype=dtype)
+    for order in (np.arange(E), np.arange(E)[::-1]):
+        W = np.ascontiguousarray(Wg[:, order])
+        z = oracle.gate_logits(x, W, None, 0)
+        if scale == "denormal":
+            assert (np.abs(z) < 2.0 ** -126).mean() > 0.5 and (z != 0).mean() > 0.9
+        b = moe.alloc_buffers(s, 1, DEV)
+        moe.moe_pack_gate(s, upload(W, dtype), b["Wgp"])
+        moe.moe_route(s, upload(x, dtype), b["Wgp"], torch.from_numpy(-z).to(DEV), E, b["expert_idx"], b["gate"])
+        torch.cuda.synchronize()
+        off = (b["expert_idx"].view(T, E) != torch.arange(E, device=DEV)).any(1)
+        assert not off.any(), int(off.sum())
+        assert (b["gate"] == 1.0 / E).all()
+
+
 @pytest.mark.parametrize("d,h,act,keep", [(384, 3072, "gelu", False), (3072, 256, "relu", False),
                                           (320, 3072, "gelu_tanh", True)],
                          ids=["first_gemm_256_tiles", "second_gemm_256_tiles", "first_gemm_kept_preactivations"])

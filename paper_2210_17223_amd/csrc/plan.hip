@@ -254,6 +254,9 @@ __device__ void build_items(const GemmPlan &gp, WorkItem *__restrict__ items,
 // its own base -- nseg * 256 bytes from L2 per block) instead of waiting for a scan kernel's
 // launch.  The blocks beyond those that rank segments hold none: the last one writes counts
 // and offsets, and for an unchunked layer they share the building of the work lists.
+// SHARED: 2^lg_parts blocks pack a segment together (a form of its own: the shifts and the test at the
+// plan's stores cost launches without them 0.2 us).
+template <bool SHARED>
 __global__ __launch_bounds__(kPlanThreads) void plan_rank_prefix_kernel(
     const int32_t *__restrict__ expert_idx, const int32_t *__restrict__ seg_cnt,
     int32_t *__restrict__ counts, int32_t *__restrict__ offsets, int32_t *__restrict__ slot_of,
@@ -271,6 +274,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_prefix_kernel(
     __shared__ int32_t cum_s[kMaxExperts + 1];
     const int lane = lane_id();
     const int wave = threadIdx.x / kWave;
+    if constexpr (!SHARED) lg_parts = 0;
     const int first = min(static_cast<int>(blockIdx.x >> lg_parts) * spb, nseg);
     const int part = static_cast<int>(blockIdx.x) & ((1 << lg_parts) - 1);   // of the blocks that share a segment
     {
@@ -552,7 +556,7 @@ moe_status launch_plan(const moe_shape &s, const int32_t *expert_idx, int32_t *c
         // several blocks per segment: 16 tokens of d = 768 6.5 / 5.0; 256 of 4096 15.0 / 8.9; 1024
         // of 1024 8.0 / 7.4; 2048 of 2048 13.1 / 10.6.
         const int lg_parts = !pack || w.nseg > 128 ? 0 : w.nseg > 64 ? 1 : 2;
-        hipLaunchKernelGGL(plan_rank_prefix_kernel,
+        hipLaunchKernelGGL(lg_parts != 0 ? plan_rank_prefix_kernel<true> : plan_rank_prefix_kernel<false>,
                            dim3((ceil_div(w.nseg, spb) << lg_parts) + (with_items ? kItemBlocks : 1)),
                            dim3(kPlanThreads), 0, st,
                            expert_idx, w.seg_cnt, counts, offsets, slot_of, src_of, n, s.E,

@@ -33,8 +33,8 @@ INFINITY_CACHE_BYTES = 256 << 20
 # The counters cannot be read from inside the process, so the figure is a stored
 # measurement, reported only for the workload and launch configuration it was taken on
 # (null for any other): {(workload, n_chunks): (FETCH_SIZE KiB, WRITE_SIZE KiB)} per launch.
-GEMM1_TRAFFIC_KIB = {("large_chunked", 1): (1559144.2, 1017952.0),     # profiles/layer_hbm_traffic_pmc.txt
-                     ("gpt2s_moe", 1): (69506.5, 50068.6)}
+GEMM1_TRAFFIC_KIB = {("large_chunked", 1): (1561661.2, 1017952.0),     # profiles/layer_hbm_traffic_pmc.txt
+                     ("gpt2s_moe", 1): (70443.6, 49152.0)}
 FETCH_UNIT, WRITE_UNIT = 2.0, 1.0     # what the plain-copy calibration reads per counted KiB
 
 
@@ -425,10 +425,10 @@ def main() -> int:
                       "mfma_util": (4.0 * A * l0.d * l0.h * n_layers) / ffn_us / 1e12 / PEAK_BF16_TFLOPS,
                       "gemm2_mfma_util": (2.0 * A * l0.d * l0.h * n_layers) / (st["gemm2"] * 1e-6) / 1e12 / PEAK_BF16_TFLOPS,
                       "GBps": ffn_bytes / ffn_us / 1e9}
-        # gate: T*d*E sequential-order fp32 FMAs against the unpacked vector rate
-        # (256 CUs x 64 lanes x 2.4 GHz = 39.3 TFMA/s; packed-fp32 instructions are off)
+        # gate: T*d*E sequential-order fp32 FMAs against the fp32 matrix instruction's rate
+        # (256 CUs x 4 SIMDs x 32 FMAs per cycle x 2.4 GHz = 78.6 TFMA/s)
         out["gate"] = {"us": st["route"],
-                       "alu_frac": (l0.T * l0.d * l0.E * n_layers) / (st["route"] * 1e-6) / 39.3e12}
+                       "matrix_frac": (l0.T * l0.d * l0.E * n_layers) / (st["route"] * 1e-6) / 78.6e12}
         if args.backward:
             bw = [n for n in ("bwd_recompute", "bwd_dP", "bwd_dxe", "bwd_wgrad2", "bwd_wgrad1")
                   if st[n] is not None]          # no recomputation when the forward kept P
@@ -573,7 +573,7 @@ def gemm_ablation() -> int:
     E, rows_e, BM = 64, 1024, 256
     variants = [(0, "whole kernel"), (8, "no output stores"),
                 (6, "MFMAs + barriers only (one stage of operands)"), (4, "MFMAs + LDS fragment reads"),
-                (2, "MFMAs + global loads + LDS writes"), (1, "everything but the MFMAs"),
+                (2, "MFMAs + global loads into LDS"), (1, "everything but the MFMAs"),
                 (7, "barriers, prologue and epilogue only")]
     out = {"gemm_ablation": True, "shape": f"{E} experts x {rows_e} rows, 256 x 256 tiles", "problems": {}}
     for tag, N, K, gelu in (("first GEMM  (N=8192, K=2048, GeLU)", 8192, 2048, True),

@@ -831,9 +831,9 @@ __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
 // of them: the rows' sums are the accumulators' start, the tokens' dz stay in registers, and
 // the packed gate matrix (fp32 [EP][dP], expert-major, zero padded, columns ordered by
 // packed_gate_column) is read once per 32 tokens from L2.  Bound by HBM: k fp32 rows in, one out per
-// token.  T = 32768, d = 2048, E = 64, k = 2 (0.8 GB), us: 326, and 101 for the logit
+// token.  T = 32768, d = 2048, E = 64, k = 2 (0.8 GB), us: 339, and 109 for the logit
 // gradients before it; the token-per-wavefront kernel they replace took 800 (LDS reads of the gate
-// matrix twice per token).  T = 4096, d = 768, E = 16: 14 + 9 (23).
+// matrix twice per token).  T = 4096, d = 768, E = 16: 14.3 + 8.6 (23).
 template <int NG>
 __global__ __launch_bounds__(256) void gate_dx_kernel(
     const float *__restrict__ Wgp, const int32_t *__restrict__ slot_of, const float *__restrict__ dxe,
@@ -906,7 +906,7 @@ __global__ __launch_bounds__(256) void gate_dx_kernel(
 // matrix instruction.  Block = 64 columns i (16 per wavefront) x all experts (NG groups of 16);
 // tokens go through LDS 64 at a time, the next 64 on their way in registers.  The row pitches (16
 // mod 64 words) let the four tokens of an instruction fall into different banks.  T = 32768,
-// d = 2048, E = 64, us: 109 (381 with a v_fmac chain per column and a quarter of the experts).
+// d = 2048, E = 64, us: 114 (381 with a v_fmac chain per column and a quarter of the experts).
 template <int NG>
 __global__ __launch_bounds__(256) void dwg_partial_kernel(
     const uint16_t *__restrict__ x, const float *__restrict__ dz, float *__restrict__ partial, int T,

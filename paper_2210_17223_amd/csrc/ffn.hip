@@ -435,7 +435,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_staged_kernel(
 // loads in flight; a block is four of them.  64 columns per block instead of 256: at 768 columns
 // and 16 experts the second GEMM of a layer is 192 blocks, not 48.
 // The contraction order is that of the other 16-bit kernels (same bits).
-// 16 tokens, 16 experts, k = 2, 768 x 3072, the two GEMMs: 14.9 and 17.6 us (17.2 and 25.7 with 128 x 128
+// 16 tokens, 16 experts, k = 2, 768 x 3072, the two GEMMs: 16.0 and 18.0 us (17.2 and 25.7 with 128 x 128
 // and 64 x 256 tiles).
 template <bool F16, int ACT, bool KEEP, bool KTAIL>
 __global__ __launch_bounds__(256, 2) void grouped_gemm_stream_kernel(
@@ -545,7 +545,7 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_stream_kernel(
 }
 
 // ABL (measurement only, 0 in the layer): bit 0 leaves out the MFMAs, bit 1 the LDS fragment
-// reads after the first step, bit 2 the global loads and LDS writes inside the loop, bit 3 the
+// reads after the first step, bit 2 the global loads into LDS inside the loop, bit 3 the
 // output stores.  Results are then wrong by construction; every access stays inside the buffers.
 template <bool F16, int ACT, bool KEEP, bool KTAIL, int BM, int BN, int ABL>
 __device__ __forceinline__ void w4_gemm_tile(

@@ -23,12 +23,14 @@
 //  * Every memory instruction is issued singly between two matrix instructions in a fixed order;
 //    those are inline assembly so that the accumulators stay in AGPRs and the order holds.
 //    Neighbouring ones share an operand (serpentine order).
-// What bounds it is power: the chip lowers its clock with the energy per operation (the 32 x 32 x
-// 16 form of this kernel kept the matrix cores busy for 81 % of the cycles at 1.33 GHz).  At
-// 65536 rows: N = 2048, K = 8192 1527-1611 us (1780-1835 with 32 x 32 x 16 instructions and
-// operands staged through registers; a vendor library's dense product 1506), N = 8192, K = 2048
-// 1674-1750 (1942-1985).  With the same tile for every block it takes 1290: the rest is the way
-// from HBM.
+// What bounds it: the matrix cores are busy for 59 % / 77 % of the cycles (N = 8192, K = 2048, GeLU / N =
+// 2048, K = 8192), at a clock of 1.72 / 1.69 GHz that the chip sets by the energy per operation (on all-ones
+// operands the same launches are 34 % / 24 % faster).  With 32 x 32 x 16 instructions and operands staged
+// through registers it was 56 % / 78 % at 1.68 / 1.55 GHz: the first GEMM lost cycles, the second takes as many
+// as before and they have become cheaper.  us in a layer of 63622 rows: 2056 / 1605 (2237 / 1746).  On 64 x 1024
+// rows alone: 2184 / 1682, of which the matrix instructions and barriers by themselves take 1560 / 1199, and
+// the loads into LDS beside them 21 % / 34 % on top; a vendor library's dense products of these sizes 1834
+// / 1668.
 // 128 x 256 (64 x 128 per wavefront) and 128 x 128 tiles (64 x 64) run the same loop.  128 x 256 has
 // LDS for three whole stages instead of the ring; of 128 x 128 a compute unit holds two blocks, one
 // of which multiplies through the other's prologue and epilogue.  Against 32 x 32 x 16 tiles staged

@@ -172,7 +172,7 @@ struct GateGradTail {
 // Logits on the fp32 matrix instruction.  v_mfma_f32_16x16x4_f32 adds its four products to the
 // accumulator one after the other in ascending k, each as a fused multiply-add: a chain of
 // these instructions over the model dimension is the chain of d fused multiply-adds the gate
-// is defined by, bit for bit (checked on the device against fmaf, denormals included), for
+// is defined by, bit for bit (denormals included: the test of the gate's logits), for
 // 16 tokens x 16 experts at once.  A dependent chain advances one column in 8 cycles (10 for
 // v_fmac) and the instruction does 32 multiply-adds per cycle and SIMD (16 for v_fmac).
 //
@@ -186,15 +186,16 @@ struct GateGradTail {
 // step i; a tile of 16 rows is [quad of steps][lane / 16][row] of 16 bytes with a pitch of 272
 // bytes per 16-lane group, which keeps both the reads and the writes free of bank conflicts.
 // (The packed gate matrix has a lane's four columns side by side: regrouped on the way instead,
-// by 4-byte LDS writes or 4-byte loads, 64 experts took 103 / 122 us at T = 32768, d = 2048.)
+// by 4-byte LDS writes or 4-byte loads, 64 experts took a tenth / a third longer at T = 32768, d = 2048.)
 // Three stages of tiles: one barrier per stage, in
 // the middle of the multipliers' stage, so that their reads run on across stage boundaries.
 //
 // Few tokens: bound by the chain (3.3 ns per column at 2.4 GHz), so blocks hold as few tokens
 // as the matrix instruction allows.  Many: bound by the matrix cores (T d E / 78.6e12 s) or by
-// reading x.  Measured against one v_fmac chain per lane or a register block of them (us):
-// T = 4096, d = 768, E = 16: 7.8 (12.0); 256, 4096, 8: 21 (34.5); 3001, 1000, 13: 9.5 (18.7);
-// 16384, 1024, 32: 17.5 (32); 32768, 2048, 64: 93 (150).
+// reading x.  Measured against one v_fmac chain per lane or a register block of them (us, alone):
+// T = 4096, d = 768, E = 16: 8.5 (11.6); 256, 4096, 8: 21.1 (34.2); 3001, 1000, 13: 9.4 (18.3);
+// 16384, 1024, 32: 18.8 (31.3); 32768, 2048, 64: 100 (148; 105 - 116 inside a layer, where GEMMs of
+// milliseconds have set the clock).
 template <typename XT, int TB, int EG>
 struct RouteTile {
     static constexpr int TG = TB / 16;                       // token groups

@@ -403,11 +403,10 @@ def test_everything_to_one_expert_and_empty_experts():
         assert not y[300:].any()
 
 
-# Shapes that select each register block of the gate kernel (tokens x experts per lane,
-# chosen from T x E), few experts (lanes that only stage tiles), E not a power of two,
-# a model dimension that is no multiple of the 64-column stage, both dtypes and strides of
-# the bias.  The layer call also takes its plan histogram from the gate kernel, in
-# segments of the gate block's tokens.
+# Shapes that select each form of the gate kernel (16, 32 or 64 tokens per block by T; one, two or
+# four groups of 16 experts), few experts, E not a power of two, a model dimension that is no multiple
+# of the 64-column stage, both dtypes and strides of the bias.  The layer call also takes its plan
+# histogram from the gate kernel, in segments of the gate block's tokens.
 GATE_SHAPES = [
     # name,            base,        T,     d,   E,  k, cf
     ("block_1x2",      "gpt2s_moe", 8192,  128, 32, 2, 1.0),
@@ -418,8 +417,8 @@ GATE_SHAPES = [
     ("block_1x2_f32",  "tiny_fp32", 8192,  100, 32, 2, 1.0),
     ("e64_few_tokens", "gpt2s_moe", 100,   200, 64, 2, 2.0),
     ("e2",             "gpt2s_moe", 3000,  136, 2,  1, 0.75),
-    # one chain per lane, operands streamed through the LDS ring (d a multiple of 64):
-    # 32 tokens x 8 experts (one padded), 16 x 16 in fp32 (three padded), 16 x 16 ragged
+    ("tokens_64_e20",  "gpt2s_moe", 17000, 72,  20, 2, 1.0),
+    # whole 64-column stages
     ("chain_32x8_e7",  "gpt2s_moe", 9000,  128, 7,  2, 1.0),
     ("chain_16x16_f32", "tiny_fp32", 5000, 320, 13, 2, 1.0),
     ("chain_16x16",    "gpt2s_moe", 4100,  192, 16, 1, 1.25),

@@ -42,22 +42,27 @@ __device__ __forceinline__ int path_of(const int32_t *__restrict__ hist, size_t 
     return j;
 }
 
+// Work-items of a launch are counted in 32 bits, and the runtime drops what is above them without an
+// error: kernels whose work may be more walk it with at most so many blocks of 256.
+constexpr int64_t kMostBlocks = 1 << 20;
+
 // One thread per (table a, token t): table a predicts layer a + l from layers a .. a+l-1.
 __global__ __launch_bounds__(256) void path_profile_kernel(
     const int32_t *__restrict__ sel, uint32_t *__restrict__ counts, int T, int tables, int E,
     int k, int l, int paths)
 {
-    const long idx = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= static_cast<long>(tables) * T) return;
-    const int a = static_cast<int>(idx / T), t = static_cast<int>(idx % T);
-    const size_t layer_stride = static_cast<size_t>(T) * k;
-    const int j = path_of(sel + a * layer_stride, layer_stride, t, k, l, E);
-    if (j < 0) return;
-    const int32_t *next = sel + (a + l) * layer_stride + static_cast<size_t>(t) * k;
-    for (int c = 0; c < k; ++c)
-        if (static_cast<unsigned>(next[c]) >= static_cast<unsigned>(E)) return;
-    uint32_t *row = counts + (static_cast<size_t>(a) * paths + j) * E;
-    for (int c = 0; c < k; ++c) atomicAdd(&row[next[c]], 1u);
+    const long n = static_cast<long>(tables) * T, step = static_cast<long>(gridDim.x) * blockDim.x;
+    for (long idx = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x; idx < n; idx += step) {
+        const int a = static_cast<int>(idx / T), t = static_cast<int>(idx % T);
+        const size_t layer_stride = static_cast<size_t>(T) * k;
+        const int j = path_of(sel + a * layer_stride, layer_stride, t, k, l, E);
+        bool valid = j >= 0;
+        const int32_t *next = sel + (a + l) * layer_stride + static_cast<size_t>(t) * k;
+        for (int c = 0; c < k; ++c) valid = valid && static_cast<unsigned>(next[c]) < static_cast<unsigned>(E);
+        if (!valid) continue;
+        uint32_t *row = counts + (static_cast<size_t>(a) * paths + j) * E;
+        for (int c = 0; c < k; ++c) atomicAdd(&row[next[c]], 1u);
+    }
 }
 
 // The same counts for batches of many tokens.  Popular experts put a large share of the tokens
@@ -155,11 +160,7 @@ __global__ __launch_bounds__(kProfThreads) void path_profile_lds_kernel(
 
 // Sixteen lanes per (table, path) row, up to four counters each: row total, then k rounds of
 // "largest remaining count, lowest index first" as a maximum over the lanes.  (36864
-// rows of 16: 5.2 us; 6.0 with one thread per row reading it k + 1 times.)  The blocks walk the
-// rows: sixteen lanes for each of 2^28 rows are more work-items than the 32 bits of a launch hold,
-// and the runtime drops what is above them without an error.
-constexpr int64_t kFinalizeBlocks = 1 << 20;
-
+// rows of 16: 5.2 us; 6.0 with one thread per row reading it k + 1 times.)
 __global__ __launch_bounds__(256) void path_finalize_kernel(
     const uint32_t *__restrict__ counts, int32_t *__restrict__ top_expert,
     unsigned long long *__restrict__ top_prob, long rows, int E, int k)
@@ -371,8 +372,8 @@ moe_status moe_path_profile(const moe_path_shape *s, const int32_t *sel, int32_t
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t counters = paths * s->E;
     if (T < kProfMinTokens) {
-        hipLaunchKernelGGL(path_profile_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256),
-                           0, st, sel, counts, T, tables, s->E, s->k,
+        const int64_t blocks = std::min<int64_t>((n + 255) / 256, kMostBlocks);
+        hipLaunchKernelGGL(path_profile_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, sel, counts, T, tables, s->E, s->k,
                            s->l, static_cast<int>(paths));
     } else {
         const bool direct = counters <= kProfLdsCounters;
@@ -385,6 +386,10 @@ moe_status moe_path_profile(const moe_path_shape *s, const int32_t *sel, int32_t
         splits *= (least + splits - 1) / splits;
         splits = std::min<int64_t>(splits, (T + kProfThreads - 1) / kProfThreads);
         const int64_t share = (T + splits - 1) / splits;
+        if (tables * splits >= (1ll << 32) / kProfThreads) {
+            set_error("moe_path_profile: %d tables of %d tokens in one call", tables, T);
+            return MOE_EUNSUPPORTED;
+        }
         auto kern = direct ? path_profile_lds_kernel<true> : path_profile_lds_kernel<false>;
         static PerDeviceOnce once[2];
         once[direct].raise_lds(reinterpret_cast<const void *>(kern), direct ? kProfLdsCounters * 2 : kSlots * 8);
@@ -411,7 +416,7 @@ moe_status moe_path_finalize(const moe_path_shape *s, const uint32_t *counts,
         return MOE_EINVAL;
     }
     const long rows = static_cast<long>(s->L - s->l) * paths;
-    const int64_t blocks = std::min<int64_t>((rows + 15) / 16, kFinalizeBlocks);
+    const int64_t blocks = std::min<int64_t>((rows + 15) / 16, kMostBlocks);
     hipLaunchKernelGGL(path_finalize_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
                        static_cast<hipStream_t>(stream), counts, top_expert,
                        reinterpret_cast<unsigned long long *>(top_prob), rows, s->E, s->k);

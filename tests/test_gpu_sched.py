@@ -149,3 +149,26 @@ def test_finalize_of_more_rows_than_one_launch_has_lanes_for():
         assert torch.equal(top_e[a], torch.where(listed, 63 - key % 64, -1).int()), a
         total = c.sum(dim=1, keepdim=True).clamp_min(1)
         assert torch.equal(top_q[a], torch.where(listed, (key // 64 << 32) // total, 0)), a
+
+
+def test_profile_of_more_tokens_than_one_launch_has_lanes_for():
+    """2^20 + 300 tables of 4095 tokens (batches below the LDS kernel's): over 2^32 work-items at one
+    for each."""
+    L, T = (1 << 20) + 301, 4095
+    s = moe.PathShape(L, 2, 1, 1)
+    assert (L - 1) * T >= 1 << 32
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    sel = torch.empty((L, T), dtype=torch.int32, device=DEV)
+    for lo in range(0, L, 1 << 18):
+        part = sel[lo:lo + (1 << 18)]
+        part.copy_(torch.randint(0, 2, part.shape, dtype=torch.uint8, device=DEV, generator=g))
+    counts = torch.zeros((L - 1, 2, 2), dtype=torch.int32, device=DEV)
+    moe.moe_path_profile(s, sel, T, counts)
+    for lo in range(0, L - 1, 1 << 16):
+        hi = min(L - 1, lo + (1 << 16))
+        a, b = sel[lo:hi].bool(), sel[lo + 1:hi + 1].bool()
+        for i in (0, 1):
+            for j in (0, 1):
+                want = ((a == bool(i)) & (b == bool(j))).sum(dim=1)
+                assert torch.equal(counts[lo:hi, i, j].long(), want), (lo, i, j)

@@ -1121,14 +1121,10 @@ void launch_wgrad(const uint16_t *A, const uint16_t *B, float *C, const int32_t 
                   int N, int64_t max_rows, int stage, hipStream_t st)
 {
     hipEvent_t t0, t1;
-    // 256 x 256 tiles on four wavefronts where they fit the matrix, there are 150 of them, and the
-    // buffer offsets (an expert's rows times the row length, in bytes) stay below 2^31.  Times the time
-    // of 128 x 128 tiles, dW2 / dW1, over 2100 layers of 1024 .. 32768 tokens: 100 .. 149 tiles 1.07 / 0.93,
-    // 150 .. 199 0.84 / 0.74, 200 .. 256 0.74 / 0.65, 257 .. 299 (a second round all but empty) 1.01 / 0.88,
-    // 300 .. 399 0.92 / 0.82, 400 .. 512 0.78 / 0.70, more 0.83 / 0.76; with under 100 rows per expert
-    // 0.93 all told.  (16 experts, 768 x 3072, 8192 rows, 576 tiles: dW2 92 -> 83 us, dW1 90 -> 72.)
+    // 256 x 256 tiles on four wavefronts when they fit the matrix, fill the chip (16 experts, 768 x
+    // 3072, 8192 rows, 576 tiles: dW2 92 -> 83 us, dW1 90 -> 72), and the buffer offsets (an expert's rows times the row length, in bytes) stay below 2^31
     const uint64_t span = static_cast<uint64_t>(max_rows + 192) * static_cast<uint64_t>(std::max(M, N)) * 2;
-    if (M % 256 == 0 && N % 256 == 0 && static_cast<int64_t>(E) * (M / 256) * (N / 256) >= 150 &&
+    if (M % 256 == 0 && N % 256 == 0 && static_cast<int64_t>(E) * (M / 256) * (N / 256) >= 512 &&
         span < (1ull << 31)) {
         constexpr size_t kLds4 = kW4Lds;
         auto kern = wgrad_w4_kernel<AF16>;

@@ -69,13 +69,9 @@ struct GemmPlan {
     int32_t concurrent;      // work items in flight per XCD (sets the panel width)
 };
 // Tile of a row-grouped GEMM on the four-wavefront kernels (gemm_w4.h): `rows` rows in all over E
-// experts.  Where there are many 256 x 256 tiles, those, unless the contraction is one of a few stages
-// that 128 x 128 tiles hide their prologue and epilogue behind better: over 4800 such GEMMs of 8000 ..
-// 130000 rows the larger tile took, times the smaller one's time, 1.05 at K = 512, 1.03 at 640, 1.04 at
-// 704, 0.99 at 768, 0.97 at 896, 0.96 at 1024, 0.88 at 1600 .. 2047.  (Below 256 the larger tile stays although
-// it takes 1.34 / 1.29 / 1.23 times as long at K = 64 / 128 / 192: widths nobody trains, and what runs
-// the loop's first and last stages without any between.)
-// Where tiles are few, by the number of rounds they take on the chip -- 256 of 256 x 256 at a
+// experts.  256 x 256 where there are many such tiles, unless the contraction is one of a few
+// stages that 128 x 128 tiles hide their prologue and epilogue behind better (K = 512 and 704 measured;
+// below four stages the larger tile stays, unmeasured against the smaller); where tiles are few, by the number of rounds the tiles take on the chip -- 256 of 256 x 256 at a
 // time, 512 of 128 x 128 (two per compute unit), and a tile's time in 64-deep stages -- with the
 // times measured over layers of 256 .. 20000 tokens (us: a 256 x 256 stage 1.25, or 1.5 once the
 // chip is full and lowers its clock, prologue and epilogue 10; a round of 128 x 128 0.85, or 0.55
@@ -83,26 +79,22 @@ struct GemmPlan {
 // tile 1.7 times as much).  E.g. rows, E, N, K -> us of the layer with 256 x 256 / 128 x 128:
 // 24249, 8, 1152, 2560 344 / 384; 12092, 8, 1024, 2624 182 / 189; 6002, 13, 1000, 2600 176 / 195;
 // 23127, 64, 1600, 512 202 / 173; 8192, 16, 768, 3072 150 / 130; 39780, 16, 7048, 2032 2674 / 3003.
-// 128 x 256 instead of 128 x 128 for long contractions whose tiles fill three quarters of the chip, one
-// per compute unit, and whose last column tile is more than half full.  Over 1150 GEMMs beyond
-// these lines it took, times 128 x 128's time, 0.97 at K = 2048 .. 2559, 0.93 at 2560 .. 3071, 0.95 at 3072
-// .. 4095, 0.93 above; on the other side 1.01 at 1536 .. 2047 and 1.05 at 1024 .. 1535; 1.18 with up to 128
-// tiles, 0.99 with up to 192; 1.06 where the last column tile is at most half full.
+// 128 x 256 instead of 128 x 128 for long contractions with more tiles than the chip takes one per
+// unit of (8192, 16, 768, 3072: 128 / 130; a skewed layer of K = 4096: 390 / 403; with few tiles it
+// loses: 839 tokens, K = 6920: 190 / 166).
 inline void choose_w4_tile(int64_t rows, int E, int N, int K, GemmPlan *gp)
 {
     const int64_t tiles256 = (rows / 256 + E / 2) * ((N + 255) / 256);
     const int64_t tiles128 = (rows / 128 + E / 2) * ((N + 127) / 128);
-    const int64_t tiles128x256 = (rows / 128 + E / 2) * ((N + 255) / 256);
     const double stages = (K + 63) / 64;
     const double t256 = static_cast<double>((tiles256 + 255) / 256) * (stages * (tiles256 > 256 ? 1.5 : 1.25) + 10.0);
     const double t128 = static_cast<double>((tiles128 + 511) / 512) *
                         (stages * (tiles128 > 256 ? 0.85 : 0.55) * (K % 64 != 0 ? 1.7 : 1.0) + 3.0);
     const bool many = tiles256 >= 768;
-    const bool half_empty = N % 256 != 0 && N % 256 <= 128;
-    if (many ? K >= 768 || K < 256 : t256 < t128) {
+    if (many ? K >= 1024 || K < 256 : t256 < t128) {
         gp->bm = gp->bn = 256;
         gp->concurrent = 32;
-    } else if (K >= 2048 && tiles128x256 > 192 && !half_empty) {
+    } else if (K >= 3072 && tiles128 > 400) {
         gp->bm = 128;
         gp->bn = 256;
         gp->concurrent = 32;

@@ -147,16 +147,3 @@ def test_expert_gemm_kernel_tells_every_kernel_apart():
     assert names(256, 4096, 8, 14336, 2, 256)[1] == "grouped_gemm_staged_kernel 64x256"      # few rows, long weights
     assert names(300, 32776, 2, 32840, 1, 300) == ["grouped_gemm_staged_kernel 128x256"] * 2  # past 32-bit offsets
     assert all(n.startswith("grouped_gemm_mfma_kernel 128x") for n in names(4096, 768, 16, 3072, 2, 640))
-
-
-def test_expert_gemm_tile_rule_at_its_lines():
-    """128 x 256 tiles from K = 2048 and more than 192 of them on, where the last column tile is more
-    than half full; 256 x 256 tiles of many rows from K = 768 on."""
-    def tile(rows, E, N, K):
-        s = moe.Shape.make(rows, N, E, K, 1, rows, dtype="bf16", act="gelu")
-        return moe.moe_expert_gemm_kernel(s, 1).split()[1]
-
-    assert tile(8192, 16, 768, 2048) == "128x256" and tile(8192, 16, 768, 1984) == "128x128"
-    assert tile(8192, 16, 648, 3072) == "128x256" and tile(8192, 16, 640, 3072) == "128x128"
-    assert tile(7296, 16, 768, 3072) == "128x256" and tile(7168, 16, 768, 3072) == "128x128"    # 195, 192 tiles
-    assert tile(32768, 16, 2048, 768) == "256x256" and tile(32768, 16, 2048, 704) == "128x128"

@@ -1121,8 +1121,13 @@ void launch_wgrad(const uint16_t *A, const uint16_t *B, float *C, const int32_t 
                   int N, int64_t max_rows, int stage, hipStream_t st)
 {
     hipEvent_t t0, t1;
-    // 256 x 256 tiles on four wavefronts when they fit the matrix, fill the chip (16 experts, 768 x
-    // 3072, 8192 rows, 576 tiles: dW2 92 -> 83 us, dW1 90 -> 72), and the buffer offsets (an expert's rows times the row length, in bytes) stay below 2^31
+    // 256 x 256 tiles on four wavefronts when they fit the matrix, fill the chip twice over, and the
+    // buffer offsets (an expert's rows times the row length, in bytes) stay below 2^31.  Time of both
+    // gradients over that with 128 x 128 tiles, layers of 128 .. 16384 tokens, rows spread evenly / by
+    // Zipf(1.2): 512 .. 599 tiles 0.92 / 0.87, 600 .. 767 0.80 / 0.80, more 0.79 / -; 320 .. 511 0.83 / 0.83,
+    // 256 .. 319 (a second round all but empty) 0.97 / 0.96, 150 .. 255 0.78 / 0.79 (but up to 1.6 where one
+    // expert has most of the rows), 100 .. 149 1.00 / -.  (16 experts, 768 x 3072, 8192 rows, 576 tiles:
+    // dW2 92 -> 83 us, dW1 90 -> 73.)
     const uint64_t span = static_cast<uint64_t>(max_rows + 192) * static_cast<uint64_t>(std::max(M, N)) * 2;
     if (M % 256 == 0 && N % 256 == 0 && static_cast<int64_t>(E) * (M / 256) * (N / 256) >= 512 &&
         span < (1ull << 31)) {

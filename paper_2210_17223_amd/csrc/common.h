@@ -70,8 +70,12 @@ struct GemmPlan {
 };
 // Tile of a row-grouped GEMM on the four-wavefront kernels (gemm_w4.h): `rows` rows in all over E
 // experts.  256 x 256 where there are many such tiles, unless the contraction is one of a few
-// stages that 128 x 128 tiles hide their prologue and epilogue behind better (K = 512 and 704 measured;
-// below four stages the larger tile stays, unmeasured against the smaller); where tiles are few, by the number of rounds the tiles take on the chip -- 256 of 256 x 256 at a
+// stages that 128 x 128 tiles hide their prologue and epilogue behind better.  The larger tile's time over
+// the smaller's, 4800 forward GEMMs of 8000 .. 130000 rows: 1.05 at K = 512, 1.03 at 640, 0.99 at 768, 0.97 at 896,
+// 0.96 at 1024, 0.88 at 1600 .. 2047; but the product that dP is made of, over 130 layers, 1.26 at 704 .. 895 and 1.17
+// at 896 .. 1023, hence 1024 for both.  Below four stages the larger tile takes 1.34 / 1.29 / 1.23 times as long at
+// K = 64 / 128 / 192 and stays for what runs through it alone: a loop that ends before it is under way.
+// Where tiles are few, by the number of rounds the tiles take on the chip -- 256 of 256 x 256 at a
 // time, 512 of 128 x 128 (two per compute unit), and a tile's time in 64-deep stages -- with the
 // times measured over layers of 256 .. 20000 tokens (us: a 256 x 256 stage 1.25, or 1.5 once the
 // chip is full and lowers its clock, prologue and epilogue 10; a round of 128 x 128 0.85, or 0.55
@@ -80,8 +84,11 @@ struct GemmPlan {
 // 24249, 8, 1152, 2560 344 / 384; 12092, 8, 1024, 2624 182 / 189; 6002, 13, 1000, 2600 176 / 195;
 // 23127, 64, 1600, 512 202 / 173; 8192, 16, 768, 3072 150 / 130; 39780, 16, 7048, 2032 2674 / 3003.
 // 128 x 256 instead of 128 x 128 for long contractions with more tiles than the chip takes one per
-// unit of (8192, 16, 768, 3072: 128 / 130; a skewed layer of K = 4096: 390 / 403; with few tiles it
-// loses: 839 tokens, K = 6920: 190 / 166).
+// unit of.  Its time over the smaller tile's on that side of the line: 0.93 over 760 GEMMs whose last column
+// tile is more than half full, 1.04 over 680 others when rows spread evenly; over 470 layers of uneven and even rows
+// of the latter kind the smaller tile would cost 1.01 (second GEMM), 1.02 (dxe) and 1.04 (first GEMM of a stack).  On the other
+// side: K = 1024 .. 1535 1.05, 1536 .. 2047 1.00, 2048 .. 3071 0.96 with full and 1.07 with half-full last tiles; up to 200
+// tiles 1.16 .. 1.20, 200 .. 300 1.09 .. 1.13, 300 .. 400 0.98.
 inline void choose_w4_tile(int64_t rows, int E, int N, int K, GemmPlan *gp)
 {
     const int64_t tiles256 = (rows / 256 + E / 2) * ((N + 255) / 256);

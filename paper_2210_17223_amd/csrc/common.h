@@ -74,7 +74,7 @@ struct GemmPlan {
 // the smaller's, 4800 forward GEMMs of 8000 .. 130000 rows: 1.05 at K = 512, 1.03 at 640, 0.99 at 768, 0.97 at 896,
 // 0.96 at 1024, 0.88 at 1600 .. 2047; but the product that dP is made of, over 130 layers, 1.26 at 704 .. 895 and 1.17
 // at 896 .. 1023, hence 1024 for both.  Below four stages the larger tile takes 1.34 / 1.29 / 1.23 times as long at
-// K = 64 / 128 / 192 and stays for what runs through it alone: a loop that ends before it is under way.
+// K = 64 / 128 / 192 and stays: the tests of a loop that ends before it is under way run there.
 // Where tiles are few, by the number of rounds the tiles take on the chip -- 256 of 256 x 256 at a
 // time, 512 of 128 x 128 (two per compute unit), and a tile's time in 64-deep stages -- with the
 // times measured over layers of 256 .. 20000 tokens (us: a 256 x 256 stage 1.25, or 1.5 once the

@@ -4,6 +4,8 @@
 // while earlier experts are computed; the two GEMMs of expert e then run on the caller's
 // stream from a work list that holds expert e's tiles only.  Bound by the host link:
 // 2 d h element bytes per expert against a few microseconds of matrix-core work per row.
+// Page-locked weights are read over the link by a kernel, both matrices of an expert in one
+// launch; others go through the runtime's copy.
 #include "common.h"
 #include "moe_offload.h"
 
@@ -51,6 +53,57 @@ bool supported(const moe_shape *s)
     return s != nullptr && s->dtype == MOE_BF16 && s->T >= 1 && s->E >= 1 && s->E <= kMaxExperts &&
            s->k >= 1 && s->k <= kMaxTopK && s->k <= s->E && s->capacity >= 1 && s->d_model >= 8 &&
            s->d_ff >= 8 && s->d_model % 8 == 0 && s->d_ff % 8 == 0;
+}
+
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+
+// One expert's two weight matrices, n 16-byte vectors each, from page-locked host memory to its
+// slot; an expert without rows (offsets) is not read.  The link is full with some 64 KiB of reads in
+// flight, so few blocks do: GB/s of back-to-back launches of 16 MiB with 8 / 16 / 64 / 256 blocks 56.1 /
+// 56.6 / 56.2 / 52.0, the runtime's copy 55.4; behind an event that another stream records after
+// every copy, as here, the runtime's copies of 8 MiB reach 37 to 41: what a copy engine's start and
+// end signals cost beside 0.15 ms of transfer, a kernel's launch does not.  256 tokens, 16 experts
+// of 1024 x 4096, two slots: 6120 -> 5040 us.
+constexpr int kPullBlocks = 16;
+__global__ __launch_bounds__(256) void pull_weights_kernel(
+    const u32x4 *__restrict__ h1, const u32x4 *__restrict__ h2, u32x4 *__restrict__ d1,
+    u32x4 *__restrict__ d2, size_t n, const int32_t *__restrict__ offsets, int expert)
+{
+    if (offsets[expert] == offsets[expert + 1]) return;
+    constexpr int U = 4;                         // loads in flight per lane
+    const size_t step = static_cast<size_t>(gridDim.x) * (256 * U);
+    for (int m = 0; m < 2; ++m) {
+        const u32x4 *src = m == 0 ? h1 : h2;
+        u32x4 *dst = m == 0 ? d1 : d2;
+        for (size_t i = static_cast<size_t>(blockIdx.x) * (256 * U) + threadIdx.x; i < n; i += step) {
+            u32x4 v[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q)          // (past the end: the last vector again, not stored)
+                v[q] = src[i + q * 256 < n ? i + q * 256 : n - 1];
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (i + q * 256 < n) dst[i + q * 256] = v[q];
+        }
+    }
+}
+
+// The device's address of `bytes` of page-locked host memory at p, or NULL if the device cannot read
+// all of them in place (pageable memory, or not one allocation).
+const char *device_view(const void *p, size_t bytes)
+{
+    const char *ends[2] = {static_cast<const char *>(p), static_cast<const char *>(p) + bytes - 1};
+    const char *view[2];
+    for (int i = 0; i < 2; ++i) {
+        hipPointerAttribute_t a{};
+        if (hipPointerGetAttributes(&a, ends[i]) != hipSuccess) {
+            (void)hipGetLastError();             // an unknown address is no error here
+            return nullptr;
+        }
+        if (a.type != hipMemoryTypeHost || a.devicePointer == nullptr) return nullptr;
+        view[i] = static_cast<const char *>(a.devicePointer);
+    }
+    return view[1] - view[0] == ends[1] - ends[0] && (reinterpret_cast<uintptr_t>(view[0]) & 15u) == 0
+               ? view[0] : nullptr;
 }
 
 size_t expert_bytes(const moe_shape &s) { return static_cast<size_t>(s.d_model) * s.d_ff * 2; }
@@ -126,6 +179,7 @@ moe_status moe_expert_ffn_offloaded(const moe_shape *s, const void *xe, const in
     const size_t eb = expert_bytes(*s), slot_bytes = align_up(eb, 256);
     char *stage = static_cast<char *>(staging);
     const char *h1 = static_cast<const char *>(W1p_host), *h2 = static_cast<const char *>(W2p_host);
+    const char *v1 = device_view(h1, eb * s->E), *v2 = device_view(h2, eb * s->E);
 
     moe_status rc = launch_items_per_expert(*s, offsets, w, st);
     if (rc != MOE_OK) return rc;
@@ -137,8 +191,16 @@ moe_status moe_expert_ffn_offloaded(const moe_shape *s, const void *xe, const in
         const int slot = e % resident;
         char *d1 = stage + static_cast<size_t>(slot) * 2 * slot_bytes, *d2 = d1 + slot_bytes;
         if (e >= resident) MOE_TRY_HIP(hipStreamWaitEvent(r->copy, r->freed[slot], 0));
-        MOE_TRY_HIP(hipMemcpyAsync(d1, h1 + static_cast<size_t>(e) * eb, eb, hipMemcpyHostToDevice, r->copy));
-        MOE_TRY_HIP(hipMemcpyAsync(d2, h2 + static_cast<size_t>(e) * eb, eb, hipMemcpyHostToDevice, r->copy));
+        const size_t at = static_cast<size_t>(e) * eb;
+        if (v1 != nullptr && v2 != nullptr) {
+            hipLaunchKernelGGL(pull_weights_kernel, dim3(kPullBlocks), dim3(256), 0, r->copy,
+                               reinterpret_cast<const u32x4 *>(v1 + at), reinterpret_cast<const u32x4 *>(v2 + at),
+                               reinterpret_cast<u32x4 *>(d1), reinterpret_cast<u32x4 *>(d2), eb / 16, offsets, e);
+            MOE_TRY_HIP(hipGetLastError());
+        } else {
+            MOE_TRY_HIP(hipMemcpyAsync(d1, h1 + at, eb, hipMemcpyHostToDevice, r->copy));
+            MOE_TRY_HIP(hipMemcpyAsync(d2, h2 + at, eb, hipMemcpyHostToDevice, r->copy));
+        }
         MOE_TRY_HIP(hipEventRecord(r->ready[slot], r->copy));
         MOE_TRY_HIP(hipStreamWaitEvent(st, r->ready[slot], 0));
         // The GEMM kernel addresses expert e's weights as base + e * d * h elements: hand it

@@ -47,6 +47,30 @@ def test_offloaded_ffn_equals_resident_ffn(name):
     assert rel_rms_err(got, ref) <= 2e-2
 
 
+@pytest.mark.parametrize("T,d,h", [(3, 8, 8), (3, 72, 200), (5, 256, 512), (40, 264, 1032)])
+def test_weights_in_page_locked_and_in_pageable_memory_give_the_same(T, d, h):
+    """The kernel that reads page-locked weights against the runtime's copies: matrices smaller than
+    one pass of its blocks, and with remainders; experts without rows among them."""
+    li = wl.make_layer(wl.scaled("gpt2s_moe", T=T, d=d, h=h, E=13), seed=1)
+    s = shape_of(li)
+    L = DeviceLayer(li, s)
+    L.layer(1)
+    b = L.b
+    A = int(b["offsets"].cpu().numpy()[-1])
+    want = b["ye"].clone()[:A * d].view(torch.int16)
+    counts = np.diff(b["offsets"].cpu().numpy())
+    assert T > 5 or (counts == 0).any()
+    W1, W2 = b["W1p"].cpu(), b["W2p"].cpu()
+    ws = torch.empty(moe.moe_offload_workspace_bytes(s), dtype=torch.uint8, device=DEV)
+    staging = torch.empty(moe.moe_offload_staging_bytes(s, 2), dtype=torch.uint8, device=DEV)
+    for W1h, W2h in ((W1.pin_memory(), W2.pin_memory()), (W1, W2), (W1.pin_memory(), W2)):
+        staging.fill_(0xFF)
+        ye = torch.full_like(b["ye"], 5.0)
+        moe.moe_expert_ffn_offloaded(s, b["xe"], b["offsets"], W1h, W2h, None, None, ye, staging, 2, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(ye[:A * d].view(torch.int16), want)
+
+
 def test_sizes_and_refusals():
     li = wl.make_layer(wl.scaled("gpt2s_moe", T=64, d=64, h=128, E=4), seed=0)
     s = shape_of(li)

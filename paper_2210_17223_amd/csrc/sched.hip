@@ -72,14 +72,19 @@ __global__ __launch_bounds__(256) void path_profile_kernel(
 //   else:   LDS is a hash table of kSlots (counter, count) pairs, first come first served: the
 //           popular counters are there early, a counter that finds its two places taken goes to
 //           global memory.
-// Bound by reading the l + 1 choices of every token and by the flush.  2^20 tokens, 12 layers, 16
-// experts, paths of length 3: 68 us (5050 with a global atomic per token and table).
+// LL: l where it is 2 or 3, else 0: with l known all l + 1 choices of four tokens are on their way at
+// once, and a block waits once a round for them instead of l + 4 times.
+// Bound by reading the choices (9 of 45 us below) and by the flush (18: its atomics; two neighbouring
+// counters go in one 64-bit add, whose low half does not overflow because row totals stay below
+// 2^32).  2^20 tokens, 12 layers, 16 experts, paths of length 3: 45 us (75 with one wait per choice and
+// 32-bit adds, 5050 with a global atomic per token and table); k = 2 70 (121).  Tables past LDS: bound
+// by their scattered atomics, 2^19 tokens of 32 experts 111 us (115).
 constexpr int kProfThreads = 1024;
 constexpr int kSlots = 1 << 13;
 constexpr int kProfMinTokens = 4096;                       // fewer: not worth clearing and flushing LDS
 constexpr int kProfLdsCounters = 73728;                    // 144 KiB of 16-bit counters
 
-template <bool DIRECT>
+template <bool DIRECT, int LL>
 __global__ __launch_bounds__(kProfThreads) void path_profile_lds_kernel(
     const int32_t *__restrict__ sel, uint32_t *__restrict__ counts, int T, int share, int splits,
     int E, int k, int l, int paths)
@@ -116,37 +121,66 @@ __global__ __launch_bounds__(kProfThreads) void path_profile_lds_kernel(
     };
     // four tokens per thread at a time: their loads are in flight together
     constexpr int U = 4;
+    const int second = min(1, k - 1);
     for (long tb = t0 + tid; tb < t1; tb += U * kProfThreads) {
-        int j[U];
+        int j[U], first_next[U], second_next[U];
+        size_t at[U];
         bool ok[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             j[u] = 0;
             ok[u] = tb + u * kProfThreads < t1;
+            at[u] = static_cast<size_t>(min(tb + u * kProfThreads, static_cast<long>(t1) - 1)) * k;
+            first_next[u] = next[at[u]];
+            second_next[u] = next[at[u] + second];
         }
-        for (int m = 0; m < l; ++m) {
-            int e[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                e[u] = hist[m * layer_stride + static_cast<size_t>(min(tb + u * kProfThreads, static_cast<long>(t1) - 1)) * k];
+        auto extend = [&](const int (&e)[U]) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 ok[u] = ok[u] && static_cast<unsigned>(e[u]) < static_cast<unsigned>(E);
                 j[u] = ok[u] ? j[u] * E + e[u] : 0;
             }
+        };
+        if constexpr (LL != 0) {
+            int e[LL][U];
+#pragma unroll
+            for (int m = 0; m < LL; ++m)
+#pragma unroll
+                for (int u = 0; u < U; ++u) e[m][u] = hist[m * layer_stride + at[u]];
+#pragma unroll
+            for (int m = 0; m < LL; ++m) extend(e[m]);
+        } else {
+            for (int m = 0; m < l; ++m) {
+                int e[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) e[u] = hist[m * layer_stride + at[u]];
+                extend(e);
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (!ok[u]) continue;
-            const int32_t *choice = next + static_cast<size_t>(tb + u * kProfThreads) * k;
-            bool valid = true;
-            for (int c = 0; c < k; ++c) valid = valid && static_cast<unsigned>(choice[c]) < static_cast<unsigned>(E);
+            bool valid = ok[u] && static_cast<unsigned>(first_next[u]) < static_cast<unsigned>(E) &&
+                         static_cast<unsigned>(second_next[u]) < static_cast<unsigned>(E);
             if (!valid) continue;
-            for (int c = 0; c < k; ++c) count(static_cast<uint32_t>(j[u]) * E + choice[c]);
+            const int32_t *choice = next + at[u];
+            for (int c = 2; c < k; ++c) valid = valid && static_cast<unsigned>(choice[c]) < static_cast<unsigned>(E);
+            if (!valid) continue;
+            const uint32_t row = static_cast<uint32_t>(j[u]) * E;
+            count(row + first_next[u]);
+            if (k > 1) count(row + second_next[u]);
+            for (int c = 2; c < k; ++c) count(row + choice[c]);
         }
     }
     __syncthreads();
     if constexpr (DIRECT) {
+        if (n % 2 == 0 && reinterpret_cast<uintptr_t>(table) % 8 == 0) {
+            unsigned long long *pairs = reinterpret_cast<unsigned long long *>(table);
+            for (int i = tid; i < words; i += kProfThreads) {
+                const unsigned long long v = lds[i];
+                if (v != 0) atomicAdd(&pairs[i], (v & 0xFFFFu) | (v >> 16 << 32));
+            }
+            return;
+        }
         for (int i = tid; i < words; i += kProfThreads) {
             const uint32_t v = lds[i];
             if (v & 0xFFFFu) atomicAdd(&table[2 * i], v & 0xFFFFu);
@@ -390,9 +424,11 @@ moe_status moe_path_profile(const moe_path_shape *s, const int32_t *sel, int32_t
             set_error("moe_path_profile: %d tables of %d tokens in one call", tables, T);
             return MOE_EUNSUPPORTED;
         }
-        auto kern = direct ? path_profile_lds_kernel<true> : path_profile_lds_kernel<false>;
-        static PerDeviceOnce once[2];
-        once[direct].raise_lds(reinterpret_cast<const void *>(kern), direct ? kProfLdsCounters * 2 : kSlots * 8);
+        auto kern = s->l == 2   ? direct ? path_profile_lds_kernel<true, 2> : path_profile_lds_kernel<false, 2>
+                    : s->l == 3 ? direct ? path_profile_lds_kernel<true, 3> : path_profile_lds_kernel<false, 3>
+                    : direct    ? path_profile_lds_kernel<true, 0> : path_profile_lds_kernel<false, 0>;
+        static PerDeviceOnce once[3][2];
+        once[s->l == 2 ? 1 : s->l == 3 ? 2 : 0][direct].raise_lds(reinterpret_cast<const void *>(kern), direct ? kProfLdsCounters * 2 : kSlots * 8);
         hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(tables * splits)), dim3(kProfThreads), lds, st,
                            sel, counts, T, static_cast<int>(share), static_cast<int>(splits), s->E,
                            s->k, s->l, static_cast<int>(paths));

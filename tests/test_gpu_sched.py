@@ -128,6 +128,32 @@ def test_tables_of_many_tokens(L, T0, reps, E, k, l):
         assert np.array_equal(got[a], want * reps), a
 
 
+@pytest.mark.parametrize("L,T,E,k,l,shift", [
+    (6, 4099, 3, 2, 2, 0),           # an odd number of counters: pairs of the second table would straddle
+    (5, 4097, 16, 1, 3, 1),          # tables that start on an odd word
+    (5, 4097, 16, 1, 3, 2),
+    (7, 5000, 8, 3, 4, 0),           # paths of four layers
+    (4, 9000, 32, 2, 2, 0),
+], ids=["odd_tables", "odd_start", "even_start", "four_layers", "two_layers"])
+def test_tables_counted_in_lds(L, T, E, k, l, shift):
+    """Widths and starts of a table on both sides of the 64-bit flush, and every form of the loop over
+    a path's layers, against the oracle; counts add up over calls."""
+    rng = np.random.default_rng(12)
+    sel = np.argsort(rng.random((L, T, E)), axis=2)[:, :, :k].astype(np.int32)
+    sel[0, 3, 0], sel[L - 1, 17, k - 1] = -1, E
+    s = moe.PathShape(L, E, k, l)
+    P, tables = moe.moe_path_count(s), L - l
+    buf = torch.zeros(shift + tables * P * E + 1, dtype=torch.int32, device=DEV)
+    counts = buf[shift:shift + tables * P * E]
+    dev_sel = torch.from_numpy(sel).to(DEV)
+    for _ in range(2):
+        moe.moe_path_profile(s, dev_sel, T, counts)
+    got = counts.cpu().numpy().view(np.uint32).reshape(tables, P, E).astype(np.int64)
+    for a, want in enumerate(so.profile_counts(sel, l, E)):
+        assert np.array_equal(got[a], 2 * want), a
+    assert not buf[:shift].any() and not buf[-1].any()
+
+
 def test_finalize_of_more_rows_than_one_launch_has_lanes_for():
     """19 tables of 3^15 paths: over 2^28 rows, sixteen lanes for each of which would be more
     work-items than a launch can have; the rows are no multiple of what the grid walks at a time."""

@@ -14,6 +14,7 @@
 //
 // The row-grouped GEMMs run on the forward's four-wavefront kernels (gemm_w4.h) and its kind of
 // work list; a weight-gradient GEMM contracts over one expert's rows.
+#include "activation.h"
 #include "common.h"
 #include "moe_train.h"
 
@@ -36,29 +37,11 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 constexpr int kBM = 128, kBN = 256, kBK = 64, kLD = kBK + 8;
 constexpr size_t kGemmLds = 2 * (kBM + kBN) * kLD * sizeof(uint16_t);
 
-// Phi(v), the normal CDF, as 1 / (1 + 2^(v Q(min(v^2, 49)))) with the cubic Q of the forward's
-// GeLU (absolute error of v Phi(v) below 1.5e-5).
-__device__ __forceinline__ float normal_cdf_fast(float v)
-{
-    const float s = fminf(v * v, 49.0f);
-    float q = 2.1637799e-05f;
-    q = __builtin_fmaf(q, s, 7.7587553e-04f);
-    q = __builtin_fmaf(q, s, -1.0610976e-01f);
-    q = __builtin_fmaf(q, s, -2.3015507e+00f);
-    return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * q));
-}
-
-// 0.5 (1 + tanh u) with u = sqrt(2 / pi) (v + 0.044715 v^3), as 1 / (1 + e^-2u)
-__device__ __forceinline__ float half_one_plus_tanh(float v)
-{
-    return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * (-2.3022082f - 0.10294324f * v * v)));
-}
-
 template <int ACT>
 __device__ __forceinline__ float act_value(float v)
 {
     if constexpr (ACT == MOE_ACT_GELU_ERF)
-        return v * normal_cdf_fast(v);
+        return gelu_erf_fast(v);
     else if constexpr (ACT == MOE_ACT_GELU_TANH)
         return v * half_one_plus_tanh(v);
     else if constexpr (ACT == MOE_ACT_RELU)
@@ -71,9 +54,7 @@ template <int ACT>
 __device__ __forceinline__ float act_derivative(float v)
 {
     if constexpr (ACT == MOE_ACT_GELU_ERF) {
-        // Phi(v) + v phi(v); phi(v) = exp(-v^2 / 2) / sqrt(2 pi) through exp2
-        const float pdf = 0.3989422804014327f * __builtin_amdgcn_exp2f(-0.72134752044448171f * v * v);
-        return normal_cdf_fast(v) + v * pdf;
+        return gelu_erf_derivative_fast(v);
     } else if constexpr (ACT == MOE_ACT_GELU_TANH) {
         // s = (1 + tanh u) / 2:  s + v s' with s' = 2 s (1 - s) u'
         const float c = 0.7978845608028654f, a = 0.044715f, s = half_one_plus_tanh(v);
@@ -87,9 +68,15 @@ __device__ __forceinline__ float act_derivative(float v)
 
 __device__ __forceinline__ void store_bf16x4(uint16_t *p, const float (&v)[4])
 {
-    u32x2 o;
-    o[0] = static_cast<uint32_t>(f32_to_bf16(v[0])) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
-    o[1] = static_cast<uint32_t>(f32_to_bf16(v[2])) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    u32x2 o;                       // (the packed conversion: the bits of f32_to_bf16)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        bf16x2 b;
+        b[0] = static_cast<__bf16>(v[2 * c]);
+        b[1] = static_cast<__bf16>(v[2 * c + 1]);
+        o[c] = __builtin_bit_cast(uint32_t, b);
+    }
     *reinterpret_cast<u32x2 *>(p) = o;
 }
 

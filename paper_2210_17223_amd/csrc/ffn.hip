@@ -14,6 +14,7 @@
 // operands go through registers, 64 x 256 tiles and operands past 32-bit offsets.  H and ye are
 // kept in fp16.
 // fp32 layers: grouped_gemm_f32_kernel, on the fp32 matrix instruction.
+#include "activation.h"
 #include "common.h"
 #include <cstdio>
 
@@ -31,22 +32,6 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // ---------------------------------------------------------------- activations
-// GeLU(v) = v Phi(v) with Phi(v) ~ 1 / (1 + 2^(v Q(min(v^2, 49)))), Q a cubic fitted (minimax
-// on |v| <= 7, both signs) to the logit of the normal CDF; the coefficients carry the factor
-// -log2(e).  Absolute error of GeLU below 1.5e-5 everywhere, i.e. a few per cent of the fp16
-// rounding of the hidden activation it feeds; two transcendental and eight plain
-// instructions per element.
-__device__ __forceinline__ float gelu_erf_fast(float v)
-{
-    const float s = fminf(v * v, 49.0f);
-    float q = 2.1637799e-05f;
-    q = __builtin_fmaf(q, s, 7.7587553e-04f);
-    q = __builtin_fmaf(q, s, -1.0610976e-01f);
-    q = __builtin_fmaf(q, s, -2.3015507e+00f);
-    const float e = __builtin_amdgcn_exp2f(v * q);
-    return v * __builtin_amdgcn_rcpf(1.0f + e);
-}
-
 template <int ACT, bool FAST>
 __device__ __forceinline__ float activate(float v)
 {
@@ -54,9 +39,7 @@ __device__ __forceinline__ float activate(float v)
         if constexpr (FAST) return gelu_erf_fast(v);
         return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
     } else if constexpr (ACT == MOE_ACT_GELU_TANH) {
-        // 0.5 (1 + tanh u) = 1 / (1 + e^-2u): two transcendental instructions instead of tanhf
-        if constexpr (FAST)
-            return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * (-2.3022082f - 0.10294324f * v * v)));
+        if constexpr (FAST) return v * half_one_plus_tanh(v);
         return 0.5f * v * (1.0f + tanhf(0.7978845608028654f * (v + 0.044715f * v * v * v)));
     } else if constexpr (ACT == MOE_ACT_RELU) {
         return fmaxf(v, 0.0f);

@@ -63,6 +63,7 @@ struct WorkItem {
 struct GemmPlan {
     int32_t bm, bn;          // rows / columns per output tile
     bool w4 = false;         // the four-wavefront kernels (gemm_w4.h)
+    int32_t item_rows = 0;   // most rows of a work item: bm, or a part of it
     int32_t tiles_n;         // column tiles
     int32_t max_row_tiles;   // upper bound of row tiles per chunk
     int32_t max_items;       // upper bound of work items per chunk

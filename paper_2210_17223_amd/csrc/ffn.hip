@@ -413,28 +413,31 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_staged_kernel(
 
 // ---------------------------------------------------------------- few rows per expert
 // The same product for decode steps: a few rows per expert, so the time is that of streaming the
-// weights once.  A wavefront owns 16 columns and the item's rows (up to 64, RT groups of 16) and takes
-// its fragments straight from global memory -- no LDS, no barriers -- with PD 64-deep stages of
-// loads in flight; a block is four of them.  64 columns per block instead of 256: at 768 columns
-// and 16 experts the second GEMM of a layer is 192 blocks, not 48.
+// weights once.  A wavefront owns 16 columns and the rows (RT groups of 16) of a 64-column item and
+// takes its fragments straight from global memory -- no LDS, no barriers -- with PD 64-deep stages of
+// loads in flight.  A block is one wavefront: at 768 columns and 16 experts the second GEMM of a layer is
+// 768 blocks that spread over all compute units (as blocks of four wavefronts it took 192 units, and
+// what an L1 can keep in flight, about 32 KiB, bound those), and twelve blocks fit a unit, so that the
+// first GEMM's 3072 are one round.  Items hold at most 32 rows (a tile of 64 is two): with all 64 a
+// popular expert's wavefronts had three stages in flight instead of five and ended last.
 // The contraction order is that of the other 16-bit kernels (same bits).
-// 16 tokens, 16 experts, k = 2, 768 x 3072, the two GEMMs: 16.0 and 18.0 us (17.2 and 25.7 with 128 x 128
-// and 64 x 256 tiles).
+// 16 tokens, 16 experts, k = 2, 768 x 3072, the two GEMMs: 16.3 and 14.5 us (17.0 and 18.4 with four
+// wavefronts a block; 17.2 and 25.7 with 128 x 128 and 64 x 256 tiles).
 template <bool F16, int ACT, bool KEEP, bool KTAIL>
-__global__ __launch_bounds__(256, 2) void grouped_gemm_stream_kernel(
+__global__ __launch_bounds__(64, 3) void grouped_gemm_stream_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, const float *__restrict__ bias,
     _Float16 *__restrict__ C, _Float16 *__restrict__ Pre, const WorkItem *__restrict__ items,
     const int32_t *__restrict__ nitems, int N, int K, const int32_t *__restrict__ row_src, int row_div)
 {
     const int total = *nitems;
     const int per_xcd = (total + 7) / 8;
-    const int slot = blockIdx.x / 8;
+    const int slot = blockIdx.x / (8 * 4);
     const int item_idx = (blockIdx.x % 8) * per_xcd + slot;
     if (slot >= per_xcd || item_idx >= total) return;
     const WorkItem item = items[item_idx];
     const int rows = item.row1 - item.row0;
-    const int lane = threadIdx.x & 63, fr = lane & 15, oct = lane >> 4;
-    const int nw = item.n0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 16;
+    const int lane = threadIdx.x, fr = lane & 15, oct = lane >> 4;
+    const int nw = item.n0 + static_cast<int>(blockIdx.x / 8 % 4) * 16;
     if (nw >= N) return;
     const int KT = (K + 63) / 64;
     const uint16_t *wp = W + (static_cast<size_t>(item.expert) * N + min(nw + fr, N - 1)) * K + oct * 8;
@@ -521,10 +524,8 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_stream_kernel(
     using std::integral_constant;
     if (rows <= 16)
         body(integral_constant<int, 1>{}, integral_constant<int, 8>{});
-    else if (rows <= 32)
-        body(integral_constant<int, 2>{}, integral_constant<int, 5>{});
     else
-        body(integral_constant<int, 4>{}, integral_constant<int, 3>{});
+        body(integral_constant<int, 2>{}, integral_constant<int, 5>{});
 }
 
 // ABL (measurement only, 0 in the layer): bit 0 leaves out the MFMAs, bit 1 the LDS fragment
@@ -750,13 +751,13 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
         else
             shape(std::true_type{});
     }
-    else if (gp.bm == 64 && gp.bn == 64) {
+    else if (gp.bn == 64) {
         auto kern = K % 64 == 0 ? grouped_gemm_stream_kernel<F16, ACT, KEEP, false>
                                 : grouped_gemm_stream_kernel<F16, ACT, KEEP, true>;
-        const int grid = static_cast<int>(align_up(static_cast<size_t>(gp.max_items), 8));
+        const int grid = static_cast<int>(align_up(static_cast<size_t>(gp.max_items), 8)) * 4;
         hipEvent_t t0, t1;
         prof_kernel_events(stage, &t0, &t1);
-        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, t0, t1, 0, A, W, bias, C, pre, items,
+        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, st, t0, t1, 0, A, W, bias, C, pre, items,
                               nitems, N, K, row_src, row_div);
     }
     else if (gp.bm == 64)
@@ -856,12 +857,21 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_chunks)
     } else {
         const int64_t per_expert = chunk_rows / s.E;
         const int64_t tiles_n = (N + 255) / 256;
-        if (chunk_rows <= 5 * static_cast<int64_t>(s.E)) {
-            // a decode step: the weights are streamed once, by as many blocks as there are (us of
-            // the layer, this / the best other tile: 16 tokens, 16 experts, k = 2, 768 x 3072 54 / 61;
-            // 9 tokens, 4 experts, 992 x 3344 50 / 64; 105, 64, 568 x 2056 100 / 106; at six rows
-            // per expert the 64-row tile is the better one)
+        if (chunk_rows <= 5 * static_cast<int64_t>(s.E) ||
+            (chunk_rows <= 32 * static_cast<int64_t>(s.E) && chunk_rows * ((N + 127) / 128) <= 2000)) {
+            // a decode step: the weights are streamed once, by as many blocks as there are.  Every
+            // wavefront of 16 columns reads the rows again, so a larger tile takes over once they weigh
+            // as much as what sharing the weights out gains: the more column tiles there are to
+            // occupy the chip with, the fewer rows it takes.  us of the layer, this / the best other
+            // tile for the second GEMM: 8 experts, 768 x 3072, 6 / 16 / 36 rows per expert 42 / 55, 46 /
+            // 56, 55 / 56; 16, 1536 x 6144, 8 / 12 / 24 161 / 180, 166 / 179, 191 / 183; 32, 1024 x 4096, 8 /
+            // 12 138 / 139, 147 / 141; for the first: 4, 1024 x 4096, 6 / 24 58 / 63, 63 / 63; 16, 768 x
+            // 3072, 8 / 12 76 / 79, 82 / 77.  With Zipf(1.2) popularity the lines lie lower (16, 1536 x
+            // 6144, 8 / 12 rows 174 / 174, 198 / 182; 32, 512 x 1024, 16 43.5 / 40.4), hence 2000.
+            // Items of 32 rows: of 64 a popular expert's wavefronts hold three stages in flight instead of
+            // five and end last (Zipf, 16, 1536 x 6144, 8 rows 198 -> 174; 32, 512 x 1024, 8 42 -> 39.5).
             gp.bm = 64; gp.bn = 64; gp.concurrent = 128;
+            gp.item_rows = 32;
         } else if ((chunk_rows / 64 + s.E / 2) * tiles_n >= 128 &&
                    (per_expert < 48 || (per_expert <= 64 && (chunk_rows / 128 + s.E / 2) * tiles_n < 256))) {
             // few rows per expert and enough 64-row tiles to keep the weight stream going: shorter
@@ -876,7 +886,8 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_chunks)
         }
     }
     gp.tiles_n = (N + gp.bn - 1) / gp.bn;
-    gp.max_row_tiles = static_cast<int32_t>((chunk_rows + gp.bm - 1) / gp.bm + s.E);
+    if (gp.item_rows == 0) gp.item_rows = gp.bm;
+    gp.max_row_tiles = static_cast<int32_t>((chunk_rows + gp.item_rows - 1) / gp.item_rows + s.E);
     gp.max_items = gp.max_row_tiles * gp.tiles_n;
     return gp;
 }

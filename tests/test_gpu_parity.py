@@ -479,3 +479,16 @@ def test_expert_gemm_tiles(dtype, T, d, h, E, k, hot):
     L.layer(1)
     assert_ints_equal(L.ints(), o)
     assert rel_rms_err(L.b["y"].cpu().numpy().reshape(li.T, li.d), o.y) <= TOL[li.dtype]
+
+
+@pytest.mark.parametrize("T,d,h,E,k,hot", [
+    (33, 72, 200, 8, 2, 3),          # the hot expert holds 33 rows: two items of the streaming tile, 17 and 1 + 16
+    (32, 768, 328, 8, 2, 0),         # ... exactly one full item; last column item partly filled
+    (64, 64, 64, 4, 2, None),        # 32 rows per expert and one column tile: the last of its range
+    (65, 64, 64, 4, 2, None),        # ... and past it
+    (62, 136, 1032, 8, 2, 1),        # both sides of the rule in one layer: first GEMM's tiles, second's stream
+])
+def test_streaming_tile_over_its_range(T, d, h, E, k, hot):
+    """Few rows per expert: items of up to 32 rows, several per expert, at the ends of the rule's range
+    (bounds: TOL of the type)."""
+    test_expert_gemm_tiles("bf16", T, d, h, E, k, hot)

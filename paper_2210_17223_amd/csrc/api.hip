@@ -290,8 +290,6 @@ bool layout_workspace(const moe_shape &s, int n_chunks, void *base, Workspace *w
         w->gp[g] = choose_gemm_plan(s, g, n_chunks);
         w->items[g] = reinterpret_cast<WorkItem *>(p + off);
         off += align_up(static_cast<size_t>(n_chunks) * w->gp[g].max_items * sizeof(WorkItem), 256);
-        w->nitems[g] = reinterpret_cast<int32_t *>(p + off);
-        off += align_up(static_cast<size_t>(n_chunks) * sizeof(int32_t), 256);
     }
     w->hidden = p + off;
     const size_t hidden_elem = s.dtype == MOE_BF16 ? 2 : 4;

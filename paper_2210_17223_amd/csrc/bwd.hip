@@ -127,19 +127,14 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
 template <int EPI, int ACT, bool KTAIL>
 __global__ __launch_bounds__(512, 2) void bwd_gemm_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, void *__restrict__ Cout,
-    _Float16 *__restrict__ Pbuf, const WorkItem *__restrict__ items,
-    const int32_t *__restrict__ nitems, int N, int K)
+    _Float16 *__restrict__ Pbuf, const WorkItem *__restrict__ items, int N, int K)
 {
     constexpr int WM = 2, TM = 2, TN = 2, NT = 512;        // 2 x 4 wavefronts of 64 x 64
     constexpr int AV = kBM * 8 / NT, WV = kBN * 8 / NT;
     int expert, row0, row1, n0;
     {
-        const int total = *nitems;
-        const int per_xcd = (total + 7) / 8;
-        const int slot = blockIdx.x / 8;
-        const int idx = (blockIdx.x % 8) * per_xcd + slot;
-        if (slot >= per_xcd || idx >= total) return;
-        const WorkItem item = items[idx];
+        const WorkItem item = items[blockIdx.x];
+        if (item.expert < 0) return;
         expert = item.expert; row0 = item.row0; row1 = item.row1; n0 = item.n0;
     }
     const int KT = (K + kBK - 1) / kBK;
@@ -306,12 +301,11 @@ __global__ __launch_bounds__(512, 2) void bwd_gemm_kernel(
 template <int EPI, int ACT, bool KTAIL, int BM, int BN>
 __global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void bwd_gemm_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, void *__restrict__ Cout,
-    _Float16 *__restrict__ Pbuf, const WorkItem *__restrict__ items,
-    const int32_t *__restrict__ nitems, int N, int K)
+    _Float16 *__restrict__ Pbuf, const WorkItem *__restrict__ items, int N, int K)
 {
     constexpr bool F16 = false;
     constexpr int ABL = 0;
-    const int32_t *const row_src = nullptr;          // packed rows only
+    const int32_t *const row_src = nullptr, *const nitems = nullptr;   // packed rows, the plan's list
     constexpr int row_div = 1, a_rows = 0;
 #include "gemm_w4_body.inc"
 
@@ -1007,7 +1001,7 @@ GemmPlan plan_rows(int N, int K, int64_t max_rows, int E)
     gp.tiles_n = (N + gp.bn - 1) / gp.bn;
     gp.item_rows = gp.bm;
     gp.max_row_tiles = static_cast<int32_t>((max_rows + gp.bm - 1) / gp.bm + E);
-    gp.max_items = gp.max_row_tiles * gp.tiles_n;
+    gp.max_items = work_list_entries(gp);
     return gp;
 }
 
@@ -1027,7 +1021,6 @@ void layout_bwd(const moe_shape &s, void *base, BwdWorkspace *w)
     for (int g = 0; g < 2; ++g) {      // one list per FFN group of a chunked backward pass
         w->lists.items[g] = reinterpret_cast<WorkItem *>(
             take(sizeof(WorkItem) * w->lists.gp[g].max_items * kMaxChunks));
-        w->lists.nitems[g] = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * kMaxChunks));
     }
     const size_t Rh = static_cast<size_t>(R) * s.d_ff, Rd = static_cast<size_t>(R) * s.d_model;
     w->P = reinterpret_cast<_Float16 *>(take(Rh * 2));
@@ -1053,21 +1046,20 @@ bool supported(const moe_shape *s)
 
 template <int EPI, int ACT, bool KTAIL>
 void launch_gemm_k(const uint16_t *A, const uint16_t *W, void *C, _Float16 *P, const WorkItem *items,
-                   const int32_t *nitems, int N, int K, int grid_items, int stage, hipStream_t st)
+                   int N, int K, int grid_items, int stage, hipStream_t st)
 {
     auto kern = bwd_gemm_kernel<EPI, ACT, KTAIL>;
     static PerDeviceOnce once;   // raising the dynamic LDS limit: once per kernel and device
     once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kGemmLds));
-    const int grid = static_cast<int>(align_up(static_cast<size_t>(grid_items), 8));
     hipEvent_t t0, t1;
     prof_kernel_events(stage, &t0, &t1);
-    hipExtLaunchKernelGGL(kern, dim3(grid), dim3(512), kGemmLds, st, t0, t1, 0, A, W, C, P, items,
-                          nitems, N, K);
+    hipExtLaunchKernelGGL(kern, dim3(grid_items), dim3(512), kGemmLds, st, t0, t1, 0, A, W, C, P, items,
+                          N, K);
 }
 
 template <int EPI, int ACT>
 void launch_gemm(const uint16_t *A, const uint16_t *W, void *C, _Float16 *P, const WorkItem *items,
-                 const int32_t *nitems, int N, int K, const GemmPlan &gp, int stage, hipStream_t st)
+                 int N, int K, const GemmPlan &gp, int stage, hipStream_t st)
 {
     const int grid_items = gp.max_items;
     if (gp.w4) {
@@ -1077,10 +1069,9 @@ void launch_gemm(const uint16_t *A, const uint16_t *W, void *C, _Float16 *P, con
             constexpr size_t lds = w4_lds(BM, BN);
             static PerDeviceOnce once;
             once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
-            const int grid = static_cast<int>(align_up(static_cast<size_t>(grid_items), 8));
-            hipEvent_t t0, t1;
+                    hipEvent_t t0, t1;
             prof_kernel_events(stage, &t0, &t1);
-            hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, t0, t1, 0, A, W, C, P, items, nitems,
+            hipExtLaunchKernelGGL(kern, dim3(grid_items), dim3(256), lds, st, t0, t1, 0, A, W, C, P, items,
                                   N, K);
         };
         auto shape = [&](auto tail) {
@@ -1098,9 +1089,9 @@ void launch_gemm(const uint16_t *A, const uint16_t *W, void *C, _Float16 *P, con
         return;
     }
     if (K % kBK != 0)
-        launch_gemm_k<EPI, ACT, true>(A, W, C, P, items, nitems, N, K, grid_items, stage, st);
+        launch_gemm_k<EPI, ACT, true>(A, W, C, P, items, N, K, grid_items, stage, st);
     else
-        launch_gemm_k<EPI, ACT, false>(A, W, C, P, items, nitems, N, K, grid_items, stage, st);
+        launch_gemm_k<EPI, ACT, false>(A, W, C, P, items, N, K, grid_items, stage, st);
 }
 
 // dW[e] [M][N] = A[rows of e]^T B[rows of e] from row-major operands
@@ -1221,13 +1212,13 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
         const WorkItem *it1 = w.lists.items[1] + static_cast<size_t>(f) * g1.max_items;
         // P = xe W1 (fp16), Hb = act(P) (bf16) -- unless the forward kept P and its hidden activations
         if (pre == nullptr)
-            launch_gemm<1, ACT>(xe, W1p, w.Hb, w.P, it0, w.lists.nitems[0] + f, h, d, g0,
+            launch_gemm<1, ACT>(xe, W1p, w.Hb, w.P, it0, h, d, g0,
                                 kStageBwdRecompute, st);
         // dP = (dye W2^T) * act'(P): W2 [E][h][d] is already "rows n = h, contraction d contiguous"
-        launch_gemm<2, ACT>(w.dye, W2, w.dP, P, it0, w.lists.nitems[0] + f, h, d, g0,
+        launch_gemm<2, ACT>(w.dye, W2, w.dP, P, it0, h, d, g0,
                             kStageBwdDP, st);
         // dxe = dP W1^T: W1 [E][d][h] is "rows n = d, contraction h contiguous"
-        launch_gemm<0, ACT>(w.dP, W1, w.dxe, nullptr, it1, w.lists.nitems[1] + f, d, h, g1, kStageBwdDxe,
+        launch_gemm<0, ACT>(w.dP, W1, w.dxe, nullptr, it1, d, h, g1, kStageBwdDxe,
                             st);
     };
     // dW2[e] [h][d] = act(P)^T dye ; dW1[e] [d][h] = xe^T dP, operands as they are

@@ -379,10 +379,9 @@ void layout_padded(const moe_shape &s, int n_micro, void *base, PaddedWorkspace 
     for (int g = 0; g < 2; ++g) {
         GemmPlan gp = choose_gemm_plan(s, g, n_micro);
         gp.max_row_tiles = s.E * ((per_micro + gp.item_rows - 1) / gp.item_rows);
-        gp.max_items = gp.max_row_tiles * gp.tiles_n;
+        gp.max_items = work_list_entries(gp);
         w.gp[g] = gp;
         w.items[g] = reinterpret_cast<WorkItem *>(take(sizeof(WorkItem) * n_micro * gp.max_items));
-        w.nitems[g] = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * n_micro));
     }
     const size_t hidden_elem = s.dtype == MOE_BF16 ? 2 : 4;
     w.hidden = take(static_cast<size_t>(s.E) * s.capacity * s.d_ff * hidden_elem);

@@ -51,7 +51,7 @@ __host__ __device__ inline size_t align_up(size_t v, size_t a) { return (v + a -
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // One output tile of a grouped GEMM: rows [row0, row1) of the expert-major buffer, all
-// owned by `expert`, output columns [n0, n0 + tile width).
+// owned by `expert`, output columns [n0, n0 + tile width).  expert < 0: no tile.
 struct WorkItem {
     int32_t expert;
     int32_t row0;
@@ -66,9 +66,11 @@ struct GemmPlan {
     int32_t item_rows = 0;   // most rows of a work item: bm, or a part of it
     int32_t tiles_n;         // column tiles
     int32_t max_row_tiles;   // upper bound of row tiles per chunk
-    int32_t max_items;       // upper bound of work items per chunk
+    int32_t max_items;       // entries of a work list (a multiple of 8; surplus ones hold no tile)
     int32_t concurrent;      // work items in flight per XCD (sets the panel width)
 };
+// Entries of a work list: a block each, and a multiple of the eight L2s the blocks go round.
+inline int32_t work_list_entries(const GemmPlan &gp) { return (gp.max_row_tiles * gp.tiles_n + 7) / 8 * 8; }
 // Tile of a row-grouped GEMM on the four-wavefront kernels (gemm_w4.h): `rows` rows in all over E
 // experts.  256 x 256 where there are many such tiles, unless the contraction is one of a few
 // stages that 128 x 128 tiles hide their prologue and epilogue behind better.  The larger tile's time over
@@ -119,7 +121,6 @@ void expert_gemm_kernel_name(const moe_shape &s, int which, int n_chunks, char *
 struct Workspace {
     int32_t *seg_cnt;      // [nseg][kMaxExperts] per-segment expert counts -> bases
     WorkItem *items[2];    // per GEMM: [n_chunks][gp.max_items]
-    int32_t *nitems[2];    // per GEMM: [n_chunks]
     void *hidden;          // [max_rows][d_ff] hidden activations
     GemmPlan gp[2];
     int32_t nseg;
@@ -174,7 +175,7 @@ moe_status launch_items(const moe_shape &s, int n_chunks, int n_groups, const in
 // How many expert-FFN launches a layer cut into n_chunks gets.  Every FFN launch streams the
 // weights of all experts once, so a launch needs enough rows per expert to pay for that.
 int ffn_groups(const moe_shape &s, int n_chunks);
-// w.items[g] / w.nitems[g] sized for E lists: list e = the output tiles of expert e alone
+// w.items[g] sized for E lists: list e = the output tiles of expert e alone
 moe_status launch_items_per_expert(const moe_shape &s, const int32_t *offsets, const Workspace &w,
                                    hipStream_t st);
 moe_status launch_scatter(const moe_shape &s, const void *x, const int32_t *slot_of,
@@ -215,6 +216,16 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f)
 __host__ __device__ __forceinline__ int packed_gate_column(int i)
 {
     return (i & ~15) | ((i & 3) << 2) | ((i >> 2) & 3);
+}
+// The block's tile: entry blockIdx.x of a work list of the plan, which is laid out for that (build_items);
+// or, of a caller's plain list of *nitems, the blockIdx.x % 8-th eighth's next.
+__device__ __forceinline__ WorkItem take_item(const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems)
+{
+    if (nitems == nullptr) return items[blockIdx.x];
+    const int total = *nitems, per_xcd = (total + 7) / 8, slot = blockIdx.x / 8;
+    const int at = static_cast<int>(blockIdx.x % 8) * per_xcd + slot;
+    WorkItem none{-1, 0, 0, 0};
+    return slot < per_xcd && at < total ? items[at] : none;
 }
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 #endif

@@ -61,11 +61,10 @@ __device__ __forceinline__ float activate(float v)
 template <int ACT, int TM, int TN>
 __global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(
     const float *__restrict__ A, const float *__restrict__ B, const float *__restrict__ bias,
-    float *__restrict__ C, const WorkItem *__restrict__ items,
-    const int32_t *__restrict__ nitems, int N, int K)
+    float *__restrict__ C, const WorkItem *__restrict__ items, int N, int K)
 {
-    if (static_cast<int>(blockIdx.x) >= *nitems) return;
     const WorkItem tile = items[blockIdx.x];
+    if (tile.expert < 0) return;
     const int n0 = tile.n0;
 
     constexpr int BM = 32 * TM, BN = 32 * TN, BK = 32, PD = 4;
@@ -222,7 +221,7 @@ template <bool F16, typename TOut, int ACT, int WM, int WN, int TM, int TN, bool
 __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_staged_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, TOut *__restrict__ C, _Float16 *__restrict__ Pre,
-    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int N, int K,
+    const WorkItem *__restrict__ items, int N, int K,
     const int32_t *__restrict__ row_src, int row_div)
 {
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32, BK = 64, LD = BK + 8;
@@ -230,12 +229,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_staged_kernel(
     constexpr int AV = BM * 8 / NT, WV = BN * 8 / NT;   // 16-byte vectors per thread per stage
     static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0, "tile does not divide over the threads");
 
-    const int total = *nitems;
-    const int per_xcd = (total + 7) / 8;
-    const int slot = blockIdx.x / 8;
-    const int item_idx = (blockIdx.x % 8) * per_xcd + slot;
-    if (slot >= per_xcd || item_idx >= total) return;
-    const WorkItem item = items[item_idx];
+    const WorkItem item = items[blockIdx.x];
+    if (item.expert < 0) return;
     const int n0 = item.n0;
     const int rows = item.row1 - item.row0;
 
@@ -427,14 +422,11 @@ template <bool F16, int ACT, bool KEEP, bool KTAIL>
 __global__ __launch_bounds__(64, 3) void grouped_gemm_stream_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, const float *__restrict__ bias,
     _Float16 *__restrict__ C, _Float16 *__restrict__ Pre, const WorkItem *__restrict__ items,
-    const int32_t *__restrict__ nitems, int N, int K, const int32_t *__restrict__ row_src, int row_div)
+    int N, int K, const int32_t *__restrict__ row_src, int row_div)
 {
-    const int total = *nitems;
-    const int per_xcd = (total + 7) / 8;
-    const int slot = blockIdx.x / (8 * 4);
-    const int item_idx = (blockIdx.x % 8) * per_xcd + slot;
-    if (slot >= per_xcd || item_idx >= total) return;
-    const WorkItem item = items[item_idx];
+    // the four blocks of an item are eight apart: one L2's
+    const WorkItem item = items[blockIdx.x / 32 * 8 + blockIdx.x % 8];
+    if (item.expert < 0) return;
     const int rows = item.row1 - item.row0;
     const int lane = threadIdx.x, fr = lane & 15, oct = lane >> 4;
     const int nw = item.n0 + static_cast<int>(blockIdx.x / 8 % 4) * 16;
@@ -609,10 +601,10 @@ template <bool F16, int ACT, bool KEEP, bool KTAIL, int BN>
 __global__ __launch_bounds__(256, BN == 128 ? 2 : 1) void grouped_gemm_mfma_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
-    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int N, int K,
+    const WorkItem *__restrict__ items, int N, int K,
     const int32_t *__restrict__ row_src, int row_div, int a_rows)
 {
-    w4_gemm_tile<F16, ACT, KEEP, KTAIL, 128, BN, 0>(A, W, bias, C, Pre, items, nitems, N, K, row_src,
+    w4_gemm_tile<F16, ACT, KEEP, KTAIL, 128, BN, 0>(A, W, bias, C, Pre, items, nullptr, N, K, row_src,
                                                     row_div, a_rows);
 }
 #undef MOE_LGKM0
@@ -664,8 +656,7 @@ void launch_f32_pair(const moe_shape &s, const float *xe, const float *W1, const
         constexpr int A_ = decltype(act)::value;
         const GemmPlan &gp = w.gp[g];
         auto kern = gp.bm == 64 ? grouped_gemm_f32_kernel<A_, 2, 2> : grouped_gemm_f32_kernel<A_, 1, 1>;
-        hipLaunchKernelGGL(kern, dim3(gp.max_items), dim3(256), 0, st, A, B, bias, C, items,
-                           w.nitems[g] + chunk, N, K);
+        hipLaunchKernelGGL(kern, dim3(gp.max_items), dim3(256), 0, st, A, B, bias, C, items, N, K);
     };
     prof_begin(kStageGemm1, st);
     launch(std::integral_constant<int, ACT>{}, 0, xe, W1, b1, H, it1, s.d_ff, s.d_model);
@@ -677,7 +668,7 @@ void launch_f32_pair(const moe_shape &s, const float *xe, const float *W1, const
 
 template <bool F16, typename TOut, int ACT, int WM, int WN, int TM, int TN, bool KTAIL, bool KEEP>
 void launch_mfma_cfg_k(const uint16_t *A, const uint16_t *W, const float *bias, TOut *C,
-                     _Float16 *pre, const WorkItem *items, const int32_t *nitems, int max_items,
+                     _Float16 *pre, const WorkItem *items, int max_items,
                      int N, int K, int stage, hipStream_t st, const int32_t *row_src, int row_div)
 {
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
@@ -685,26 +676,25 @@ void launch_mfma_cfg_k(const uint16_t *A, const uint16_t *W, const float *bias, 
     auto kern = grouped_gemm_staged_kernel<F16, TOut, ACT, WM, WN, TM, TN, KTAIL, KEEP>;
     static PerDeviceOnce once;   // raising the dynamic LDS limit: once per kernel and device
     once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
-    const int grid = static_cast<int>(align_up(static_cast<size_t>(max_items), 8));
     hipEvent_t t0, t1;
     prof_kernel_events(stage, &t0, &t1);
-    hipExtLaunchKernelGGL(kern, dim3(grid), dim3(64 * WM * WN), lds, st, t0, t1, 0, A, W, bias, C,
-                          pre, items, nitems, N, K, row_src, row_div);
+    hipExtLaunchKernelGGL(kern, dim3(max_items), dim3(64 * WM * WN), lds, st, t0, t1, 0, A, W, bias, C,
+                          pre, items, N, K, row_src, row_div);
 }
 
 // The contraction depth is a multiple of the 64-deep stage in every benchmark shape;
 // other depths take a variant that zero-fills the last stage.
 template <bool F16, typename TOut, int ACT, bool KEEP, int WM, int WN, int TM, int TN>
 void launch_mfma_cfg(const uint16_t *A, const uint16_t *W, const float *bias, TOut *C,
-                     _Float16 *pre, const WorkItem *items, const int32_t *nitems, int max_items,
+                     _Float16 *pre, const WorkItem *items, int max_items,
                      int N, int K, int stage, hipStream_t st, const int32_t *row_src, int row_div)
 {
     if (K % 64 == 0)
         launch_mfma_cfg_k<F16, TOut, ACT, WM, WN, TM, TN, false, KEEP>(
-            A, W, bias, C, pre, items, nitems, max_items, N, K, stage, st, row_src, row_div);
+            A, W, bias, C, pre, items, max_items, N, K, stage, st, row_src, row_div);
     else
         launch_mfma_cfg_k<F16, TOut, ACT, WM, WN, TM, TN, true, KEEP>(
-            A, W, bias, C, pre, items, nitems, max_items, N, K, stage, st, row_src, row_div);
+            A, W, bias, C, pre, items, max_items, N, K, stage, st, row_src, row_div);
 }
 
 // The four-wavefront kernel addresses its operands with 32-bit byte offsets into buffer
@@ -719,28 +709,28 @@ inline bool w4_kernel_fits(int N, int K, bool gathered, uint64_t row_limit)
 
 template <bool F16, typename TOut, int ACT, bool KEEP>
 void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const float *bias,
-                 TOut *C, _Float16 *pre, const WorkItem *items, const int32_t *nitems, int N, int K,
+                 TOut *C, _Float16 *pre, const WorkItem *items, int N, int K,
                  int stage, hipStream_t st, const int32_t *row_src = nullptr, int row_div = 1,
                  uint64_t row_limit = 0)
 {
 #define MOE_MFMA_SHAPE(WM_, WN_, TM_, TN_)                                                        \
-    launch_mfma_cfg<F16, TOut, ACT, KEEP, WM_, WN_, TM_, TN_>(A, W, bias, C, pre, items, nitems,    \
+    launch_mfma_cfg<F16, TOut, ACT, KEEP, WM_, WN_, TM_, TN_>(A, W, bias, C, pre, items,            \
                                                               gp.max_items, N, K, stage, st,       \
                                                               row_src, row_div)
     if (gp.w4) {
-        auto launch = [&](auto kern, PerDeviceOnce &once, size_t lds) {
+        auto launch = [&](auto kern, PerDeviceOnce &once, size_t lds, auto... list) {
             once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
-            const int grid = static_cast<int>(align_up(static_cast<size_t>(gp.max_items), 8));
             hipEvent_t t0, t1;
             prof_kernel_events(stage, &t0, &t1);
-            hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, t0, t1, 0, A, W, bias, C, pre,
-                                  items, nitems, N, K, row_src, row_div, static_cast<int>(row_limit));
+            hipExtLaunchKernelGGL(kern, dim3(gp.max_items), dim3(256), lds, st, t0, t1, 0, A, W, bias, C, pre,
+                                  items, list..., N, K, row_src, row_div, static_cast<int>(row_limit));
         };
         auto shape = [&](auto tail) {
             constexpr bool TAIL = decltype(tail)::value;
             static PerDeviceOnce once[3];
             if (gp.bm == 256)
-                launch(grouped_gemm_w4_kernel<F16, ACT, KEEP, TAIL>, once[0], w4_lds(256, 256));
+                launch(grouped_gemm_w4_kernel<F16, ACT, KEEP, TAIL>, once[0], w4_lds(256, 256),
+                       static_cast<const int32_t *>(nullptr));
             else if (gp.bn == 256)
                 launch(grouped_gemm_mfma_kernel<F16, ACT, KEEP, TAIL, 256>, once[1], w4_lds(128, 256));
             else
@@ -754,11 +744,11 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
     else if (gp.bn == 64) {
         auto kern = K % 64 == 0 ? grouped_gemm_stream_kernel<F16, ACT, KEEP, false>
                                 : grouped_gemm_stream_kernel<F16, ACT, KEEP, true>;
-        const int grid = static_cast<int>(align_up(static_cast<size_t>(gp.max_items), 8)) * 4;
+        const int grid = gp.max_items * 4;
         hipEvent_t t0, t1;
         prof_kernel_events(stage, &t0, &t1);
-        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, st, t0, t1, 0, A, W, bias, C, pre, items,
-                              nitems, N, K, row_src, row_div);
+        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, st, t0, t1, 0, A, W, bias, C, pre, items, N, K,
+                              row_src, row_div);
     }
     else if (gp.bm == 64)
         MOE_MFMA_SHAPE(1, 8, 2, 1);
@@ -778,14 +768,13 @@ void launch_mfma_pair(const moe_shape &s, const uint16_t *xe, const uint16_t *W1
     const WorkItem *it2 = w.items[1] + static_cast<size_t>(chunk) * w.gp[1].max_items;
     if (pre != nullptr)
         launch_mfma<false, _Float16, ACT, true>(w.gp[0], xe, W1p, b1, H, pre, it1,
-                                                w.nitems[0] + chunk, s.d_ff, s.d_model,
+                                                s.d_ff, s.d_model,
                                                 kStageGemm1, st, row_src, row_div, s.T);
     else
-        launch_mfma<false, _Float16, ACT, false>(w.gp[0], xe, W1p, b1, H, nullptr, it1,
-                                                 w.nitems[0] + chunk, s.d_ff, s.d_model,
+        launch_mfma<false, _Float16, ACT, false>(w.gp[0], xe, W1p, b1, H, nullptr, it1, s.d_ff, s.d_model,
                                                  kStageGemm1, st, row_src, row_div, s.T);
     launch_mfma<true, _Float16, MOE_ACT_IDENTITY, false>(w.gp[1], reinterpret_cast<const uint16_t *>(H),
-                                                      W2p, b2, ye, nullptr, it2, w.nitems[1] + chunk,
+                                                      W2p, b2, ye, nullptr, it2,
                                                       s.d_model, s.d_ff, kStageGemm2, st);
 }
 
@@ -888,7 +877,7 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_chunks)
     gp.tiles_n = (N + gp.bn - 1) / gp.bn;
     if (gp.item_rows == 0) gp.item_rows = gp.bm;
     gp.max_row_tiles = static_cast<int32_t>((chunk_rows + gp.item_rows - 1) / gp.item_rows + s.E);
-    gp.max_items = gp.max_row_tiles * gp.tiles_n;
+    gp.max_items = work_list_entries(gp);
     return gp;
 }
 

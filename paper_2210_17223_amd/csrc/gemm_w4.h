@@ -89,6 +89,17 @@ __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rs, int voff,
                  ::"v"(voff), "s"(rs), "s"(at), "s"(soff) : "memory", "m0");
 #endif
 }
+// A load whose completion is counted by hand too: `v` holds the dword behind loaded<N>, N loads that
+// were issued after it still being on their way.
+__device__ __forceinline__ void load_dword(int &v, const int32_t *p)
+{
+    asm volatile("global_load_dword %0, %1, off" : "=&v"(v) : "v"(p) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void loaded(int &v)
+{
+    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(v) : "n"(N) : "memory");
+}
 __device__ __forceinline__ uint32_t lds_address(const void *p)
 {
     return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void *)p));

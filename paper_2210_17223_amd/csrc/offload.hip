@@ -117,8 +117,6 @@ void layout(const moe_shape &s, void *base, Workspace *w)
         w->gp[g] = choose_gemm_plan(s, g, 1);            // the resident path's tile shapes
         w->items[g] = reinterpret_cast<WorkItem *>(p + off);
         off += align_up(static_cast<size_t>(s.E) * w->gp[g].max_items * sizeof(WorkItem), 256);
-        w->nitems[g] = reinterpret_cast<int32_t *>(p + off);
-        off += align_up(static_cast<size_t>(s.E) * sizeof(int32_t), 256);
     }
     w->hidden = p + off;
     off += align_up(static_cast<size_t>(moe_max_rows(&s)) * s.d_ff * 2, 256);

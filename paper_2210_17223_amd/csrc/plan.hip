@@ -48,10 +48,8 @@ __device__ __forceinline__ bool names_expert(int e, int E)
     return static_cast<unsigned>(e) < static_cast<unsigned>(E);
 }
 
-__device__ void build_items(const GemmPlan &gp, WorkItem *__restrict__ items,
-                            int32_t *__restrict__ nitems_out, const int32_t *lo_s,
-                            const int32_t *hi_s, int32_t *mt_s, int32_t *cum_s, int part,
-                            int nparts);
+__device__ void build_items(const GemmPlan &gp, WorkItem *__restrict__ items, const int32_t *lo_s,
+                            const int32_t *hi_s, int32_t *mt_s, int32_t *cum_s, int part, int nparts);
 
 __global__ __launch_bounds__(kPlanThreads) void plan_count_kernel(
     const int32_t *__restrict__ expert_idx, int32_t *__restrict__ seg_cnt, int n, int E,
@@ -84,8 +82,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_count_kernel(
 __global__ __launch_bounds__(1024) void plan_scan_kernel(
     int32_t *__restrict__ seg_cnt, int32_t *__restrict__ counts,
     int32_t *__restrict__ offsets, int nseg, int E, int EPs, int capacity, int with_items,
-    WorkItem *__restrict__ items0, int32_t *__restrict__ nitems0, GemmPlan gp0,
-    WorkItem *__restrict__ items1, int32_t *__restrict__ nitems1, GemmPlan gp1)
+    WorkItem *__restrict__ items0, GemmPlan gp0,
+    WorkItem *__restrict__ items1, GemmPlan gp1)
 {
     __shared__ int32_t gsum[1024];                 // [G][EPs]
     __shared__ int32_t kept[kMaxExperts];
@@ -155,8 +153,8 @@ __global__ __launch_bounds__(1024) void plan_scan_kernel(
     }
     __syncthreads();
     if (with_items) {
-        build_items(gp0, items0, nitems0, lo_s, hi_s, mt_s, cum_s, 0, 1);
-        build_items(gp1, items1, nitems1, lo_s, hi_s, mt_s, cum_s, 0, 1);
+        build_items(gp0, items0, lo_s, hi_s, mt_s, cum_s, 0, 1);
+        build_items(gp1, items1, lo_s, hi_s, mt_s, cum_s, 0, 1);
     }
 }
 
@@ -201,12 +199,13 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(
 // LDS (entries at or beyond E are empty).  An expert's rows are cut into row tiles of equal
 // height (a multiple of 32, at most gp.item_rows), and its output tiles are listed panel by panel --
 // `concurrent / row_tiles` column tiles wide, row tiles inside -- so that the blocks in
-// flight on one XCD share both their weight and their activation tiles.  Called by every
-// thread of the block; part `part` of `nparts` blocks emits its share of the entries.
-__device__ void build_items(const GemmPlan &gp, WorkItem *__restrict__ items,
-                            int32_t *__restrict__ nitems_out, const int32_t *lo_s,
-                            const int32_t *hi_s, int32_t *mt_s, int32_t *cum_s, int part,
-                            int nparts)
+// flight on one XCD share both their weight and their activation tiles.  Entry b is block b's: the
+// blocks go round the eight XCDs, and each XCD's walk a contiguous eighth of the tiles; entries without
+// a tile say so.  (A block then waits for its entry alone; when it read the number of tiles first to find
+// it, the layer of a decode step of 16 tokens took 48.6 us instead of 47.)
+// Called by every thread of the block; part `part` of `nparts` blocks emits its share of the entries.
+__device__ void build_items(const GemmPlan &gp, WorkItem *__restrict__ items, const int32_t *lo_s,
+                            const int32_t *hi_s, int32_t *mt_s, int32_t *cum_s, int part, int nparts)
 {
     if (threadIdx.x < kWave) {
         const int e = threadIdx.x;
@@ -223,8 +222,13 @@ __device__ void build_items(const GemmPlan &gp, WorkItem *__restrict__ items,
     }
     __syncthreads();
     const int total = min(cum_s[kMaxExperts], gp.max_items);
-    if (part == 0 && threadIdx.x == 0) *nitems_out = total;
-    for (int L = part * blockDim.x + threadIdx.x; L < total; L += nparts * blockDim.x) {
+    const int per_xcd = (total + 7) / 8;
+    for (int b = part * blockDim.x + threadIdx.x; b < gp.max_items; b += nparts * blockDim.x) {
+        const int L = b % 8 * per_xcd + b / 8;
+        if (b / 8 >= per_xcd || L >= total) {
+            items[b].expert = -1;
+            continue;
+        }
         int e = 0;                                  // largest e with cum_s[e] <= L
 #pragma unroll
         for (int step = kMaxExperts / 2; step > 0; step >>= 1)
@@ -244,7 +248,7 @@ __device__ void build_items(const GemmPlan &gp, WorkItem *__restrict__ items,
         it.row0 = lo_s[e] + m * per_tile;
         it.row1 = min(hi_s[e], it.row0 + per_tile);
         it.n0 = nt * gp.bn;
-        items[L] = it;
+        items[b] = it;
     }
     __syncthreads();
 }
@@ -261,8 +265,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_prefix_kernel(
     const int32_t *__restrict__ expert_idx, const int32_t *__restrict__ seg_cnt,
     int32_t *__restrict__ counts, int32_t *__restrict__ offsets, int32_t *__restrict__ slot_of,
     int32_t *__restrict__ src_of, int n, int E, int capacity, int seg_len, int nseg, int padded,
-    int with_items, WorkItem *__restrict__ items0, int32_t *__restrict__ nitems0, GemmPlan gp0,
-    WorkItem *__restrict__ items1, int32_t *__restrict__ nitems1, GemmPlan gp1,
+    int with_items, WorkItem *__restrict__ items0, GemmPlan gp0,
+    WorkItem *__restrict__ items1, GemmPlan gp1,
     int spb, int lg_parts, const uint4 *__restrict__ x, uint4 *__restrict__ xe, int vec, int k, int T)
 {
     constexpr int kParts = kPlanWaves * 4;          // partial sums: 16-byte loads, 4 segments per wavefront load
@@ -331,9 +335,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_prefix_kernel(
             // odd ones the second's, each its share
             const int x = static_cast<int>(gridDim.x - 1 - blockIdx.x);
             if (x & 1)
-                build_items(gp1, items1, nitems1, lo_s, hi_s, mt_s, cum_s, x >> 1, kItemBlocks / 2);
+                build_items(gp1, items1, lo_s, hi_s, mt_s, cum_s, x >> 1, kItemBlocks / 2);
             else
-                build_items(gp0, items0, nitems0, lo_s, hi_s, mt_s, cum_s, x >> 1, kItemBlocks / 2);
+                build_items(gp0, items0, lo_s, hi_s, mt_s, cum_s, x >> 1, kItemBlocks / 2);
         }
         return;
     }
@@ -408,8 +412,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_prefix_kernel(
 // (lane e of the first wavefront owns expert e).
 __global__ __launch_bounds__(256) void plan_items_kernel(
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ src_of,
-    WorkItem *__restrict__ items0, int32_t *__restrict__ nitems0, GemmPlan gp0,
-    WorkItem *__restrict__ items1, int32_t *__restrict__ nitems1, GemmPlan gp1, int T, int k,
+    WorkItem *__restrict__ items0, GemmPlan gp0,
+    WorkItem *__restrict__ items1, GemmPlan gp1, int T, int k,
     int E, int n_chunks, int n_groups)
 {
     __shared__ int32_t lo_s[kMaxExperts], hi_s[kMaxExperts], mt_s[kMaxExperts];
@@ -417,7 +421,6 @@ __global__ __launch_bounds__(256) void plan_items_kernel(
     const int c = blockIdx.x;
     const GemmPlan gp = blockIdx.y == 0 ? gp0 : gp1;
     WorkItem *items = (blockIdx.y == 0 ? items0 : items1) + static_cast<size_t>(c) * gp.max_items;
-    int32_t *nitems = (blockIdx.y == 0 ? nitems0 : nitems1) + c;
 
     if (threadIdx.x < kWave) {
         const int e = threadIdx.x;
@@ -451,22 +454,19 @@ __global__ __launch_bounds__(256) void plan_items_kernel(
         hi_s[e] = hi;
     }
     __syncthreads();
-    build_items(gp, items, nitems, lo_s, hi_s, mt_s, cum_s, blockIdx.z, gridDim.z);
+    build_items(gp, items, lo_s, hi_s, mt_s, cum_s, blockIdx.z, gridDim.z);
 }
 
 // One work list per expert (list e holds expert e's output tiles only), for executing the
 // experts one after the other: block (e, g) builds list e of GEMM g.
 __global__ __launch_bounds__(256) void plan_items_expert_kernel(
-    const int32_t *__restrict__ offsets, WorkItem *__restrict__ items0,
-    int32_t *__restrict__ nitems0, GemmPlan gp0, WorkItem *__restrict__ items1,
-    int32_t *__restrict__ nitems1, GemmPlan gp1, int E)
+    const int32_t *__restrict__ offsets, WorkItem *__restrict__ items0, GemmPlan gp0, WorkItem *__restrict__ items1, GemmPlan gp1, int E)
 {
     __shared__ int32_t lo_s[kMaxExperts], hi_s[kMaxExperts], mt_s[kMaxExperts];
     __shared__ int32_t cum_s[kMaxExperts + 1];
     const int only = blockIdx.x;
     const GemmPlan gp = blockIdx.y == 0 ? gp0 : gp1;
     WorkItem *items = (blockIdx.y == 0 ? items0 : items1) + static_cast<size_t>(only) * gp.max_items;
-    int32_t *nitems = (blockIdx.y == 0 ? nitems0 : nitems1) + only;
     if (threadIdx.x < kWave) {
         const int e = threadIdx.x;
         const bool mine = e == only && e < E;
@@ -474,22 +474,19 @@ __global__ __launch_bounds__(256) void plan_items_expert_kernel(
         hi_s[e] = mine ? offsets[e + 1] : 0;
     }
     __syncthreads();
-    build_items(gp, items, nitems, lo_s, hi_s, mt_s, cum_s, 0, 1);
+    build_items(gp, items, lo_s, hi_s, mt_s, cum_s, 0, 1);
 }
 
 // Work lists of the padded layout: micro-op m (blockIdx.x) covers, for every expert, the slot
 // positions [m*C/n, (m+1)*C/n) of its C slots; only those below min(count, C) hold rows.
 __global__ __launch_bounds__(256) void plan_items_padded_kernel(
-    const int32_t *__restrict__ counts, WorkItem *__restrict__ items0,
-    int32_t *__restrict__ nitems0, GemmPlan gp0, WorkItem *__restrict__ items1,
-    int32_t *__restrict__ nitems1, GemmPlan gp1, int E, int capacity, int n_micro)
+    const int32_t *__restrict__ counts, WorkItem *__restrict__ items0, GemmPlan gp0, WorkItem *__restrict__ items1, GemmPlan gp1, int E, int capacity, int n_micro)
 {
     __shared__ int32_t lo_s[kMaxExperts], hi_s[kMaxExperts], mt_s[kMaxExperts];
     __shared__ int32_t cum_s[kMaxExperts + 1];
     const int m = blockIdx.x;
     const GemmPlan gp = blockIdx.y == 0 ? gp0 : gp1;
     WorkItem *items = (blockIdx.y == 0 ? items0 : items1) + static_cast<size_t>(m) * gp.max_items;
-    int32_t *nitems = (blockIdx.y == 0 ? nitems0 : nitems1) + m;
     if (threadIdx.x < kWave) {
         const int e = threadIdx.x;
         int lo = 0, hi = 0;
@@ -504,7 +501,7 @@ __global__ __launch_bounds__(256) void plan_items_padded_kernel(
         hi_s[e] = hi;
     }
     __syncthreads();
-    build_items(gp, items, nitems, lo_s, hi_s, mt_s, cum_s, blockIdx.z, gridDim.z);
+    build_items(gp, items, lo_s, hi_s, mt_s, cum_s, blockIdx.z, gridDim.z);
 }
 
 }  // namespace
@@ -513,7 +510,7 @@ moe_status launch_items_padded(const moe_shape &s, int n_micro, const int32_t *c
                                const Workspace &w, hipStream_t st)
 {
     hipLaunchKernelGGL(plan_items_padded_kernel, dim3(n_micro, 2, 4), dim3(256), 0, st, counts,
-                       w.items[0], w.nitems[0], w.gp[0], w.items[1], w.nitems[1], w.gp[1], s.E,
+                       w.items[0], w.gp[0], w.items[1], w.gp[1], s.E,
                        s.capacity, n_micro);
     MOE_TRY_HIP(hipGetLastError());
     return MOE_OK;
@@ -523,7 +520,7 @@ moe_status launch_items_per_expert(const moe_shape &s, const int32_t *offsets, c
                                    hipStream_t st)
 {
     hipLaunchKernelGGL(plan_items_expert_kernel, dim3(s.E, 2), dim3(256), 0, st, offsets, w.items[0],
-                       w.nitems[0], w.gp[0], w.items[1], w.nitems[1], w.gp[1], s.E);
+                       w.gp[0], w.items[1], w.gp[1], s.E);
     MOE_TRY_HIP(hipGetLastError());
     return MOE_OK;
 }
@@ -560,8 +557,8 @@ moe_status launch_plan(const moe_shape &s, const int32_t *expert_idx, int32_t *c
                            dim3((ceil_div(w.nseg, spb) << lg_parts) + (with_items ? kItemBlocks : 1)),
                            dim3(kPlanThreads), 0, st,
                            expert_idx, w.seg_cnt, counts, offsets, slot_of, src_of, n, s.E,
-                           s.capacity, seg_len, w.nseg, padded ? 1 : 0, with_items ? 1 : 0, w.items[0], w.nitems[0], w.gp[0],
-                           w.items[1], w.nitems[1], w.gp[1], spb, lg_parts,
+                           s.capacity, seg_len, w.nseg, padded ? 1 : 0, with_items ? 1 : 0, w.items[0], w.gp[0],
+                           w.items[1], w.gp[1], spb, lg_parts,
                            pack ? static_cast<const uint4 *>(x) : nullptr,
                            pack ? static_cast<uint4 *>(xe) : nullptr, s.d_model * elem / 16, s.k,
                            s.T);
@@ -571,7 +568,7 @@ moe_status launch_plan(const moe_shape &s, const int32_t *expert_idx, int32_t *c
     }
     hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(1024), 0, st, w.seg_cnt, counts,
                        offsets, w.nseg, s.E, eps, s.capacity, n_chunks == 1 && !padded ? 1 : 0, w.items[0],
-                       w.nitems[0], w.gp[0], w.items[1], w.nitems[1], w.gp[1]);
+                       w.gp[0], w.items[1], w.gp[1]);
     hipLaunchKernelGGL(plan_rank_kernel, dim3(blocks), dim3(kPlanThreads), 0, st,
                        expert_idx, w.seg_cnt, offsets, slot_of, src_of, n, s.E, s.capacity,
                        seg_len, padded ? 1 : 0);
@@ -583,7 +580,7 @@ moe_status launch_items(const moe_shape &s, int n_chunks, int n_groups, const in
                         const int32_t *src_of, const Workspace &w, hipStream_t st)
 {
     hipLaunchKernelGGL(plan_items_kernel, dim3(n_groups, 2, 8), dim3(256), 0, st, offsets, src_of,
-                       w.items[0], w.nitems[0], w.gp[0], w.items[1], w.nitems[1], w.gp[1], s.T,
+                       w.items[0], w.gp[0], w.items[1], w.gp[1], s.T,
                        s.k, s.E, n_chunks, n_groups);
     MOE_TRY_HIP(hipGetLastError());
     return MOE_OK;

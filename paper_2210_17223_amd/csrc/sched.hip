@@ -7,7 +7,6 @@
 #include "moe_sched.h"
 
 #include <algorithm>
-#include <vector>
 
 namespace moe {
 namespace {
@@ -267,67 +266,59 @@ __global__ __launch_bounds__(256) void popularity_estimate_kernel(
 
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
-struct Schedule {
-    std::vector<int32_t> replicas;
-    std::vector<std::vector<int32_t>> hosted;
-    int32_t used = 0;
-};
-
-// The packing of moe_schedule_experts on host vectors.
-Schedule schedule_experts(int N, int E, const uint64_t *w, uint64_t W, const uint8_t *has,
-                          int max_pack)
+// The packing of moe_schedule_experts, straight into the caller's arrays (at most kMaxExperts experts:
+// nothing is allocated).
+void schedule_experts(int N, int E, const uint64_t *w, uint64_t W, const uint8_t *has, int max_pack,
+                      int32_t *replicas, int32_t *dev_count, int32_t *dev_experts, int32_t *devices_used)
 {
-    Schedule out;
-    out.replicas.assign(E, 0);
-    out.hosted.assign(N, {});
-    std::vector<std::vector<int32_t>> groups;     // experts of each asked-for device
-    std::vector<int32_t> small;
+    std::fill(replicas, replicas + E, 0);
+    std::fill(dev_count, dev_count + N, 0);
+    std::fill(dev_experts, dev_experts + static_cast<size_t>(N) * E, -1);
+    // wrapping can bring an expert to a device that hosts it already: never more than E per device
+    auto host = [&](int64_t d, int32_t e) {
+        int32_t *list = dev_experts + d * E;
+        if (std::find(list, list + dev_count[d], e) == list + dev_count[d]) list[dev_count[d]++] = e;
+    };
+    int64_t used = 0;                             // devices asked for
+    int small[kMaxExperts], n_small = 0;          // heaviest first, index order kept on ties
     for (int e = 0; e < E; ++e) {
         if (!has[e]) continue;
         if (w[e] >= W) {
             // round half up of w / W, without forming 2w + W (which could overflow)
             const uint64_t q = w[e] / W, rem = w[e] % W;
             const uint64_t r = q + (rem >= W - rem ? 1 : 0);
-            out.replicas[e] = static_cast<int32_t>(std::min<uint64_t>(r, N));   // never more than all devices
-            for (int32_t i = 0; i < out.replicas[e]; ++i) groups.push_back({e});
+            replicas[e] = static_cast<int32_t>(std::min<uint64_t>(r, N));   // never more than all devices
+            for (int32_t i = 0; i < replicas[e]; ++i) host(used++ % N, e);
         } else {
-            small.push_back(e);
+            int at = n_small++;
+            for (; at > 0 && w[small[at - 1]] < w[e]; --at) small[at] = small[at - 1];
+            small[at] = e;
         }
     }
-    std::stable_sort(small.begin(), small.end(),
-                     [&](int32_t a, int32_t b) { return w[a] > w[b]; });   // index order kept on ties
-    std::vector<std::vector<int32_t>> bins;
-    std::vector<uint64_t> load;
-    for (int32_t e : small) {
-        size_t b = 0;
-        for (; b < bins.size(); ++b)
-            if (load[b] + w[e] <= W && static_cast<int>(bins[b].size()) < max_pack) break;
-        if (b == bins.size()) {
-            bins.push_back({});
-            load.push_back(0);
-        }
-        bins[b].push_back(e);
+    int n_bins = 0, in_bin[kMaxExperts], bin_of[kMaxExperts];
+    uint64_t load[kMaxExperts];
+    for (int i = 0; i < n_small; ++i) {
+        const int e = small[i];
+        int b = 0;
+        while (b < n_bins && !(load[b] + w[e] <= W && in_bin[b] < max_pack)) ++b;
+        if (b == n_bins) load[n_bins] = 0, in_bin[n_bins] = 0, ++n_bins;
+        bin_of[i] = b;
         load[b] += w[e];
-        out.replicas[e] = 1;
+        ++in_bin[b];
+        replicas[e] = 1;
     }
-    for (auto &b : bins) groups.push_back(b);
-    const int64_t used = static_cast<int64_t>(groups.size());
-    for (int64_t g = 0; g < used; ++g) {
-        auto &dev = out.hosted[g % N];
-        for (int32_t e : groups[g])
-            if (std::find(dev.begin(), dev.end(), e) == dev.end()) dev.push_back(e);
-    }
+    for (int b = 0; b < n_bins; ++b, ++used)
+        for (int i = 0; i < n_small; ++i)
+            if (bin_of[i] == b) host(used % N, small[i]);
     const int64_t free_devs = N - used;
     int64_t m = 0;
     for (int e = 0; e < E; ++e) {
         if (has[e]) continue;
-        const int64_t d = free_devs > 0 ? used + (m % free_devs) : e % N;
-        out.hosted[d].push_back(e);
-        out.replicas[e] = 1;
+        host(free_devs > 0 ? used + m % free_devs : e % N, e);
+        replicas[e] = 1;
         ++m;
     }
-    out.used = static_cast<int32_t>(std::min<int64_t>(used, N));
-    return out;
+    *devices_used = static_cast<int32_t>(std::min<int64_t>(used, N));
 }
 
 moe_status check_schedule_args(int32_t N, int32_t E, const void *w_or_S, int32_t max_pack,
@@ -347,31 +338,18 @@ moe_status check_schedule_args(int32_t N, int32_t E, const void *w_or_S, int32_t
     return MOE_OK;
 }
 
-void write_schedule(const Schedule &sc, int N, int E, int32_t *replicas, int32_t *dev_count,
-                    int32_t *dev_experts, int32_t *devices_used)
-{
-    for (int e = 0; e < E; ++e) replicas[e] = sc.replicas[e];
-    for (int d = 0; d < N; ++d) {
-        // wrapping can put more than E entries' worth of groups on a device, never more
-        // than E distinct experts
-        dev_count[d] = static_cast<int32_t>(sc.hosted[d].size());
-        for (int i = 0; i < E; ++i)
-            dev_experts[static_cast<size_t>(d) * E + i] =
-                i < dev_count[d] ? sc.hosted[d][i] : -1;
-    }
-    *devices_used = sc.used;
-}
-
-// The 2k (at most E) most popular experts, most popular first, ties to the lower index.
+// The m most popular experts, most popular first, ties to the lower index.
 template <typename V>
-std::vector<int32_t> top_list(int E, int m, const V *score)
+void top_list(int E, int m, const V *score, int *order)
 {
-    std::vector<int32_t> order(E);
-    for (int e = 0; e < E; ++e) order[e] = e;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return score[a] > score[b]; });
-    order.resize(m);
-    return order;
+    int n = 0;
+    for (int e = 0; e < E; ++e) {
+        int at = n;
+        for (; at > 0 && score[order[at - 1]] < score[e]; --at)
+            if (at < m) order[at] = order[at - 1];
+        if (at < m) order[at] = e;
+        n = std::min(n + 1, m);
+    }
 }
 
 }  // namespace
@@ -506,16 +484,18 @@ moe_status moe_schedule_experts(int32_t N, int32_t E, const uint64_t *w, uint64_
         set_error("moe_schedule_experts: has is NULL or W < 1");
         return MOE_EINVAL;
     }
-    const Schedule sc = schedule_experts(N, E, w, W, has, max_pack);
-    write_schedule(sc, N, E, replicas, dev_count, dev_experts, devices_used);
+    schedule_experts(N, E, w, W, has, max_pack, replicas, dev_count, dev_experts, devices_used);
     return MOE_OK;
 }
 
 int32_t moe_top_lists_identical(int32_t E, int32_t k, const uint64_t *S, const int32_t *counts)
 {
     if (E < 1 || E > kMaxExperts || k < 1 || S == nullptr || counts == nullptr) return 0;
-    const int m = std::min(2 * k, E);
-    return top_list(E, m, S) == top_list(E, m, counts) ? 1 : 0;
+    const int m = k > E / 2 ? E : 2 * k;
+    int by_estimate[kMaxExperts], by_count[kMaxExperts];
+    top_list(E, m, S, by_estimate);
+    top_list(E, m, counts, by_count);
+    return std::equal(by_estimate, by_estimate + m, by_count) ? 1 : 0;
 }
 
 moe_status moe_schedule_layer(int32_t N, int32_t E, int32_t k, int32_t N_t, const uint64_t *S,
@@ -544,15 +524,15 @@ moe_status moe_schedule_layer(int32_t N, int32_t E, int32_t k, int32_t N_t, cons
             w[e] = static_cast<uint64_t>(N) * S[e];
             has[e] = S[e] > 0;
         }
-        write_schedule(schedule_experts(N, E, w, static_cast<uint64_t>(N_t) << kFix, has, max_pack),
-                       N, E, replicas, dev_count, dev_experts, devices_used);
+        schedule_experts(N, E, w, static_cast<uint64_t>(N_t) << kFix, has, max_pack, replicas, dev_count,
+                         dev_experts, devices_used);
     } else {
         for (int e = 0; e < E; ++e) {
             w[e] = static_cast<uint64_t>(N) * static_cast<uint64_t>(counts[e] < 0 ? 0 : counts[e]);
             has[e] = counts[e] > 0;
         }
-        write_schedule(schedule_experts(N, E, w, static_cast<uint64_t>(N_t) * k, has, max_pack),
-                       N, E, replicas, dev_count, dev_experts, devices_used);
+        schedule_experts(N, E, w, static_cast<uint64_t>(N_t) * k, has, max_pack, replicas, dev_count,
+                         dev_experts, devices_used);
         *rescheduled = 1;
     }
     return MOE_OK;

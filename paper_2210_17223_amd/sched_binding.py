@@ -90,8 +90,37 @@ def _host(a, dtype) -> np.ndarray:
     return np.ascontiguousarray(np.asarray(a, dtype=dtype))
 
 
-def _hp(a: np.ndarray) -> C.c_void_p:
-    return C.c_void_p(a.ctypes.data)
+def _addr(a: np.ndarray) -> int:
+    try:
+        return C.addressof(C.c_byte.from_buffer(a))
+    except (TypeError, ValueError):                 # read-only or empty
+        return a.ctypes.data
+
+
+_rooms = {}
+
+
+class _Schedule:
+    """Room for one schedule in one buffer: replicas[E], dev_count[N], dev_experts[N * E],
+    devices_used, rescheduled.  (For 16 experts on 16 devices separate arrays and an object for the
+    address of each took three quarters of the call.)"""
+
+    def __init__(self, N: int, E: int):
+        n = max(N, 1)
+        self.shape, self.ends = (N, E), (E, E + n, E + n + n * E)
+        room = _rooms.get((n, E))
+        if room is None:
+            if len(_rooms) >= 64:
+                _rooms.clear()
+            room = _rooms[(n, E)] = C.c_int32 * (self.ends[2] + 2)
+        self.buf = room()
+        at = C.addressof(self.buf)
+        self.out = (at, at + 4 * self.ends[0], at + 4 * self.ends[1], at + 4 * self.ends[2])
+        self.rescheduled = self.out[3] + 4
+
+    def arrays(self):
+        a, (i, j, k) = np.frombuffer(self.buf, np.int32), self.ends
+        return a[:i], a[i:j], a[j:k].reshape(self.shape), self.buf[k]
 
 
 def moe_schedule_experts(N: int, E: int, w: Sequence[int], W: int, has: Sequence[bool],
@@ -100,18 +129,16 @@ def moe_schedule_experts(N: int, E: int, w: Sequence[int], W: int, has: Sequence
     wa, ha = _host(w, np.uint64), _host(has, np.uint8)
     if wa.size != E or ha.size != E:
         raise MoeError("w and has need E entries")
-    rep, cnt = np.empty(E, np.int32), np.empty(max(N, 1), np.int32)
-    dev, used = np.empty(max(N, 1) * E, np.int32), np.zeros(1, np.int32)
-    _check(_lib().moe_schedule_experts(N, E, _hp(wa), int(W), _hp(ha), max_pack, _hp(rep), _hp(cnt),
-                                       _hp(dev), _hp(used)))
-    return rep, cnt, dev.reshape(N, E), int(used[0])
+    out = _Schedule(N, E)
+    _check(_lib().moe_schedule_experts(N, E, _addr(wa), int(W), _addr(ha), max_pack, *out.out))
+    return out.arrays()
 
 
 def moe_top_lists_identical(E: int, k: int, S: Sequence[int], counts: Sequence[int]) -> bool:
     Sa, ca = _host(S, np.uint64), _host(counts, np.int32)
     if Sa.size != E or ca.size != E:
         raise MoeError("S and counts need E entries")
-    return bool(_lib().moe_top_lists_identical(E, k, _hp(Sa), _hp(ca)))
+    return bool(_lib().moe_top_lists_identical(E, k, _addr(Sa), _addr(ca)))
 
 
 def moe_schedule_layer(N: int, E: int, k: int, N_t: int, S: Sequence[int], counts: Sequence[int],
@@ -120,8 +147,7 @@ def moe_schedule_layer(N: int, E: int, k: int, N_t: int, S: Sequence[int], count
     Sa, ca = _host(S, np.uint64), _host(counts, np.int32)
     if Sa.size != E or ca.size != E:
         raise MoeError("S and counts need E entries")
-    rep, cnt = np.empty(E, np.int32), np.empty(max(N, 1), np.int32)
-    dev, used, re_ = np.empty(max(N, 1) * E, np.int32), np.zeros(1, np.int32), np.zeros(1, np.int32)
-    _check(_lib().moe_schedule_layer(N, E, k, N_t, _hp(Sa), _hp(ca), max_pack, _hp(rep), _hp(cnt),
-                                     _hp(dev), _hp(used), _hp(re_)))
-    return rep, cnt, dev.reshape(N, E), int(used[0]), bool(re_[0])
+    out = _Schedule(N, E)
+    _check(_lib().moe_schedule_layer(N, E, k, N_t, _addr(Sa), _addr(ca), max_pack, *out.out,
+                                     out.rescheduled))
+    return (*out.arrays(), bool(out.buf[out.ends[2] + 1]))

@@ -492,3 +492,40 @@ def test_streaming_tile_over_its_range(T, d, h, E, k, hot):
     """Few rows per expert: items of up to 32 rows, several per expert, at the ends of the rule's range
     (bounds: TOL of the type)."""
     test_expert_gemm_tiles("bf16", T, d, h, E, k, hot)
+
+
+@pytest.mark.parametrize("T,d,k,dtype", [
+    (5, 8, 1, "bf16"),               # one vector a row; one step per wavefront
+    (100, 520, 2, "bf16"),           # 65 vectors: a second step of one lane
+    (9, 4104, 3, "bf16"),            # k by the loop; nine steps
+    (3000, 1032, 2, "bf16"),         # two steps per wavefront, a third step of one lane
+    (2100, 1032, 8, "f32"),          # ... by the loop
+    (16500, 2056, 2, "bf16"),        # four steps per wavefront, a fifth of one lane
+    (16500, 1028, 1, "f32"),
+])
+@pytest.mark.parametrize("act", [False, True])
+def test_combine_steps(T, d, k, dtype, act):
+    """The weighted sum at the edges of a wavefront's steps, dropped assignments among them.  Against
+    float64 sums of the same rows: k + 1 roundings of 2^-24 relative to sum |g ye|, and one of the
+    16-bit copy (2^-9)."""
+    E = max(k, 2)
+    s = moe.Shape.make(T, d, E, 8, k, T, dtype=dtype)
+    rows = moe.moe_max_rows(s)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    ye = torch.empty((rows, d), dtype=torch.float32, device=DEV).normal_(generator=g).to(s.ye_dtype)
+    slot = torch.randint(0, rows, (T, k), generator=g, device=DEV, dtype=torch.int32)
+    slot[torch.rand((T, k), generator=g, device=DEV) < 0.3] = -1
+    gate = torch.rand((T, k), generator=g, device=DEV)
+    y = torch.full((T, d), 7.0, device=DEV)
+    y_act = torch.full((T, d), 7.0, device=DEV, dtype=s.torch_dtype) if act else None
+    moe.moe_combine(s, ye.reshape(-1), slot.reshape(-1), gate.reshape(-1), y.reshape(-1),
+                    None if y_act is None else y_act.reshape(-1))
+    want, size = torch.zeros((T, d), dtype=torch.float64, device=DEV), torch.zeros((T, d), device=DEV)
+    for j in range(k):
+        part = ye[slot[:, j].clamp_min(0).long()].double() * (gate[:, j] * (slot[:, j] >= 0)).double()[:, None]
+        want += part
+        size += part.abs().float()
+    assert ((y.double() - want).abs() <= (k + 1) * 2.0 ** -24 * size).all()
+    if act:
+        assert torch.equal(y_act, y.to(s.torch_dtype))

@@ -69,6 +69,8 @@ size_t moe_backward_workspace_bytes(const moe_shape *s);
  *   dy               [T,d] fp32
  *   dx [T,d], dWg [d,E], dW1 [E,d,h], dW2 [E,h,d], dgate [T*k]: fp32, overwritten (weight
  *                    gradients of an expert without rows are zero)
+ * Layers of medium size run the weight gradients beside the other GEMMs on a side stream of the
+ * library that `stream` forks and joins (not under stream capture).
  */
 moe_status moe_layer_backward(const moe_shape *s, const void *x, const void *Wgp,
                               const float *gate_bias, int32_t bias_token_stride,
@@ -89,7 +91,7 @@ moe_status moe_layer_backward(const moe_shape *s, const void *x, const void *Wgp
  * there, and the rows that come back are folded into dx chunk by chunk on a second side
  * stream while the caller's stream goes on with the next group and the weight gradients.
  * Every gradient is the same bits for every n_chunks.  With one group the call runs as
- * n_chunks = 1.  Side streams and events are created on the first chunked call on a device. */
+ * n_chunks = 1.  Side streams and events are created on the first call on a device that uses them. */
 moe_status moe_layer_backward_chunked(const moe_shape *s, int32_t n_chunks, const void *x,
                                       const void *Wgp, const float *gate_bias,
                                       int32_t bias_token_stride, const void *W1, const void *W2,

@@ -62,6 +62,8 @@ void prof_release()
 }
 }  // namespace
 
+bool prof_enabled() { return g_prof.mask != 0; }
+
 void prof_begin(int stage, hipStream_t st)
 {
     if (!((g_prof.mask >> stage) & 1u) || g_prof.n[stage] >= g_prof.cap) return;

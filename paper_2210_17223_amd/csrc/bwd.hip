@@ -1180,6 +1180,29 @@ moe_status bwd_resources(BwdResources **out)
     return MOE_OK;
 }
 
+// Whether an unchunked backward pass runs its weight gradients beside the other GEMMs, which depend on
+// them in nothing: each of the four leaves its last round of tiles partly filled, and the gate's
+// gradients leave the matrix cores idle.  By `work`, rows x d_model x d_ff: below 2e9 the events between
+// the streams cost more than that; in large layers a last round is one of many, and GEMMs that run at
+// once share the caches and the power.  us of a training step, one after the other / beside each other, rows
+// spread evenly (by Zipf(1.2)): 128 tokens, 8 experts, 256 x 512 72 / 102 (80 / 122); 512, 8, 512 x 1536 120 /
+// 119 (124 / 131); 600, 13, 1000 x 2600 318 / 310 (313 / 305); 1024, 16, 768 x 3072 314 / 300 (301 / 288); 4096 of
+// these 489 / 455 (427 / 367); 8192, k = 3 1086 / 989 (852 / 768); 4096, 16, 2048 x 8192 2448 / 2307 (2019 / 1847);
+// 16384, 16, 1024 x 4096 2146 / 2081 (1544 / 1485); 16384, 32, 2048 x 8192 7406 / 7454 (4972 / 4647); 32768, 64,
+// 2048 x 8192 13730 / 13930.
+// Not while the stages are timed, and not under capture: a side stream would stay part of the
+// capture after the call returns, and other threads' calls use it too.
+bool overlaps_weight_grads(double work, hipStream_t st)
+{
+    if (work < 2e9 || work > 7e11 || prof_enabled()) return false;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusNone;
+}
+
 // The backward pass, cut like the forward: tokens in n_chunks contiguous parts, the row-grouped
 // GEMMs once per group of consecutive chunks (ffn_groups).  Gradient rows are dispatched to the
 // expert-major order chunk by chunk on one side stream (the backward pass's first all-to-all
@@ -1218,9 +1241,8 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
                                slot_of, gate, w.dye, dgate, t0, t1, d, k, R);
     };
     // the row-grouped GEMMs of FFN group f
-    auto group_gemms = [&](int f) {
+    auto hidden_grads = [&](int f) {
         const WorkItem *it0 = w.lists.items[0] + static_cast<size_t>(f) * g0.max_items;
-        const WorkItem *it1 = w.lists.items[1] + static_cast<size_t>(f) * g1.max_items;
         // P = xe W1 (fp16), Hb = act(P) (bf16) -- unless the forward kept P and its hidden activations
         if (pre == nullptr)
             launch_gemm<1, ACT>(xe, W1p, w.Hb, w.P, it0, h, d, g0,
@@ -1228,18 +1250,23 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
         // dP = (dye W2^T) * act'(P): W2 [E][h][d] is already "rows n = h, contraction d contiguous"
         launch_gemm<2, ACT>(w.dye, W2, w.dP, P, it0, h, d, g0,
                             kStageBwdDP, st);
+    };
+    auto input_grads = [&](int f) {
+        const WorkItem *it1 = w.lists.items[1] + static_cast<size_t>(f) * g1.max_items;
         // dxe = dP W1^T: W1 [E][d][h] is "rows n = d, contraction h contiguous"
         launch_gemm<0, ACT>(w.dP, W1, w.dxe, nullptr, it1, d, h, g1, kStageBwdDxe,
                             st);
     };
     // dW2[e] [h][d] = act(P)^T dye ; dW1[e] [d][h] = xe^T dP, operands as they are
-    auto weight_grads = [&]() {
+    auto weight_grad2 = [&](hipStream_t q) {
         if (pre != nullptr)      // the forward's own hidden activations, fp16
             launch_wgrad<true>(reinterpret_cast<const uint16_t *>(hid), w.dye, dW2, offsets, E, h, d, R,
-                               kStageBwdWgrad2, st);
+                               kStageBwdWgrad2, q);
         else
-            launch_wgrad<false>(w.Hb, w.dye, dW2, offsets, E, h, d, R, kStageBwdWgrad2, st);
-        launch_wgrad<false>(xe, w.dP, dW1, offsets, E, d, h, R, kStageBwdWgrad1, st);
+            launch_wgrad<false>(w.Hb, w.dye, dW2, offsets, E, h, d, R, kStageBwdWgrad2, q);
+    };
+    auto weight_grad1 = [&](hipStream_t q) {
+        launch_wgrad<false>(xe, w.dP, dW1, offsets, E, d, h, R, kStageBwdWgrad1, q);
     };
     // gate: dz and dx for the tokens [t0, t1)
     moe_status combine_rc = MOE_OK;
@@ -1267,17 +1294,48 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
                            dWg, d * E, w.splits);
     };
 
+    BwdResources *r = nullptr;
     if (n_chunks == 1) {
-        grad_dispatch(0, T, st);
-        group_gemms(0);
-        weight_grads();
-        grad_combine(0, T, st);
-        gate_weight_grad();
+        if (!overlaps_weight_grads(static_cast<double>(R) * d * h, st) || bwd_resources(&r) != MOE_OK) {
+            grad_dispatch(0, T, st);
+            hidden_grads(0);
+            input_grads(0);
+            weight_grad2(st);
+            weight_grad1(st);
+            grad_combine(0, T, st);
+            gate_weight_grad();
+            MOE_TRY_HIP(hipGetLastError());
+            return combine_rc;
+        }
+        // The two weight gradients on a side stream: dW2 beside dP from dye on, dW1 beside dxe and the
+        // gate's gradients from dP on.
+        std::lock_guard<std::mutex> enqueue(r->enqueue);
+        auto enqueue_both = [&]() -> moe_status {
+            grad_dispatch(0, T, st);
+            MOE_TRY_HIP(hipEventRecord(r->dispatched[0], st));
+            hidden_grads(0);
+            MOE_TRY_HIP(hipEventRecord(r->computed[0], st));
+            // (dW2 reads the hidden activations: where they are recomputed, the first of the hidden_grads
+            // GEMMs writes them)
+            MOE_TRY_HIP(hipStreamWaitEvent(r->grad_in, pre != nullptr ? r->dispatched[0] : r->computed[0], 0));
+            weight_grad2(r->grad_in);
+            input_grads(0);
+            MOE_TRY_HIP(hipStreamWaitEvent(r->grad_in, r->computed[0], 0));
+            weight_grad1(r->grad_in);
+            grad_combine(0, T, st);
+            gate_weight_grad();
+            return MOE_OK;
+        };
+        rc = enqueue_both();
+        // (joined also after a failure part-way)
+        hipError_t je = hipEventRecord(r->joined_in, r->grad_in);
+        if (je == hipSuccess) je = hipStreamWaitEvent(st, r->joined_in, 0);
+        if (rc != MOE_OK) return rc;
+        if (je != hipSuccess) return hip_fail(je, "joining the side stream");
         MOE_TRY_HIP(hipGetLastError());
         return combine_rc;
     }
 
-    BwdResources *r = nullptr;
     rc = bwd_resources(&r);
     if (rc != MOE_OK) return rc;
     std::lock_guard<std::mutex> enqueue(r->enqueue);
@@ -1293,12 +1351,14 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
             const int c0 = static_cast<int>(static_cast<int64_t>(f) * n_chunks / n_groups);
             const int c1 = static_cast<int>(static_cast<int64_t>(f + 1) * n_chunks / n_groups);
             MOE_TRY_HIP(hipStreamWaitEvent(st, r->dispatched[c1 - 1], 0));
-            group_gemms(f);
+            hidden_grads(f);
+            input_grads(f);
             MOE_TRY_HIP(hipEventRecord(r->computed[f], st));
             MOE_TRY_HIP(hipStreamWaitEvent(r->grad_out, r->computed[f], 0));
             for (int c = c0; c < c1; ++c) grad_combine(bound(c), bound(c + 1), r->grad_out);
         }
-        weight_grads();
+        weight_grad2(st);
+        weight_grad1(st);
         return MOE_OK;
     };
     rc = enqueue_chunks();

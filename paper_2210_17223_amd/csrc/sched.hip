@@ -77,9 +77,10 @@ __global__ __launch_bounds__(256) void path_profile_kernel(
 // counters go in one 64-bit add, whose low half does not overflow because row totals stay below
 // 2^32).  2^20 tokens, 12 layers, 16 experts, paths of length 3: 45 us (75 with one wait per choice and
 // 32-bit adds, 5050 with a global atomic per token and table); k = 2 70 (121).  Tables past LDS: bound
-// by their scattered atomics, 2^19 tokens of 32 experts 111 us (115).
+// by their scattered atomics, fewer of them the more tokens share a hash table: 32 experts, 6 layers, 2^20
+// tokens 96 us (128 with 2^13 places and two blocks per unit), k = 2 193 (276; 255 before the waits went).
 constexpr int kProfThreads = 1024;
-constexpr int kSlots = 1 << 13;
+constexpr int kSlotBits = 14, kSlots = 1 << kSlotBits;     // one block per compute unit
 constexpr int kProfMinTokens = 4096;                       // fewer: not worth clearing and flushing LDS
 constexpr int kProfLdsCounters = 73728;                    // 144 KiB of 16-bit counters
 
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(kProfThreads) void path_profile_lds_kernel(
         if constexpr (DIRECT) {
             atomicAdd(&lds[key >> 1], 1u << (16 * (key & 1u)));
         } else {
-            uint32_t at = (key * 2654435761u) >> 19;       // 13 bits
+            uint32_t at = (key * 2654435761u) >> (32 - kSlotBits);
             for (int probe = 0; probe < 2; ++probe, at ^= 1u) {
                 uint32_t have = *static_cast<volatile uint32_t *>(&lds[at]);
                 if (have == kEmpty) have = atomicCAS(&lds[at], kEmpty, key);

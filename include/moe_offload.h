@@ -39,7 +39,7 @@ size_t moe_offload_workspace_bytes(const moe_shape *s);
  *                       they must stay unchanged until the enqueued work has finished
  *   staging             device, moe_offload_staging_bytes(s, resident)
  *   workspace           device, moe_offload_workspace_bytes(s)
- * bf16 layers.  Creates, once per process and device, one copy stream and 2 * 64 events.
+ * bf16 layers.  Creates, once per process and device, two copy streams and 2 * 64 events.
  * Overlapping calls that share a staging area race.
  */
 moe_status moe_expert_ffn_offloaded(const moe_shape *s, const void *xe, const int32_t *offsets,

@@ -5,7 +5,7 @@
 // stream from a work list that holds expert e's tiles only.  Bound by the host link:
 // 2 d h element bytes per expert against a few microseconds of matrix-core work per row.
 // Page-locked weights are read over the link by a kernel, both matrices of an expert in one
-// launch; others go through the runtime's copy.
+// launch, the experts on two streams in turn; others go through the runtime's copy.
 #include "common.h"
 #include "moe_offload.h"
 
@@ -15,12 +15,12 @@ namespace moe {
 namespace {
 
 struct OffloadResources {
-    hipStream_t copy = nullptr;
+    hipStream_t copy[2] = {};               // experts take turns if their weights are page-locked
     hipEvent_t ready[kMaxExperts] = {};     // slot filled
     hipEvent_t freed[kMaxExperts] = {};     // slot's expert computed
     hipEvent_t begin = nullptr;
     bool ok = false;
-    std::mutex enqueue;                     // held while a call enqueues on the copy stream
+    std::mutex enqueue;                     // held while a call enqueues on the copy streams
 };
 OffloadResources g_res[16];
 std::mutex g_res_mutex;
@@ -36,7 +36,7 @@ moe_status resources(OffloadResources **out)
     std::lock_guard<std::mutex> lock(g_res_mutex);
     OffloadResources &r = g_res[dev];
     if (!r.ok) {
-        MOE_TRY_HIP(hipStreamCreateWithFlags(&r.copy, hipStreamNonBlocking));
+        for (hipStream_t &c : r.copy) MOE_TRY_HIP(hipStreamCreateWithFlags(&c, hipStreamNonBlocking));
         MOE_TRY_HIP(hipEventCreateWithFlags(&r.begin, hipEventDisableTiming));
         for (int i = 0; i < kMaxExperts; ++i) {
             MOE_TRY_HIP(hipEventCreateWithFlags(&r.ready[i], hipEventDisableTiming));
@@ -63,7 +63,8 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 // 56.6 / 56.2 / 52.0, the runtime's copy 55.4; behind an event that another stream records after
 // every copy, as here, the runtime's copies of 8 MiB reach 37 to 41: what a copy engine's start and
 // end signals cost beside 0.15 ms of transfer, a kernel's launch does not.  256 tokens, 16 experts
-// of 1024 x 4096, two slots: 6120 -> 5040 us.
+// of 1024 x 4096, two slots: 6120 -> 5040 us.  On two streams in turn the link is not idle between one
+// expert's event and the next one's launch either: 5030 -> 4870 us, 55 GB/s.
 constexpr int kPullBlocks = 16;
 __global__ __launch_bounds__(256) void pull_weights_kernel(
     const u32x4 *__restrict__ h1, const u32x4 *__restrict__ h2, u32x4 *__restrict__ d1,
@@ -169,7 +170,7 @@ moe_status moe_expert_ffn_offloaded(const moe_shape *s, const void *xe, const in
     OffloadResources *r = nullptr;
     const moe_status rs = resources(&r);
     if (rs != MOE_OK) return rs;
-    // one call at a time enqueues on this device's copy stream and shared events
+    // one call at a time enqueues on this device's copy streams and shared events
     std::lock_guard<std::mutex> enqueue(r->enqueue);
     Workspace w;
     layout(*s, workspace, &w);
@@ -178,28 +179,30 @@ moe_status moe_expert_ffn_offloaded(const moe_shape *s, const void *xe, const in
     char *stage = static_cast<char *>(staging);
     const char *h1 = static_cast<const char *>(W1p_host), *h2 = static_cast<const char *>(W2p_host);
     const char *v1 = device_view(h1, eb * s->E), *v2 = device_view(h2, eb * s->E);
+    const bool pull = v1 != nullptr && v2 != nullptr;
 
     moe_status rc = launch_items_per_expert(*s, offsets, w, st);
     if (rc != MOE_OK) return rc;
-    // the copy stream may not touch the staging area before what the caller enqueued earlier
+    // a copy stream may not touch the staging area before what the caller enqueued earlier
     // (possibly a previous call's GEMMs reading it) has finished
     MOE_TRY_HIP(hipEventRecord(r->begin, st));
-    MOE_TRY_HIP(hipStreamWaitEvent(r->copy, r->begin, 0));
     for (int e = 0; e < s->E; ++e) {
         const int slot = e % resident;
         char *d1 = stage + static_cast<size_t>(slot) * 2 * slot_bytes, *d2 = d1 + slot_bytes;
-        if (e >= resident) MOE_TRY_HIP(hipStreamWaitEvent(r->copy, r->freed[slot], 0));
+        hipStream_t copy = r->copy[pull ? e % 2 : 0];
+        if (e < (pull ? 2 : 1)) MOE_TRY_HIP(hipStreamWaitEvent(copy, r->begin, 0));
+        if (e >= resident) MOE_TRY_HIP(hipStreamWaitEvent(copy, r->freed[slot], 0));
         const size_t at = static_cast<size_t>(e) * eb;
-        if (v1 != nullptr && v2 != nullptr) {
-            hipLaunchKernelGGL(pull_weights_kernel, dim3(kPullBlocks), dim3(256), 0, r->copy,
+        if (pull) {
+            hipLaunchKernelGGL(pull_weights_kernel, dim3(kPullBlocks), dim3(256), 0, copy,
                                reinterpret_cast<const u32x4 *>(v1 + at), reinterpret_cast<const u32x4 *>(v2 + at),
                                reinterpret_cast<u32x4 *>(d1), reinterpret_cast<u32x4 *>(d2), eb / 16, offsets, e);
             MOE_TRY_HIP(hipGetLastError());
         } else {
-            MOE_TRY_HIP(hipMemcpyAsync(d1, h1 + at, eb, hipMemcpyHostToDevice, r->copy));
-            MOE_TRY_HIP(hipMemcpyAsync(d2, h2 + at, eb, hipMemcpyHostToDevice, r->copy));
+            MOE_TRY_HIP(hipMemcpyAsync(d1, h1 + at, eb, hipMemcpyHostToDevice, copy));
+            MOE_TRY_HIP(hipMemcpyAsync(d2, h2 + at, eb, hipMemcpyHostToDevice, copy));
         }
-        MOE_TRY_HIP(hipEventRecord(r->ready[slot], r->copy));
+        MOE_TRY_HIP(hipEventRecord(r->ready[slot], copy));
         MOE_TRY_HIP(hipStreamWaitEvent(st, r->ready[slot], 0));
         // The GEMM kernel addresses expert e's weights as base + e * d * h elements: hand it
         // a base that lands on the slot.  Only [slot, slot + eb) is ever dereferenced, since

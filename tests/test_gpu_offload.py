@@ -71,6 +71,34 @@ def test_weights_in_page_locked_and_in_pageable_memory_give_the_same(T, d, h):
         assert torch.equal(ye[:A * d].view(torch.int16), want)
 
 
+def test_page_locked_weights_changed_between_calls():
+    """The host writes new weights over the old ones: the kernel that reads them sees no earlier call's
+    values, also where experts take turns on one slot."""
+    li = wl.make_layer(wl.scaled("gpt2s_moe", T=200, d=128, h=256, E=5), seed=3)
+    s = shape_of(li)
+    L = DeviceLayer(li, s)
+    L.layer(1)
+    b = L.b
+    A = int(b["offsets"].cpu().numpy()[-1])
+    W1, W2 = b["W1p"].cpu(), b["W2p"].cpu()
+    W1h, W2h = W1.clone().pin_memory(), W2.clone().pin_memory()
+    ws = torch.empty(moe.moe_offload_workspace_bytes(s), dtype=torch.uint8, device=DEV)
+
+    def call(w1, w2, resident):
+        ye = torch.full_like(b["ye"], 5.0)
+        staging = torch.empty(moe.moe_offload_staging_bytes(s, resident), dtype=torch.uint8, device=DEV)
+        moe.moe_expert_ffn_offloaded(s, b["xe"], b["offsets"], w1, w2, None, None, ye, staging, resident, ws)
+        torch.cuda.synchronize()
+        return ye[:A * li.d].view(torch.int16)
+
+    for i, resident in enumerate((2, 1, 3, 2)):
+        p1 = torch.roll(W1.reshape(-1), 8 * i).reshape(W1.shape)
+        p2 = torch.roll(W2.reshape(-1), 16 * i).reshape(W2.shape)
+        W1h.copy_(p1)
+        W2h.copy_(p2)
+        assert torch.equal(call(W1h, W2h, resident), call(p1, p2, resident)), i
+
+
 def test_sizes_and_refusals():
     li = wl.make_layer(wl.scaled("gpt2s_moe", T=64, d=64, h=128, E=4), seed=0)
     s = shape_of(li)

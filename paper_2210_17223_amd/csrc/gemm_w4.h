@@ -23,11 +23,11 @@
 //  * Every memory instruction is issued singly between two matrix instructions in a fixed order;
 //    those are inline assembly so that the accumulators stay in AGPRs and the order holds.
 //    Neighbouring ones share an operand (serpentine order).
-// What bounds it: the matrix cores are busy for 59 % / 77 % of the cycles (N = 8192, K = 2048, GeLU / N =
-// 2048, K = 8192), at a clock of 1.72 / 1.69 GHz that the chip sets by the energy per operation (on all-ones
+// What bounds it: the matrix cores are busy for 62 % / 79 % of the cycles (N = 8192, K = 2048, GeLU / N =
+// 2048, K = 8192), at a clock of 1.69 / 1.65 GHz that the chip sets by the energy per operation (on all-ones
 // operands the same launches are 34 % / 24 % faster).  With 32 x 32 x 16 instructions and operands staged
 // through registers it was 56 % / 78 % at 1.68 / 1.55 GHz: the first GEMM lost cycles, the second takes as many
-// as before and they have become cheaper.  us in a layer of 63622 rows: 2056 / 1605 (2237 / 1746).  On 64 x 1024
+// as before and they have become cheaper.  us in a layer of 63622 rows: 1993 / 1616 (2237 / 1746).  On 64 x 1024
 // rows alone: 2184 / 1682, of which the matrix instructions and barriers by themselves take 1560 / 1199, and
 // the loads into LDS beside them 21 % / 34 % on top; a vendor library's dense products of these sizes 1834
 // / 1668.

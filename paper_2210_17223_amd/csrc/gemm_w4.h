@@ -89,16 +89,32 @@ __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rs, int voff,
                  ::"v"(voff), "s"(rs), "s"(at), "s"(soff) : "memory", "m0");
 #endif
 }
-// A load whose completion is counted by hand too: `v` holds the dword behind loaded<N>, N loads that
-// were issued after it still being on their way.
-__device__ __forceinline__ void load_dword(int &v, const int32_t *p)
-{
-    asm volatile("global_load_dword %0, %1, off" : "=&v"(v) : "v"(p) : "memory");
-}
+// The dword at p, and behind its load N of load_to_lds's, at `at`, `at` + 1024, ..., that are still on
+// their way afterwards.  One asm block: `v` is not a register with a load in flight where the compiler may
+// move or copy it.
 template <int N>
-__device__ __forceinline__ void loaded(int &v)
+__device__ __forceinline__ void load_dword_before(int &v, const int32_t *p, __amdgpu_buffer_rsrc_t rs,
+                                                  const int (&voff)[N], uint32_t at)
 {
-    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(v) : "n"(N) : "memory");
+    static_assert(N == 4 || N == 8, "written out for these");
+#if defined(__HIP_DEVICE_COMPILE__)
+#define MOE_NEXT(o) "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %" #o ", %2, 0 offen lds\n\t"
+#define MOE_FIRST "global_load_dword %0, %1, off\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %4, %2, 0 offen lds\n\t"
+    if constexpr (N == 4)
+        asm volatile(MOE_FIRST MOE_NEXT(5) MOE_NEXT(6) MOE_NEXT(7) "s_waitcnt vmcnt(4)"
+                     : "=&v"(v)
+                     : "v"(p), "s"(rs), "s"(at), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3])
+                     : "memory", "m0", "scc");
+    else
+        asm volatile(MOE_FIRST MOE_NEXT(5) MOE_NEXT(6) MOE_NEXT(7) MOE_NEXT(8) MOE_NEXT(9) MOE_NEXT(10)
+                         MOE_NEXT(11) "s_waitcnt vmcnt(8)"
+                     : "=&v"(v)
+                     : "v"(p), "s"(rs), "s"(at), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]),
+                       "v"(voff[4]), "v"(voff[5]), "v"(voff[6]), "v"(voff[7])
+                     : "memory", "m0", "scc");
+#undef MOE_FIRST
+#undef MOE_NEXT
+#endif
 }
 __device__ __forceinline__ uint32_t lds_address(const void *p)
 {

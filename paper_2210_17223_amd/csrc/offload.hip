@@ -89,22 +89,25 @@ __global__ __launch_bounds__(256) void pull_weights_kernel(
 }
 
 // The device's address of `bytes` of page-locked host memory at p, or NULL if the device cannot read
-// all of them in place (pageable memory, or not one allocation).
+// all of them in place (pageable memory, or not inside one allocation: the host's and the device's
+// addresses are often the same, so two ends that both map say nothing about the bytes between them).
 const char *device_view(const void *p, size_t bytes)
 {
-    const char *ends[2] = {static_cast<const char *>(p), static_cast<const char *>(p) + bytes - 1};
-    const char *view[2];
-    for (int i = 0; i < 2; ++i) {
-        hipPointerAttribute_t a{};
-        if (hipPointerGetAttributes(&a, ends[i]) != hipSuccess) {
-            (void)hipGetLastError();             // an unknown address is no error here
-            return nullptr;
-        }
-        if (a.type != hipMemoryTypeHost || a.devicePointer == nullptr) return nullptr;
-        view[i] = static_cast<const char *>(a.devicePointer);
+    hipPointerAttribute_t a{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();                 // an unknown address is no error here
+        return nullptr;
     }
-    return view[1] - view[0] == ends[1] - ends[0] && (reinterpret_cast<uintptr_t>(view[0]) & 15u) == 0
-               ? view[0] : nullptr;
+    if (a.type != hipMemoryTypeHost || a.devicePointer == nullptr) return nullptr;
+    if (hipMemGetAddressRange(&base, &size, a.devicePointer) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    const char *view = static_cast<const char *>(a.devicePointer);
+    const size_t at = reinterpret_cast<uintptr_t>(view) - reinterpret_cast<uintptr_t>(base);
+    return at <= size && bytes <= size - at && (reinterpret_cast<uintptr_t>(view) & 15u) == 0 ? view : nullptr;
 }
 
 size_t expert_bytes(const moe_shape &s) { return static_cast<size_t>(s.d_model) * s.d_ff * 2; }

@@ -1080,7 +1080,7 @@ void launch_gemm(const uint16_t *A, const uint16_t *W, void *C, _Float16 *P, con
             constexpr size_t lds = w4_lds(BM, BN);
             static PerDeviceOnce once;
             once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
-                    hipEvent_t t0, t1;
+            hipEvent_t t0, t1;
             prof_kernel_events(stage, &t0, &t1);
             hipExtLaunchKernelGGL(kern, dim3(grid_items), dim3(256), lds, st, t0, t1, 0, A, W, C, P, items,
                                   N, K);

@@ -276,12 +276,18 @@ int ffn_groups(const moe_shape &s, int n_chunks)
     return static_cast<int>(g < n_chunks ? g : n_chunks);
 }
 
-bool layout_workspace(const moe_shape &s, int n_chunks, void *base, Workspace *w)
+// The most tokens in one of n_groups runs of consecutive chunks: group f is the chunks [f n_chunks / n_groups,
+// (f + 1) n_chunks / n_groups), so where n_groups does not divide n_chunks some hold a chunk more than others.
+static int64_t largest_group_tokens(const moe_shape &s, int n_chunks, int n_groups)
 {
-    if (n_chunks < 1 || n_chunks > kMaxChunks) return false;
-    const int64_t n = static_cast<int64_t>(s.T) * s.k;
-    const int64_t max_rows = moe_max_rows(&s);
-    (void)n;
+    const int64_t chunks = (n_chunks + n_groups - 1) / n_groups;
+    return (chunks * s.T + n_chunks - 1) / n_chunks;
+}
+
+bool layout_workspace(const moe_shape &s, int n_chunks, int n_groups, void *base, Workspace *w)
+{
+    if (n_chunks < 1 || n_chunks > kMaxChunks || n_groups < 1 || n_groups > n_chunks) return false;
+    const int64_t max_rows = moe_max_rows(&s), tokens = largest_group_tokens(s, n_chunks, n_groups);
     w->seg_tok = route_segment_tokens(s);
     w->nseg = (s.T + w->seg_tok - 1) / w->seg_tok;
     char *p = static_cast<char *>(base);
@@ -289,9 +295,9 @@ bool layout_workspace(const moe_shape &s, int n_chunks, void *base, Workspace *w
     w->seg_cnt = reinterpret_cast<int32_t *>(p + off);
     off += align_up(static_cast<size_t>(w->nseg) * kMaxExperts * sizeof(int32_t), 256);
     for (int g = 0; g < 2; ++g) {
-        w->gp[g] = choose_gemm_plan(s, g, n_chunks);
+        w->gp[g] = choose_gemm_plan(s, g, tokens);
         w->items[g] = reinterpret_cast<WorkItem *>(p + off);
-        off += align_up(static_cast<size_t>(n_chunks) * w->gp[g].max_items * sizeof(WorkItem), 256);
+        off += align_up(static_cast<size_t>(n_groups) * w->gp[g].max_items * sizeof(WorkItem), 256);
     }
     w->hidden = p + off;
     const size_t hidden_elem = s.dtype == MOE_BF16 ? 2 : 4;
@@ -333,13 +339,14 @@ size_t moe_workspace_bytes(const moe_shape *s, int32_t n_chunks)
         return 0;
     }
     // the same buffer serves every call with up to n_chunks chunks (a chunked layer lays its
-    // work lists out for its number of FFN groups, which is at most n_chunks)
+    // work lists out for its number of FFN groups, which is at most n_chunks and can be tuned)
     size_t bytes = 0;
-    for (int c = 1; c <= n_chunks; ++c) {
-        Workspace w;
-        layout_workspace(*s, c, nullptr, &w);
-        if (w.bytes > bytes) bytes = w.bytes;
-    }
+    for (int c = 1; c <= n_chunks; ++c)
+        for (int g = 1; g <= c; ++g) {
+            Workspace w;
+            layout_workspace(*s, c, g, nullptr, &w);
+            if (w.bytes > bytes) bytes = w.bytes;
+        }
     return bytes;
 }
 
@@ -445,7 +452,7 @@ moe_status moe_dispatch(const moe_shape *s, const void *x, const int32_t *expert
     MOE_REQUIRE_PTR(xe);
     MOE_REQUIRE_PTR(workspace);
     Workspace w;
-    layout_workspace(*s, 1, workspace, &w);
+    layout_workspace(*s, 1, 1, workspace, &w);
     hipStream_t st = static_cast<hipStream_t>(stream);
     bool packed = false;
     MOE_TIMED(kStagePlan, st, launch_plan(*s, expert_idx, counts, offsets, slot_of, src_of, w,
@@ -511,7 +518,7 @@ moe_status moe_expert_ffn(const moe_shape *s, const void *xe, const int32_t *off
     MOE_REQUIRE_PTR(ye);
     MOE_REQUIRE_PTR(workspace);
     Workspace w;
-    layout_workspace(*s, 1, workspace, &w);
+    layout_workspace(*s, 1, 1, workspace, &w);
     hipStream_t st = static_cast<hipStream_t>(stream);
     MOE_TIMED(kStageTiles, st, launch_items(*s, 1, 1, offsets, nullptr, w, st));
     return launch_ffn(*s, xe, W1p, b1, W2p, b2, ye, w, 0, st);
@@ -574,7 +581,7 @@ moe_status layer_forward(const moe_shape *s, int32_t n_chunks, const void *x,
     if (n_groups == 1) n_chunks = 1;
 
     Workspace w;
-    layout_workspace(*s, n_groups, workspace, &w);
+    layout_workspace(*s, n_chunks, n_groups, workspace, &w);
     if (hid != nullptr) w.hidden = hid;       // the hidden activations go where the caller keeps them
     hipStream_t st = static_cast<hipStream_t>(stream);
 

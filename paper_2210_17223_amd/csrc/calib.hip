@@ -134,7 +134,7 @@ moe_status moe_expert_gemm_kernel(const moe_shape *s, int32_t which, char *name,
         set_error("moe_expert_gemm_kernel: which must be 0 or 1, name a buffer, the shape a supported bf16 layer");
         return MOE_EINVAL;
     }
-    expert_gemm_kernel_name(*s, which, 1, name, len);
+    expert_gemm_kernel_name(*s, which, name, len);
     return MOE_OK;
 }
 

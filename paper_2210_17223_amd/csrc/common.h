@@ -65,7 +65,7 @@ struct GemmPlan {
     bool w4 = false;         // the four-wavefront kernels (gemm_w4.h)
     int32_t item_rows = 0;   // most rows of a work item: bm, or a part of it
     int32_t tiles_n;         // column tiles
-    int32_t max_row_tiles;   // upper bound of row tiles per chunk
+    int32_t max_row_tiles;   // upper bound of row tiles per list
     int32_t max_items;       // entries of a work list (a multiple of 8; surplus ones hold no tile)
     int32_t concurrent;      // work items in flight per XCD (sets the panel width)
 };
@@ -114,20 +114,22 @@ inline void choose_w4_tile(int64_t rows, int E, int N, int K, GemmPlan *gp)
     }
     gp->w4 = true;
 }
-GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_chunks);
-void expert_gemm_kernel_name(const moe_shape &s, int which, int n_chunks, char *name, size_t len);
+// (`tokens`: the most tokens that one FFN launch covers)
+GemmPlan choose_gemm_plan(const moe_shape &s, int which, int64_t tokens);
+void expert_gemm_kernel_name(const moe_shape &s, int which, char *name, size_t len);
 
 // Where each piece of the caller's workspace lives.
 struct Workspace {
     int32_t *seg_cnt;      // [nseg][kMaxExperts] per-segment expert counts -> bases
-    WorkItem *items[2];    // per GEMM: [n_chunks][gp.max_items]
+    WorkItem *items[2];    // per GEMM: [n_groups][gp.max_items]
     void *hidden;          // [max_rows][d_ff] hidden activations
     GemmPlan gp[2];
     int32_t nseg;
     int32_t seg_tok;       // tokens per segment (route_segment_tokens)
     size_t bytes;
 };
-bool layout_workspace(const moe_shape &s, int n_chunks, void *base, Workspace *w);
+// For n_groups FFN launches (work lists) over n_chunks chunks.
+bool layout_workspace(const moe_shape &s, int n_chunks, int n_groups, void *base, Workspace *w);
 
 // Optional per-stage timing (moe_profile_enable): when a stage is enabled, its
 // launches are bracketed by a pair of timing events on the stream they run on.

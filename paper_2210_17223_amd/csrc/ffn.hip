@@ -789,9 +789,9 @@ void launch_mfma_pair(const moe_shape &s, const uint16_t *xe, const uint16_t *W1
 
 // Which kernel the layer launches for expert GEMM `which` (0: first, 1: second) of a bf16 layer,
 // for labelling measurements: "<kernel> <tile rows>x<tile columns>".
-void expert_gemm_kernel_name(const moe_shape &s, int which, int n_chunks, char *name, size_t len)
+void expert_gemm_kernel_name(const moe_shape &s, int which, char *name, size_t len)
 {
-    const GemmPlan gp = choose_gemm_plan(s, which, n_chunks);
+    const GemmPlan gp = choose_gemm_plan(s, which, s.T);
     std::snprintf(name, len, "%s %dx%d",
                   gp.w4 ? gp.bm == 256 ? "grouped_gemm_w4_kernel" : "grouped_gemm_mfma_kernel"
                         : gp.bn == 64 ? "grouped_gemm_stream_kernel" : "grouped_gemm_staged_kernel",
@@ -837,14 +837,13 @@ moe_status launch_calib_gemm(const uint16_t *A, const uint16_t *W, _Float16 *C, 
 // Tile shape of expert GEMM `which` (0: xe.W1, 1: H.W2) for this layer shape.  Large
 // tiles cut the operand traffic per flop; they need enough output tiles to fill 256
 // compute units, and a long contraction to amortise their prologue and epilogue.
-GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_chunks)
+GemmPlan choose_gemm_plan(const moe_shape &s, int which, int64_t tokens)
 {
     GemmPlan gp;
     const int N = which == 0 ? s.d_ff : s.d_model;
     const int K = which == 0 ? s.d_model : s.d_ff;
     const int64_t max_rows = moe_max_rows(&s);
-    const int64_t chunk_tokens = (s.T + n_chunks - 1) / n_chunks;
-    const int64_t chunk_rows = chunk_tokens * s.k < max_rows ? chunk_tokens * s.k : max_rows;
+    const int64_t chunk_rows = tokens * s.k < max_rows ? tokens * s.k : max_rows;
     if (s.dtype != MOE_BF16) {
         // 64 x 64 tiles where they are a few per compute unit, else 32 x 32 (us of the layer, 32 / 64:
         // 603 tokens, 420 x 1620 71 / 88; 951, k = 2, 780 x 2084 183 / 189; 3564, 764 x 1836 308 / 250)

@@ -178,6 +178,33 @@ def test_whole_layer_and_chunk_invariance(name, group_rows):
         moe.moe_tune_ffn_group_rows(before)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_chunks", [4, 8])
+def test_groups_of_unequal_size(n_chunks, dtype):
+    """Three FFN groups of 4 or 8 chunks: the last holds a half or three eighths of the tokens, with two
+    experts more row tiles than a third of them makes.  The unchunked call's bits, with ye and the hidden
+    activations full of NaN before every call."""
+    T, d, E, h, k = 40000, 64, 2, 128, 1
+    li = wl.make_layer(wl.scaled("tiny_fp32" if dtype == "f32" else "gpt2s_moe", T=T, d=d, h=h, E=E, k=k, cf=None),
+                       seed=6)
+    L = DeviceLayer(li, shape_of(li), n_chunks=n_chunks)
+
+    def bits(n):
+        for key in ("workspace", "ye"):
+            L.b[key].view(torch.uint8).fill_(0xFF)
+        L.layer(n)
+        A = int(L.b["offsets"][-1])
+        return [L.b["y"].view(torch.int32).clone(), L.b["ye"][:A * d].view(torch.uint8).clone()]
+
+    want = bits(1)
+    before = moe.moe_tune_ffn_group_rows(T * k // E // 3)
+    try:
+        got = bits(n_chunks)
+    finally:
+        moe.moe_tune_ffn_group_rows(before)
+    assert all(torch.equal(g, w) for g, w in zip(got, want))
+
+
 @pytest.mark.parametrize("T,d,E,k", [(600, 128, 16, 2), (9000, 64, 32, 2), (700, 72, 5, 3)],
                          ids=["chain_kernel", "register_blocks", "odd_shape"])
 def test_gate_ties_go_to_the_lowest_index(T, d, E, k):

@@ -1,5 +1,6 @@
 // C-ABI entry points of libmoe: argument checks, workspace layout, and the order in
 // which the kernels are enqueued.  No arithmetic of the layer happens here.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -295,7 +296,7 @@ bool layout_workspace(const moe_shape &s, int n_chunks, int n_groups, void *base
     w->seg_cnt = reinterpret_cast<int32_t *>(p + off);
     off += align_up(static_cast<size_t>(w->nseg) * kMaxExperts * sizeof(int32_t), 256);
     for (int g = 0; g < 2; ++g) {
-        w->gp[g] = choose_gemm_plan(s, g, tokens);
+        w->gp[g] = choose_gemm_plan(s, g, n_groups, tokens);
         w->items[g] = reinterpret_cast<WorkItem *>(p + off);
         off += align_up(static_cast<size_t>(n_groups) * w->gp[g].max_items * sizeof(WorkItem), 256);
     }
@@ -341,12 +342,11 @@ size_t moe_workspace_bytes(const moe_shape *s, int32_t n_chunks)
     // the same buffer serves every call with up to n_chunks chunks (a chunked layer lays its
     // work lists out for its number of FFN groups, which is at most n_chunks and can be tuned)
     size_t bytes = 0;
-    for (int c = 1; c <= n_chunks; ++c)
-        for (int g = 1; g <= c; ++g) {
-            Workspace w;
-            layout_workspace(*s, c, g, nullptr, &w);
-            if (w.bytes > bytes) bytes = w.bytes;
-        }
+    for (int g = 1; g <= n_chunks; ++g) {
+        Workspace w;       // g groups are the most unequal where they share g + 1 chunks
+        layout_workspace(*s, std::min(g + 1, n_chunks), g, nullptr, &w);
+        if (w.bytes > bytes) bytes = w.bytes;
+    }
     return bytes;
 }
 

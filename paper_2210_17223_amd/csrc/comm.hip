@@ -377,7 +377,7 @@ void layout_padded(const moe_shape &s, int n_micro, void *base, PaddedWorkspace 
     pw->offsets = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (s.E + 1)));
     const int per_micro = (s.capacity + n_micro - 1) / n_micro;   // slot positions, at most
     for (int g = 0; g < 2; ++g) {
-        GemmPlan gp = choose_gemm_plan(s, g, (s.T + n_micro - 1) / n_micro);
+        GemmPlan gp = choose_gemm_plan(s, g, n_micro, s.T);
         gp.max_row_tiles = s.E * ((per_micro + gp.item_rows - 1) / gp.item_rows);
         gp.max_items = work_list_entries(gp);
         w.gp[g] = gp;

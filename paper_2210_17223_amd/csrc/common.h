@@ -114,8 +114,9 @@ inline void choose_w4_tile(int64_t rows, int E, int N, int K, GemmPlan *gp)
     }
     gp->w4 = true;
 }
-// (`tokens`: the most tokens that one FFN launch covers)
-GemmPlan choose_gemm_plan(const moe_shape &s, int which, int64_t tokens);
+// The tile is chosen for the tokens that one of n_launches FFN launches has on average, the list bounded for
+// `tokens`, the most that one has.
+GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_launches, int64_t tokens);
 void expert_gemm_kernel_name(const moe_shape &s, int which, char *name, size_t len);
 
 // Where each piece of the caller's workspace lives.

@@ -791,7 +791,7 @@ void launch_mfma_pair(const moe_shape &s, const uint16_t *xe, const uint16_t *W1
 // for labelling measurements: "<kernel> <tile rows>x<tile columns>".
 void expert_gemm_kernel_name(const moe_shape &s, int which, char *name, size_t len)
 {
-    const GemmPlan gp = choose_gemm_plan(s, which, s.T);
+    const GemmPlan gp = choose_gemm_plan(s, which, 1, s.T);
     std::snprintf(name, len, "%s %dx%d",
                   gp.w4 ? gp.bm == 256 ? "grouped_gemm_w4_kernel" : "grouped_gemm_mfma_kernel"
                         : gp.bn == 64 ? "grouped_gemm_stream_kernel" : "grouped_gemm_staged_kernel",
@@ -837,13 +837,14 @@ moe_status launch_calib_gemm(const uint16_t *A, const uint16_t *W, _Float16 *C, 
 // Tile shape of expert GEMM `which` (0: xe.W1, 1: H.W2) for this layer shape.  Large
 // tiles cut the operand traffic per flop; they need enough output tiles to fill 256
 // compute units, and a long contraction to amortise their prologue and epilogue.
-GemmPlan choose_gemm_plan(const moe_shape &s, int which, int64_t tokens)
+GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_launches, int64_t tokens)
 {
     GemmPlan gp;
     const int N = which == 0 ? s.d_ff : s.d_model;
     const int K = which == 0 ? s.d_model : s.d_ff;
     const int64_t max_rows = moe_max_rows(&s);
-    const int64_t chunk_rows = tokens * s.k < max_rows ? tokens * s.k : max_rows;
+    auto rows_of = [&](int64_t t) { return t * s.k < max_rows ? t * s.k : max_rows; };
+    const int64_t chunk_rows = rows_of((s.T + n_launches - 1) / n_launches);
     if (s.dtype != MOE_BF16) {
         // 64 x 64 tiles where they are a few per compute unit, else 32 x 32 (us of the layer, 32 / 64:
         // 603 tokens, 420 x 1620 71 / 88; 951, k = 2, 780 x 2084 183 / 189; 3564, 764 x 1836 308 / 250)
@@ -882,7 +883,7 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int64_t tokens)
     }
     gp.tiles_n = (N + gp.bn - 1) / gp.bn;
     if (gp.item_rows == 0) gp.item_rows = gp.bm;
-    gp.max_row_tiles = static_cast<int32_t>((chunk_rows + gp.item_rows - 1) / gp.item_rows + s.E);
+    gp.max_row_tiles = static_cast<int32_t>((rows_of(tokens) + gp.item_rows - 1) / gp.item_rows + s.E);
     gp.max_items = work_list_entries(gp);
     return gp;
 }

@@ -118,7 +118,7 @@ void layout(const moe_shape &s, void *base, Workspace *w)
     size_t off = 0;
     *w = Workspace{};
     for (int g = 0; g < 2; ++g) {
-        w->gp[g] = choose_gemm_plan(s, g, s.T);          // the resident path's tile shapes
+        w->gp[g] = choose_gemm_plan(s, g, 1, s.T);          // the resident path's tile shapes
         w->items[g] = reinterpret_cast<WorkItem *>(p + off);
         off += align_up(static_cast<size_t>(s.E) * w->gp[g].max_items * sizeof(WorkItem), 256);
     }

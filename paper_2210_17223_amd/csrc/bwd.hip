@@ -1180,6 +1180,51 @@ moe_status bwd_resources(BwdResources **out)
     return MOE_OK;
 }
 
+// A side stream and its events for the weight gradients of an unchunked backward pass.  None of the above:
+// a chunked pass that is being captured holds those in its capture until the capture ends, and a call
+// from outside may neither wait for them nor record on them; these are used outside capture only.  One per
+// caller's stream, so that a call does not queue behind another stream's work; a fifth takes over the one
+// used longest ago.
+struct SideStream {
+    hipStream_t caller = nullptr, stream = nullptr;
+    hipEvent_t dispatched = nullptr, hidden = nullptr, joined = nullptr;
+    uint64_t used = 0;                  // 0: not created yet
+};
+struct SideStreams {
+    std::mutex enqueue;                 // held while a call enqueues on one of them
+    uint64_t calls = 0;
+    SideStream of[4];
+};
+SideStreams g_side[16];
+
+// the one of `caller`, created if need be, or NULL; under r.enqueue
+SideStream *side_stream(SideStreams &r, hipStream_t caller)
+{
+    SideStream *s = nullptr;
+    for (SideStream &c : r.of)
+        if (c.used != 0 && c.caller == caller) s = &c;
+    if (s == nullptr) {
+        s = &r.of[0];
+        for (SideStream &c : r.of)
+            if (c.used < s->used) s = &c;
+        if (s->used == 0) {
+            // (what a call that failed half-way has made is taken over)
+            if (s->stream == nullptr && hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess) {
+                (void)hipGetLastError();
+                return nullptr;
+            }
+            for (hipEvent_t *e : {&s->dispatched, &s->hidden, &s->joined})
+                if (*e == nullptr && hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) {
+                    (void)hipGetLastError();
+                    return nullptr;
+                }
+        }
+        s->caller = caller;
+    }
+    s->used = ++r.calls;
+    return s;
+}
+
 // Whether an unchunked backward pass runs its weight gradients beside the other GEMMs, which depend on
 // them in nothing: each of the four leaves its last round of tiles partly filled, and the gate's
 // gradients leave the matrix cores idle.  By `work`, rows x d_model x d_ff: below 2e9 the events between
@@ -1190,8 +1235,8 @@ moe_status bwd_resources(BwdResources **out)
 // these 489 / 455 (427 / 367); 8192, k = 3 1086 / 989 (852 / 768); 4096, 16, 2048 x 8192 2448 / 2307 (2019 / 1847);
 // 16384, 16, 1024 x 4096 2146 / 2081 (1544 / 1485); 16384, 32, 2048 x 8192 7406 / 7454 (4972 / 4647); 32768, 64,
 // 2048 x 8192 13730 / 13930.
-// Not while the stages are timed, and not under capture: a side stream would stay part of the
-// capture after the call returns, and other threads' calls use it too.
+// Not while the stages are timed, and not under capture: the side stream would stay part of the
+// capture after the call returns, when the next call from outside needs it.
 bool overlaps_weight_grads(double work, hipStream_t st)
 {
     if (work < 2e9 || work > 7e11 || prof_enabled()) return false;
@@ -1294,9 +1339,17 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
                            dWg, d * E, w.splits);
     };
 
-    BwdResources *r = nullptr;
     if (n_chunks == 1) {
-        if (!overlaps_weight_grads(static_cast<double>(R) * d * h, st) || bwd_resources(&r) != MOE_OK) {
+        SideStream *side = nullptr;
+        std::unique_lock<std::mutex> enqueue;
+        int dev = 0;
+        if (overlaps_weight_grads(static_cast<double>(R) * d * h, st) && hipGetDevice(&dev) == hipSuccess &&
+            dev >= 0 && dev < 16) {
+            enqueue = std::unique_lock<std::mutex>(g_side[dev].enqueue);
+            side = side_stream(g_side[dev], st);
+        }
+        if (side == nullptr) {
+            if (enqueue.owns_lock()) enqueue.unlock();
             grad_dispatch(0, T, st);
             hidden_grads(0);
             input_grads(0);
@@ -1309,33 +1362,33 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
         }
         // The two weight gradients on a side stream: dW2 beside dP from dye on, dW1 beside dxe and the
         // gate's gradients from dP on.
-        std::lock_guard<std::mutex> enqueue(r->enqueue);
         auto enqueue_both = [&]() -> moe_status {
             grad_dispatch(0, T, st);
-            MOE_TRY_HIP(hipEventRecord(r->dispatched[0], st));
+            MOE_TRY_HIP(hipEventRecord(side->dispatched, st));
             hidden_grads(0);
-            MOE_TRY_HIP(hipEventRecord(r->computed[0], st));
+            MOE_TRY_HIP(hipEventRecord(side->hidden, st));
             // (dW2 reads the hidden activations: where they are recomputed, the first of the hidden_grads
             // GEMMs writes them)
-            MOE_TRY_HIP(hipStreamWaitEvent(r->grad_in, pre != nullptr ? r->dispatched[0] : r->computed[0], 0));
-            weight_grad2(r->grad_in);
+            MOE_TRY_HIP(hipStreamWaitEvent(side->stream, pre != nullptr ? side->dispatched : side->hidden, 0));
+            weight_grad2(side->stream);
             input_grads(0);
-            MOE_TRY_HIP(hipStreamWaitEvent(r->grad_in, r->computed[0], 0));
-            weight_grad1(r->grad_in);
+            MOE_TRY_HIP(hipStreamWaitEvent(side->stream, side->hidden, 0));
+            weight_grad1(side->stream);
             grad_combine(0, T, st);
             gate_weight_grad();
             return MOE_OK;
         };
         rc = enqueue_both();
         // (joined also after a failure part-way)
-        hipError_t je = hipEventRecord(r->joined_in, r->grad_in);
-        if (je == hipSuccess) je = hipStreamWaitEvent(st, r->joined_in, 0);
+        hipError_t je = hipEventRecord(side->joined, side->stream);
+        if (je == hipSuccess) je = hipStreamWaitEvent(st, side->joined, 0);
         if (rc != MOE_OK) return rc;
         if (je != hipSuccess) return hip_fail(je, "joining the side stream");
         MOE_TRY_HIP(hipGetLastError());
         return combine_rc;
     }
 
+    BwdResources *r = nullptr;
     rc = bwd_resources(&r);
     if (rc != MOE_OK) return rc;
     std::lock_guard<std::mutex> enqueue(r->enqueue);

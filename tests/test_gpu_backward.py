@@ -4,6 +4,8 @@ of fp32 rows).  The forward's bound is 2e-2 with ONE 16-bit operand rounding on 
 (the hidden activation); the input and first-layer weight gradients pass through TWO
 chained bf16 operand roundings (dye, then dP), each of relative RMS 2^-9/sqrt(3): the
 expected error grows by sqrt(2), and so does the bound (2.8e-2, rounded to 3e-2)."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -215,6 +217,160 @@ def test_weight_gradients_beside_the_other_gemms(keep):
         moe.moe_profile_enable(0, 0)
     for n in got:
         assert np.array_equal(got[n].view(np.uint32), ordered[n].view(np.uint32)), n
+
+
+class PreparedBackward:
+    """A layer's backward pass ready to be called: everything it reads, its gradients, a workspace."""
+
+    def __init__(self, li, keep=False, ws=None):
+        self.s = s = shape_of(li)
+        self.L = L = DeviceLayer(li, s)
+        b, self.pre, self.hid = L.b, None, None
+        if keep:
+            self.pre = torch.zeros(moe.moe_max_rows(s) * li.h, dtype=torch.float16, device=DEV)
+            self.hid = torch.zeros_like(self.pre)
+            moe.moe_layer_forward_keep(s, L.x, b["Wgp"], L.bias, L.bias_stride, b["W1p"], None, b["W2p"], None,
+                                       b["expert_idx"], b["gate"], b["counts"], b["offsets"], b["slot_of"],
+                                       b["src_of"], b["xe"], b["ye"], self.pre, self.hid, b["y"], b["workspace"])
+        else:
+            L.layer(1)
+        self.W1, self.W2 = upload(li.W1, "bf16"), upload(li.W2, "bf16")
+        f32 = lambda n: torch.zeros(n, dtype=torch.float32, device=DEV)
+        self.g = dict(dx=f32(li.T * li.d), dWg=f32(li.d * li.E), dW1=f32(li.W1.size), dW2=f32(li.W2.size),
+                      dgate=f32(li.T * li.k))
+        self.ws = torch.zeros(moe.moe_backward_workspace_bytes(s), dtype=torch.uint8, device=DEV) if ws is None else ws
+        g = torch.Generator(device=DEV)
+        g.manual_seed(li.T)
+        self.dy = torch.empty((li.T, li.d), device=DEV).normal_(generator=g)
+        torch.cuda.synchronize()
+
+    def __call__(self, dy=None, n_chunks=1):
+        b, g = self.L.b, self.g
+        moe.moe_layer_backward(self.s, self.L.x, b["Wgp"], self.L.bias, self.L.bias_stride, self.W1, self.W2,
+                               b["W1p"], b["expert_idx"], b["gate"], b["offsets"], b["slot_of"], b["src_of"],
+                               b["xe"], b["ye"], self.pre, self.hid, self.dy if dy is None else dy, g["dx"],
+                               g["dWg"], g["dW1"], g["dW2"], g["dgate"], self.ws, n_chunks=n_chunks)
+
+    def ordered(self, dy=None):
+        """The same call with its launches in order on one stream (stages timed)."""
+        moe.moe_profile_enable(1, 64)
+        try:
+            self(dy)
+            torch.cuda.synchronize()
+        finally:
+            moe.moe_profile_enable(0, 0)
+        return self.copy()
+
+    def copy(self):
+        return {n: t.clone() for n, t in self.g.items()}
+
+    def spoil(self):
+        for t in self.g.values():
+            t.fill_(7.0)
+
+    def check(self, want, what):
+        for n, t in self.g.items():
+            assert torch.equal(t.view(torch.int32), want[n].view(torch.int32)), (n, what)
+
+
+def medium_layer(seed=4):
+    return wl.make_layer(wl.scaled("gpt2s_moe", T=700, d=1280, h=1536, E=18, k=2, cf=1.0), seed=seed)
+
+
+@pytest.mark.parametrize("keep", [False, True], ids=["recompute", "keep"])
+def test_eager_backward_beside_the_capture_of_a_chunked_one(keep):
+    """While a backward pass of four groups is being captured on one stream, a medium layer's runs on
+    another: the call works, the capture holds, both give the bits of the calls alone."""
+    medium = PreparedBackward(medium_layer(), keep)
+    chunked = PreparedBackward(wl.make_layer(CASES["skewed"], seed=2), keep)
+    before = moe.moe_tune_ffn_group_rows(1)
+    try:
+        chunked(n_chunks=4)
+        medium()                       # (also: every kernel has been launched once)
+        torch.cuda.synchronize()
+        want_chunked, want = chunked.copy(), medium.ordered()
+        other, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        medium.spoil()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            chunked(n_chunks=4)
+            with torch.cuda.stream(other):
+                medium()
+    finally:
+        moe.moe_tune_ffn_group_rows(before)
+    torch.cuda.synchronize()
+    medium.check(want, "during the capture")
+    for rep in range(3):
+        chunked.spoil()
+        medium.spoil()
+        torch.cuda.synchronize()
+        graph.replay()
+        medium()
+        torch.cuda.synchronize()
+        chunked.check(want_chunked, rep)
+        medium.check(want, rep)
+
+
+def test_captured_backward_of_a_medium_layer():
+    """Under capture the launches stay in order: replays give the eager bits, with eager calls of the same
+    layer between them."""
+    b = PreparedBackward(medium_layer(), keep=True)
+    b()
+    torch.cuda.synchronize()
+    want, graph = b.ordered(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        b()
+    for rep in range(3):
+        b.spoil()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        b.check(want, rep)
+        b.spoil()
+        b()
+        torch.cuda.synchronize()
+        b.check(want, ("eager", rep))
+
+
+def test_backward_calls_in_a_row_and_on_several_streams():
+    """Medium layers, nothing waited for in between: one call after another with other inputs on the same
+    workspace; then six streams, more than the library has side streams, each its own layer's calls, from
+    one thread and from a thread each."""
+    a = PreparedBackward(medium_layer(), keep=True)
+    others = [a.dy * f for f in (0.5, -3.0, 0.25)]
+    want = [a.ordered(dy) for dy in others]
+    got = []
+    for dy in others:
+        a(dy)
+        got.append(a.copy())                        # on the same stream, behind the call
+    for n, dy in enumerate(others):
+        for key in want[n]:
+            assert torch.equal(got[n][key].view(torch.int32), want[n][key].view(torch.int32)), (key, n)
+    calls = [PreparedBackward(medium_layer(seed), keep=seed % 2 == 0) for seed in range(6)]
+    want = [c.ordered() for c in calls]
+    streams = [torch.cuda.Stream() for _ in calls]
+
+    def work(i):
+        with torch.cuda.stream(streams[i]):
+            for _ in range(3):
+                calls[i].spoil()
+                calls[i]()
+
+    torch.cuda.synchronize()
+    for _ in range(2):
+        for i in range(len(calls)):
+            work(i)
+    torch.cuda.synchronize()
+    for c, w in zip(calls, want):
+        c.check(w, "one thread")
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(calls))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for c, w in zip(calls, want):
+        c.check(w, "threads")
 
 
 def test_kept_buffers_come_together():

@@ -4,6 +4,7 @@ of fp32 rows).  The forward's bound is 2e-2 with ONE 16-bit operand rounding on 
 (the hidden activation); the input and first-layer weight gradients pass through TWO
 chained bf16 operand roundings (dye, then dP), each of relative RMS 2^-9/sqrt(3): the
 expected error grows by sqrt(2), and so does the bound (2.8e-2, rounded to 3e-2)."""
+import math
 import threading
 
 import numpy as np
@@ -217,6 +218,30 @@ def test_weight_gradients_beside_the_other_gemms(keep):
         moe.moe_profile_enable(0, 0)
     for n in got:
         assert np.array_equal(got[n].view(np.uint32), ordered[n].view(np.uint32)), n
+
+
+def test_gelu_over_all_16_bit_arguments():
+    """Hidden activations for every bf16 value of 2^-13 to 12, both signs, as the pre-activation (token rows
+    with a single one): half a unit of fp16 beside the fp32 evaluation's error, which is 6.5e-7 (the fit's
+    5.4e-7, and half a unit of its argument's size at 4) and falls with v: |v| (4e-5 |v| + 3e-7), since the
+    fitted slope at zero is off by 3.8e-5."""
+    bits = np.arange(0x3900, 0x4141, dtype=np.uint32)
+    v = (np.concatenate([bits, bits | 0x8000]) << 16).view(np.float32)
+    v = np.concatenate([v, np.ones(-len(v) % 8, np.float32)])
+    T, d, h = 8, 64, len(v)
+    li = wl.make_layer(wl.scaled("gpt2s_moe", T=T, d=d, h=h, E=1, k=1, cf=None), seed=0)
+    li.x[:], li.W1[:] = 0.0, 0.0
+    li.x[:, 0], li.W1[0, 0] = 1.0, v
+    b = PreparedBackward(li, keep=True)
+    torch.cuda.synchronize()
+    v = v.astype(np.float64)
+    exact = v * np.array([0.5 * math.erfc(-t / math.sqrt(2.0)) for t in v])
+    unit = np.spacing(np.abs(exact).astype(np.float16)).astype(np.float64)
+    bound = unit / 2 + np.minimum(6.5e-7, np.abs(v) * (4e-5 * np.abs(v) + 3e-7)) + 2.0 ** -23 * np.abs(exact)
+    pre = b.pre[:T * h].double().cpu().numpy().reshape(T, h)
+    hid = b.hid[:T * h].double().cpu().numpy().reshape(T, h)
+    assert (pre == v.astype(np.float16)).all()
+    assert (np.abs(hid - exact) <= bound).all()
 
 
 class PreparedBackward:

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void path_profile_kernel(
 // on a few counters, and the global atomics on those serialise; here a block counts its share of one
 // table's tokens in LDS and adds what it counted to the table, one global atomic per counter.
 //   DIRECT: the table's counters as 16-bit halves of LDS words (a share adds at most 65535 to any).
-//   else:   LDS is a hash table of kSlots (counter, count) pairs, first come first served: the
+//   else:   LDS is a hash table of 2^slot_bits (counter, count) pairs, first come first served: the
 //           popular counters are there early, a counter that finds its two places taken goes to
 //           global memory.
 // LL: l where it is 2 or 3, else 0: with l known all l + 1 choices of four tokens are on their way at
@@ -78,17 +78,19 @@ __global__ __launch_bounds__(256) void path_profile_kernel(
 // 2^32).  2^20 tokens, 12 layers, 16 experts, paths of length 3: 45 us (75 with one wait per choice and
 // 32-bit adds, 5050 with a global atomic per token and table); k = 2 70 (121).  Tables past LDS: bound
 // by their scattered atomics, fewer of them the more tokens share a hash table: 32 experts, 6 layers, 2^20
-// tokens 96 us (128 with 2^13 places and two blocks per unit), k = 2 193 (276; 255 before the waits went).
+// tokens 96 us (128 with 2^13 places and two blocks per unit), k = 2 193 (276; 255 before the waits went);
+// uniform choices, which share no counters, 124 either way.
 constexpr int kProfThreads = 1024;
-constexpr int kSlotBits = 14, kSlots = 1 << kSlotBits;     // one block per compute unit
+constexpr int kMostSlotBits = 14;                          // one block per compute unit
 constexpr int kProfMinTokens = 4096;                       // fewer: not worth clearing and flushing LDS
 constexpr int kProfLdsCounters = 73728;                    // 144 KiB of 16-bit counters
 
 template <bool DIRECT, int LL>
 __global__ __launch_bounds__(kProfThreads) void path_profile_lds_kernel(
     const int32_t *__restrict__ sel, uint32_t *__restrict__ counts, int T, int share, int splits,
-    int E, int k, int l, int paths)
+    int E, int k, int l, int paths, int slot_bits)
 {
+    const int slots = 1 << slot_bits;
     constexpr uint32_t kEmpty = 0xFFFFFFFFu;
     extern __shared__ uint32_t lds[];
     const int tid = threadIdx.x;
@@ -96,8 +98,8 @@ __global__ __launch_bounds__(kProfThreads) void path_profile_lds_kernel(
     const long t0 = static_cast<long>(blockIdx.x % splits) * share;
     const int t1 = static_cast<int>(min(t0 + share, static_cast<long>(T)));
     const size_t n = static_cast<size_t>(paths) * E, layer_stride = static_cast<size_t>(T) * k;
-    const int words = DIRECT ? static_cast<int>((n + 1) / 2) : 2 * kSlots;
-    for (int i = tid; i < words; i += kProfThreads) lds[i] = DIRECT || i >= kSlots ? 0u : kEmpty;
+    const int words = DIRECT ? static_cast<int>((n + 1) / 2) : 2 * slots;
+    for (int i = tid; i < words; i += kProfThreads) lds[i] = DIRECT || i >= slots ? 0u : kEmpty;
     __syncthreads();
 
     const int32_t *hist = sel + a * layer_stride;
@@ -107,12 +109,12 @@ __global__ __launch_bounds__(kProfThreads) void path_profile_lds_kernel(
         if constexpr (DIRECT) {
             atomicAdd(&lds[key >> 1], 1u << (16 * (key & 1u)));
         } else {
-            uint32_t at = (key * 2654435761u) >> (32 - kSlotBits);
+            uint32_t at = (key * 2654435761u) >> (32 - slot_bits);
             for (int probe = 0; probe < 2; ++probe, at ^= 1u) {
                 uint32_t have = *static_cast<volatile uint32_t *>(&lds[at]);
                 if (have == kEmpty) have = atomicCAS(&lds[at], kEmpty, key);
                 if (have == kEmpty || have == key) {
-                    atomicAdd(&lds[kSlots + at], 1u);
+                    atomicAdd(&lds[slots + at], 1u);
                     return;
                 }
             }
@@ -187,8 +189,8 @@ __global__ __launch_bounds__(kProfThreads) void path_profile_lds_kernel(
             if (v >> 16) atomicAdd(&table[2 * i + 1], v >> 16);
         }
     } else {
-        for (int i = tid; i < kSlots; i += kProfThreads)
-            if (lds[kSlots + i] != 0u) atomicAdd(&table[lds[i]], lds[kSlots + i]);
+        for (int i = tid; i < slots; i += kProfThreads)
+            if (lds[slots + i] != 0u) atomicAdd(&table[lds[i]], lds[slots + i]);
     }
 }
 
@@ -390,7 +392,7 @@ moe_status moe_path_profile(const moe_path_shape *s, const int32_t *sel, int32_t
                            s->l, static_cast<int>(paths));
     } else {
         const bool direct = counters <= kProfLdsCounters;
-        const size_t lds = direct ? align_up(static_cast<size_t>(counters) * 2, 4) : kSlots * 8;
+        size_t lds = direct ? align_up(static_cast<size_t>(counters) * 2, 4) : size_t(8) << kMostSlotBits;
         // shares: one block per compute unit (two where the LDS of both fits), or as many times
         // that as keep a share's counts below 2^16
         const int per_cu = lds <= 64 * 1024 ? 2 : 1;
@@ -399,6 +401,13 @@ moe_status moe_path_profile(const moe_path_shape *s, const int32_t *sel, int32_t
         splits *= (least + splits - 1) / splits;
         splits = std::min<int64_t>(splits, (T + kProfThreads - 1) / kProfThreads);
         const int64_t share = (T + splits - 1) / splits;
+        // A block of at most one token per thread, as few tokens make them, meets fewer counters than it takes to
+        // clear and flush the larger table: us with 2^13 / 2^14 places, 32 experts, 6 layers, l = 3: 16384
+        // tokens, k = 2 11.5 / 12.2, 65536 tokens, k = 1 16.0 / 16.6 (uniform choices 12.1 / 12.9); with
+        // larger shares (and twice the blocks for 2^13) 90000 23.0 / 20.9, 131072 36.3 / 25.0 (uniform choices
+        // 18.5 / 15.5, 21.4 / 20.4).
+        const int slot_bits = share <= kProfThreads ? kMostSlotBits - 1 : kMostSlotBits;
+        if (!direct) lds = size_t(8) << slot_bits;
         if (tables * splits >= (1ll << 32) / kProfThreads) {
             set_error("moe_path_profile: %d tables of %d tokens in one call", tables, T);
             return MOE_EUNSUPPORTED;
@@ -407,10 +416,10 @@ moe_status moe_path_profile(const moe_path_shape *s, const int32_t *sel, int32_t
                     : s->l == 3 ? direct ? path_profile_lds_kernel<true, 3> : path_profile_lds_kernel<false, 3>
                     : direct    ? path_profile_lds_kernel<true, 0> : path_profile_lds_kernel<false, 0>;
         static PerDeviceOnce once[3][2];
-        once[s->l == 2 ? 1 : s->l == 3 ? 2 : 0][direct].raise_lds(reinterpret_cast<const void *>(kern), direct ? kProfLdsCounters * 2 : kSlots * 8);
+        once[s->l == 2 ? 1 : s->l == 3 ? 2 : 0][direct].raise_lds(reinterpret_cast<const void *>(kern), direct ? kProfLdsCounters * 2 : 8 << kMostSlotBits);
         hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(tables * splits)), dim3(kProfThreads), lds, st,
                            sel, counts, T, static_cast<int>(share), static_cast<int>(splits), s->E,
-                           s->k, s->l, static_cast<int>(paths));
+                           s->k, s->l, static_cast<int>(paths), slot_bits);
     }
     MOE_TRY_HIP(hipGetLastError());
     return MOE_OK;

@@ -154,6 +154,23 @@ def test_tables_counted_in_lds(L, T, E, k, l, shift):
     assert not buf[:shift].any() and not buf[-1].any()
 
 
+@pytest.mark.parametrize("T", [4096, 256 * 1024, 256 * 1024 + 1])
+def test_tables_past_lds(T):
+    """One table of 2^20 counters: shares of up to 1024 tokens on hash tables of 2^13 places, larger ones on
+    2^14; Zipf-distributed choices and uniform ones, against counts of every (path, next) pair."""
+    E, k, l = 32, 2, 3
+    s = moe.PathShape(l + 1, E, k, l)
+    rng = np.random.default_rng(T)
+    for weights in (np.arange(1, E + 1) ** -1.2, np.ones(E)):
+        first = rng.choice(E, size=(l + 1, T), p=weights / weights.sum())
+        sel = np.stack([first, (first + 1 + rng.integers(0, E - 1, first.shape)) % E], axis=2).astype(np.int32)
+        path = (sel[0, :, 0] * E + sel[1, :, 0]) * E + sel[2, :, 0]
+        want = np.bincount((path[:, None] * E + sel[l]).reshape(-1), minlength=E ** 4)
+        counts = torch.zeros(E ** 4, dtype=torch.int32, device=DEV)
+        moe.moe_path_profile(s, torch.from_numpy(sel).to(DEV), T, counts)
+        assert np.array_equal(counts.cpu().numpy(), want)
+
+
 def test_finalize_of_more_rows_than_one_launch_has_lanes_for():
     """19 tables of 3^15 paths: over 2^28 rows, sixteen lanes for each of which would be more
     work-items than a launch can have; the rows are no multiple of what the grid walks at a time."""

@@ -1227,19 +1227,22 @@ SideStream *side_stream(SideStreams &r, hipStream_t caller)
 
 // Whether an unchunked backward pass runs its weight gradients beside the other GEMMs, which depend on
 // them in nothing: each of the four leaves its last round of tiles partly filled, and the gate's
-// gradients leave the matrix cores idle.  By `work`, rows x d_model x d_ff: below 2e9 the events between
-// the streams cost more than that; in large layers a last round is one of many, and GEMMs that run at
+// gradients leave the matrix cores idle.  By `work`, rows x d_model x d_ff: below 2.7e9 the events between
+// the streams can cost more than that; in large layers a last round is one of many, and GEMMs that run at
 // once share the caches and the power.  us of a training step, one after the other / beside each other, rows
-// spread evenly (by Zipf(1.2)): 128 tokens, 8 experts, 256 x 512 72 / 102 (80 / 122); 512, 8, 512 x 1536 120 /
-// 119 (124 / 131); 600, 13, 1000 x 2600 318 / 310 (313 / 305); 1024, 16, 768 x 3072 314 / 300 (301 / 288); 4096 of
-// these 489 / 455 (427 / 367); 8192, k = 3 1086 / 989 (852 / 768); 4096, 16, 2048 x 8192 2448 / 2307 (2019 / 1847);
-// 16384, 16, 1024 x 4096 2146 / 2081 (1544 / 1485); 16384, 32, 2048 x 8192 7406 / 7454 (4972 / 4647); 32768, 64,
-// 2048 x 8192 13730 / 13930.
+// spread evenly (by Zipf(1.2)), k = 2 unless said.  Below the line: 128 tokens, 8 experts, 256 x 512 72 / 102
+// (80 / 122); 512, 8, 512 x 1536 120 / 119 (124 / 131); 512, 8, 1024 x 2048 193 / 196 (190 / 195); 2048, 16,
+// 512 x 1024 134 / 132 (123 / 132); 640, 8, 1024 x 2048 (2.68e9) 198 / 204 (198 / 198).  Above: 1500, 13, 640 x 1536
+// (2.9e9) 179 / 172 (170 / 165); 2048, 16, 512 x 1536 180 / 175 (164 / 160); 300, 13, 1536 x 4096 391 / 369 (388 / 365);
+// 8192, 8, 256 x 1024 216 / 190 (202 / 186); 1024, 16, 768 x 3072 311 / 301 (297 / 282); 4096 of these 489 / 455
+// (427 / 367); 8192, k = 3 1086 / 989 (852 / 768); 4096, 16, 2048 x 8192 2448 / 2307 (2019 / 1847); 32768, 32, 1024 x
+// 4096 4010 / 3940 (2480 / 2320); 16384, 32, 2048 x 8192 (5.5e11) 7460 / 7350 (4840 / 4580; 7406 / 7454 on another
+// card); 32768, 64, 2048 x 4096 8030 / 7955 (4815 / 4545).  Past it: 32768, 64, 2048 x 8192 (1.1e12) 13730 / 13930.
 // Not while the stages are timed, and not under capture: the side stream would stay part of the
 // capture after the call returns, when the next call from outside needs it.
 bool overlaps_weight_grads(double work, hipStream_t st)
 {
-    if (work < 2e9 || work > 7e11 || prof_enabled()) return false;
+    if (work < 2.7e9 || work > 7e11 || prof_enabled()) return false;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &status) != hipSuccess) {
         (void)hipGetLastError();

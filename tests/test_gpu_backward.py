@@ -201,11 +201,11 @@ def test_kept_activations_through_the_large_weight_gradient_tiles():
 
 @pytest.mark.parametrize("keep", [False, True], ids=["recompute", "keep"])
 def test_weight_gradients_beside_the_other_gemms(keep):
-    """Rows x d x h above 2e9: the weight gradients run on a side stream, and in launch order while
+    """Rows x d x h above 2.7e9: the weight gradients run on a side stream, and in launch order while
     stages are timed.  The same bits either way, and the oracle's gradients, on 5 x 6 tiles of 256 x 256
     (squares of four that end inside a band)."""
     li = wl.make_layer(wl.scaled("gpt2s_moe", T=700, d=1280, h=1536, E=18, k=2, cf=1.0), seed=4)
-    assert moe.moe_max_rows(shape_of(li)) * li.d * li.h >= 2e9
+    assert moe.moe_max_rows(shape_of(li)) * li.d * li.h >= 2.7e9
     got, o = run_backward(li, keep=keep)
     for n, shape in (("dW1", li.W1.shape), ("dW2", li.W2.shape)):
         for e in range(li.E):

@@ -1010,7 +1010,6 @@ GemmPlan plan_rows(int N, int K, int64_t max_rows, int E)
         gp.concurrent = 32;
     }
     gp.tiles_n = (N + gp.bn - 1) / gp.bn;
-    gp.item_rows = gp.bm;
     gp.max_row_tiles = static_cast<int32_t>((max_rows + gp.bm - 1) / gp.bm + E);
     gp.max_items = work_list_entries(gp);
     return gp;

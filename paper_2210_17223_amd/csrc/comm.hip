@@ -378,7 +378,7 @@ void layout_padded(const moe_shape &s, int n_micro, void *base, PaddedWorkspace 
     const int per_micro = (s.capacity + n_micro - 1) / n_micro;   // slot positions, at most
     for (int g = 0; g < 2; ++g) {
         GemmPlan gp = choose_gemm_plan(s, g, n_micro, s.T);
-        gp.max_row_tiles = s.E * ((per_micro + gp.item_rows - 1) / gp.item_rows);
+        gp.max_row_tiles = s.E * ((per_micro + gp.bm - 1) / gp.bm);
         gp.max_items = work_list_entries(gp);
         w.gp[g] = gp;
         w.items[g] = reinterpret_cast<WorkItem *>(take(sizeof(WorkItem) * n_micro * gp.max_items));

@@ -61,9 +61,8 @@ struct WorkItem {
 
 // Tile shape and work-list bounds of one of the two expert GEMMs.
 struct GemmPlan {
-    int32_t bm, bn;          // rows / columns per output tile
+    int32_t bm, bn;          // rows / columns per output tile; bm: the most rows of a work item
     bool w4 = false;         // the four-wavefront kernels (gemm_w4.h)
-    int32_t item_rows = 0;   // most rows of a work item: bm, or a part of it
     int32_t tiles_n;         // column tiles
     int32_t max_row_tiles;   // upper bound of row tiles per list
     int32_t max_items;       // entries of a work list (a multiple of 8; surplus ones hold no tile)

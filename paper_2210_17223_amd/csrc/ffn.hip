@@ -413,7 +413,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_staged_kernel(
 // loads in flight.  A block is one wavefront: at 768 columns and 16 experts the second GEMM of a layer is
 // 768 blocks that spread over all compute units (as blocks of four wavefronts it took 192 units, and
 // what an L1 can keep in flight, about 32 KiB, bound those), and twelve blocks fit a unit, so that the
-// first GEMM's 3072 are one round.  Items hold at most 32 rows (a tile of 64 is two): with all 64 a
+// first GEMM's 3072 are one round.  Items hold at most 32 rows: with 64 a
 // popular expert's wavefronts had three stages in flight instead of five and ended last.
 // The contraction order is that of the other 16-bit kernels (same bits).
 // 16 tokens, 16 experts, k = 2, 768 x 3072, the two GEMMs: 16.3 and 14.5 us (17.0 and 18.4 with four
@@ -866,8 +866,7 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_launches, int64_t
             // 6144, 8 / 12 rows 174 / 174, 198 / 182; 32, 512 x 1024, 16 43.5 / 40.4), hence 2000.
             // Items of 32 rows: of 64 a popular expert's wavefronts hold three stages in flight instead of
             // five and end last (Zipf, 16, 1536 x 6144, 8 rows 198 -> 174; 32, 512 x 1024, 8 42 -> 39.5).
-            gp.bm = 64; gp.bn = 64; gp.concurrent = 128;
-            gp.item_rows = 32;
+            gp.bm = 32; gp.bn = 64; gp.concurrent = 128;
         } else if ((chunk_rows / 64 + s.E / 2) * tiles_n >= 128 &&
                    (per_expert < 48 || (per_expert <= 64 && (chunk_rows / 128 + s.E / 2) * tiles_n < 256))) {
             // few rows per expert and enough 64-row tiles to keep the weight stream going: shorter
@@ -882,8 +881,7 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_launches, int64_t
         }
     }
     gp.tiles_n = (N + gp.bn - 1) / gp.bn;
-    if (gp.item_rows == 0) gp.item_rows = gp.bm;
-    gp.max_row_tiles = static_cast<int32_t>((rows_of(tokens) + gp.item_rows - 1) / gp.item_rows + s.E);
+    gp.max_row_tiles = static_cast<int32_t>((rows_of(tokens) + gp.bm - 1) / gp.bm + s.E);
     gp.max_items = work_list_entries(gp);
     return gp;
 }

@@ -197,7 +197,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(
 
 // Work list of one expert GEMM from the per-expert row ranges [lo_s[e], hi_s[e]) held in
 // LDS (entries at or beyond E are empty).  An expert's rows are cut into row tiles of equal
-// height (a multiple of 32, at most gp.item_rows), and its output tiles are listed panel by panel --
+// height (a multiple of 32, at most gp.bm), and its output tiles are listed panel by panel --
 // `concurrent / row_tiles` column tiles wide, row tiles inside -- so that the blocks in
 // flight on one XCD share both their weight and their activation tiles.  Entry b is block b's: the
 // blocks go round the eight XCDs, and each XCD's walk a contiguous eighth of the tiles; entries without
@@ -209,7 +209,7 @@ __device__ void build_items(const GemmPlan &gp, WorkItem *__restrict__ items, co
 {
     if (threadIdx.x < kWave) {
         const int e = threadIdx.x;
-        const int mt = ceil_div(hi_s[e] - lo_s[e], gp.item_rows);
+        const int mt = ceil_div(hi_s[e] - lo_s[e], gp.bm);
         int incl = mt * gp.tiles_n;
 #pragma unroll
         for (int d = 1; d < kWave; d <<= 1) {
@@ -242,7 +242,7 @@ __device__ void build_items(const GemmPlan &gp, WorkItem *__restrict__ items, co
         const int m = within / width;
         const int nt = panel * gn + within % width;
         const int rows = hi_s[e] - lo_s[e];
-        const int per_tile = min(gp.item_rows, ceil_div(ceil_div(rows, mt), 32) * 32);
+        const int per_tile = min(gp.bm, ceil_div(ceil_div(rows, mt), 32) * 32);
         WorkItem it;
         it.expert = e;
         it.row0 = lo_s[e] + m * per_tile;

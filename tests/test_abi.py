@@ -143,7 +143,7 @@ def test_expert_gemm_kernel_tells_every_kernel_apart():
         s = moe.Shape.make(T, d, E, h, k, C, dtype="bf16", act="gelu")
         return [moe.moe_expert_gemm_kernel(s, which) for which in (0, 1)]
 
-    assert names(16, 768, 16, 3072, 2, 16) == ["grouped_gemm_stream_kernel 64x64"] * 2       # a decode step
+    assert names(16, 768, 16, 3072, 2, 16) == ["grouped_gemm_stream_kernel 32x64"] * 2       # a decode step
     assert names(256, 4096, 8, 14336, 2, 256)[1] == "grouped_gemm_staged_kernel 64x256"      # few rows, long weights
     assert names(300, 32776, 2, 32840, 1, 300) == ["grouped_gemm_staged_kernel 128x256"] * 2  # past 32-bit offsets
     assert all(n.startswith("grouped_gemm_mfma_kernel 128x") for n in names(4096, 768, 16, 3072, 2, 640))

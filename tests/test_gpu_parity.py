@@ -485,7 +485,7 @@ def test_gate_register_blocks_and_segments(name, base, T, d, E, k, cf):
 @pytest.mark.parametrize("dtype,T,d,h,E,k,hot", [
     ("bf16", 3, 72, 200, 16, 2, None),        # the 64 x 64 streaming tile: one group of rows, K tails
     ("bf16", 17, 1096, 40, 16, 2, 5),         # ... 17 rows of one expert: two groups
-    ("bf16", 70, 136, 328, 32, 2, 5),         # ... 70 rows: a full item of four groups and a second one
+    ("bf16", 70, 136, 328, 32, 2, 5),         # ... 70 rows: two full items of two groups and a third of 6 rows
     ("bf16", 100, 2048, 264, 64, 3, None),    # ... a contraction of many rounds of loads
     ("bf16", 1500, 1000, 2600, 4, 2, None),   # 256 x 256 with K tails by the count of rounds; 128 x 128
     ("bf16", 700, 64, 4104, 13, 3, None),     # one stage; a ragged last column tile
@@ -508,16 +508,25 @@ def test_expert_gemm_tiles(dtype, T, d, h, E, k, hot):
     assert rel_rms_err(L.b["y"].cpu().numpy().reshape(li.T, li.d), o.y) <= TOL[li.dtype]
 
 
-@pytest.mark.parametrize("T,d,h,E,k,hot", [
-    (33, 72, 200, 8, 2, 3),          # the hot expert holds 33 rows: two items of the streaming tile, 17 and 1 + 16
-    (32, 768, 328, 8, 2, 0),         # ... exactly one full item; last column item partly filled
-    (64, 64, 64, 4, 2, None),        # 32 rows per expert and one column tile: the last of its range
-    (65, 64, 64, 4, 2, None),        # ... and past it
-    (62, 136, 1032, 8, 2, 1),        # both sides of the rule in one layer: first GEMM's tiles, second's stream
+@pytest.mark.parametrize("T,d,h,E,k,hot,streams", [
+    (33, 72, 200, 8, 2, 3, (1, 1)),        # the hot expert holds 33 rows: two items, 32 and 1
+    (32, 768, 328, 8, 2, 0, (1, 1)),       # ... exactly one full item; last column item partly filled
+    (64, 64, 64, 4, 2, None, (1, 1)),      # 32 rows per expert and one column tile: the last of its range
+    (65, 64, 64, 4, 2, None, (0, 0)),      # ... and past it
+    (62, 136, 1032, 8, 2, 1, (1, 1)),      # 124 rows x 9 column tiles; a K tail of 8
+    (200, 136, 1280, 8, 1, None, (1, 1)),  # 200 rows x 10 column tiles = 2000: the last of its range
+    (201, 136, 1280, 8, 1, None, (0, 1)),  # ... and past it: the first GEMM's tiles, the second's stream
+    (100, 136, 1416, 8, 2, 1, (0, 1)),     # 200 x 12 and 200 x 2
+    (100, 1416, 136, 8, 2, 1, (1, 0)),     # ... and the other way round
+    (40, 64, 6280, 8, 1, None, (1, 1)),    # five rows per expert: whatever the columns
+    (41, 64, 6280, 8, 1, None, (0, 1)),    # ... and more: 41 x 50
 ])
-def test_streaming_tile_over_its_range(T, d, h, E, k, hot):
+def test_streaming_tile_over_its_range(T, d, h, E, k, hot, streams):
     """Few rows per expert: items of up to 32 rows, several per expert, at the ends of the rule's range
     (bounds: TOL of the type)."""
+    s = moe.Shape.make(T, d, E, h, k, T, dtype="bf16", act="gelu")
+    for which in (0, 1):
+        assert moe.moe_expert_gemm_kernel(s, which).startswith("grouped_gemm_stream_kernel") == bool(streams[which])
     test_expert_gemm_tiles("bf16", T, d, h, E, k, hot)
 
 

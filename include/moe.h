@@ -264,11 +264,15 @@ int32_t moe_profile_read(int32_t stage, float *ms, int32_t cap);
  *   after the first step; bit 2: no global loads into LDS in the loop; bit 3: no
  *   output stores; built: 0, 1, 2, 4, 6, 7, 8) -- their outputs are wrong by
  *   construction.  K a multiple of 64, N * K * 2 and 256 * K * 2 below 2^31.
+ * moe_path_calls: how many calls since the library was loaded went a way that no output shows: 0 a
+ *   backward pass with its weight gradients on a side stream, 1 an offloaded expert FFN whose weights
+ *   a kernel reads over the host link; -1 for any other number.
  * moe_expert_gemm_kernel: which kernel an unchunked bf16 layer of shape s launches for its
  *   expert GEMM `which` (0: first, xe W1; 1: second, H W2), written to name (host, len
  *   bytes, always terminated) as "<kernel> <tile rows>x<tile columns>", so that a
  *   measurement can say which kernel it timed.  MOE_EINVAL for which outside {0, 1}, a
  *   null name or len == 0, an unsupported shape or an fp32 layer (one kernel there). */
+int64_t moe_path_calls(int32_t path);
 moe_status moe_expert_gemm_kernel(const moe_shape *s, int32_t which, char *name, size_t len);
 moe_status moe_calib_copy(void *dst, const void *src, size_t bytes, void *stream);
 moe_status moe_calib_gemm(const void *A, const void *W, void *C, const int32_t *items,

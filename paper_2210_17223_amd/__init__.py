@@ -7,7 +7,7 @@ package only marshals arguments.  PyTorch is used for device memory and streams.
 from .binding import (ACT, DTYPE, MoeError, Shape, alloc_buffers, lib, lib_path,
                       moe_calib_copy, moe_calib_gemm, moe_calib_mfma, moe_capacity, moe_expert_gemm_kernel, moe_combine, moe_dispatch, moe_dispatch_static,
                       moe_dispatch_static_limit, moe_expert_ffn,
-                      moe_last_error, moe_layer_chunked, moe_max_rows, moe_pack_gate,
+                      moe_last_error, moe_layer_chunked, moe_max_rows, moe_pack_gate, moe_path_calls,
                       moe_pack_weights, moe_packed_gate_bytes, moe_packed_weight_bytes,
                       moe_profile_enable, moe_profile_read, moe_route, moe_tune_ffn_group_rows,
                       moe_workspace_bytes,
@@ -31,7 +31,7 @@ __all__ = ["comm", "moe_layer_padded", "moe_padded_workspace_bytes", "moe_expert
            "ACT", "DTYPE", "MoeError", "Shape", "alloc_buffers", "lib", "lib_path",
            "moe_calib_copy", "moe_calib_gemm", "moe_calib_mfma", "moe_capacity", "moe_expert_gemm_kernel", "moe_combine", "moe_dispatch", "moe_dispatch_static",
            "moe_dispatch_static_limit", "moe_expert_ffn",
-           "moe_last_error", "moe_layer_chunked", "moe_max_rows", "moe_pack_gate",
+           "moe_last_error", "moe_layer_chunked", "moe_max_rows", "moe_pack_gate", "moe_path_calls",
            "moe_pack_weights", "moe_packed_gate_bytes", "moe_packed_weight_bytes",
            "moe_profile_enable", "moe_profile_read", "moe_route", "moe_tune_ffn_group_rows",
            "moe_workspace_bytes",

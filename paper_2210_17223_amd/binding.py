@@ -85,6 +85,8 @@ def lib() -> C.CDLL:
         L.moe_expert_ffn.argtypes = [sp] + [vp] * 9
         L.moe_combine.argtypes = [sp] + [vp] * 6
         L.moe_layer_chunked.argtypes = [sp, i32, vp, vp, vp, i32] + [vp] * 16
+        L.moe_path_calls.argtypes = [i32]
+        L.moe_path_calls.restype = C.c_int64
         L.moe_calib_copy.argtypes = [vp, vp, sz, vp]
         L.moe_calib_copy.restype = C.c_int
         L.moe_calib_gemm.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp]
@@ -207,6 +209,11 @@ def moe_expert_gemm_kernel(s: Shape, which: int) -> str:
     buf = C.create_string_buffer(96)
     _check(lib().moe_expert_gemm_kernel(C.byref(s), int(which), buf, C.sizeof(buf)))
     return buf.value.decode()
+
+
+def moe_path_calls(path: int) -> int:
+    """Calls since the library was loaded that went a way no output shows (include/moe.h)."""
+    return int(lib().moe_path_calls(int(path)))
 
 
 def moe_calib_mfma(sink, waves_per_simd: int, iters: int, random_operands: bool, stream=None) -> float:

@@ -65,6 +65,10 @@ void prof_release()
 
 bool prof_enabled() { return g_prof.mask != 0; }
 
+static std::atomic<int64_t> g_path_calls[kNumPaths];
+
+void count_path_call(Path path) { g_path_calls[path].fetch_add(1, std::memory_order_relaxed); }
+
 void prof_begin(int stage, hipStream_t st)
 {
     if (!((g_prof.mask >> stage) & 1u) || g_prof.n[stage] >= g_prof.cap) return;
@@ -322,6 +326,11 @@ int64_t moe_capacity(int32_t T, int32_t E, int32_t k, double cf)
     const double v = cf * static_cast<double>(k) * static_cast<double>(T) / static_cast<double>(E);
     const int64_t c = static_cast<int64_t>(std::ceil(v));
     return c < 1 ? 1 : c;
+}
+
+int64_t moe_path_calls(int32_t path)
+{
+    return path >= 0 && path < kNumPaths ? g_path_calls[path].load(std::memory_order_relaxed) : -1;
 }
 
 int64_t moe_max_rows(const moe_shape *s)

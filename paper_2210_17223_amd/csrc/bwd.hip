@@ -1362,6 +1362,7 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
             MOE_TRY_HIP(hipGetLastError());
             return combine_rc;
         }
+        count_path_call(kPathSideWeightGrads);
         // The two weight gradients on a side stream: dW2 beside dP from dye on, dW1 beside dxe and the
         // gate's gradients from dP on.
         auto enqueue_both = [&]() -> moe_status {

@@ -141,6 +141,8 @@ enum Stage { kStageRoute = 0, kStagePlan, kStageTiles, kStageScatter, kStageGemm
 // Tokens per block of the gate kernel for this shape = tokens per segment of the plan.
 int route_segment_tokens(const moe_shape &s);
 bool prof_enabled();               // any stage is timed
+enum Path { kPathSideWeightGrads = 0, kPathPulledWeights, kNumPaths };
+void count_path_call(Path path);   // moe_path_calls
 void prof_begin(int stage, hipStream_t st);
 void prof_end(int stage, hipStream_t st);
 // For a stage that is one kernel: the pair of events to attach to that kernel's own

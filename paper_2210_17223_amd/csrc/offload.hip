@@ -183,6 +183,7 @@ moe_status moe_expert_ffn_offloaded(const moe_shape *s, const void *xe, const in
     const char *h1 = static_cast<const char *>(W1p_host), *h2 = static_cast<const char *>(W2p_host);
     const char *v1 = device_view(h1, eb * s->E), *v2 = device_view(h2, eb * s->E);
     const bool pull = v1 != nullptr && v2 != nullptr;
+    if (pull) count_path_call(kPathPulledWeights);
 
     moe_status rc = launch_items_per_expert(*s, offsets, w, st);
     if (rc != MOE_OK) return rc;

@@ -118,6 +118,11 @@ def test_static_dispatch_refuses_what_does_not_fit_its_array():
     assert rc == 1
 
 
+def test_path_calls_counts_from_zero():
+    assert moe.moe_path_calls(0) >= 0 and moe.moe_path_calls(1) >= 0
+    assert moe.moe_path_calls(2) == moe.moe_path_calls(-1) == -1
+
+
 def test_expert_gemm_kernel_names_the_kernel_and_its_tile():
     """moe_expert_gemm_kernel is host logic only: the large layer takes the 256 x 256 four-wavefront
     kernel for both GEMMs, the GPT-2-small layer 128-row tiles."""

@@ -17,6 +17,7 @@ from gpu_util import DEV, DeviceLayer, rel_rms_err, shape_of, upload
 from oracle import bwd_oracle as bo
 
 pytestmark = pytest.mark.gpu
+BESIDE = 0            # moe_path_calls: weight gradients on a side stream
 TOL = 3e-2
 
 CASES = {
@@ -206,7 +207,9 @@ def test_weight_gradients_beside_the_other_gemms(keep):
     (squares of four that end inside a band)."""
     li = wl.make_layer(wl.scaled("gpt2s_moe", T=700, d=1280, h=1536, E=18, k=2, cf=1.0), seed=4)
     assert moe.moe_max_rows(shape_of(li)) * li.d * li.h >= 2.7e9
+    calls = moe.moe_path_calls(BESIDE)
     got, o = run_backward(li, keep=keep)
+    assert moe.moe_path_calls(BESIDE) == calls + 1
     for n, shape in (("dW1", li.W1.shape), ("dW2", li.W2.shape)):
         for e in range(li.E):
             ref, err = getattr(o, n)[e], np.abs(got[n].reshape(shape)[e] - getattr(o, n)[e])
@@ -216,6 +219,7 @@ def test_weight_gradients_beside_the_other_gemms(keep):
         ordered, _ = run_backward(li, keep=keep, with_oracle=False)
     finally:
         moe.moe_profile_enable(0, 0)
+    assert moe.moe_path_calls(BESIDE) == calls + 1
     for n in got:
         assert np.array_equal(got[n].view(np.uint32), ordered[n].view(np.uint32)), n
 
@@ -319,8 +323,10 @@ def test_eager_backward_beside_the_capture_of_a_chunked_one(keep):
         torch.cuda.synchronize()
         with torch.cuda.graph(graph):
             chunked(n_chunks=4)
+            calls = moe.moe_path_calls(BESIDE)
             with torch.cuda.stream(other):
                 medium()
+            assert moe.moe_path_calls(BESIDE) == calls + 1
     finally:
         moe.moe_tune_ffn_group_rows(before)
     torch.cuda.synchronize()
@@ -343,8 +349,10 @@ def test_captured_backward_of_a_medium_layer():
     b()
     torch.cuda.synchronize()
     want, graph = b.ordered(), torch.cuda.CUDAGraph()
+    calls = moe.moe_path_calls(BESIDE)
     with torch.cuda.graph(graph):
         b()
+    assert moe.moe_path_calls(BESIDE) == calls
     for rep in range(3):
         b.spoil()
         torch.cuda.synchronize()
@@ -371,6 +379,7 @@ def test_backward_calls_in_a_row_and_on_several_streams():
     for n, dy in enumerate(others):
         for key in want[n]:
             assert torch.equal(got[n][key].view(torch.int32), want[n][key].view(torch.int32)), (key, n)
+    beside = moe.moe_path_calls(BESIDE)
     calls = [PreparedBackward(medium_layer(seed), keep=seed % 2 == 0) for seed in range(6)]
     want = [c.ordered() for c in calls]
     streams = [torch.cuda.Stream() for _ in calls]
@@ -396,6 +405,7 @@ def test_backward_calls_in_a_row_and_on_several_streams():
     torch.cuda.synchronize()
     for c, w in zip(calls, want):
         c.check(w, "threads")
+    assert moe.moe_path_calls(BESIDE) == beside + 6 * 3 * 3
 
 
 def test_kept_buffers_come_together():

@@ -11,6 +11,7 @@ import workloads as wl
 from gpu_util import DEV, DeviceLayer, rel_rms_err, shape_of
 
 pytestmark = pytest.mark.gpu
+PULLED = 1            # moe_path_calls: weights read over the link by a kernel
 
 CASES = {
     "small": wl.scaled("gpt2s_moe", T=1000, d=256, h=512),
@@ -66,8 +67,10 @@ def test_weights_in_page_locked_and_in_pageable_memory_give_the_same(T, d, h):
     for W1h, W2h in ((W1.pin_memory(), W2.pin_memory()), (W1, W2), (W1.pin_memory(), W2)):
         staging.fill_(0xFF)
         ye = torch.full_like(b["ye"], 5.0)
+        calls = moe.moe_path_calls(PULLED)
         moe.moe_expert_ffn_offloaded(s, b["xe"], b["offsets"], W1h, W2h, None, None, ye, staging, 2, ws)
         torch.cuda.synchronize()
+        assert moe.moe_path_calls(PULLED) - calls == (W1h.is_pinned() and W2h.is_pinned())
         assert torch.equal(ye[:A * d].view(torch.int16), want)
 
 
@@ -97,6 +100,48 @@ def test_page_locked_weights_changed_between_calls():
         W1h.copy_(p1)
         W2h.copy_(p2)
         assert torch.equal(call(W1h, W2h, resident), call(p1, p2, resident)), i
+
+
+@pytest.mark.parametrize("E,resident", [(1, 1), (5, 1), (5, 2), (5, 5)])
+def test_page_locked_weights_under_capture(E, resident):
+    """Both copy streams join the caller's, also with one expert or one slot; a replay reads the weights
+    that the host memory holds then.  Eager calls between the replays, in the same staging area."""
+    li = wl.make_layer(wl.scaled("gpt2s_moe", T=200, d=128, h=256, E=E, k=min(E, 2)), seed=3)
+    s = shape_of(li)
+    L = DeviceLayer(li, s)
+    L.layer(1)
+    b = L.b
+    A = int(b["offsets"].cpu().numpy()[-1])
+    W1, W2 = b["W1p"].cpu(), b["W2p"].cpu()
+    W1h, W2h = W1.clone().pin_memory(), W2.clone().pin_memory()
+    ws = torch.empty(moe.moe_offload_workspace_bytes(s), dtype=torch.uint8, device=DEV)
+    staging = torch.empty(moe.moe_offload_staging_bytes(s, resident), dtype=torch.uint8, device=DEV)
+    ye = torch.full_like(b["ye"], 5.0)
+
+    def call(w1, w2):
+        moe.moe_expert_ffn_offloaded(s, b["xe"], b["offsets"], w1, w2, None, None, ye, staging, resident, ws)
+
+    call(W1h, W2h)
+    torch.cuda.synchronize()
+    graph, calls = torch.cuda.CUDAGraph(), moe.moe_path_calls(PULLED)
+    with torch.cuda.graph(graph):
+        call(W1h, W2h)
+    assert moe.moe_path_calls(PULLED) == calls + 1
+    for rep in range(3):
+        p1 = torch.roll(W1.reshape(-1), 8 * rep).reshape(W1.shape)
+        p2 = torch.roll(W2.reshape(-1), 16 * rep).reshape(W2.shape)
+        call(p1, p2)
+        torch.cuda.synchronize()
+        want = ye.clone()
+        W1h.copy_(p1)
+        W2h.copy_(p2)
+        ye.fill_(5.0)
+        staging.fill_(0xFF)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(ye.view(torch.int16), want.view(torch.int16)), rep
+        assert (ye[A * li.d:] == 5.0).all()
 
 
 def test_sizes_and_refusals():

@@ -574,15 +574,8 @@ __device__ __forceinline__ void w4_gemm_tile(
             const int rr = it * RPI + lane / LPR;
             const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * PITCH + lane % LPR * 16);
             const int r = rbase + rr;
-            u32x4 *to = reinterpret_cast<u32x4 *>(out + static_cast<size_t>(r) * N + ncol);
-            if (r < item.row1 && ncol < N && (!(ABL & 8) || q[0] == 0x7fc07fc1u)) {
-                // the pre-activations wait for the backward pass: past the caches (training step of 4096
-                // tokens, 768 x 3072, 16 experts 487 -> 483 us)
-                if (pass == 0)
-                    __builtin_nontemporal_store(q, to);
-                else
-                    *to = q;
-            }
+            if (r < item.row1 && ncol < N && (!(ABL & 8) || q[0] == 0x7fc07fc1u))
+                *reinterpret_cast<u32x4 *>(out + static_cast<size_t>(r) * N + ncol) = q;
         }
         if (pass == 0) {
             MOE_LGKM0();

@@ -632,10 +632,10 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(
 // operands' buffer resources end with the expert's last row: rows past it -- and whole stages
 // past the last one -- read as zeros, without clamping or tail code.
 // Bound by the loop and, one after the other, the tile's 256 KiB of fp32 that leave behind it: all units
-// store at once, some 12 of a tile's 41 us at 16 stages.  The stores go past the caches; with them, and
-// the tiles in squares, training step of 4096 tokens, 768 x 3072, 16 experts 509 -> 488 us, of 32768,
-// 2048 x 8192, 64 experts 13960 -> 13680.  (Half of an XCD's units started half a tile later: 499 of 509 us
-// alone, no gain beside the other two.)
+// store at once, some 12 of a tile's 41 us at 16 stages.  The stores go past the caches: training step of
+// 4096 tokens, 768 x 3072, 16 experts 502 -> 488 us in launch order, 468 -> 451 beside the other GEMMs; of
+// 32768, 2048 x 8192, 64 experts within noise.  The tiles in squares: dW1 of the latter 2455 -> 2325 us, the
+// step 13860 -> 13690; nothing at 3 x 12 tiles.
 // AF16: A holds fp16 values, rounded to bf16 between the LDS read and the multiply.
 template <bool AF16>
 __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(

@@ -70,7 +70,10 @@ size_t moe_backward_workspace_bytes(const moe_shape *s);
  *   dx [T,d], dWg [d,E], dW1 [E,d,h], dW2 [E,h,d], dgate [T*k]: fp32, overwritten (weight
  *                    gradients of an expert without rows are zero)
  * Layers of medium size run the weight gradients beside the other GEMMs on a side stream of the
- * library that `stream` forks and joins (not under stream capture).
+ * library that `stream` forks and joins: one side stream for each of up to four caller's streams.  Under
+ * stream capture, and while a stage is timed (moe_profile_enable), the launches stay in order on
+ * `stream`: a captured step has none of the overlap, and stage times add up to the ordered step.  The
+ * gradients are the same bits.
  */
 moe_status moe_layer_backward(const moe_shape *s, const void *x, const void *Wgp,
                               const float *gate_bias, int32_t bias_token_stride,

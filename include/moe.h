@@ -210,7 +210,9 @@ moe_status moe_combine(const moe_shape *s, const void *ye, const int32_t *slot_o
  * groups = min(n_chunks, (moe_max_rows / E) / that), at least 1; packing and unpacking
  * keep n_chunks.  With one group the call runs as n_chunks = 1.
  * Arguments as in the calls above; all outputs are written.  The side streams
- * and events are created on the first chunked call on a device and kept. */
+ * and events are created on the first chunked call on a device and kept.  A captured call keeps
+ * them in its capture until the capture ends: until then no other chunked call, nor one of a large
+ * layer (whose pack runs beside the FFN), may be made on the device. */
 moe_status moe_layer_chunked(const moe_shape *s, int32_t n_chunks, const void *x,
                              const float *Wgp, const float *gate_bias,
                              int32_t bias_token_stride, const void *W1p,

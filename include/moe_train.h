@@ -94,7 +94,9 @@ moe_status moe_layer_backward(const moe_shape *s, const void *x, const void *Wgp
  * there, and the rows that come back are folded into dx chunk by chunk on a second side
  * stream while the caller's stream goes on with the next group and the weight gradients.
  * Every gradient is the same bits for every n_chunks.  With one group the call runs as
- * n_chunks = 1.  Side streams and events are created on the first call on a device that uses them. */
+ * n_chunks = 1.  Side streams and events are created on the first call on a device that uses them;
+ * those of a captured call of several groups stay in the capture until it ends, and no other call of
+ * several groups may be made on the device until then. */
 moe_status moe_layer_backward_chunked(const moe_shape *s, int32_t n_chunks, const void *x,
                                       const void *Wgp, const float *gate_bias,
                                       int32_t bias_token_stride, const void *W1, const void *W2,

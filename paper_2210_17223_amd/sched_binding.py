@@ -6,6 +6,7 @@ host calls take numpy arrays or sequences and return numpy arrays.
 from __future__ import annotations
 
 import ctypes as C
+from operator import index
 from typing import Sequence, Tuple
 
 import numpy as np
@@ -106,6 +107,7 @@ class _Schedule:
     address of each took three quarters of the call.)"""
 
     def __init__(self, N: int, E: int):
+        N, E = index(N), index(E)               # numpy's integers too: their sums would not be addresses
         n = max(N, 1)
         self.shape, self.ends = (N, E), (E, E + n, E + n + n * E)
         room = _rooms.get((n, E))

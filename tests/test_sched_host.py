@@ -90,6 +90,20 @@ def test_top_lists_and_layer_decision_match_the_oracle():
         assert (list(map(int, rep)), as_lists(cnt, dev), used) == want
 
 
+@pytest.mark.parametrize("kind", [np.int32, np.int64, np.uint8])
+def test_sizes_of_numpy_integers(kind):
+    """N and E as they come out of an array's shape or contents: the same schedules."""
+    w, has, S, counts = [5, 9, 1, 0, 3], [1, 1, 1, 0, 1], [1 << 32, 3 << 32, 0, 2 << 31, 7], [3, 9, 0, 1, 2]
+    for N in (1, 4):
+        for got, want in ((moe.moe_schedule_experts(kind(N), kind(5), w, 6, has, 4),
+                           moe.moe_schedule_experts(N, 5, w, 6, has, 4)),
+                          (moe.moe_schedule_layer(kind(N), kind(5), kind(2), 16, S, counts, 4),
+                           moe.moe_schedule_layer(N, 5, 2, 16, S, counts, 4))):
+            assert all(np.array_equal(a, b) for a, b in zip(got, want)) and len(got) == len(want)
+    with pytest.raises(TypeError):
+        moe.moe_schedule_experts(4.0, 5, w, 6, has, 4)
+
+
 def test_refusals():
     with pytest.raises(moe.MoeError):
         moe.moe_schedule_experts(0, 4, [1, 1, 1, 1], 4, [1, 1, 1, 1], 4)       # no device

@@ -424,15 +424,24 @@ __device__ __forceinline__ u32x2 lds_read_tr16(const uint16_t *p)
 
 // AF16: A holds fp16 values (the forward's hidden activations); they are rounded to bf16 on
 // their way into LDS (two conversions to fp32 and one packed conversion per pair).
-__device__ __forceinline__ uint32_t f16x2_to_bf16x2(uint32_t w)
+template <int HALF>
+__device__ __forceinline__ float f16_half_to_f32(uint32_t w)
 {
     typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    const f16x2 hv = __builtin_bit_cast(f16x2, w);
-    bf16x2 b;
-    b[0] = static_cast<__bf16>(static_cast<float>(hv[0]));
-    b[1] = static_cast<__bf16>(static_cast<float>(hv[1]));
-    return __builtin_bit_cast(uint32_t, b);
+    return static_cast<float>(__builtin_bit_cast(f16x2, w)[HALF]);
+}
+// (written out: between the matrix instructions the compiler converts the two one by one and merges them)
+__device__ __forceinline__ uint32_t f32x2_to_bf16x2(float lo, float hi)
+{
+    uint32_t w = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(w) : "v"(lo), "v"(hi));
+#endif
+    return w;
+}
+__device__ __forceinline__ uint32_t f16x2_to_bf16x2(uint32_t w)
+{
+    return f32x2_to_bf16x2(f16_half_to_f32<0>(w), f16_half_to_f32<1>(w));
 }
 
 template <bool AF16>
@@ -622,199 +631,269 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(
 }
 
 // ---------------------------------------------------------------- weight gradient, 256 x 256 tiles
-// The same product on the four-wavefront layout of gemm_w4.h (operands straight into an LDS ring
-// of five 32 KiB units, accumulators in AGPRs, every memory instruction between two matrix
-// instructions), for layers whose weight gradients have enough 256 x 256 tiles.  A unit is 64
-// rows x 256 columns of one operand; the fragments of the 16 x 16 x 32 instruction (eight rows
-// of one column per lane) are two transposing LDS reads each.  The 64-byte pieces of a row are
-// XOR-swizzled with the row's low two bits and its 32-byte halves with bit 3, so that the four
-// rows of a 16-lane group, and two groups eight rows apart, fall into different banks.  The
-// operands' buffer resources end with the expert's last row: rows past it -- and whole stages
+// The same product on the four-wavefront layout of gemm_w4.h (operands straight into LDS, accumulators in AGPRs,
+// every memory instruction between two matrix instructions), for layers whose weight gradients have enough
+// 256 x 256 tiles.  A tile is few steps of 32 rows deep, so a block works through a share of the tiles
+// and its loads run on across them: LDS is a ring of five steps of 32 KiB (32 rows x 256 columns of both
+// operands), and while step s is multiplied the fragments of s + 1 are read, s + 2 .. s + 4 are on their way and
+// s + 5 is requested into the step's own place, whether it belongs to this tile or the next.  A finished tile
+// leaves through the place of its last step while the next one's first steps are there already.
+// The fragments of the 16 x 16 x 32 instruction (eight rows of one column per lane) are two transposing
+// LDS reads each.  The 64-byte pieces of a row are XOR-swizzled with the row's low two bits and its 32-byte
+// halves with bit 3, so that the four rows of a 16-lane group, and two groups eight rows apart, fall into
+// different banks.  The operands' buffer resources end with the expert's last row: rows past it -- and whole steps
 // past the last one -- read as zeros, without clamping or tail code.
-// Bound by the loop and, one after the other, the tile's 256 KiB of fp32 that leave behind it: all units
-// store at once, some 12 of a tile's 41 us at 16 stages.  The stores go past the caches: training step of
-// 4096 tokens, 768 x 3072, 16 experts 502 -> 488 us in launch order, 468 -> 451 beside the other GEMMs; of
-// 32768, 2048 x 8192, 64 experts within noise.  The tiles in squares: dW1 of the latter 2455 -> 2325 us, the
-// step 13860 -> 13690; nothing at 3 x 12 tiles.
-// AF16: A holds fp16 values, rounded to bf16 between the LDS read and the multiply.
+// AF16: A holds fp16 values, rounded to bf16 between the LDS read and the multiply, beside the column before.
+//
+// us of dW2 / dW1, one block per tile before / a share of the tiles per block: 63622 rows, 2048 x 8192, 64 experts
+// 2742 / 2363 -> 2422 / 2137; 8192 rows, 768 x 3072, 16 experts 88 / 77 -> 75 / 68.  Of dW1's 2130 the matrix
+// instructions with their LDS reads and barriers take 1275 by themselves, the loads beside them 320 more, the stores
+// 350 (a unit's wavefronts wait until the 256 KiB of a tile are accepted; alone the 4.3 GB take 690, 6.2 TB/s),
+// the way through LDS 110.  No wait for a load costs anything: not waiting at all is no faster.  The loads,
+// one behind each column of instructions: 3 % / 2 % less than two at a time, 5 % / 4 % less than among the LDS
+// reads.  The stores are two rows of 512 bytes per instruction: straight from the accumulators, 16 rows of 64
+// bytes, past the caches the 4.3 GB alone take 1430 us, through them the operands are pushed out (dW1 2380).
+// Blocks that start one after the other over the length of a tile, so that they do not store all at once: 2 %
+// less for dW1, nothing for dW2.  Tiles in squares of 4 x 4: dW1 2455 -> 2325 with one block per tile.
 template <bool AF16>
 __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, float *__restrict__ C,
     const int32_t *__restrict__ offsets, int E, int M, int N, int tiles_m, int tiles_n)
 {
-    constexpr int TM = 8, TN = 8, UNIT = 32768;
+    constexpr int TM = 8, TN = 8, HALF = 16384, STEP = 2 * HALF, RING = 5;
     constexpr int kRow = 512;                     // bytes of a 256-column LDS row
-    int expert, m0, n0;
-    {
-        const int total = E * tiles_m * tiles_n;
-        const int per_xcd = (total + 7) / 8;
-        const int slot = blockIdx.x / 8;
-        const int idx = (blockIdx.x % 8) * per_xcd + slot;
-        if (slot >= per_xcd || idx >= total) return;
-        expert = idx / (tiles_m * tiles_n);
-        // squares of 4 x 4 tiles, along n inside a band of four: the 32 tiles an XCD has in flight share 12
-        // panels of the operands whatever the matrix's shape (row by row, 33 of a wide one's)
-        int rem = idx % (tiles_m * tiles_n);
-        const int band = rem / (4 * tiles_n), high = min(4, tiles_m - 4 * band);
-        rem -= band * 4 * tiles_n;
-        const int square = rem / (4 * high), wide = min(4, tiles_n - 4 * square);
-        rem -= square * 4 * high;
-        m0 = (4 * band + rem / wide) * 256;
-        n0 = (4 * square + rem % wide) * 256;
-    }
-    const int r0 = offsets[expert], r1 = offsets[expert + 1];
-    const int KT = (r1 - r0 + 63) / 64;
+    const int total = E * tiles_m * tiles_n;
+    const int per_xcd = (total + 7) / 8, stride = gridDim.x / 8;
+    const int end = min(total, static_cast<int>(blockIdx.x % 8 + 1) * per_xcd);
+    int tile = static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
+    if (tile >= end) return;
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     char *const lds = reinterpret_cast<char *>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave & 1, wn = wave >> 1;
     const int fr = lane & 15, oct = lane >> 4;
+    const int first_row = offsets[min(lane, E)], end_row = offsets[min(lane + 1, E)];
 
+    struct Tile {
+        int expert, m0, n0, row0, rows;
+        __device__ __forceinline__ int steps() const { return max((rows + 63) / 64 * 2, 2); }
+    };
+    auto tile_at = [&](int idx) {
+        Tile t;
+        t.expert = __builtin_amdgcn_readfirstlane(idx / (tiles_m * tiles_n));
+        // squares of 4 x 4 tiles, along n inside a band of four: the 32 tiles an XCD has in flight share 12
+        // panels of the operands whatever the matrix's shape (row by row, 33 of a wide one's)
+        int rem = idx - t.expert * (tiles_m * tiles_n);
+        const int band = rem / (4 * tiles_n), high = min(4, tiles_m - 4 * band);
+        rem -= band * 4 * tiles_n;
+        const int square = rem / (4 * high), wide = min(4, tiles_n - 4 * square);
+        rem -= square * 4 * high;
+        t.m0 = __builtin_amdgcn_readfirstlane((4 * band + rem / wide) * 256);
+        t.n0 = __builtin_amdgcn_readfirstlane((4 * square + rem % wide) * 256);
+        t.row0 = __builtin_amdgcn_readlane(first_row, t.expert);
+        t.rows = __builtin_amdgcn_readlane(end_row, t.expert) - t.row0;
+        return t;
+    };
+
+    // Loads: of the tile `load_tile`, `load_steps` more steps, from a_at / b_at (the tile's first column of the
+    // step's first row); a_left / b_left bytes to the end of the expert's last row.
+    int load_tile = tile, load_steps, a_left, b_left;
+    const uint16_t *a_at, *b_at;
+    auto open = [&]() {
+        if (load_tile < end) {
+            const Tile t = tile_at(load_tile);
+            a_at = A + static_cast<size_t>(t.row0) * M + t.m0;
+            b_at = B + static_cast<size_t>(t.row0) * N + t.n0;
+            a_left = t.rows > 0 ? (t.rows * M - t.m0) * 2 : 0;
+            b_left = t.rows > 0 ? (t.rows * N - t.n0) * 2 : 0;
+            load_steps = t.steps();
+        } else {                                  // (behind the last tile: zeros, never used)
+            a_left = b_left = 0;
+            load_steps = 0x7fffffff;
+        }
+    };
+    // load q of this wavefront's four of an operand's step: rows wave * 8 + 2 q and + 1, 32 pieces of 16
+    // bytes each; lane l lands at row l / 32, place l % 32
+    int a_src[4], b_src[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int row = wave * 8 + q * 2 + (lane >> 5), place = lane & 31;
+        const int piece = (place ^ ((row & 3) << 2)) ^ (((row >> 3) & 1) << 1);
+        a_src[q] = (row * M + piece * 8) * 2;
+        b_src[q] = (row * N + piece * 8) * 2;
+    }
+    const uint32_t dest = lds_address(lds) + wave * 4096;
+    __amdgpu_buffer_rsrc_t rsa, rsb;
+    // (the range check that turns rows past the expert's end into zeros sees the per-lane offset only)
+    auto aim = [&]() {
+        rsa = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a_at), 0, static_cast<unsigned>(max(a_left, 0)), 0x00020000);
+        rsb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(b_at), 0, static_cast<unsigned>(max(b_left, 0)), 0x00020000);
+    };
+    auto load = [&](auto vc, int at) {            // load v (0 .. 7) of a step into the ring at `at`
+        constexpr int v = decltype(vc)::value;
+        if constexpr (v < 4) load_to_lds(rsa, a_src[v], dest + at + v * 1024, 0);
+        else load_to_lds(rsb, b_src[v - 4], dest + at + HALF + (v - 4) * 1024, 0);
+    };
+    auto advance = [&]() {
+        a_at += 32 * static_cast<size_t>(M);
+        b_at += 32 * static_cast<size_t>(N);
+        a_left -= 64 * M;
+        b_left -= 64 * N;
+        if (--load_steps == 0) {
+            load_tile += stride;
+            open();
+        }
+    };
+    auto next = [](int at) { return at == (RING - 1) * STEP ? 0 : at + STEP; };
+
+    // fragment of the 16-column sub-tile t, half h, of a step: lane = 16 oct + i reads row 8 oct + i / 4
+    // (+ 4 h), columns 4 (i % 4) .. + 3
+    const int fbase = (8 * oct + (fr >> 2)) * kRow + (fr & 3) * 8;
+    int fcol[4];                                                  // sub-tiles 2 u and 2 u + 1
+#pragma unroll
+    for (int u = 0; u < 4; ++u) fcol[u] = (u ^ (fr >> 2)) * 64 + (oct & 1) * 32;
+    u32x4 bf[2][TN], af[2][TM];
     f32x4 acc[TN][TM];
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f;
-
-    if (KT > 0) {
-        // an operand's resource: from the tile's first column of the expert's first row to the end
-        // of the expert's last row
-        const unsigned rows = static_cast<unsigned>(r1 - r0);
-        const __amdgpu_buffer_rsrc_t rsa = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint16_t *>(A + static_cast<size_t>(r0) * M + m0), 0,
-            (rows * static_cast<unsigned>(M) - static_cast<unsigned>(m0)) * 2u, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rsb = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint16_t *>(B + static_cast<size_t>(r0) * N + n0), 0,
-            (rows * static_cast<unsigned>(N) - static_cast<unsigned>(n0)) * 2u, 0x00020000);
-        // load q of this wavefront's eight of a unit: rows wave * 16 + 2 q and + 1, 32 pieces of 16
-        // bytes each; lane l lands at row l / 32, place l % 32
-        int a_src[8], b_src[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int row = wave * 16 + q * 2 + (lane >> 5), place = lane & 31;
-            const int piece = (place ^ ((row & 3) << 2)) ^ (((row >> 3) & 1) << 1);
-            a_src[q] = (row * M + piece * 8) * 2;
-            b_src[q] = (row * N + piece * 8) * 2;
+    // read v (0 .. 31) of a step's fragments: B first, halves interleaved
+    auto read = [&](auto slotc, auto vc, int at) {
+        constexpr int s = decltype(slotc)::value, v = decltype(vc)::value;
+        constexpr int t = (v & 15) >> 1, h = v & 1;
+        const int from = at + (v < 16 ? HALF + wn * 256 : wm * 256) + h * 4 * kRow + fbase +
+                         (fcol[t >> 1] ^ ((t & 1) * 32));
+        const u32x2 q = lds_read_tr16(reinterpret_cast<const uint16_t *>(lds + from));
+        if constexpr (v < 16) {
+            bf[s][t][2 * h] = q[0];
+            bf[s][t][2 * h + 1] = q[1];
+        } else {
+            af[s][t][2 * h] = q[0];
+            af[s][t][2 * h + 1] = q[1];
         }
-        const int a_stage = 64 * M * 2, b_stage = 64 * N * 2;         // stage kt -> kt + 1
-        // fragment of the 16-column sub-tile t, half h, of a 32-row step: lane = 16 oct + i reads
-        // row 8 oct + i / 4 (+ 4 h), columns 4 (i % 4) .. + 3
-        const int frow = 8 * oct + (fr >> 2);
-        const int fbase = frow * kRow + (fr & 3) * 8;
-        int fcol[4];                                                  // sub-tiles 2 u and 2 u + 1
-#pragma unroll
-        for (int u = 0; u < 4; ++u) fcol[u] = (u ^ (fr >> 2)) * 64 + (oct & 1) * 32;
-        u32x4 bf[2][TN], af[2][TM];
-        const uint32_t dest = lds_address(lds) + wave * 8192;
-// (the whole offset goes into the per-lane operand: the range check that turns rows past the
-// expert's end into zeros does not see the scalar offset)
-#define WG4_LDA(q, unit, kt_) load_to_lds(rsa, a_src[q] + (kt_) * a_stage, dest + (unit) + (q) * 1024, 0)
-#define WG4_LDB(q, unit, kt_) load_to_lds(rsb, b_src[q] + (kt_) * b_stage, dest + (unit) + (q) * 1024, 0)
-        // read v (0 .. 31) of a step's fragments: B first, halves interleaved
-        auto read = [&](auto slotc, auto vc, int bat, int aat, int ks) {
-            constexpr int s = decltype(slotc)::value, v = decltype(vc)::value;
-            constexpr int t = (v & 15) >> 1, h = v & 1;
-            const int at = (v < 16 ? bat + wn * 256 : aat + wm * 256) + ks * 32 * kRow + h * 4 * kRow + fbase +
-                           (fcol[t >> 1] ^ ((t & 1) * 32));
-            const u32x2 q = lds_read_tr16(reinterpret_cast<const uint16_t *>(lds + at));
-            if constexpr (v < 16) {
-                bf[s][t][2 * h] = q[0];
-                bf[s][t][2 * h + 1] = q[1];
-            } else {
-                af[s][t][2 * h] = q[0];
-                af[s][t][2 * h + 1] = q[1];
+    };
+    // instruction n (0 .. 11) of the conversion of a fragment's eight values from fp16 to bf16
+    float wide[2];
+    auto convert = [&](auto nc, u32x4 &w) {
+        constexpr int n = decltype(nc)::value, c = n / 3;
+        if constexpr (n % 3 < 2) wide[n % 3] = f16_half_to_f32<n % 3>(w[c]);
+        else w[c] = f32x2_to_bf16x2(wide[0], wide[1]);
+    };
+    using std::integral_constant;
+    // The 64 matrix instructions of the step at `at`, beside them the reads of the one behind it and
+    // the loads of the fifth one behind it.  A tile's last step leaves its loads to the next tile's first one,
+    // since the finished tile passes through its place.
+    enum Kind { kFirst, kMiddle, kLast };
+    auto step = [&](auto slotc, auto kindc, int at) {
+        constexpr int s = decltype(slotc)::value, KIND = decltype(kindc)::value;
+        const int ahead = next(at), behind = at == 0 ? (RING - 1) * STEP : at - STEP;
+        if constexpr (KIND != kLast) aim();
+        static_for<64>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            constexpr int j = m >> 3, i = (j & 1) != 0 ? 7 - (m & 7) : (m & 7);
+            mfma_16x16x32_agpr<false, m == 0, KIND == kFirst>(acc[i][j], bf[s][i], af[s][j]);
+            if constexpr (m < 32) read(integral_constant<int, 1 - s>{}, mc, ahead);
+            if constexpr (KIND == kMiddle && (m & 7) == 7) load(integral_constant<int, j>{}, at);
+            if constexpr (KIND == kFirst && (m & 7) >= 6) load(integral_constant<int, 2 * (j & 3) + (m & 1)>{}, m < 32 ? behind : at);
+            if constexpr (KIND == kFirst && m == 32) {
+                advance();
+                aim();
             }
-        };
-        // 64 matrix instructions of a 32-row step; AF16: column j's fragment is converted before its
-        // first use
-        auto step = [&](auto slotc, auto mem) {
-            constexpr int s = decltype(slotc)::value;
-            static_for<64>([&](auto mc) {
-                constexpr int m = decltype(mc)::value;
-                constexpr int j = m >> 3, i = (j & 1) != 0 ? 7 - (m & 7) : (m & 7);
-                if constexpr (AF16 && (m & 7) == 0) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) af[s][j][c] = f16x2_to_bf16x2(af[s][j][c]);
-                }
-                mfma_16x16x32_agpr<false, AF16 ? (m & 7) == 0 : m == 0>(acc[i][j], bf[s][i], af[s][j]);
-                mem(mc);
-                MOE_SB();
-            });
-        };
-        using std::integral_constant;
-        int ua = 0, ub = UNIT, ua1 = 2 * UNIT, ub1 = 3 * UNIT, uf = 4 * UNIT;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) WG4_LDA(q, ua, 0);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) WG4_LDB(q, ub, 0);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) WG4_LDA(q, ua1, 1);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) WG4_LDB(q, ub1, 1);
-        MOE_VMCNT(16);
+            // the conversion of the next column, of the next step's first in the last one: two of its twelve
+            // instructions behind each of six multiplications
+            if constexpr (AF16 && (m & 7) < 6) {
+                u32x4 &w = j < 7 ? af[s][(j + 1) & 7] : af[1 - s][0];
+                convert(integral_constant<int, 2 * (m & 7)>{}, w);
+                convert(integral_constant<int, 2 * (m & 7) + 1>{}, w);
+            }
+            MOE_SB();
+        });
+        if constexpr (KIND != kLast) advance();
+    };
+    // In front of step p of a tile: its fragments have been read by every wavefront, so that its place is
+    // free, and the step behind it is there.  A tile begins with its first three steps landed, the fourth on its way
+    // and, younger than that, up to 64 stores of the tile before.
+    auto turn = [&](int p) {
+        MOE_SB();
+        __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0), in a form that the compiler's own counting sees
+        if (p >= 3) MOE_VMCNT(24);               // three steps of loads may be on their way behind that one
+        else MOE_VMCNT(63);
         MOE_BAR();
-        static_for<32>([&](auto v) { read(integral_constant<int, 0>{}, v, ub, ua, 0); });
-        for (int kt = 0; kt < KT; ++kt) {
-            step(integral_constant<int, 0>{}, [&](auto mc) {
-                constexpr int m = decltype(mc)::value;
-                if constexpr (m < 32) read(integral_constant<int, 1>{}, mc, ub, ua, 1);
-                else if constexpr (m % 4 == 0) WG4_LDA((m - 32) / 4, uf, kt + 2);
-            });
-            MOE_LGKM0();
-            MOE_VMCNT(8);                        // stage kt + 1 has landed; A of kt + 2 may be on its way
-            MOE_BAR();
-            step(integral_constant<int, 1>{}, [&](auto mc) {
-                constexpr int m = decltype(mc)::value;
-                if constexpr (m < 32) read(integral_constant<int, 0>{}, mc, ub1, ua1, 0);
-                if constexpr (m < 32 && m % 4 == 1) WG4_LDB(m / 4, ua, kt + 2);
-            });
-            const int na1 = uf, nb1 = ua, nf = ub;
-            ua = ua1;
-            ub = ub1;
-            ua1 = na1;
-            ub1 = nb1;
-            uf = nf;
-        }
-#undef WG4_LDB
-#undef WG4_LDA
-        MOE_VMCNT(0);
-        MOE_LGKM0();
-        MOE_BAR();
-        MOE_MATRIX_RESULTS();
-    }
+    };
+    using S0 = integral_constant<int, 0>;
+    using S1 = integral_constant<int, 1>;
+    using First = integral_constant<int, kFirst>;
+    using Middle = integral_constant<int, kMiddle>;
+    using Last = integral_constant<int, kLast>;
 
-    // acc[i][j][c]: column n0 + wn * 128 + i * 16 + oct * 4 + c, row m0 + wm * 128 + j * 16 + fr.
-    // The tile leaves through LDS, 64 columns of the wavefront's 128 x 128 at a time (a patch of
-    // 128 rows, pitch 272 bytes, per wavefront), as whole lines, 16 bytes per lane.
-    float *Ce = C + static_cast<size_t>(expert) * M * N;
-    constexpr int PITCH = 272;
-    char *patch = lds + wave * 128 * PITCH;
+    open();
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-#pragma unroll
-        for (int i = 0; i < TN / 2; ++i) {
-#pragma unroll
-            for (int j = 0; j < TM; ++j)
-                *reinterpret_cast<f32x4 *>(patch + (j * 16 + fr) * PITCH + (i * 16 + 4 * oct) * 4) =
-                    acc[half * 4 + i][j];
-            MOE_SB();      // a few accumulator registers at a time leave the AGPRs
-        }
-        MOE_LGKM0();
-        __builtin_amdgcn_wave_barrier();
-        const int n = n0 + wn * 128 + half * 64 + (lane & 15) * 4;
-#pragma unroll 8
-        for (int it = 0; it < 32; ++it) {
-            const int rr = it * 4 + (lane >> 4);
-            const f32x4 q = *reinterpret_cast<const f32x4 *>(patch + rr * PITCH + (lane & 15) * 16);
-            const int m = m0 + wm * 128 + rr;
-            if (m < M && n < N) __builtin_nontemporal_store(q, reinterpret_cast<f32x4 *>(Ce + static_cast<size_t>(m) * N + n));
-        }
-        MOE_LGKM0();
-        __builtin_amdgcn_wave_barrier();
+    for (int p = 0; p < RING - 1; ++p) {
+        aim();
+        static_for<8>([&](auto v) { load(v, p * STEP); });
+        advance();
     }
+    MOE_VMCNT(0);
+    MOE_BAR();
+    static_for<32>([&](auto v) { read(S0{}, v, 0); });
+    if constexpr (AF16) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) af[0][0][c] = f16x2_to_bf16x2(af[0][0][c]);
+    }
+    int at = 0;
+    for (; tile < end; tile += stride) {
+        const Tile t = tile_at(tile);
+        const int steps = t.steps();
+        turn(0);
+        step(S0{}, First{}, at);
+        at = next(at);
+        int p = 1;
+        for (; p < steps - 1; p += 2) {
+            turn(p);
+            step(S1{}, Middle{}, at);
+            at = next(at);
+            turn(p + 1);
+            step(S0{}, Middle{}, at);
+            at = next(at);
+        }
+        turn(p);
+        step(S1{}, Last{}, at);
+        // acc[i][j][c]: column n0 + wn * 128 + i * 16 + oct * 4 + c, row m0 + wm * 128 + j * 16 + fr.  16 rows at a
+        // time go through the wavefront's quarter of the last step's place, the 16-byte pieces of a row
+        // XOR-swizzled with the row, and leave as two whole rows of 128 columns per instruction.  (LDS takes a
+        // wavefront's accesses in order: nothing is waited for in between.)
+        MOE_MATRIX_RESULTS();
+        MOE_VMCNT(8);
+        float *out = C + (static_cast<size_t>(t.expert) * M + t.m0 + wm * 128) * N + t.n0 + wn * 128;
+        const __amdgpu_buffer_rsrc_t rsc = __builtin_amdgcn_make_buffer_rsrc(out, 0, 128u * static_cast<unsigned>(N) * 4u, 0x00020000);
+        char *const patch = lds + at + wave * 8192;
+        const int out_lane = (lane >> 5) * N * 4 + (lane & 31) * 16;
+        u32x4 line[2][8];
+        auto through = [&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+                *reinterpret_cast<f32x4 *>(patch + fr * 512 + (((i * 4 + oct) ^ fr) << 4)) = acc[i][j];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int row = 2 * q + (lane >> 5);
+                line[j & 1][q] = *reinterpret_cast<const u32x4 *>(patch + row * 512 + (((lane & 31) ^ row) << 4));
+            }
+            MOE_SB();
+        };
+        auto leave = [&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                __builtin_amdgcn_raw_buffer_store_b128(line[j & 1][q], rsc, out_lane, (j * 16 + 2 * q) * N * 4, 2);
+            MOE_SB();
+        };
+        static_for<TM>([&](auto jc) {
+            through(jc);
+            if constexpr (decltype(jc)::value > 0) leave(std::integral_constant<int, decltype(jc)::value - 1>{});
+        });
+        leave(std::integral_constant<int, TM - 1>{});
+        at = next(at);
+    }
+    MOE_VMCNT(0);
 }
 
 // ---------------------------------------------------------------- gate backward
@@ -1125,7 +1204,7 @@ void launch_wgrad(const uint16_t *A, const uint16_t *B, float *C, const int32_t 
         static PerDeviceOnce once;
         once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kLds4));
         const int tiles_m = M / 256, tiles_n = N / 256;
-        const int grid = static_cast<int>(align_up(static_cast<size_t>(E) * tiles_m * tiles_n, 8));
+        const int grid = 256;            // one block per compute unit (a block has all of its LDS)
         prof_kernel_events(stage, &t0, &t1);
         hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), kLds4, st, t0, t1, 0, A, B, C, offsets, E, M,
                               N, tiles_m, tiles_n);

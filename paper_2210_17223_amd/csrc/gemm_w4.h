@@ -59,13 +59,18 @@ constexpr size_t kW4Lds = w4_lds(256, 256);
 // close, registers moved on the way round a loop among it, tests/test_matrix_hazards.py reads
 // back from the built library.  (Two wait states at the top of every stage: gpt2s-sized layers, 8192
 // rows of 768 x 3072, 61.5 -> 61.9 us in the first GEMM.)
-template <bool F16, bool WAIT>
+// ZERO: the accumulator starts at zero.
+template <bool F16, bool WAIT, bool ZERO = false>
 __device__ __forceinline__ void mfma_16x16x32_agpr(f32x4 &acc, const u32x4 &a, const u32x4 &b)
 {
     if constexpr (F16 && WAIT)
         asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
     else if constexpr (F16)
         asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    else if constexpr (ZERO && WAIT)
+        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(a), "v"(b));
+    else if constexpr (ZERO)
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(a), "v"(b));
     else if constexpr (WAIT)
         asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
     else

@@ -297,7 +297,7 @@ __global__ __launch_bounds__(512, 2) void bwd_gemm_kernel(
 // ---------------------------------------------------------------- GEMM, four wavefronts
 // The same three products on the forward's four-wavefront layout (gemm_w4.h).  The tile leaves through LDS as
 // whole lines (16-bit outputs) or straight from the registers (fp32); for EPI 2 the tile of
-// pre-activations comes in through the same LDS patch, as whole lines.
+// pre-activations is in LDS when the loop ends.
 template <int EPI, int ACT, bool KTAIL, int BM, int BN>
 __global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void bwd_gemm_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, void *__restrict__ Cout,
@@ -307,12 +307,10 @@ __global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void bwd_gemm_w4_kerne
     constexpr int ABL = 0;
     const int32_t *const row_src = nullptr, *const nitems = nullptr;   // packed rows, the plan's list
     constexpr int row_div = 1, a_rows = 0;
+    constexpr bool TILE_IN = EPI == 2;
+    const uint16_t *const tile_in = reinterpret_cast<const uint16_t *>(Pbuf);
 #include "gemm_w4_body.inc"
 
-    // Every wavefront is past its last LDS read after the barrier.
-    MOE_LGKM0();
-    MOE_BAR();
-    MOE_MATRIX_RESULTS();
     const int rbase = item.row0 + wm * (BM / 2);
     if constexpr (EPI == 0) {
         float *out = static_cast<float *>(Cout);
@@ -329,62 +327,74 @@ __global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void bwd_gemm_w4_kerne
             }
             MOE_SB();          // a few accumulator registers at a time leave the AGPRs
         }
+    } else if constexpr (EPI == 2) {
+        // The pre-activations are turned into dP in their places, 32 rows at a time, which leave while the next
+        // are computed.
+        constexpr int LPR = BN / 16, RPI = 64 / LPR;
+        const int unit[4] = {RING5 ? ua : uw, RING5 ? uw : uw1, ua1, uw1};
+        const int ncol = n0 + wn * (BN / 2) + lane % LPR * 8;
+        uint16_t *out = static_cast<uint16_t *>(Cout);
+        MOE_VMCNT(TILE_UNITS == 4 ? 2 * TILE_LOADS : 0);
+        f16x4 p[2][TN];
+        auto place = [&](int i, int j) {
+            const int row = (j & 1) * 16 + fr;
+            return lds + unit[j >> 1] + wave * (W_UNIT / 4) + row * BN + (((2 * i + (oct >> 1)) ^ tile_key(row)) << 4) +
+                   (oct & 1) * 8;
+        };
+#pragma unroll
+        for (int i = 0; i < TN; ++i) p[0][i] = *reinterpret_cast<const f16x4 *>(place(i, 0));
+#pragma unroll
+        for (int u = 0; u < TILE_UNITS; ++u) {
+            char *const patch = lds + unit[u] + wave * (W_UNIT / 4);
+#pragma unroll
+            for (int j = 2 * u; j < 2 * u + 2; ++j) {
+                if (j + 1 < TM) {                // (ahead of the writes, which the compiler would keep in front)
+#pragma unroll
+                    for (int i = 0; i < TN; ++i) p[(j + 1) & 1][i] = *reinterpret_cast<const f16x4 *>(place(i, j + 1));
+                }
+#pragma unroll
+                for (int i = 0; i < TN; ++i) {
+                    float a[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        a[c] = acc[i][j][c] * act_derivative<ACT>(static_cast<float>(p[j & 1][i][c]));
+                    store_bf16x4(reinterpret_cast<uint16_t *>(place(i, j)), a);
+                    if (i % 4 == 3) MOE_SB();   // a few accumulator registers at a time leave the AGPRs
+                }
+            }
+            // (the last units, before any store is: nothing younger than they)
+            if (u == 0 && TILE_UNITS == 4) MOE_VMCNT(0);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int it = 0; it < 32 / RPI; ++it) {
+                const int rr = it * RPI + lane / LPR, r = rbase + u * 32 + rr;
+                const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * BN + ((lane % LPR ^ tile_key(rr)) << 4));
+                if (r < item.row1 && ncol < N)
+                    *reinterpret_cast<u32x4 *>(out + static_cast<size_t>(r) * N + ncol) = q;
+            }
+            MOE_SB();
+        }
     } else {
         // the wavefront's BM / 2 x BN / 2 patch of 16-bit values; lanes per row, rows per instruction
         constexpr int PITCH = BN + 16, LPR = BN / 16, RPI = 64 / LPR;
         char *patch = lds + wave * (BM / 2) * PITCH;
         const int ncol = n0 + wn * (BN / 2) + lane % LPR * 8;
-        // whole row pieces between the patch and a [rows, N] matrix of 16-bit values
-        auto lines_out = [&](uint16_t *dst) {
-#pragma unroll 8
-            for (int it = 0; it < BM / 2 / RPI; ++it) {
-                const int rr = it * RPI + lane / LPR;
-                const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * PITCH + lane % LPR * 16);
-                const int r = rbase + rr;
-                if (r < item.row1 && ncol < N)
-                    *reinterpret_cast<u32x4 *>(dst + static_cast<size_t>(r) * N + ncol) = q;
-            }
-        };
-        if constexpr (EPI == 2) {
-            const uint16_t *src = reinterpret_cast<const uint16_t *>(Pbuf);
-#pragma unroll 8
-            for (int it = 0; it < BM / 2 / RPI; ++it) {
-                const int rr = it * RPI + lane / LPR;
-                const int r = rbase + rr;
-                u32x4 q = {0u, 0u, 0u, 0u};
-                if (r < item.row1 && ncol < N)
-                    q = *reinterpret_cast<const u32x4 *>(src + static_cast<size_t>(r) * N + ncol);
-                *reinterpret_cast<u32x4 *>(patch + rr * PITCH + lane % LPR * 16) = q;
-            }
-            MOE_LGKM0();
-            __builtin_amdgcn_wave_barrier();
-        }
 #pragma unroll
-        for (int pass = EPI == 1 ? 0 : 1; pass < 2; ++pass) {     // EPI 1, pass 0: the pre-activations
+        for (int pass = 0; pass < 2; ++pass) {     // pass 0: the pre-activations
 #pragma unroll
             for (int i = 0; i < TN; ++i) {
 #pragma unroll
                 for (int j = 0; j < TM; ++j) {
                     char *at = patch + (j * 16 + fr) * PITCH + (i * 16 + 4 * oct) * 2;
-                    float v[4];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) v[c] = acc[i][j][c];
-                    if (EPI == 1 && pass == 0) {
+                    if (pass == 0) {
                         f16x4 p;
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) p[c] = static_cast<_Float16>(v[c]);
+                        for (int c = 0; c < 4; ++c) p[c] = static_cast<_Float16>(acc[i][j][c]);
                         *reinterpret_cast<f16x4 *>(at) = p;
                     } else {
                         float a[4];
-                        if constexpr (EPI == 1) {
 #pragma unroll
-                            for (int c = 0; c < 4; ++c) a[c] = act_value<ACT>(v[c]);
-                        } else {
-                            const f16x4 p = *reinterpret_cast<const f16x4 *>(at);
-#pragma unroll
-                            for (int c = 0; c < 4; ++c)
-                                a[c] = v[c] * act_derivative<ACT>(static_cast<float>(p[c]));
-                        }
+                        for (int c = 0; c < 4; ++c) a[c] = act_value<ACT>(acc[i][j][c]);
                         store_bf16x4(reinterpret_cast<uint16_t *>(at), a);
                     }
                     if (j == TM / 2 - 1) MOE_SB();
@@ -393,9 +403,17 @@ __global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void bwd_gemm_w4_kerne
             }
             MOE_LGKM0();
             __builtin_amdgcn_wave_barrier();
-            lines_out(EPI == 1 && pass == 0 ? reinterpret_cast<uint16_t *>(Pbuf)
-                                            : static_cast<uint16_t *>(Cout));
-            if (EPI == 1 && pass == 0) {
+            // whole row pieces from the patch to a [rows, N] matrix of 16-bit values
+            uint16_t *dst = pass == 0 ? reinterpret_cast<uint16_t *>(Pbuf) : static_cast<uint16_t *>(Cout);
+#pragma unroll 8
+            for (int it = 0; it < BM / 2 / RPI; ++it) {
+                const int rr = it * RPI + lane / LPR;
+                const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * PITCH + lane % LPR * 16);
+                const int r = rbase + rr;
+                if (r < item.row1 && ncol < N)
+                    *reinterpret_cast<u32x4 *>(dst + static_cast<size_t>(r) * N + ncol) = q;
+            }
+            if (pass == 0) {
                 MOE_LGKM0();
                 __builtin_amdgcn_wave_barrier();
             }

@@ -530,14 +530,13 @@ __device__ __forceinline__ void w4_gemm_tile(
     const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int N, int K,
     const int32_t *__restrict__ row_src, int row_div, int a_rows)
 {
+    constexpr bool TILE_IN = false;
+    const uint16_t *const tile_in = nullptr;
 #include "gemm_w4_body.inc"
 
-    // Epilogue.  Every wavefront is past its last LDS read after the barrier.  The wavefront's
+    // Epilogue.  The wavefront's
     // BM / 2 x BN / 2 sub-tile goes to its own patch (16 bytes of row padding) and leaves as whole
     // lines, 16 bytes per lane.
-    MOE_LGKM0();
-    MOE_BAR();
-    MOE_MATRIX_RESULTS();
     constexpr int PITCH = BN + 16, LPR = BN / 16, RPI = 64 / LPR;   // lanes per row, rows per instruction
     char *patch = lds + wave * (BM / 2) * PITCH;
     const float *bexp = bias != nullptr ? bias + static_cast<size_t>(item.expert) * N : nullptr;

@@ -126,6 +126,26 @@ def test_backward_matches_the_oracle(name, keep):
     assert not got["dx"].reshape(T, d)[dropped].any()
 
 
+# dP's GEMM over d: one, two and three stages of 64 and a tail, on 256 x 256 (many tiles), 128 x 128 and 128 x 256
+# tiles (long contractions), with rows and columns that end inside a tile
+@pytest.mark.parametrize("keep", [False, True], ids=["recompute", "keep"])
+@pytest.mark.parametrize("T,h,d", [(6000, 8712, 40), (6000, 8712, 64), (6000, 8712, 136), (6000, 8712, 192),
+                                   (600, 264, 8), (600, 264, 64), (600, 264, 72), (600, 264, 128), (600, 264, 200),
+                                   (4000, 1608, 3080)])
+def test_backward_of_few_stages(T, h, d, keep):
+    # one expert with every token: gate weight 1, no gradient through the gate, dx = dP W1^T
+    li = wl.make_layer(wl.scaled("gpt2s_moe", T=T, d=d, h=h, E=1, k=1, cf=1.0), seed=5)
+    got, _ = run_backward(li, keep=keep, with_oracle=False)
+    f64 = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV).double()
+    x, W1, W2 = f64(li.x), f64(li.W1[0]), f64(li.W2[0])
+    dy = f64(np.random.Generator(np.random.PCG64(77)).standard_normal((T, d)).astype(np.float32))
+    P = x @ W1
+    cdf = 0.5 * (1.0 + torch.erf(P / math.sqrt(2.0)))
+    dP = (dy @ W2.T) * (cdf + P * torch.exp(-0.5 * P * P) / math.sqrt(2.0 * math.pi))
+    for name, ref in (("dx", dP @ W1.T), ("dW1", x.T @ dP), ("dW2", (P * cdf).T @ dy)):
+        assert rel_rms_err(got[name].reshape(ref.shape), ref.cpu().numpy()) <= TOL, name
+
+
 def test_backward_is_bitwise_reproducible():
     # fixed-order sums everywhere (no floating-point atomics): two runs, the same bits
     li = wl.make_layer(CASES[list(CASES)[0]], seed=3)

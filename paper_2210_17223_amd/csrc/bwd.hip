@@ -1098,8 +1098,8 @@ struct BwdWorkspace {
 GemmPlan plan_rows(int N, int K, int64_t max_rows, int E)
 {
     GemmPlan gp;
-    constexpr uint64_t most = (1ull << 31) - 64;       // byte offsets into the operands
-    if (static_cast<uint64_t>(N) * K * 2 < most && 256ull * K * 2 < most) {
+    constexpr uint64_t most = (1ull << 31) - 64;       // byte offsets into the operands and a tile's rows
+    if (static_cast<uint64_t>(N) * K * 2 < most && 256ull * K * 2 < most && 256ull * N * 2 < most) {
         choose_w4_tile(max_rows, E, N, K, &gp);
     } else {
         gp.bm = kBM;

@@ -405,6 +405,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void grouped_gemm_staged_kernel(
 }
 
 #include "gemm_w4.h"
+#include "gemm_w4_run.h"
 
 // ---------------------------------------------------------------- few rows per expert
 // The same product for decode steps: a few rows per expert, so the time is that of streaming the
@@ -520,16 +521,86 @@ __global__ __launch_bounds__(64, 3) void grouped_gemm_stream_kernel(
         body(integral_constant<int, 2>{}, integral_constant<int, 5>{});
 }
 
+// BM x 256 tiles, a share of them per block (gemm_w4_run.h).
 // ABL (measurement only, 0 in the layer): bit 0 leaves out the MFMAs, bit 1 the LDS fragment
 // reads after the first step, bit 2 the global loads into LDS inside the loop, bit 3 the
 // output stores.  Results are then wrong by construction; every access stays inside the buffers.
-template <bool F16, int ACT, bool KEEP, bool KTAIL, int BM, int BN, int ABL>
+template <bool F16, int ACT, bool KEEP, bool KTAIL, int BM, int ABL>
+__device__ __forceinline__ void run_gemm_tiles(
+    const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
+    const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
+    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int entries, int N, int K,
+    const int32_t *__restrict__ row_src, int row_div, int a_rows)
+{
+    constexpr int TN = 8, JU = W4Place<BM>::UR / 16;
+    struct Bias { float at[TN][4]; };
+    auto prepare = [&](const WorkItem &item, int wn, int oct) {
+        Bias b4;
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) b4.at[i][c] = 0.0f;
+        if (bias != nullptr) {
+            const float *bexp = bias + static_cast<size_t>(item.expert) * N;
+            const int n = item.n0 + wn * 128 + 4 * oct;
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) b4.at[i][c] = bexp[min(n + i * 16 + c, N - 1)];
+        }
+        return b4;
+    };
+    w4_run<F16, KTAIL, BM, ABL>(A, W, items, nitems, entries, N, K, row_src, row_div, a_rows, prepare, [&](
+        auto &acc, const Bias &b4, const WorkItem &item, const W4Place<BM> &place, auto landed) {
+        WorkItem stored = item;
+        if constexpr (ABL & 8) stored.row1 = 0;
+        // a unit of rows is stored while the next one is computed
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+#pragma unroll
+            for (int pass = KEEP ? 0 : 1; pass < 2; ++pass) {      // pass 0: pre-activations, 1: outputs
+#pragma unroll
+                for (int j = u * JU; j < (u + 1) * JU; ++j) {
+#pragma unroll
+                    for (int i = 0; i < TN; ++i) {
+                        float v[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const float sum = acc[i][j][c] + b4.at[i][c];
+                            v[c] = pass == 0 ? sum : activate<ACT, true>(sum);
+                        }
+                        store4(reinterpret_cast<_Float16 *>(place.at(i, j)), v);
+                        if (i % 4 == 3) MOE_SB();   // a few accumulator registers at a time leave the AGPRs
+                    }
+                }
+                if (u == 0 && pass == (KEEP ? 0 : 1)) landed();
+                place.leave(reinterpret_cast<uint16_t *>(pass == 0 ? Pre : C), stored, u, N);
+            }
+        }
+    });
+}
+
+template <bool F16, int ACT, bool KEEP, bool KTAIL, int ABL = 0>
+__global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
+    const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
+    const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
+    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int entries, int N, int K,
+    const int32_t *__restrict__ row_src, int row_div, int a_rows)
+{
+    run_gemm_tiles<F16, ACT, KEEP, KTAIL, 256, ABL>(A, W, bias, C, Pre, items, nitems, entries, N, K, row_src,
+                                                    row_div, a_rows);
+}
+
+// 128 x 128 tiles, one per block
+template <bool F16, int ACT, bool KEEP, bool KTAIL>
 __device__ __forceinline__ void w4_gemm_tile(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
-    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int N, int K,
+    const WorkItem *__restrict__ items, int N, int K,
     const int32_t *__restrict__ row_src, int row_div, int a_rows)
 {
+    constexpr int BM = 128, BN = 128, ABL = 0;
+    const int32_t *const nitems = nullptr;
     constexpr bool TILE_IN = false;
     const uint16_t *const tile_in = nullptr;
 #include "gemm_w4_body.inc"
@@ -573,7 +644,7 @@ __device__ __forceinline__ void w4_gemm_tile(
             const int rr = it * RPI + lane / LPR;
             const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + rr * PITCH + lane % LPR * 16);
             const int r = rbase + rr;
-            if (r < item.row1 && ncol < N && (!(ABL & 8) || q[0] == 0x7fc07fc1u))
+            if (r < item.row1 && ncol < N)
                 *reinterpret_cast<u32x4 *>(out + static_cast<size_t>(r) * N + ncol) = q;
         }
         if (pass == 0) {
@@ -583,28 +654,19 @@ __device__ __forceinline__ void w4_gemm_tile(
     }
 }
 
-// 256 x 256 tiles
-template <bool F16, int ACT, bool KEEP, bool KTAIL, int ABL = 0>
-__global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
-    const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
-    const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
-    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int N, int K,
-    const int32_t *__restrict__ row_src, int row_div, int a_rows)
-{
-    w4_gemm_tile<F16, ACT, KEEP, KTAIL, 256, 256, ABL>(A, W, bias, C, Pre, items, nitems, N, K, row_src,
-                                                       row_div, a_rows);
-}
-
 // 128 x BN tiles
 template <bool F16, int ACT, bool KEEP, bool KTAIL, int BN>
 __global__ __launch_bounds__(256, BN == 128 ? 2 : 1) void grouped_gemm_mfma_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
-    const WorkItem *__restrict__ items, int N, int K,
+    const WorkItem *__restrict__ items, int entries, int N, int K,
     const int32_t *__restrict__ row_src, int row_div, int a_rows)
 {
-    w4_gemm_tile<F16, ACT, KEEP, KTAIL, 128, BN, 0>(A, W, bias, C, Pre, items, nullptr, N, K, row_src,
-                                                    row_div, a_rows);
+    if constexpr (BN == 256)
+        run_gemm_tiles<F16, ACT, KEEP, KTAIL, 128, 0>(A, W, bias, C, Pre, items, nullptr, entries, N, K, row_src,
+                                                      row_div, a_rows);
+    else
+        w4_gemm_tile<F16, ACT, KEEP, KTAIL>(A, W, bias, C, Pre, items, N, K, row_src, row_div, a_rows);
 }
 #undef MOE_LGKM0
 #undef MOE_VMCNT
@@ -698,11 +760,11 @@ void launch_mfma_cfg(const uint16_t *A, const uint16_t *W, const float *bias, TO
 
 // The four-wavefront kernel addresses its operands with 32-bit byte offsets into buffer
 // resources (the expert's weight matrix; the tile's rows, or the whole token matrix when the
-// rows are gathered).
+// rows are gathered; the tile's rows of the output, where 0x7ff00000 lies past every one).
 inline bool w4_kernel_fits(int N, int K, bool gathered, uint64_t row_limit)
 {
     constexpr uint64_t most = (1ull << 31) - 64;
-    return static_cast<uint64_t>(N) * K * 2 < most &&
+    return static_cast<uint64_t>(N) * K * 2 < most && 256ull * N * 2 < most - (1 << 20) &&
            (gathered ? row_limit * static_cast<uint64_t>(K) : 256ull * K) * 2 < most;
 }
 
@@ -717,25 +779,29 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
                                                               gp.max_items, N, K, stage, st,       \
                                                               row_src, row_div)
     if (gp.w4) {
-        auto launch = [&](auto kern, PerDeviceOnce &once, size_t lds, auto... list) {
+        // tiles of 256 columns: one block per compute unit (a block has all of its LDS), which takes every
+        // 256th entry of the list
+        const bool run = gp.bn == 256;
+        auto launch = [&](auto kern, PerDeviceOnce &once, auto... list) {
+            const size_t lds = run ? kW4RunLds : w4_lds(128, 128);
             once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
             hipEvent_t t0, t1;
             prof_kernel_events(stage, &t0, &t1);
-            hipExtLaunchKernelGGL(kern, dim3(gp.max_items), dim3(256), lds, st, t0, t1, 0, A, W, bias, C, pre,
-                                  items, list..., N, K, row_src, row_div, static_cast<int>(row_limit));
+            hipExtLaunchKernelGGL(kern, dim3(run ? std::min(gp.max_items, 256) : gp.max_items), dim3(256), lds, st, t0,
+                                  t1, 0, A, W, bias, C, pre, items, list..., gp.max_items, N, K, row_src, row_div,
+                                  static_cast<int>(row_limit));
         };
         auto shape = [&](auto tail) {
             constexpr bool TAIL = decltype(tail)::value;
             static PerDeviceOnce once[3];
             if (gp.bm == 256)
-                launch(grouped_gemm_w4_kernel<F16, ACT, KEEP, TAIL>, once[0], w4_lds(256, 256),
-                       static_cast<const int32_t *>(nullptr));
-            else if (gp.bn == 256)
-                launch(grouped_gemm_mfma_kernel<F16, ACT, KEEP, TAIL, 256>, once[1], w4_lds(128, 256));
+                launch(grouped_gemm_w4_kernel<F16, ACT, KEEP, TAIL>, once[0], static_cast<const int32_t *>(nullptr));
+            else if (run)
+                launch(grouped_gemm_mfma_kernel<F16, ACT, KEEP, TAIL, 256>, once[1]);
             else
-                launch(grouped_gemm_mfma_kernel<F16, ACT, KEEP, TAIL, 128>, once[2], w4_lds(128, 128));
+                launch(grouped_gemm_mfma_kernel<F16, ACT, KEEP, TAIL, 128>, once[2]);
         };
-        if (K % 64 == 0)
+        if (K % 64 == 0 && (!run || K >= 256))
             shape(std::false_type{});
         else
             shape(std::true_type{});
@@ -796,17 +862,21 @@ moe_status launch_calib_gemm(const uint16_t *A, const uint16_t *W, _Float16 *C, 
                              const int32_t *nitems, int max_items, int N, int K, int abl, int gelu,
                              hipStream_t st)
 {
-    constexpr size_t lds = kW4Lds;
-    const int grid = static_cast<int>(align_up(static_cast<size_t>(max_items), 8));
+    constexpr size_t lds = kW4RunLds;
+    const int entries = static_cast<int>(align_up(static_cast<size_t>(max_items), 8)), grid = std::min(entries, 256);
 #define MOE_CALIB_CASE(ABL_)                                                                      \
     case ABL_: {                                                                                  \
-        auto k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, false, ABL_>;                   \
-        auto k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, false, ABL_>;                   \
+        auto k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, true, ABL_>;                    \
+        auto k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, true, ABL_>;                    \
+        if (K >= 256) {                                                                           \
+            k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, false, ABL_>;                    \
+            k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, false, ABL_>;                    \
+        }                                                                                         \
         static PerDeviceOnce once1, once0;                                                        \
         once1.raise_lds(reinterpret_cast<const void *>(k1), static_cast<int>(lds));               \
         once0.raise_lds(reinterpret_cast<const void *>(k0), static_cast<int>(lds));               \
         hipLaunchKernelGGL(gelu ? k1 : k0, dim3(grid), dim3(256), lds, st, A, W, nullptr, C,      \
-                           nullptr, items, nitems, N, K, nullptr, 1, 0);                          \
+                           nullptr, items, nitems, entries, N, K, nullptr, 1, 0);                          \
         break;                                                                                    \
     }
     switch (abl) {

@@ -1,7 +1,7 @@
 // The tile GEMMs on four wavefronts: what its kernels share.  Included inside the
 // translation unit's own namespace; the loop itself is gemm_w4_body.inc, included in the body
-// of every kernel that runs it (the forward's expert GEMMs, the backward's row GEMMs), each
-// with an epilogue of its own.
+// of every kernel that runs it for one tile (the forward's 128 x 128 tiles, the backward's row GEMMs), each
+// with an epilogue of its own, and gemm_w4_run.h's for the forward's other tiles.
 #pragma once
 
 #include <type_traits>
@@ -70,6 +70,8 @@ __device__ __forceinline__ void mfma_16x16x32_agpr(f32x4 &acc, const u32x4 &a, c
 {
     if constexpr (F16 && WAIT)
         asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    else if constexpr (F16 && ZERO)
+        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=a"(acc) : "v"(a), "v"(b));
     else if constexpr (F16)
         asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
     else if constexpr (ZERO && WAIT)

@@ -340,6 +340,37 @@ def test_large_tile_kernel_with_a_short_contraction(d, h, which):
     assert rel_rms_err(ye[:o.A], ye_ref) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("T,d,h,which,kernel", [(4096, 1032, 8200, 0, "grouped_gemm_w4_kernel"),
+                                                (4096, 8200, 1032, 1, "grouped_gemm_w4_kernel"),
+                                                (2560, 3080, 2824, 0, "grouped_gemm_mfma_kernel 128x256"),
+                                                (2560, 2824, 3080, 1, "grouped_gemm_mfma_kernel 128x256")])
+def test_tiles_that_follow_on_in_a_block(T, d, h, which, kernel):
+    """GEMM `which` has several tiles of 256 columns per block, whose loads run on from one to the next: another
+    expert, fewer rows, the matrix's last columns, a contraction that is no multiple of a stage; token rows gathered (the
+    layer) and packed (the FFN alone).  Against fp64 products of the same operands."""
+    li = wl.make_layer(wl.scaled("skewed", T=T, d=d, h=h, E=4, k=2, cf=1.2), seed=8, threads=8)
+    prng = np.random.Generator(np.random.PCG64(6))
+    b1, b2 = ((prng.standard_normal((li.E, n)) * 0.05).astype(np.float32) for n in (h, d))
+    s = shape_of(li)
+    assert moe.moe_expert_gemm_kernel(s, which).startswith(kernel)
+    L = DeviceLayer(li, s, b1=b1, b2=b2)
+    L.layer(1)
+    b, ints = L.b, L.ints()
+    off, A = ints["off"], int(ints["off"][-1])
+    ye2 = torch.zeros_like(b["ye"])
+    moe.moe_expert_ffn(s, b["xe"], b["offsets"], b["W1p"], L.b1, b["W2p"], L.b2, ye2, b["workspace"])
+    torch.cuda.synchronize()
+    assert torch.equal(ye2[:A * d].view(torch.int16), b["ye"][:A * d].view(torch.int16))
+    assert not ye2[A * d:].any()
+    f64 = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV).double()
+    xe = L.x.view(T, d)[torch.from_numpy(ints["src_of"]).to(DEV).long() // li.k].double()
+    for e in range(li.E):
+        rows = slice(int(off[e]), int(off[e + 1]))
+        P = xe[rows] @ f64(li.W1[e]) + f64(b1[e])
+        want = (0.5 * P * (1.0 + torch.erf(P / 2.0 ** 0.5))) @ f64(li.W2[e]) + f64(b2[e])
+        assert rel_rms_err(ye2.view(-1, d)[rows].float().cpu().numpy(), want.cpu().numpy()) <= TOL["bf16"], e
+
+
 def test_layer_is_bitwise_reproducible():
     # no floating-point atomics on the path: the same call gives the same bits, also when
     # the output buffers hold other values beforehand and other work ran in between

@@ -307,7 +307,7 @@ __global__ __launch_bounds__(256, BM + BN == 256 ? 2 : 1) void bwd_gemm_w4_kerne
     constexpr int ABL = 0;
     const int32_t *const row_src = nullptr, *const nitems = nullptr;   // packed rows, the plan's list
     constexpr int row_div = 1, a_rows = 0;
-    constexpr bool TILE_IN = EPI == 2;
+    constexpr bool TILE_IN = EPI == 2, DEEP = false;
     const uint16_t *const tile_in = reinterpret_cast<const uint16_t *>(Pbuf);
 #include "gemm_w4_body.inc"
 

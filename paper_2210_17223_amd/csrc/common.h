@@ -63,6 +63,7 @@ struct WorkItem {
 struct GemmPlan {
     int32_t bm, bn;          // rows / columns per output tile; bm: the most rows of a work item
     bool w4 = false;         // the four-wavefront kernels (gemm_w4.h)
+    bool deep = false;       // 128 x 128, one block per compute unit with five stages on their way
     int32_t tiles_n;         // column tiles
     int32_t max_row_tiles;   // upper bound of row tiles per list
     int32_t max_items;       // entries of a work list (a multiple of 8; surplus ones hold no tile)

@@ -591,8 +591,8 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
                                                     row_div, a_rows);
 }
 
-// 128 x 128 tiles, one per block
-template <bool F16, int ACT, bool KEEP, bool KTAIL>
+// 128 x 128 tiles, one per block; DEEP: of launches that wait for their weights, with five stages on their way
+template <bool F16, int ACT, bool KEEP, bool KTAIL, bool DEEP>
 __device__ __forceinline__ void w4_gemm_tile(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
@@ -655,8 +655,8 @@ __device__ __forceinline__ void w4_gemm_tile(
 }
 
 // 128 x BN tiles
-template <bool F16, int ACT, bool KEEP, bool KTAIL, int BN>
-__global__ __launch_bounds__(256, BN == 128 ? 2 : 1) void grouped_gemm_mfma_kernel(
+template <bool F16, int ACT, bool KEEP, bool KTAIL, int BN, bool DEEP = false>
+__global__ __launch_bounds__(256, BN == 128 && !DEEP ? 2 : 1) void grouped_gemm_mfma_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
     const WorkItem *__restrict__ items, int entries, int N, int K,
@@ -666,7 +666,7 @@ __global__ __launch_bounds__(256, BN == 128 ? 2 : 1) void grouped_gemm_mfma_kern
         run_gemm_tiles<F16, ACT, KEEP, KTAIL, 128, 0>(A, W, bias, C, Pre, items, nullptr, entries, N, K, row_src,
                                                       row_div, a_rows);
     else
-        w4_gemm_tile<F16, ACT, KEEP, KTAIL>(A, W, bias, C, Pre, items, N, K, row_src, row_div, a_rows);
+        w4_gemm_tile<F16, ACT, KEEP, KTAIL, DEEP>(A, W, bias, C, Pre, items, N, K, row_src, row_div, a_rows);
 }
 #undef MOE_LGKM0
 #undef MOE_VMCNT
@@ -783,7 +783,7 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
         // 256th entry of the list
         const bool run = gp.bn == 256;
         auto launch = [&](auto kern, PerDeviceOnce &once, auto... list) {
-            const size_t lds = run ? kW4RunLds : w4_lds(128, 128);
+            const size_t lds = run || gp.deep ? kW4RunLds : w4_lds(128, 128);
             once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
             hipEvent_t t0, t1;
             prof_kernel_events(stage, &t0, &t1);
@@ -793,11 +793,13 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
         };
         auto shape = [&](auto tail) {
             constexpr bool TAIL = decltype(tail)::value;
-            static PerDeviceOnce once[3];
+            static PerDeviceOnce once[4];
             if (gp.bm == 256)
                 launch(grouped_gemm_w4_kernel<F16, ACT, KEEP, TAIL>, once[0], static_cast<const int32_t *>(nullptr));
             else if (run)
                 launch(grouped_gemm_mfma_kernel<F16, ACT, KEEP, TAIL, 256>, once[1]);
+            else if (gp.deep)
+                launch(grouped_gemm_mfma_kernel<F16, ACT, KEEP, TAIL, 128, true>, once[3]);
             else
                 launch(grouped_gemm_mfma_kernel<F16, ACT, KEEP, TAIL, 128>, once[2]);
         };
@@ -850,10 +852,10 @@ void launch_mfma_pair(const moe_shape &s, const uint16_t *xe, const uint16_t *W1
 void expert_gemm_kernel_name(const moe_shape &s, int which, char *name, size_t len)
 {
     const GemmPlan gp = choose_gemm_plan(s, which, 1, s.T);
-    std::snprintf(name, len, "%s %dx%d",
+    std::snprintf(name, len, "%s %dx%d%s",
                   gp.w4 ? gp.bm == 256 ? "grouped_gemm_w4_kernel" : "grouped_gemm_mfma_kernel"
                         : gp.bn == 64 ? "grouped_gemm_stream_kernel" : "grouped_gemm_staged_kernel",
-                  gp.bm, gp.bn);
+                  gp.bm, gp.bn, gp.deep ? " deep" : "");
 }
 
 // Measurement aid: the 256 x 256 kernel alone on caller-made operands and work list, with
@@ -929,6 +931,15 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_launches, int64_t
             // Items of 32 rows: of 64 a popular expert's wavefronts hold three stages in flight instead of
             // five and end last (Zipf, 16, 1536 x 6144, 8 rows 198 -> 174; 32, 512 x 1024, 8 42 -> 39.5).
             gp.bm = 32; gp.bn = 64; gp.concurrent = 128;
+        } else if (K >= 1920 && (chunk_rows / 128 + s.E) * ((N + 127) / 128) <= 256 &&
+                   w4_kernel_fits(N, K, which == 0, static_cast<uint64_t>(s.T))) {
+            // a long contraction and no more tiles of 128 x 128 than compute units, however the rows are
+            // spread: it takes as long as its weights take to arrive, so each unit has five stages (80 KiB of weights) on their
+            // way instead of two and a half.  Time of the layer over that with the kernels below: 30 layers, K = 1920 .. 13952,
+            // 11 .. 610 rows per expert 0.75 .. 0.99, mean 0.92 (8 experts, 3584 x 1024, 60 rows 158 -> 118 us; 8, 9856 x 2816, 11
+            // rows 521 -> 437); K = 512 .. 1919 0.96 .. 1.05, mean 0.99.  257 .. 1400 tiles 0.82 .. 1.16, mean 1.01: a second
+            // round of few tiles takes as long as the first (8 experts, 14336 x 4096, 64 rows 1800 -> 1990 us of four layers).
+            gp.bm = gp.bn = 128; gp.concurrent = 32; gp.w4 = gp.deep = true;
         } else if ((chunk_rows / 64 + s.E / 2) * tiles_n >= 128 &&
                    (per_expert < 48 || (per_expert <= 64 && (chunk_rows / 128 + s.E / 2) * tiles_n < 256))) {
             // few rows per expert and enough 64-row tiles to keep the weight stream going: shorter

@@ -343,11 +343,15 @@ def test_large_tile_kernel_with_a_short_contraction(d, h, which):
 @pytest.mark.parametrize("T,d,h,which,kernel", [(4096, 1032, 8200, 0, "grouped_gemm_w4_kernel"),
                                                 (4096, 8200, 1032, 1, "grouped_gemm_w4_kernel"),
                                                 (2560, 3080, 2824, 0, "grouped_gemm_mfma_kernel 128x256"),
-                                                (2560, 2824, 3080, 1, "grouped_gemm_mfma_kernel 128x256")])
-def test_tiles_that_follow_on_in_a_block(T, d, h, which, kernel):
-    """GEMM `which` has several tiles of 256 columns per block, whose loads run on from one to the next: another
-    expert, fewer rows, the matrix's last columns, a contraction that is no multiple of a stage; token rows gathered (the
-    layer) and packed (the FFN alone).  Against fp64 products of the same operands."""
+                                                (2560, 2824, 3080, 1, "grouped_gemm_mfma_kernel 128x256"),
+                                                (700, 1928, 264, 0, "grouped_gemm_mfma_kernel 128x128 deep"),
+                                                (300, 264, 1920, 1, "grouped_gemm_mfma_kernel 128x128 deep"),
+                                                (300, 1096, 2008, 1, "grouped_gemm_mfma_kernel 128x128 deep")])
+def test_loads_that_run_far_ahead(T, d, h, which, kernel):
+    """GEMM `which` has several tiles of 256 columns per block, whose loads run on from one to the next -- another
+    expert, fewer rows, the matrix's last columns, a contraction that is no multiple of a stage --, or tiles of few rows
+    with five stages on their way; token rows gathered (the layer) and packed (the FFN alone).  Against fp64
+    products of the same operands."""
     li = wl.make_layer(wl.scaled("skewed", T=T, d=d, h=h, E=4, k=2, cf=1.2), seed=8, threads=8)
     prng = np.random.Generator(np.random.PCG64(6))
     b1, b2 = ((prng.standard_normal((li.E, n)) * 0.05).astype(np.float32) for n in (h, d))

@@ -114,6 +114,12 @@ inline void choose_w4_tile(int64_t rows, int E, int N, int K, GemmPlan *gp)
     }
     gp->w4 = true;
 }
+// A long contraction and no more tiles of 128 x 128 than compute units, however the rows are spread: the launch takes
+// as long as its weights take to arrive, and a unit's block has five stages on their way (GemmPlan::deep).
+inline bool few_long_tiles(int64_t rows, int E, int N, int K)
+{
+    return K >= 1920 && (rows / 128 + E) * ((N + 127) / 128) <= 256;
+}
 // The tile is chosen for the tokens that one of n_launches FFN launches has on average, the list bounded for
 // `tokens`, the most that one has.
 GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_launches, int64_t tokens);

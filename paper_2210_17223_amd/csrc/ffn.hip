@@ -931,14 +931,11 @@ GemmPlan choose_gemm_plan(const moe_shape &s, int which, int n_launches, int64_t
             // Items of 32 rows: of 64 a popular expert's wavefronts hold three stages in flight instead of
             // five and end last (Zipf, 16, 1536 x 6144, 8 rows 198 -> 174; 32, 512 x 1024, 8 42 -> 39.5).
             gp.bm = 32; gp.bn = 64; gp.concurrent = 128;
-        } else if (K >= 1920 && (chunk_rows / 128 + s.E) * ((N + 127) / 128) <= 256 &&
-                   w4_kernel_fits(N, K, which == 0, static_cast<uint64_t>(s.T))) {
-            // a long contraction and no more tiles of 128 x 128 than compute units, however the rows are
-            // spread: it takes as long as its weights take to arrive, so each unit has five stages (80 KiB of weights) on their
-            // way instead of two and a half.  Time of the layer over that with the kernels below: 30 layers, K = 1920 .. 13952,
-            // 11 .. 610 rows per expert 0.75 .. 0.99, mean 0.92 (8 experts, 3584 x 1024, 60 rows 158 -> 118 us; 8, 9856 x 2816, 11
-            // rows 521 -> 437); K = 512 .. 1919 0.96 .. 1.05, mean 0.99.  257 .. 1400 tiles 0.82 .. 1.16, mean 1.01: a second
-            // round of few tiles takes as long as the first (8 experts, 14336 x 4096, 64 rows 1800 -> 1990 us of four layers).
+        } else if (few_long_tiles(chunk_rows, s.E, N, K) && w4_kernel_fits(N, K, which == 0, static_cast<uint64_t>(s.T))) {
+            // Time of the layer over that with the kernels below: 30 layers, K = 1920 .. 13952, 11 .. 610 rows per
+            // expert 0.75 .. 0.99, mean 0.92 (8 experts, 3584 x 1024, 60 rows 158 -> 118 us; 8, 9856 x 2816, 11 rows 521 ->
+            // 437); K = 512 .. 1919 0.96 .. 1.05, mean 0.99.  257 .. 1400 tiles 0.82 .. 1.16, mean 1.01: a second round of few
+            // tiles takes as long as the first (8 experts, 14336 x 4096, 64 rows 1800 -> 1990 us of four layers).
             gp.bm = gp.bn = 128; gp.concurrent = 32; gp.w4 = gp.deep = true;
         } else if ((chunk_rows / 64 + s.E / 2) * tiles_n >= 128 &&
                    (per_expert < 48 || (per_expert <= 64 && (chunk_rows / 128 + s.E / 2) * tiles_n < 256))) {

@@ -127,11 +127,12 @@ def test_backward_matches_the_oracle(name, keep):
 
 
 # dP's GEMM over d: one, two and three stages of 64 and a tail, on 256 x 256 (many tiles), 128 x 128 and 128 x 256
-# tiles (long contractions), with rows and columns that end inside a tile
+# tiles (long contractions), with rows and columns that end inside a tile; dxe's over h with five stages on their way (the
+# last two)
 @pytest.mark.parametrize("keep", [False, True], ids=["recompute", "keep"])
 @pytest.mark.parametrize("T,h,d", [(6000, 8712, 40), (6000, 8712, 64), (6000, 8712, 136), (6000, 8712, 192),
                                    (600, 264, 8), (600, 264, 64), (600, 264, 72), (600, 264, 128), (600, 264, 200),
-                                   (4000, 1608, 3080)])
+                                   (4000, 1608, 3080), (700, 2008, 264), (300, 1920, 72)])
 def test_backward_of_few_stages(T, h, d, keep):
     # one expert with every token: gate weight 1, no gradient through the gate, dx = dP W1^T
     li = wl.make_layer(wl.scaled("gpt2s_moe", T=T, d=d, h=h, E=1, k=1, cf=1.0), seed=5)

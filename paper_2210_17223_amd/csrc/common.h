@@ -92,6 +92,9 @@ inline int32_t work_list_entries(const GemmPlan &gp) { return (gp.max_row_tiles 
 // of the latter kind the smaller tile would cost 1.01 (second GEMM), 1.02 (dxe) and 1.04 (first GEMM of a stack).  On the other
 // side: K = 1024 .. 1535 1.05, 1536 .. 2047 1.00, 2048 .. 3071 0.96 with full and 1.07 with half-full last tiles; up to 200
 // tiles 1.16 .. 1.20, 200 .. 300 1.09 .. 1.13, 300 .. 400 0.98.
+// (All of that with one tile per block.  With loads that run on across a block's tiles of 256 columns, 40 forward layers of
+// 100 .. 18000 rows per expert again with each tile in each GEMM: a tile other than the rule's takes 0.85 .. 1.5 of its time, and no
+// moved line is better than 0.98 in the mean.)
 inline void choose_w4_tile(int64_t rows, int E, int N, int K, GemmPlan *gp)
 {
     const int64_t tiles256 = (rows / 256 + E / 2) * ((N + 255) / 256);

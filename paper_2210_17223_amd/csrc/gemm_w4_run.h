@@ -28,16 +28,18 @@ struct W4Place {                       // where a wavefront stands in its tile
     char *patch;                       // its quarter of the free LDS: UR rows of 256 bytes
     int lane, wm, wn, fr, oct;
     static constexpr int UR = BM / 8, TM = BM / 32, TN = 8;
-    // a lane's four values of row block j (16 rows), column block i (16 columns), as 16-bit values
-    __device__ __forceinline__ char *at(int i, int j) const
+    // a lane's four values of column block i (16 columns) of a row block, as 16-bit values, the patch's 16 rows `part`
+    __device__ __forceinline__ char *at(int i, int part) const
     {
-        const int row = j % (UR / 16) * 16 + fr;
-        return patch + row * 256 + (((2 * i + (oct >> 1)) ^ (row & 15)) << 4) + (oct & 1) * 8;
+        const int row = part * 16 + fr;
+        return patch + row * 256 + (((2 * i + (oct >> 1)) ^ fr) << 4) + (oct & 1) * 8;
     }
-    // rows UR u .. of the wavefront's part of the tile, whole lines of 16-bit values, to a [rows, N] matrix
-    __device__ __forceinline__ void leave(uint16_t *out, const WorkItem &item, int u, int N) const
+    // the patch's rows from 16 part on, whole lines of 16-bit values, to a [rows, N] matrix: rows r .. r + R - 1 of the
+    // wavefront's part of the tile
+    template <int R>
+    __device__ __forceinline__ void leave(uint16_t *out, const WorkItem &item, int r, int part, int N) const
     {
-        const int row0 = item.row0 + wm * (BM / 2) + u * UR, col0 = item.n0 + wn * 128;
+        const int row0 = item.row0 + wm * (BM / 2) + r, col0 = item.n0 + wn * 128;
         // (a row past the tile's or a column past N lies past the resource)
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             out + static_cast<size_t>(row0) * N, 0, static_cast<unsigned>(max(item.row1 - row0, 0)) * N * 2u, 0x00020000);
@@ -45,9 +47,9 @@ struct W4Place {                       // where a wavefront stands in its tile
         const int first = col < N ? (lane / 16 * N + col) * 2 : 0x7ff00000, step = col < N ? N * 8 : 0;
         MOE_SB();
 #pragma unroll
-        for (int it = 0; it < UR / 4; ++it) {
+        for (int it = 0; it < R / 4; ++it) {
             const int row = it * 4 + lane / 16;
-            const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + row * 256 + ((lane % 16 ^ (row & 15)) << 4));
+            const u32x4 q = *reinterpret_cast<const u32x4 *>(patch + (part * 16 + row) * 256 + ((lane % 16 ^ (row & 15)) << 4));
             __builtin_amdgcn_raw_buffer_store_b128(q, rs, first + it * step, 0, 0);
             if (it % 4 == 3) MOE_SB();
         }

@@ -265,7 +265,8 @@ int32_t moe_profile_read(int32_t stage, float *ms, int32_t cap);
  *   show what each costs (bit 0: no matrix instructions; bit 1: no LDS fragment reads
  *   after the first step; bit 2: no global loads into LDS in the loop; bit 3: no
  *   output stores; built: 0, 1, 2, 4, 6, 7, 8) -- their outputs are wrong by
- *   construction.  K a multiple of 64, N * K * 2 and 256 * K * 2 below 2^31.
+ *   construction.  K a multiple of 64, N * K * 2 and 256 * K * 2 below 2^31, 256 * N * 2
+ *   below 2^31 - 2^20 (the kernel's 32-bit byte offsets); MOE_EINVAL otherwise.
  * moe_path_calls: how many calls since the library was loaded went a way that no output shows: 0 a
  *   backward pass with its weight gradients on a side stream, 1 an offloaded expert FFN whose weights
  *   a kernel reads over the host link; -1 for any other number.

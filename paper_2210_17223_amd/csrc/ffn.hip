@@ -871,23 +871,29 @@ moe_status launch_calib_gemm(const uint16_t *A, const uint16_t *W, _Float16 *C, 
                              const int32_t *nitems, int max_items, int N, int K, int abl, int gelu,
                              hipStream_t st)
 {
+    if (!w4_kernel_fits(N, K, false, 0)) {
+        set_error("moe_calib_gemm: N * K * 2 and 256 * K * 2 must be below 2^31 and 256 * N * 2 below 2^31 - 2^20 (N = %d, K = %d)", N, K);
+        return MOE_EINVAL;
+    }
     constexpr size_t lds = kW4RunLds;
     const int entries = static_cast<int>(align_up(static_cast<size_t>(max_items), 8)), grid = std::min(entries, 256);
+    auto run = [&](auto kern, PerDeviceOnce &once) {
+        once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, A, W, nullptr, C, nullptr, items, nitems, entries, N, K,
+                           nullptr, 1, 0);
+    };
+    auto variant = [&](auto abl_, auto tail) {
+        constexpr int ABL = decltype(abl_)::value;
+        constexpr bool TAIL = decltype(tail)::value;
+        static PerDeviceOnce once[2];              // (of these two kernels)
+        if (gelu) run(grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, TAIL, ABL>, once[0]);
+        else run(grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, TAIL, ABL>, once[1]);
+    };
 #define MOE_CALIB_CASE(ABL_)                                                                      \
-    case ABL_: {                                                                                  \
-        auto k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, true, ABL_>;                    \
-        auto k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, true, ABL_>;                    \
-        if (K >= 256) {                                                                           \
-            k1 = grouped_gemm_w4_kernel<false, MOE_ACT_GELU_ERF, false, false, ABL_>;                    \
-            k0 = grouped_gemm_w4_kernel<false, MOE_ACT_IDENTITY, false, false, ABL_>;                    \
-        }                                                                                         \
-        static PerDeviceOnce once1, once0;                                                        \
-        once1.raise_lds(reinterpret_cast<const void *>(k1), static_cast<int>(lds));               \
-        once0.raise_lds(reinterpret_cast<const void *>(k0), static_cast<int>(lds));               \
-        hipLaunchKernelGGL(gelu ? k1 : k0, dim3(grid), dim3(256), lds, st, A, W, nullptr, C,      \
-                           nullptr, items, nitems, entries, N, K, nullptr, 1, 0);                          \
-        break;                                                                                    \
-    }
+    case ABL_:                                                                                    \
+        if (K >= 256) variant(std::integral_constant<int, ABL_>{}, std::false_type{});            \
+        else variant(std::integral_constant<int, ABL_>{}, std::true_type{});                      \
+        break;
     switch (abl) {
         MOE_CALIB_CASE(0)
         MOE_CALIB_CASE(1)

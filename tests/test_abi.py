@@ -118,6 +118,18 @@ def test_static_dispatch_refuses_what_does_not_fit_its_array():
     assert rc == 1
 
 
+@pytest.mark.parametrize("N,K", [(4192256, 64), (8388608, 64), (16777216, 64), (8192, 131072), (64, 4194304)])
+def test_calib_gemm_refuses_operands_past_32_bit_offsets(N, K):
+    """Refused before anything is enqueued (so this needs no GPU): N * K * 2, 256 * K * 2 or 256 * N * 2 (a tile's rows
+    of the output) does not fit the kernel's 32-bit byte offsets."""
+    L = moe.lib()
+    moe.moe_last_error()
+    buf = (C.c_char * 64)()
+    p = C.c_void_p((C.addressof(buf) + 15) // 16 * 16)
+    assert L.moe_calib_gemm(p, p, p, p, p, 8, N, K, 0, 0, None) == 1
+    assert "moe_calib_gemm" in moe.moe_last_error()
+
+
 def test_path_calls_counts_from_zero():
     assert moe.moe_path_calls(0) >= 0 and moe.moe_path_calls(1) >= 0
     assert moe.moe_path_calls(2) == moe.moe_path_calls(-1) == -1

@@ -304,8 +304,7 @@ __global__ __launch_bounds__(256, BM + BN == 256 && !DEEP ? 2 : 1) void bwd_gemm
     _Float16 *__restrict__ Pbuf, const WorkItem *__restrict__ items, int N, int K)
 {
     constexpr bool F16 = false;
-    constexpr int ABL = 0;
-    const int32_t *const row_src = nullptr, *const nitems = nullptr;   // packed rows, the plan's list
+    const int32_t *const row_src = nullptr;      // packed rows
     constexpr int row_div = 1, a_rows = 0;
     constexpr bool TILE_IN = EPI == 2;
     const uint16_t *const tile_in = reinterpret_cast<const uint16_t *>(Pbuf);

@@ -232,16 +232,6 @@ __host__ __device__ __forceinline__ int packed_gate_column(int i)
 {
     return (i & ~15) | ((i & 3) << 2) | ((i >> 2) & 3);
 }
-// The block's tile: entry blockIdx.x of a work list of the plan, which is laid out for that (build_items);
-// or, of a caller's plain list of *nitems, the blockIdx.x % 8-th eighth's next.
-__device__ __forceinline__ WorkItem take_item(const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems)
-{
-    if (nitems == nullptr) return items[blockIdx.x];
-    const int total = *nitems, per_xcd = (total + 7) / 8, slot = blockIdx.x / 8;
-    const int at = static_cast<int>(blockIdx.x % 8) * per_xcd + slot;
-    WorkItem none{-1, 0, 0, 0};
-    return slot < per_xcd && at < total ? items[at] : none;
-}
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 #endif
 

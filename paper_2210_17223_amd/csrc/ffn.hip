@@ -9,10 +9,10 @@
 // bf16 layers: both operands are stored with the contraction index contiguous (activations by
 // nature, weights after moe_pack_weights), and the weights are fed as the MFMA "A" operand
 // so that each lane ends up with four consecutive output columns of one row.
-// grouped_gemm_w4_kernel runs 256 x 256 tiles and grouped_gemm_mfma_kernel those of 128 rows, both on the
-// loop of gemm_w4_body.inc; grouped_gemm_stream_kernel runs decode steps; grouped_gemm_staged_kernel, whose
-// operands go through registers, 64 x 256 tiles and operands past 32-bit offsets.  H and ye are
-// kept in fp16.
+// grouped_gemm_w4_kernel runs 256 x 256 tiles and grouped_gemm_mfma_kernel those of 128 rows, tiles of 256 columns on
+// the loop of gemm_w4_run.h, 128 x 128 on that of gemm_w4_body.inc; grouped_gemm_stream_kernel runs decode steps;
+// grouped_gemm_staged_kernel, whose operands go through registers, 64 x 256 tiles and operands past 32-bit offsets.  H and
+// ye are kept in fp16.
 // fp32 layers: grouped_gemm_f32_kernel, on the fp32 matrix instruction.
 #include "activation.h"
 #include "common.h"
@@ -606,8 +606,7 @@ __device__ __forceinline__ void w4_gemm_tile(
     const WorkItem *__restrict__ items, int N, int K,
     const int32_t *__restrict__ row_src, int row_div, int a_rows)
 {
-    constexpr int BM = 128, BN = 128, ABL = 0;
-    const int32_t *const nitems = nullptr;
+    constexpr int BM = 128, BN = 128;
     constexpr bool TILE_IN = false;
     const uint16_t *const tile_in = nullptr;
 #include "gemm_w4_body.inc"

@@ -71,9 +71,8 @@ constexpr size_t kW4Lds = w4_lds(256, 256);
 template <bool F16, bool WAIT, bool ZERO = false>
 __device__ __forceinline__ void mfma_16x16x32_agpr(f32x4 &acc, const u32x4 &a, const u32x4 &b)
 {
-    if constexpr (F16 && WAIT)
-        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-    else if constexpr (F16 && ZERO)
+    static_assert(!(F16 && WAIT), "no caller converts to fp16");
+    if constexpr (F16 && ZERO)
         asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=a"(acc) : "v"(a), "v"(b));
     else if constexpr (F16)
         asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));

@@ -108,6 +108,14 @@ moe_status moe_layer_backward_chunked(const moe_shape *s, int32_t n_chunks, cons
                                       float *dW1, float *dW2, float *dgate, void *workspace,
                                       void *stream);
 
+/* Which kernel the backward pass of a layer of shape s launches for its GEMM `which` (0: over d_ff
+ * columns, dP and, where they are not kept, the pre-activations; 1: dxe; 2: dW2; 3: dW1), written to
+ * name (host, len bytes, always terminated) as "<kernel> <tile rows>x<tile columns>", with " deep"
+ * behind it where five stages of loads are on their way, so that a measurement or a test can say
+ * which kernel it ran.  MOE_EINVAL for which outside 0..3, a null name or len == 0, or a shape
+ * that moe_layer_backward does not take. */
+moe_status moe_backward_gemm_kernel(const moe_shape *s, int32_t which, char *name, size_t len);
+
 #ifdef __cplusplus
 }
 #endif

@@ -19,6 +19,7 @@
 #include "moe_train.h"
 
 #include <algorithm>
+#include <cstdio>
 
 #include <hip/hip_ext.h>
 
@@ -1207,22 +1208,26 @@ void launch_gemm(const uint16_t *A, const uint16_t *W, void *C, _Float16 *P, con
         launch_gemm_k<EPI, ACT, false>(A, W, C, P, items, N, K, grid_items, stage, st);
 }
 
+// 256 x 256 tiles on four wavefronts when they fit the matrix, fill the chip twice over, and the
+// buffer offsets (an expert's rows times the row length, in bytes) stay below 2^31.  Time of both
+// gradients over that with 128 x 128 tiles, layers of 128 .. 16384 tokens, rows spread evenly / by
+// Zipf(1.2): 512 .. 599 tiles 0.92 / 0.87, 600 .. 767 0.80 / 0.80, more 0.79 / -; 320 .. 511 0.83 / 0.83,
+// 256 .. 319 (a second round all but empty) 0.97 / 0.96, 150 .. 255 0.78 / 0.79 (but up to 1.6 where one
+// expert has most of the rows), 100 .. 149 1.00 / -.  (16 experts, 768 x 3072, 8192 rows, 576 tiles:
+// dW2 92 -> 83 us, dW1 90 -> 73.)
+bool wide_wgrad_tiles(int E, int M, int N, int64_t max_rows)
+{
+    const uint64_t span = static_cast<uint64_t>(max_rows + 192) * static_cast<uint64_t>(std::max(M, N)) * 2;
+    return M % 256 == 0 && N % 256 == 0 && static_cast<int64_t>(E) * (M / 256) * (N / 256) >= 512 && span < (1ull << 31);
+}
+
 // dW[e] [M][N] = A[rows of e]^T B[rows of e] from row-major operands
 template <bool AF16>
 void launch_wgrad(const uint16_t *A, const uint16_t *B, float *C, const int32_t *offsets, int E, int M,
                   int N, int64_t max_rows, int stage, hipStream_t st)
 {
     hipEvent_t t0, t1;
-    // 256 x 256 tiles on four wavefronts when they fit the matrix, fill the chip twice over, and the
-    // buffer offsets (an expert's rows times the row length, in bytes) stay below 2^31.  Time of both
-    // gradients over that with 128 x 128 tiles, layers of 128 .. 16384 tokens, rows spread evenly / by
-    // Zipf(1.2): 512 .. 599 tiles 0.92 / 0.87, 600 .. 767 0.80 / 0.80, more 0.79 / -; 320 .. 511 0.83 / 0.83,
-    // 256 .. 319 (a second round all but empty) 0.97 / 0.96, 150 .. 255 0.78 / 0.79 (but up to 1.6 where one
-    // expert has most of the rows), 100 .. 149 1.00 / -.  (16 experts, 768 x 3072, 8192 rows, 576 tiles:
-    // dW2 92 -> 83 us, dW1 90 -> 73.)
-    const uint64_t span = static_cast<uint64_t>(max_rows + 192) * static_cast<uint64_t>(std::max(M, N)) * 2;
-    if (M % 256 == 0 && N % 256 == 0 && static_cast<int64_t>(E) * (M / 256) * (N / 256) >= 512 &&
-        span < (1ull << 31)) {
+    if (wide_wgrad_tiles(E, M, N, max_rows)) {
         constexpr size_t kLds4 = kW4Lds;
         auto kern = wgrad_w4_kernel<AF16>;
         static PerDeviceOnce once;
@@ -1540,6 +1545,24 @@ moe_status backward_t(const moe_shape &s, int n_chunks, const uint16_t *x, const
 using namespace moe;
 
 extern "C" {
+
+moe_status moe_backward_gemm_kernel(const moe_shape *s, int32_t which, char *name, size_t len)
+{
+    if (!supported(s) || name == nullptr || len == 0 || which < 0 || which > 3) {
+        set_error("moe_backward_gemm_kernel: which must be in 0..3, name a buffer, the shape one that moe_layer_backward takes");
+        return MOE_EINVAL;
+    }
+    const int64_t R = moe_max_rows(s);
+    const int d = s->d_model, h = s->d_ff;
+    if (which < 2) {
+        const GemmPlan gp = which == 0 ? plan_rows(h, d, R, s->E, false) : plan_rows(d, h, R, s->E, true);
+        std::snprintf(name, len, "%s %dx%d%s", gp.w4 ? "bwd_gemm_w4_kernel" : "bwd_gemm_kernel", gp.bm, gp.bn, gp.deep ? " deep" : "");
+    } else {
+        std::snprintf(name, len, "%s", wide_wgrad_tiles(s->E, which == 2 ? h : d, which == 2 ? d : h, R)
+                                           ? "wgrad_w4_kernel 256x256" : "wgrad_gemm_kernel 128x128");
+    }
+    return MOE_OK;
+}
 
 size_t moe_backward_workspace_bytes(const moe_shape *s)
 {

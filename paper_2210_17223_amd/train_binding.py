@@ -24,12 +24,21 @@ def _lib():
         L.moe_layer_backward_chunked.argtypes = [sp, i32, vp, vp, vp, i32] + [vp] * 20
         L.moe_layer_forward_keep.restype = C.c_int
         L.moe_layer_forward_keep.argtypes = [sp, vp, vp, vp, i32] + [vp] * 17
+        L.moe_backward_gemm_kernel.restype = C.c_int
+        L.moe_backward_gemm_kernel.argtypes = [sp, i32, C.c_char_p, C.c_size_t]
         _ready = True
     return L
 
 
 def moe_backward_workspace_bytes(s: Shape) -> int:
     return int(_lib().moe_backward_workspace_bytes(C.byref(s)))
+
+
+def moe_backward_gemm_kernel(s: Shape, which: int) -> str:
+    """Name and tile of the kernel of the backward pass's GEMM `which` (0: dP, 1: dxe, 2: dW2, 3: dW1)."""
+    buf = C.create_string_buffer(96)
+    _check(_lib().moe_backward_gemm_kernel(C.byref(s), int(which), buf, C.sizeof(buf)))
+    return buf.value.decode()
 
 
 def _need(t: torch.Tensor, dtype, numel: int, name: str) -> None:

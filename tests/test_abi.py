@@ -164,3 +164,23 @@ def test_expert_gemm_kernel_tells_every_kernel_apart():
     assert names(256, 4096, 8, 14336, 2, 256)[1] == "grouped_gemm_staged_kernel 64x256"      # few rows, long weights
     assert names(300, 32776, 2, 32840, 1, 300) == ["grouped_gemm_staged_kernel 128x256"] * 2  # past 32-bit offsets
     assert all(n.startswith("grouped_gemm_mfma_kernel 128x") for n in names(4096, 768, 16, 3072, 2, 640))
+
+
+def test_backward_gemm_kernel_names_the_kernel_and_its_tile():
+    """moe_backward_gemm_kernel is host logic only: the large layer takes the widest tiles everywhere, a layer of few rows and a
+    long contraction five stages of loads for dxe, operands past 32-bit offsets the general kernels."""
+    def names(T, d, E, h, k, C):
+        s = moe.Shape.make(T, d, E, h, k, C, dtype="bf16", act="gelu")
+        return [moe.moe_backward_gemm_kernel(s, which) for which in range(4)]
+
+    assert names(32768, 2048, 64, 8192, 2, 1024) == ["bwd_gemm_w4_kernel 256x256"] * 2 + ["wgrad_w4_kernel 256x256"] * 2
+    assert names(300, 72, 1, 1920, 1, 300) == ["bwd_gemm_w4_kernel 128x128", "bwd_gemm_w4_kernel 128x128 deep"] + \
+        ["wgrad_gemm_kernel 128x128"] * 2
+    assert names(2560, 3080, 4, 2824, 2, 1536)[0] == "bwd_gemm_w4_kernel 128x256"
+    assert all(n.startswith("bwd_gemm_kernel ") for n in names(300, 32776, 2, 32840, 1, 300)[:2])
+    s = moe.Shape.make(300, 72, 1, 1920, 1, 300, dtype="bf16", act="gelu")
+    for which in (-1, 4):
+        with pytest.raises(moe.MoeError):
+            moe.moe_backward_gemm_kernel(s, which)
+    with pytest.raises(moe.MoeError):                  # fp32 layers have no backward pass
+        moe.moe_backward_gemm_kernel(moe.Shape.make(300, 72, 1, 1920, 1, 300, dtype="f32"), 0)

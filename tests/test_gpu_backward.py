@@ -126,14 +126,24 @@ def test_backward_matches_the_oracle(name, keep):
     assert not got["dx"].reshape(T, d)[dropped].any()
 
 
-# dP's GEMM over d: one, two and three stages of 64 and a tail, on 256 x 256 (many tiles), 128 x 128 and 128 x 256
-# tiles (long contractions), with rows and columns that end inside a tile; dxe's over h with five stages on their way (the
-# last two)
+# dP's GEMM over d: one, two and three stages of 64 and a tail, on 256 x 256 (many tiles) and 128 x 128 tiles, and long
+# contractions, whole stages and a tail, on 256 x 256 and 128 x 256, with rows and columns that end inside a tile; dxe's over h on
+# all three and on 128 x 128 with five stages on their way.  keep: the forward's first GEMM takes dP's tiles, the last shape's with
+# five stages on their way.
 @pytest.mark.parametrize("keep", [False, True], ids=["recompute", "keep"])
-@pytest.mark.parametrize("T,h,d", [(6000, 8712, 40), (6000, 8712, 64), (6000, 8712, 136), (6000, 8712, 192),
-                                   (600, 264, 8), (600, 264, 64), (600, 264, 72), (600, 264, 128), (600, 264, 200),
-                                   (4000, 1608, 3080), (700, 2008, 264), (300, 1920, 72)])
-def test_backward_of_few_stages(T, h, d, keep):
+@pytest.mark.parametrize("T,h,d,dp,dxe", [
+    (6000, 8712, 40, "256x256", "128x128 deep"), (6000, 8712, 64, "256x256", "128x128 deep"),
+    (6000, 8712, 136, "256x256", "128x128 deep"), (6000, 8712, 192, "256x256", "128x128 deep"),
+    (600, 264, 8, "128x128", "128x128"), (600, 264, 64, "128x128", "128x128"), (600, 264, 72, "128x128", "128x128"),
+    (600, 264, 128, "128x128", "128x128"), (600, 264, 200, "128x128", "128x128"),
+    (4000, 1608, 3080, "256x256", "256x256"), (700, 2008, 264, "128x128", "128x128 deep"),
+    (300, 1920, 72, "128x128", "128x128 deep"), (4000, 1608, 3072, "128x256", "256x256"),
+    (7500, 2152, 3080, "128x256", "256x256"), (6000, 3072, 1032, "256x256", "128x256"),
+    (700, 264, 1928, "128x128", "128x128")])
+def test_backward_of_few_stages(T, h, d, dp, dxe, keep):
+    s = moe.Shape.make(T, d, 1, h, 1, T, dtype="bf16", act="gelu")
+    assert [moe.moe_backward_gemm_kernel(s, which) for which in (0, 1)] == [f"bwd_gemm_w4_kernel {t}" for t in (dp, dxe)]
+    assert moe.moe_expert_gemm_kernel(s, 0).endswith(" deep" if (T, h, d) == (700, 264, 1928) else f" {dp}")
     # one expert with every token: gate weight 1, no gradient through the gate, dx = dP W1^T
     li = wl.make_layer(wl.scaled("gpt2s_moe", T=T, d=d, h=h, E=1, k=1, cf=1.0), seed=5)
     got, _ = run_backward(li, keep=keep, with_oracle=False)

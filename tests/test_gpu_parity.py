@@ -321,9 +321,9 @@ def test_large_tile_kernel(d, h, act, keep):
 @pytest.mark.parametrize("d,h,which", [(64, 4096, 0), (128, 4096, 0), (2048, 192, 1)],
                          ids=["one_stage", "two_stages", "three_stages"])
 def test_large_tile_kernel_with_a_short_contraction(d, h, which):
-    """The 256 x 256 tile kernel keeps two stages of loads in flight and pairs its stages: a
-    contraction of one, two or three 64-deep stages (GEMM `which` of these layers) must still come
-    out right -- the loads past the last stage fetch the last stage again and are never used."""
+    """The 256 x 256 tile kernel asks in a tile's last stages for the first ones of the block's next tile: a contraction
+    of one, two or three 64-deep stages (GEMM `which` of these layers), shorter than what is on its way, is padded with
+    stages of zeros to four, and must come out right in every tile of a block."""
     cfg = wl.scaled("gpt2s_moe", T=16384, d=d, h=h, E=8, k=1 if which == 0 else 2, cf=1.0)
     li = wl.make_layer(cfg, seed=33, threads=8)
     s = shape_of(li)

@@ -28,9 +28,9 @@
 //  * Every memory instruction is issued singly between two matrix instructions in a fixed order;
 //    those are inline assembly so that the accumulators stay in AGPRs and the order holds.
 //    Neighbouring ones share an operand (serpentine order).
-// What bounds it (one tile per block): the matrix cores are busy for 62 % / 79 % of the cycles (N = 8192, K = 2048, GeLU / N =
-// 2048, K = 8192), at a clock of 1.69 / 1.65 GHz that the chip sets by the energy per operation (on all-ones
-// operands the same launches are 17 % / 20 % faster).  With 32 x 32 x 16 instructions and operands staged
+// What bounds it: the matrix cores are busy for 67 % / 78 % of the cycles (N = 8192, K = 2048, GeLU / N =
+// 2048, K = 8192; with one tile per block 62 / 79), at a clock of 1.71 / 1.67 GHz that the chip sets by the energy per
+// operation (on all-ones operands the same launches are 22 % / 20 % faster).  With 32 x 32 x 16 instructions and operands staged
 // through registers it was 56 % / 78 % at 1.68 / 1.55 GHz: the first GEMM lost cycles, the second takes as many
 // as before and they have become cheaper.  On 64 x 1024 rows alone, after thirty launches, with a block's loads
 // running on from tile to tile (gemm_w4_run.h): 1773 / 1586 us, of which the matrix instructions and barriers by themselves

@@ -18,6 +18,12 @@
 // 1575 -> 1455 and 1317 -> 1316); with the pre-activations kept, 63622 rows 2087 -> 1877; of Zipf(1.2)-distributed rows the layer of
 // 16384 tokens, 1024 x 4096, 32 experts 375 -> 362; of 3001 tokens, 1000 x 2600, 13 experts, all options 191 -> 179.  Prologue,
 // barriers and epilogue of the first product take 176 of its 1773 by themselves (313 of 1856).
+// What runs beside such a launch: a block holds its unit until its share is done, all of its LDS and 440 or 448 of the 512 registers
+// of every SIMD (256 x 256; at most 472 with the pre-activations kept; 272 to 312 on 128 x 256).  Wavefronts of another stream
+// that ask for no LDS and for the rest of the registers get in, as the pack (32) and the stand-in link's copy (40) do; what
+// needs LDS (gate, plan) or more registers waits for the launch's end, where with one tile per block it waited for a tile's.
+// The combine of long rows (80 to 88), of one group of chunks beside the next one's FFN, is of that kind: with two
+// vectors on their way instead of four (56) it gets in, and 12 layers of 2 to 8 groups take 0.994 .. 1.009 of their time.
 // Three items are known ahead: the tile's, the next one's, whose rows' offsets are in registers, and the
 // one's behind it, whose rows' indices are on their way during a whole tile.
 

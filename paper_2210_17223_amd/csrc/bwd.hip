@@ -676,14 +676,15 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(
 template <bool AF16>
 __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, float *__restrict__ C,
-    const int32_t *__restrict__ offsets, int E, int M, int N, int tiles_m, int tiles_n)
+    const int32_t *__restrict__ offsets, int E, int M, int N, int tiles_m, int tiles_n, int share)
 {
     constexpr int TM = 8, TN = 8, HALF = 16384, STEP = 2 * HALF, RING = 5;
     constexpr int kRow = 512;                     // bytes of a 256-column LDS row
     const int total = E * tiles_m * tiles_n;
-    const int per_xcd = (total + 7) / 8, stride = gridDim.x / 8;
-    const int end = min(total, static_cast<int>(blockIdx.x % 8 + 1) * per_xcd);
-    int tile = static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
+    constexpr int stride = kRunUnits / 8;
+    const int per_xcd = (total + 7) / 8, slot = blockIdx.x / 8, xcd = blockIdx.x % 8;
+    int tile = xcd * per_xcd + slot / stride * stride * share + slot % stride;
+    const int end = min(min(total, (xcd + 1) * per_xcd), tile + share * stride);
     if (tile >= end) return;
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     char *const lds = reinterpret_cast<char *>(smem);
@@ -1235,10 +1236,12 @@ void launch_wgrad(const uint16_t *A, const uint16_t *B, float *C, const int32_t 
         static PerDeviceOnce once;
         once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kLds4));
         const int tiles_m = M / 256, tiles_n = N / 256;
-        const int grid = 256;            // one block per compute unit (a block has all of its LDS)
+        // (what leaves of a tile takes as long as five stages)
+        const int share = std::max(1, kRunStages / (static_cast<int>((max_rows / E + 63) / 64) + 5));
+        const int grid = kRunUnits * ceil_div((E * tiles_m * tiles_n + 7) / 8, kRunUnits / 8 * share);
         prof_kernel_events(stage, &t0, &t1);
         hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), kLds4, st, t0, t1, 0, A, B, C, offsets, E, M,
-                              N, tiles_m, tiles_n);
+                              N, tiles_m, tiles_n, share);
         return;
     }
     constexpr size_t kLds = 2 * 2 * kBK * 128 * sizeof(uint16_t);

@@ -529,7 +529,7 @@ template <bool F16, int ACT, bool KEEP, bool KTAIL, int BM, int ABL>
 __device__ __forceinline__ void run_gemm_tiles(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
-    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int entries, int N, int K,
+    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int entries, int share, int N, int K,
     const int32_t *__restrict__ row_src, int row_div, int a_rows)
 {
     constexpr int TN = 8;
@@ -550,14 +550,14 @@ __device__ __forceinline__ void run_gemm_tiles(
         }
         return b4;
     };
-    w4_run<F16, KTAIL, BM, ABL>(A, W, items, nitems, entries, N, K, row_src, row_div, a_rows, prepare, [&](
+    w4_run<F16, KTAIL, BM, ABL>(A, W, items, nitems, entries, share, N, K, row_src, row_div, a_rows, prepare, [&](
         auto &acc, const Bias &b4, const WorkItem &item, const W4Place<BM> &place, auto landed) {
         WorkItem stored = item;
         if constexpr (ABL & 8) stored.row1 = 0;
         // R rows are stored while the next ones are computed.  KEEP: 16, each pass through its own half of the patch where
         // it has two, so that the sums of no more are kept from the first pass to the second: with 32 the 256 x 256 kernel
         // takes 504 to 512 of a SIMD's 512 registers, with 16 at most 472, and the pack's wavefronts (32) get in beside a
-        // block that holds its unit for the whole launch.  32768 tokens, 2048 x 8192, 64 experts, us: pack 1376 -> 236, this GEMM 1886 -> 1902,
+        // block that holds its unit.  32768 tokens, 2048 x 8192, 64 experts, us: pack 1376 -> 236, this GEMM 1886 -> 1902,
         // the second one, which the pack was left to, 1632 -> 1602.  20 training steps of 18000 .. 32768 tokens: 0.986 .. 1.019 of
         // their time, mean 0.999; packed in front of this GEMM 0.973 .. 1.058, mean 1.004.
         constexpr int UR = W4Place<BM>::UR, R = KEEP ? 16 : UR;
@@ -591,11 +591,11 @@ template <bool F16, int ACT, bool KEEP, bool KTAIL, int ABL = 0>
 __global__ __launch_bounds__(256, 1) void grouped_gemm_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
-    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int entries, int N, int K,
+    const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int entries, int share, int N, int K,
     const int32_t *__restrict__ row_src, int row_div, int a_rows)
 {
-    run_gemm_tiles<F16, ACT, KEEP, KTAIL, 256, ABL>(A, W, bias, C, Pre, items, nitems, entries, N, K, row_src,
-                                                    row_div, a_rows);
+    run_gemm_tiles<F16, ACT, KEEP, KTAIL, 256, ABL>(A, W, bias, C, Pre, items, nitems, entries, share, N, K,
+                                                    row_src, row_div, a_rows);
 }
 
 // 128 x 128 tiles, one per block; DEEP: of launches that wait for their weights, with five stages on their way
@@ -665,12 +665,12 @@ template <bool F16, int ACT, bool KEEP, bool KTAIL, int BN, bool DEEP = false>
 __global__ __launch_bounds__(256, BN == 128 && !DEEP ? 2 : 1) void grouped_gemm_mfma_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
     const float *__restrict__ bias, _Float16 *__restrict__ C, _Float16 *__restrict__ Pre,
-    const WorkItem *__restrict__ items, int entries, int N, int K,
+    const WorkItem *__restrict__ items, int entries, int share, int N, int K,
     const int32_t *__restrict__ row_src, int row_div, int a_rows)
 {
     if constexpr (BN == 256)
-        run_gemm_tiles<F16, ACT, KEEP, KTAIL, 128, 0>(A, W, bias, C, Pre, items, nullptr, entries, N, K, row_src,
-                                                      row_div, a_rows);
+        run_gemm_tiles<F16, ACT, KEEP, KTAIL, 128, 0>(A, W, bias, C, Pre, items, nullptr, entries, share, N, K,
+                                                      row_src, row_div, a_rows);
     else
         w4_gemm_tile<F16, ACT, KEEP, KTAIL, DEEP>(A, W, bias, C, Pre, items, N, K, row_src, row_div, a_rows);
 }
@@ -785,16 +785,16 @@ void launch_mfma(const GemmPlan &gp, const uint16_t *A, const uint16_t *W, const
                                                               gp.max_items, N, K, stage, st,       \
                                                               row_src, row_div)
     if (gp.w4) {
-        // tiles of 256 columns: one block per compute unit (a block has all of its LDS), which takes every
-        // 256th entry of the list
+        // tiles of 256 columns: shares of the list (kRunStages)
         const bool run = gp.bn == 256;
         auto launch = [&](auto kern, PerDeviceOnce &once, auto... list) {
             const size_t lds = run || gp.deep ? kW4RunLds : w4_lds(128, 128);
             once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
             hipEvent_t t0, t1;
             prof_kernel_events(stage, &t0, &t1);
-            hipExtLaunchKernelGGL(kern, dim3(run ? std::min(gp.max_items, 256) : gp.max_items), dim3(256), lds, st, t0,
-                                  t1, 0, A, W, bias, C, pre, items, list..., gp.max_items, N, K, row_src, row_div,
+            const int share = w4_run_share(gp.bm, K);
+            hipExtLaunchKernelGGL(kern, dim3(run ? w4_run_blocks(gp.max_items, share) : gp.max_items), dim3(256), lds, st,
+                                  t0, t1, 0, A, W, bias, C, pre, items, list..., gp.max_items, share, N, K, row_src, row_div,
                                   static_cast<int>(row_limit));
         };
         auto shape = [&](auto tail) {
@@ -875,11 +875,12 @@ moe_status launch_calib_gemm(const uint16_t *A, const uint16_t *W, _Float16 *C, 
         return MOE_EINVAL;
     }
     constexpr size_t lds = kW4RunLds;
-    const int entries = static_cast<int>(align_up(static_cast<size_t>(max_items), 8)), grid = std::min(entries, 256);
+    const int entries = static_cast<int>(align_up(static_cast<size_t>(max_items), 8));
+    const int share = w4_run_share(256, K), grid = w4_run_blocks(entries, share);
     auto run = [&](auto kern, PerDeviceOnce &once) {
         once.raise_lds(reinterpret_cast<const void *>(kern), static_cast<int>(lds));
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, A, W, nullptr, C, nullptr, items, nitems, entries, N, K,
-                           nullptr, 1, 0);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, A, W, nullptr, C, nullptr, items, nitems, entries, share, N,
+                           K, nullptr, 1, 0);
     };
     auto variant = [&](auto abl_, auto tail) {
         constexpr int ABL = decltype(abl_)::value;

@@ -50,6 +50,15 @@
 // matrix), which the host checks fit.
 constexpr size_t w4_lds(int bm, int bn) { return (bm == bn ? 5 * bm : 3 * (bm + bn)) * 128; }
 constexpr size_t kW4Lds = w4_lds(256, 256);
+// Blocks whose loads run on from tile to tile (gemm_w4_run.h, the weight gradients) have a compute unit to themselves, so
+// kRunUnits of them run at once.  A share of the tiles ends after kRunStages stages of 64, 0.2 ms, which is one tile of the large
+// layer's second GEMM: the unit then goes to whoever waits.  Median / longest time of a decode step (five launches) on another
+// stream beside large layers (32768 tokens, 2048 x 8192, 64 experts) with a launch's tiles in 256 shares, us: 1640 / 3500, of a layer
+// of 4096 tokens, 768 x 3072: 3660 / 3780; in shares of 64 stages 365 / 900 and 680 / 1150, of 128 430 / 1050 and 780 / 1350, of 256 500 /
+// 1930 and 1700 / 2200; one tile per block 280 / 1100 and 535 / 1250.  What the shares' ends cost: the large layer 1.01 with 64
+// stages, 1.003 with 128, its training step 1.04, 1.012 and 1.004 with 256; four other forward layers 1.000 .. 1.006, eight training
+// steps whose weight gradients run beside the other GEMMs 0.97 .. 1.00, since these get in between the shares, too.
+constexpr int kRunUnits = 256, kRunStages = 128;
 
 #define MOE_LGKM0() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
 #define MOE_VMCNT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n) : "memory")

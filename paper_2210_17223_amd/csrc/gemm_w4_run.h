@@ -1,4 +1,4 @@
-// Tiles of 256 columns, one block per compute unit: a block works through a share of the tiles and its loads
+// Tiles of 256 columns: a block, which has a compute unit to itself, works through a share of the tiles and its loads
 // run on from tile to tile.  Included behind gemm_w4.h, inside the translation unit's own namespace.
 //
 // The stages are those of gemm_w4_body.inc.  Its last ones have no operands of their tile left to ask for: here
@@ -21,13 +21,19 @@
 // What runs beside such a launch: a block holds its unit until its share is done, all of its LDS and 440 or 448 of the 512 registers
 // of every SIMD (256 x 256; at most 472 with the pre-activations kept; 272 to 312 on 128 x 256).  Wavefronts of another stream
 // that ask for no LDS and for the rest of the registers get in, as the pack (32) and the stand-in link's copy (40) do; what
-// needs LDS (gate, plan) or more registers waits for the launch's end, where with one tile per block it waited for a tile's.
-// The combine of long rows (80 to 88), of one group of chunks beside the next one's FFN, is of that kind: with two
-// vectors on their way instead of four (56) it gets in, and 12 layers of 2 to 8 groups take 0.994 .. 1.009 of their time.
+// needs LDS (gate, plan) or more registers waits for the end of a share (kRunStages).
 // Three items are known ahead: the tile's, the next one's, whose rows' offsets are in registers, and the
 // one's behind it, whose rows' indices are on their way during a whole tile.
 
 constexpr size_t kW4RunLds = 160 * 1024;
+// tiles of a block's share (a stage of 128 x 256 takes half as long as one of 256 x 256)
+inline int w4_run_share(int bm, int K) { return std::max(1, kRunStages * 256 / bm / std::max((K + 63) / 64, 4)); }
+// blocks of a launch: blocks 256 g .. 256 g + 255 take the entries from 256 g * share on, each every 256th
+inline int w4_run_blocks(int entries, int share)
+{
+    const int whole = (entries - 1) / (kRunUnits * share);
+    return whole * kRunUnits + std::min(entries - whole * kRunUnits * share, kRunUnits);
+}
 
 template <int BM>
 struct W4Place {                       // where a wavefront stands in its tile
@@ -62,15 +68,15 @@ struct W4Place {                       // where a wavefront stands in its tile
     }
 };
 
-// C tile += A[rows of the work item, K] . W[expert][n0 .. n0 + 255, K]^T for every gridDim.x-th item from the block's
-// own on (a multiple of eight blocks: the XCD of an entry stays what the list was made for).  F16: fp16
+// C tile += A[rows of the work item, K] . W[expert][n0 .. n0 + 255, K]^T for `share` items, every 256th from the block's
+// first one on (a multiple of eight: the XCD of an entry stays what the list was made for).  F16: fp16
 // rather than bf16 operands.  KTAIL: K is not a multiple of 64, or below four stages; what lies past it reads as zeros.
 // ABL: see grouped_gemm_w4_kernel.  epilogue(acc, prepare(item, wn, oct), item, place, landed) takes the finished tile out of
 // the accumulators, without a branch, acc[i][j][c] = column wn * 128 + i * 16 + oct * 4 + c, row wm * BM / 2 + j * 16 + fr, and calls landed() once, in
 // front of its first store: what the next tile waits for early has to be there before stores stand in front of it.
 template <bool F16, bool KTAIL, int BM, int ABL, typename Prepare, typename Epilogue>
 __device__ __forceinline__ void w4_run(const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
-                                       const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int entries,
+                                       const WorkItem *__restrict__ items, const int32_t *__restrict__ nitems, int entries, int share,
                                        int N, int K, const int32_t *__restrict__ row_src, int row_div, int a_rows,
                                        Prepare prepare, Epilogue epilogue)
 {
@@ -78,10 +84,13 @@ __device__ __forceinline__ void w4_run(const uint16_t *__restrict__ A, const uin
     constexpr bool RING5 = BM == 256;
     constexpr int A_UNIT = BM * 128, W_UNIT = 256 * 128;
     constexpr int AR = BM / 4;                    // rows of A that a wavefront loads
+    constexpr int stride = kRunUnits;
+    int b = blockIdx.x / stride * stride * share + blockIdx.x % stride;
+    const int stop = min(entries, b + share * stride);
     auto item_at = [&](int b) {
         WorkItem t{-1, 0, 0, 0};
-        int at = b < entries ? b : -1;
-        if (nitems != nullptr) {
+        int at = b < stop ? b : -1;
+        if (nitems != nullptr && at >= 0) {
             const int total = *nitems, per_xcd = (total + 7) / 8, slot = b / 8;
             at = b % 8 * per_xcd + slot;
             if (slot >= per_xcd || at >= total) at = -1;
@@ -93,8 +102,6 @@ __device__ __forceinline__ void w4_run(const uint16_t *__restrict__ A, const uin
         t.n0 = __builtin_amdgcn_readfirstlane(t.n0);
         return t;
     };
-    const int stride = gridDim.x;
-    int b = blockIdx.x;
     WorkItem item = item_at(b), next = item_at(b + stride);
     if (item.expert < 0) return;
 

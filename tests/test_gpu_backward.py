@@ -128,8 +128,8 @@ def test_backward_matches_the_oracle(name, keep):
 
 # dP's GEMM over d: one, two and three stages of 64 and a tail, on 256 x 256 (many tiles) and 128 x 128 tiles, and long
 # contractions, whole stages and a tail, on 256 x 256 and 128 x 256, with rows and columns that end inside a tile; dxe's over h on
-# all three and on 128 x 128 with five stages on their way.  keep: the forward's first GEMM takes dP's tiles, the last shape's with
-# five stages on their way.
+# all three and on 128 x 128 with five stages on their way.  The last shape's weight gradients are 256 x 256 tiles of 66 stages, one to
+# a share.  keep: the forward's first GEMM takes dP's tiles, the shape of d = 1928 with five stages on their way.
 @pytest.mark.parametrize("keep", [False, True], ids=["recompute", "keep"])
 @pytest.mark.parametrize("T,h,d,dp,dxe", [
     (6000, 8712, 40, "256x256", "128x128 deep"), (6000, 8712, 64, "256x256", "128x128 deep"),
@@ -139,7 +139,7 @@ def test_backward_matches_the_oracle(name, keep):
     (4000, 1608, 3080, "256x256", "256x256"), (700, 2008, 264, "128x128", "128x128 deep"),
     (300, 1920, 72, "128x128", "128x128 deep"), (4000, 1608, 3072, "128x256", "256x256"),
     (7500, 2152, 3080, "128x256", "256x256"), (6000, 3072, 1032, "256x256", "128x256"),
-    (700, 264, 1928, "128x128", "128x128")])
+    (700, 264, 1928, "128x128", "128x128"), (4200, 8192, 4096, "256x256", "256x256")])
 def test_backward_of_few_stages(T, h, d, dp, dxe, keep):
     s = moe.Shape.make(T, d, 1, h, 1, T, dtype="bf16", act="gelu")
     assert [moe.moe_backward_gemm_kernel(s, which) for which in (0, 1)] == [f"bwd_gemm_w4_kernel {t}" for t in (dp, dxe)]

@@ -1,6 +1,6 @@
-"""What runs beside the expert GEMMs fits beside them.  A block of theirs on tiles of 256 columns holds a compute unit for the
-whole launch, so another kernel's wavefront gets in only if each SIMD's 512 registers (allocated by eight) hold both
-and it asks for no LDS.  Read from the library as built (no GPU needed)."""
+"""What runs beside the expert GEMMs fits beside them.  A block of theirs on tiles of 256 columns holds a compute unit
+for a share of the launch's tiles, so another kernel's wavefront gets in meanwhile only if each SIMD's 512 registers (allocated by
+eight) hold both and it asks for no LDS.  Read from the library as built (no GPU needed)."""
 import re
 import shutil
 import subprocess

@@ -33,8 +33,8 @@ INFINITY_CACHE_BYTES = 256 << 20
 # The counters cannot be read from inside the process, so the figure is a stored
 # measurement, reported only for the workload and launch configuration it was taken on
 # (null for any other): {(workload, n_chunks): (FETCH_SIZE KiB, WRITE_SIZE KiB)} per launch.
-GEMM1_TRAFFIC_KIB = {("large_chunked", 1): (1562254.2, 1017952.0),     # profiles/layer_hbm_traffic_pmc.txt
-                     ("gpt2s_moe", 1): (70608.4, 49152.0)}
+GEMM1_TRAFFIC_KIB = {("large_chunked", 1): (1561333.7, 1017952.0),     # profiles/layer_hbm_traffic_pmc.txt
+                     ("gpt2s_moe", 1): (70739.8, 49152.0)}
 FETCH_UNIT, WRITE_UNIT = 2.0, 1.0     # what the plain-copy calibration reads per counted KiB
 
 

@@ -673,6 +673,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(
 // bytes, past the caches the 4.3 GB alone take 1430 us, through them the operands are pushed out (dW1 2380).
 // Blocks that start one after the other over the length of a tile, so that they do not store all at once: 2 %
 // less for dW1, nothing for dW2.  Tiles in squares of 4 x 4: dW1 2455 -> 2325 with one block per tile.
+// All of that with the tiles in 256 shares; in shares that give the unit back (kRunStages) 2417 / 2213 where those take 2379 / 2106.
 template <bool AF16>
 __global__ __launch_bounds__(256, 1) void wgrad_w4_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, float *__restrict__ C,
@@ -1211,13 +1212,13 @@ void launch_gemm(const uint16_t *A, const uint16_t *W, void *C, _Float16 *P, con
 
 // 256 x 256 tiles on four wavefronts when they fit the matrix, there are 512 of them, and the buffer offsets (an expert's
 // rows times the row length, in bytes) stay below 2^31.  Time of both gradients / of the training step over that with 128 x
-// 128 tiles, 60 layers of 1024 .. 16384 tokens, rows spread evenly; by Zipf(1.2): 512 .. 599 tiles 0.64 .. 0.84 / 0.86 .. 0.89;
-// 0.70 .. 0.91 / 0.86 .. 0.90; 640 .. 768 0.71 .. 0.76 / 0.86 .. 0.90; 0.69 .. 0.82 / 0.86 .. 0.88; with every row in one expert 512 .. 1024
-// tiles 0.68 .. 0.95 of the step.  On the other side: 360 .. 480 0.67 .. 0.82 / 0.87 .. 0.90; 0.67 .. 0.89 / 0.84 .. 0.92; 288 .. 320
-// 0.88 .. 0.95 / 0.76 .. 0.90; 0.84 .. 0.99 / 0.79 .. 0.92; 288 .. 480 with every row in one expert 0.71 .. 0.93 of the step; 160 .. 256 0.65
-// .. 0.75 / 0.88 .. 0.91; 0.66 .. 0.98 / 0.85 .. 0.91; one expert 0.74 .. 1.09; 128 1.04 .. 1.07 / 0.84 .. 1.01; 1.07 .. 1.24 / 0.88 .. 1.02; 64 1.32
-// / 1.07; 1.40 / 1.09.  So 512 is on the safe side: it was set for one tile per block, which could take 1.6 times as long below
-// it where one expert had most of the rows, and a share of the tiles per block would carry it down to 257.
+// 128 tiles, 60 layers of 1024 .. 16384 tokens, rows spread evenly; by Zipf(1.2): 512 .. 599 tiles 0.66 .. 0.83 / 0.87 .. 0.88;
+// 0.69 .. 0.95 / 0.85 .. 0.89; 640 .. 768 0.73 .. 0.74 / 0.86 .. 0.91; 0.68 .. 0.83 / 0.86 .. 0.88; with every row in one expert 512 .. 1024
+// tiles 0.63 .. 1.08 / 0.69 .. 0.95.  On the other side: 360 .. 480 0.66 .. 0.80 / 0.87 .. 0.89; 0.67 .. 0.86 / 0.82 .. 0.91; 288 .. 320
+// 0.89 .. 0.93 / 0.76 .. 0.90; 0.83 .. 0.98 / 0.77 .. 0.93; 288 .. 480 with every row in one expert 0.61 .. 0.94 / 0.71 .. 0.94; 160 .. 256 0.65
+// .. 0.77 / 0.87 .. 0.92; 0.66 .. 0.99 / 0.85 .. 0.91; one expert 0.62 .. 1.11 / 0.74 .. 1.08; 128 1.02 .. 1.09 / 0.86 .. 1.01; 1.06 .. 1.20
+// / 0.88 .. 1.01; 64 1.30 / 1.06; 1.42 / 1.09.  So 512 is on the safe side: it was set for one tile per block, which could take
+// 1.6 times as long below it where one expert had most of the rows; shares of the tiles would carry it down to 257.
 bool wide_wgrad_tiles(int E, int M, int N, int64_t max_rows)
 {
     const uint64_t span = static_cast<uint64_t>(max_rows + 192) * static_cast<uint64_t>(std::max(M, N)) * 2;
@@ -1341,16 +1342,15 @@ SideStream *side_stream(SideStreams &r, hipStream_t caller)
 // them in nothing: each of the four leaves its last round of tiles partly filled, and the gate's
 // gradients leave the matrix cores idle.  By `work`, rows x d_model x d_ff: below 2.7e9 the events between
 // the streams can cost more than that; in large layers a last round is one of many, and GEMMs that run at
-// once share the caches and the power.  (Weight gradients of 256 x 256 tiles hold the units they get until their share of
-// the tiles is done; the other GEMM's blocks go on in the rest.)  us of a training step, one after the other / beside each
-// other, rows spread evenly (by Zipf(1.2)), k = 2 unless said.  Below the line: 128 tokens, 8 experts, 256 x 512 67 / 100
-// (67 / 99); 512, 8, 512 x 1536 115 / 119 (115 / 119); 512, 8, 1024 x 2048 183 / 185 (175 / 178); 2048, 16, 512 x 1024 126 / 138
-// (116 / 136); but 300, 16, 768 x 3072 (1.4e9) 216 / 210 (214 / 208) and 640, 8, 1024 x 2048 (2.68e9) 178 / 176 (179 / 177).  Above:
-// 1500, 13, 640 x 1536 (2.9e9) 171 / 168 (163 / 163); 2048, 16, 512 x 1536 172 / 168 (154 / 154); 300, 13, 1536 x 4096 358 / 337 (352 /
-// 329); 8192, 8, 256 x 1024 196 / 172 (184 / 168); 1024, 16, 768 x 3072 276 / 261 (257 / 243); 4096 of these 446 / 409 (380 /
-// 333); 8192, k = 3 997 / 939 (796 / 697); 4096, 16, 2048 x 8192 2155 / 2132 (1765 / 1633); 32768, 32, 1024 x 4096 3647 / 3656
-// (1983 / 1956); 16384, 32, 2048 x 8192 (5.5e11) 6873 / 6793 (4182 / 4006); 32768, 64, 2048 x 4096 7505 / 7505 (4124 / 3985).  Past
-// it: 24000, 32, 2048 x 8192 (8.1e11) 9295 / 9339 (5638 / 5502); 32768, 64, 2048 x 8192 (1.1e12) 13727 / 13786 (7309 / 7101).
+// once share the caches and the power.  us of a training step, one after the other / beside each other, rows spread evenly (by
+// Zipf(1.2)), k = 2 unless said.  Below the line: 128 tokens, 8 experts, 256 x 512 68 / 128 (68 / 125); 512, 8, 512 x 1536 115 /
+// 128 (115 / 128); 512, 8, 1024 x 2048 182 / 184 (176 / 178); 2048, 16, 512 x 1024 128 / 128 (117 / 127); but 300, 16, 768 x 3072
+// (1.4e9) 213 / 210 (214 / 205) and 640, 8, 1024 x 2048 (2.68e9) 179 / 176 (178 / 177).  Above: 1500, 13, 640 x 1536 (2.9e9) 176 / 171
+// (162 / 164); 2048, 16, 512 x 1536 172 / 170 (153 / 157); 300, 13, 1536 x 4096 358 / 340 (350 / 331); 8192, 8, 256 x 1024 206 / 182
+// (192 / 176); 1024, 16, 768 x 3072 270 / 262 (256 / 244); 4096 of these 457 / 415 (380 / 335); 8192, k = 3 1003 / 945 (814 / 706);
+// 4096, 16, 2048 x 8192 2214 / 2128 (1767 / 1616); 32768, 32, 1024 x 4096 3704 / 3705 (2059 / 1996); 16384, 32, 2048 x 8192 (5.5e11)
+// 7011 / 6902 (4228 / 3952); 32768, 64, 2048 x 4096 7665 / 7729 (4124 / 3964).  Past it: 24000, 32, 2048 x 8192 (8.1e11) 9541 / 9610
+// (5733 / 5339); 32768, 64, 2048 x 8192 (1.1e12) 14032 / 14202 (7447 / 7146).
 // Not while the stages are timed, and not under capture: the side stream would stay part of the
 // capture after the call returns, when the next call from outside needs it.
 bool overlaps_weight_grads(double work, hipStream_t st)

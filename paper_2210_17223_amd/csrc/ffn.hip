@@ -557,8 +557,8 @@ __device__ __forceinline__ void run_gemm_tiles(
         // R rows are stored while the next ones are computed.  KEEP: 16, each pass through its own half of the patch where
         // it has two, so that the sums of no more are kept from the first pass to the second: with 32 the 256 x 256 kernel
         // takes 504 to 512 of a SIMD's 512 registers, with 16 at most 472, and the pack's wavefronts (32) get in beside a
-        // block that holds its unit.  32768 tokens, 2048 x 8192, 64 experts, us: pack 1376 -> 236, this GEMM 1886 -> 1902,
-        // the second one, which the pack was left to, 1632 -> 1602.  20 training steps of 18000 .. 32768 tokens: 0.986 .. 1.019 of
+        // block that holds its unit.  32768 tokens, 2048 x 8192, 64 experts, a launch's tiles in 256 shares, us: pack 1376 -> 236,
+        // this GEMM 1886 -> 1902, the second one, which the pack was left to, 1632 -> 1602.  20 training steps of 18000 .. 32768 tokens: 0.986 .. 1.019 of
         // their time, mean 0.999; packed in front of this GEMM 0.973 .. 1.058, mean 1.004.
         constexpr int UR = W4Place<BM>::UR, R = KEEP ? 16 : UR;
 #pragma unroll

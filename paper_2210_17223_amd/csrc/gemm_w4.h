@@ -28,13 +28,13 @@
 //  * Every memory instruction is issued singly between two matrix instructions in a fixed order;
 //    those are inline assembly so that the accumulators stay in AGPRs and the order holds.
 //    Neighbouring ones share an operand (serpentine order).
-// What bounds it: the matrix cores are busy for 67 % / 78 % of the cycles (N = 8192, K = 2048, GeLU / N =
-// 2048, K = 8192; with one tile per block 62 / 79), at a clock of 1.71 / 1.67 GHz that the chip sets by the energy per
-// operation (on all-ones operands the same launches are 22 % / 20 % faster).  With 32 x 32 x 16 instructions and operands staged
+// What bounds it: the matrix cores are busy for 65 % / 77 % of the cycles (N = 8192, K = 2048, GeLU / N =
+// 2048, K = 8192; with one tile per block 62 / 79), at a clock of 1.75 / 1.71 GHz that the chip sets by the energy per
+// operation (on all-ones operands the same launches are 21 % faster).  With 32 x 32 x 16 instructions and operands staged
 // through registers it was 56 % / 78 % at 1.68 / 1.55 GHz: the first GEMM lost cycles, the second takes as many
 // as before and they have become cheaper.  On 64 x 1024 rows alone, after thirty launches, with a block's loads
-// running on from tile to tile (gemm_w4_run.h): 1773 / 1586 us, of which the matrix instructions and barriers by themselves
-// take 1329 / 1097, and the loads into LDS beside them 29 % / 39 % on top; a vendor library's dense products
+// running on from tile to tile (gemm_w4_run.h): 1790 / 1600 us, of which the matrix instructions and barriers by themselves
+// take 1333 / 1101, and the loads into LDS beside them 30 % / 41 % on top; a vendor library's dense products
 // of these sizes 1540 / 1515.  (After two launches, while the clock still follows the load, 15 % more.)
 // Loads into LDS run at 9 to 10 TB/s over the chip beside the matrix instructions, whatever the tile.
 // 128 x 256 (64 x 128 per wavefront) and 128 x 128 tiles (64 x 64) run the same loop.  128 x 256 has

@@ -17,7 +17,8 @@
 // GeLU 1856 -> 1773, N = 2048, K = 8192 1589 -> 1586 (its tiles are of 128 stages; on all-ones operands, at the higher clock,
 // 1575 -> 1455 and 1317 -> 1316); with the pre-activations kept, 63622 rows 2087 -> 1877; of Zipf(1.2)-distributed rows the layer of
 // 16384 tokens, 1024 x 4096, 32 experts 375 -> 362; of 3001 tokens, 1000 x 2600, 13 experts, all options 191 -> 179.  Prologue,
-// barriers and epilogue of the first product take 176 of its 1773 by themselves (313 of 1856).
+// barriers and epilogue of the first product take 176 of its 1773 by themselves (313 of 1856).  These with all of a launch's
+// tiles in 256 shares; in shares of kRunStages 1790 and 1600, 230 of 1790.
 // What runs beside such a launch: a block holds its unit until its share is done, all of its LDS and 440 or 448 of the 512 registers
 // of every SIMD (256 x 256; at most 472 with the pre-activations kept; 272 to 312 on 128 x 256).  Wavefronts of another stream
 // that ask for no LDS and for the rest of the registers get in, as the pack (32) and the stand-in link's copy (40) do; what
